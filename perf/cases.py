@@ -213,3 +213,25 @@ def tolerance(case):
     if case["dtype"] == "f32":
         return {"rel": 4e-3, "max": 0.99, "differ": 4e-6}
     return {"rel": 1e-2, "max": 0.99, "differ": 8e-6}
+
+
+def exact(case, seed):
+    """Y and db of the same pass in float64.  I and the sums that it routes (dH, dW) have no such value: near-ties,
+    which a correct implementation may decide either way, move whole rows of them (see tolerance)."""
+    s = prepare(case, seed)
+    batches = s.batches if s.path == "micro" else [s]
+    with torch.no_grad():
+        Ws, db = s.W.detach(), None
+        for b in batches:
+            Y = torch.empty((case["B"], case["V"]), dtype=torch.float64, device=DEV)
+            rows = [b.H[k][b.mask[k] != 0].double() for k in range(case["B"])]
+            for v0 in range(0, case["V"], 16384):
+                Wc = Ws[v0:v0 + 16384].double().t().contiguous()
+                for k, h in enumerate(rows):
+                    Y[k, v0:v0 + 16384] = (h @ Wc).amax(dim=0)
+            Y = torch.log1p(torch.relu(Y + s.bias.detach().double()))
+            if s.path in ("serve", "encode"):
+                return Y
+            g = torch.where(Y > 0, b.dY.double() * torch.exp(-Y), torch.zeros_like(Y)).sum(dim=0)
+            db = g if db is None else db + g
+    return {"Y": Y, "I": None, "dH": [None for _ in batches] if s.path == "micro" else None, "dW": None, "db": db}
