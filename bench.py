@@ -331,7 +331,7 @@ def main():
     w = inp.workload
     fwd_flops = flops_forward(inp)
     traffic = measured_traffic(args.workload) or {}
-    roof = {"bound": "mfma", "kernel": "fwd_bf16_kernel (fused GEMM + max/argmax + activation)",
+    roof = {"bound": "mfma", "kernel": "fwd_mfma_kernel (fused GEMM + max/argmax + activation)",
             "achieved": fwd_flops / (res["fwd_ms"] * 1e-3) / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
             "traffic": traffic.get("fwd_bytes"), "traffic_unit": "bytes per launch",
             "traffic_source": traffic.get("source"),

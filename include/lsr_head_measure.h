@@ -75,7 +75,8 @@ int lsr_gather_probe(const void* table, size_t window_bytes, int steps, int laun
  *   [6] buckets per wave in the sliced dH gather (0: whole-row dH kernel, D not a multiple of 64)
  *   [7] rows of the sliced dW gather's staging tile (0: whole-row dW kernel)
  *   [8] sequences per launch of the sliced dW gather (B: one launch)
- *   [9] chunks the forward grid provides for (the longest token list the shape allows)
+ *   [9] chunks the forward grid provides for (the longest token list the shape allows); float32 problems are cut
+ *       into whole sequences instead, in windows of the length the launch picks
  *   [10] rows per segment of the packed token list (32, or 8 for batches of short sequences)
  *   [11] 1 if the forward runs one resident workgroup per CU over its units (shallow problems), else 0
  *   [12] 1 if the column slices of the sliced dH gather are owned by XCDs (small batches), else 0

@@ -1,5 +1,5 @@
-// Fused forward for bf16 inputs on gfx950: GEMM tile (MFMA, fp32 accumulate) + masked running
-// max/argmax over the sequence + bias/ReLU/log1p on the reduced B x V result.
+// Fused forward on gfx950: GEMM tile (MFMA, fp32 accumulate) + masked running max/argmax over the sequence
+// + bias/ReLU/log1p on the reduced B x V result, for bfloat16 or float32 H and W.
 //
 // Paper Sec. 3 "Forward Pass": log(1+ReLU(x)) is monotone, so the maximum over the sequence is
 // taken on raw logits while they still sit in accumulator registers and the activation is
@@ -7,7 +7,7 @@
 //
 // Tiling.  A workgroup of 8 waves (2 per SIMD) owns a 256 (tokens) x 256 (vocabulary) output tile;
 // wave (wm, wn) owns four 32-row blocks x columns [64 wn, 64 wn + 64), i.e. 4 x 2 blocks of the
-// 32x32x16 bf16 MFMA.  Tokens are the MFMA's row dimension: in the 32x32 accumulator layout a lane
+// 32x32x16 bf16 MFMA (32x32x2 in float32; the 32x32 accumulator layout is the same).  Tokens are the MFMA's row dimension: in the 32x32 accumulator layout a lane
 // holds 16 rows of ONE column, so the max over tokens starts as a plain in-lane reduction, is
 // finished with one exchange between the two half-waves; what is left per tile is one value per
 // (block, column), which goes through LDS to the scan that joins the blocks of a sequence.
@@ -16,7 +16,7 @@
 // ring of LDS tiles.  Two loaders:
 //   DMA = true  : global_load_lds (16 bytes per lane straight into LDS, no staging registers),
 //                 slabs issued NS-1 iterations ahead, one barrier per slab.  Needs D % BK == 0.
-//   DMA = false : global -> registers -> LDS, one slab ahead (BK = 64, NS = 2).  Handles any D that
+//   DMA = false : global -> registers -> LDS, one slab ahead (NS = 2).  Handles any D that
 //                 is a multiple of 8 (the last slab is zero-filled).
 // Rows are XOR-swizzled inside a slab so that the 16-byte fragment reads are bank-conflict free.
 //
@@ -44,6 +44,11 @@
 // leaves its pair in slot `chunk` of the part_m / part_s arrays; a small kernel (fwd_merge_kernel) joins
 // the pieces and finalises.  Chunks of whole sequences would need no such pass but end in short tiles
 // and need the lengths on the host to size.
+// Float32 does it the other way round: its chunks are whole sequences (chunk c holds the sequences whose
+// first segment lies in the window [c L, (c + 1) L) of the list, found by searching the table of first
+// segments; a window in which no sequence begins is an empty chunk).  Its tiles are bound by the matrix
+// rate, so a short last tile costs only what its live blocks cost and a search per unit is nothing beside a
+// unit, and no slots and no merge pass are needed.
 // Two launch modes (template parameter RES, chosen by the host from the shape).  Deep problems launch
 // one workgroup per unit and let the hardware hand units out in order, which keeps the workgroups of an
 // XCD on neighbouring units and their shared rows of H and W in its L2.  Shallow problems (a few short
@@ -61,6 +66,7 @@
 namespace lsr {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int FWD_TM = 256;        // tile rows (tokens)
@@ -94,9 +100,27 @@ __device__ __forceinline__ ChunkSplit chunk_split(int n_segs, int tpc, int spt) 
     return cs;
 }
 
+// First entry of the ascending table seg0[0 .. B] that is at least `target` (at most seg0[B]): a 64-way
+// search by one wave, all lanes active.
+__device__ __forceinline__ int first_segment_from(const int* seg0, int B, int target) {
+    const int lane = threadIdx.x & 63;
+    int lo = 0, n = B + 1;                    // the answer is one of lo .. lo + n - 1
+    while (n > 1) {
+        const int step = (n + 63) >> 6;
+        const int at = lo + lane * step;
+        const bool below = lane * step < n && seg0[min(at, B)] < target;
+        const int c = __popcll(__ballot(below));              // samples below the target come first
+        if (c == 0) break;                    // seg0[lo] is the answer
+        const int end = min(n, c * step + 1); // entries up to the first sample at or above the target
+        lo += (c - 1) * step + 1;
+        n = end - ((c - 1) * step + 1);
+    }
+    return __builtin_amdgcn_readfirstlane(seg0[lo]);
+}
+
 struct FwdParams {
-    const uint16_t* H;
-    const uint16_t* W;
+    const void* H;           // bfloat16 or float32, as the kernel's element type
+    const void* W;
     const float* bias;
     const int2* rows;        // [n_segs * SEG] per packed row: (row of H = b*S + s, position s)
     const int* blk_meta;     // [n_segs] sequence index b, ORed with FWD_META_LAST / _EMPTY / _FIRST
@@ -109,6 +133,8 @@ struct FwdParams {
     int n_vtiles;            // ceil(V / tile columns)
     int n_chunks;            // chunks the grid provides for (from the longest block list the shape allows)
     int tpc;                 // most tiles per chunk
+    const int* seg0;         // [B + 1] first segment of every sequence (float32: chunks of whole sequences)
+    int chunk_segs;          // float32: segments per window of a chunk
     int gv;                  // vocabulary tiles per L2-sharing group
 };
 
@@ -117,9 +143,9 @@ struct FwdParams {
 // (256 bytes, all 64 banks) per cycle.  Measured on gfx950 with 4 waves reading: 128-byte rows
 // XORed with row bits 1..3, or 64-byte rows XORed with row bits 2..3, take 4 cycles per wave
 // read (conflict free); XOR with the low row bits takes 8; no swizzle 32.
-template <int BK>
+template <int ROW_BYTES>
 __device__ __forceinline__ int lds_swz(int r) {
-    return BK == 64 ? (r >> 1) & 7 : (r >> 2) & 3;
+    return ROW_BYTES == 128 ? (r >> 1) & 7 : (r >> 2) & 3;
 }
 
 // Tile row of accumulator register r (0..15) of a lane in the given half-wave, in tile block blk:
@@ -128,23 +154,37 @@ __device__ __forceinline__ int acc_row(int blk, int r, int half) {
     return blk * FWD_BLK + (r >> 2) * 8 + half * 4 + (r & 3);
 }
 
+// A fragment is 16 bytes of one tile row per lane, and a k-step the two 16-byte chunks the half-waves hold:
+// 16 elements of K in bfloat16 (one MFMA), 8 in float32 (four, each taking one element of either chunk; which
+// k of the slab an MFMA's k index stands for does not matter as long as both operands agree).
+__device__ __forceinline__ floatx16 mma_chunk(bf16x8 a, bf16x8 b, floatx16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ floatx16 mma_chunk(floatx4 a, floatx4 b, floatx16 c) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], c, 0, 0, 0);
+    return c;
+}
+template <typename T> struct FwdFrag;
+template <> struct FwdFrag<uint16_t> { typedef bf16x8 type; };
+template <> struct FwdFrag<float> { typedef floatx4 type; };
+
 // One K slab of MFMAs for the first NA of this wave's four row blocks, fragments read per k-step
 // (register-staged loader; the direct-to-LDS pipeline uses mma_rot below).
-template <int NA, int KS>
+template <typename Frag, int NA, int KS>
 __device__ __forceinline__ void mma_slab(const uint8_t* sa, int a_stride, const uint8_t* sb, int b_stride,
                                          const int (&fsw)[KS], floatx16 (&acc)[4][2]) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-        bf16x8 fa[NA], fb[2];
+        Frag fa[NA], fb[2];
 #pragma unroll
-        for (int c = 0; c < 2; ++c) fb[c] = *reinterpret_cast<const bf16x8*>(sb + c * b_stride + fsw[ks]);
+        for (int c = 0; c < 2; ++c) fb[c] = *reinterpret_cast<const Frag*>(sb + c * b_stride + fsw[ks]);
 #pragma unroll
-        for (int i = 0; i < NA; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(sa + i * a_stride + fsw[ks]);
+        for (int i = 0; i < NA; ++i) fa[i] = *reinterpret_cast<const Frag*>(sa + i * a_stride + fsw[ks]);
 #pragma unroll
         for (int i = 0; i < NA; ++i)
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
-                acc[i][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[c], acc[i][c], 0, 0, 0);
+            for (int c = 0; c < 2; ++c) acc[i][c] = mma_chunk(fa[i], fb[c], acc[i][c]);
     }
 }
 
@@ -158,9 +198,9 @@ __device__ __forceinline__ void mma_slab(const uint8_t* sa, int a_stride, const 
 //           k-steps 0 .. KS-2 (reading 1 .. KS-1)
 //   MODE 2  after the last slab of the tile: its k-step KS-1
 // The order of the MFMAs on every accumulator is the same as without the rotation.
-template <int NA, int KS, int MODE, int NDMA, int SPREAD, typename DmaFn>
+template <int NA, int KS, int MODE, int NDMA, int SPREAD, typename Frag, typename DmaFn>
 __device__ __forceinline__ void mma_rot(const uint8_t* sa, int a_stride, const uint8_t* sb, int b_stride,
-                                        const int (&fsw)[KS], bf16x8 (&fa)[2][4], bf16x8 (&fb)[2][2],
+                                        const int (&fsw)[KS], Frag (&fa)[2][4], Frag (&fb)[2][2],
                                         floatx16 (&acc)[4][2], DmaFn&& dma) {
     static_assert(KS % 2 == 0 && KS >= 2, "buffer parity must not depend on the slab");
     constexpr int M = NA * 2;
@@ -168,9 +208,9 @@ __device__ __forceinline__ void mma_rot(const uint8_t* sa, int a_stride, const u
     constexpr int GROUPS = MODE == 0 ? KS - 1 : (MODE == 1 ? KS : 1);
     if constexpr (MODE == 0) {
 #pragma unroll
-        for (int c = 0; c < 2; ++c) fb[0][c] = *reinterpret_cast<const bf16x8*>(sb + c * b_stride + fsw[0]);
+        for (int c = 0; c < 2; ++c) fb[0][c] = *reinterpret_cast<const Frag*>(sb + c * b_stride + fsw[0]);
 #pragma unroll
-        for (int i = 0; i < NA; ++i) fa[0][i] = *reinterpret_cast<const bf16x8*>(sa + i * a_stride + fsw[0]);
+        for (int i = 0; i < NA; ++i) fa[0][i] = *reinterpret_cast<const Frag*>(sa + i * a_stride + fsw[0]);
     }
 #pragma unroll
     for (int g = 0; g < GROUPS; ++g) {
@@ -181,17 +221,16 @@ __device__ __forceinline__ void mma_rot(const uint8_t* sa, int a_stride, const u
             if (rk >= 0 && q < NA + 2) {
                 if (q == 0 || q == 2) {
                     const int c = q >> 1;
-                    fb[nxt][c] = *reinterpret_cast<const bf16x8*>(sb + c * b_stride + fsw[rk < 0 ? 0 : rk]);
+                    fb[nxt][c] = *reinterpret_cast<const Frag*>(sb + c * b_stride + fsw[rk < 0 ? 0 : rk]);
                 } else {
                     const int i = q == 1 ? 0 : q - 2;
-                    fa[nxt][i] = *reinterpret_cast<const bf16x8*>(sa + i * a_stride + fsw[rk < 0 ? 0 : rk]);
+                    fa[nxt][i] = *reinterpret_cast<const Frag*>(sa + i * a_stride + fsw[rk < 0 ? 0 : rk]);
                 }
             }
         };
 #pragma unroll
         for (int m = 0; m < M; ++m) {
-            acc[m >> 1][m & 1] =
-                __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][m >> 1], fb[cur][m & 1], acc[m >> 1][m & 1], 0, 0, 0);
+            acc[m >> 1][m & 1] = mma_chunk(fa[cur][m >> 1], fb[cur][m & 1], acc[m >> 1][m & 1]);
             if (rk == KS - 1) {
                 // the reads before a barrier have to be back when the wave reaches it: two per MFMA,
                 // so that the last one still has most of the group to return
@@ -214,22 +253,28 @@ __device__ __forceinline__ void mma_rot(const uint8_t* sa, int a_stride, const u
     }
 }
 
-template <int KS>
+template <typename Frag, int KS>
 __device__ __forceinline__ void mma_dispatch(int na, const uint8_t* sa, int a_stride, const uint8_t* sb, int b_stride,
                                              const int (&fsw)[KS], floatx16 (&acc)[4][2]) {
     switch (na) {
-        case 4: mma_slab<4, KS>(sa, a_stride, sb, b_stride, fsw, acc); break;
-        case 3: mma_slab<3, KS>(sa, a_stride, sb, b_stride, fsw, acc); break;
-        case 2: mma_slab<2, KS>(sa, a_stride, sb, b_stride, fsw, acc); break;
-        case 1: mma_slab<1, KS>(sa, a_stride, sb, b_stride, fsw, acc); break;
+        case 4: mma_slab<Frag, 4, KS>(sa, a_stride, sb, b_stride, fsw, acc); break;
+        case 3: mma_slab<Frag, 3, KS>(sa, a_stride, sb, b_stride, fsw, acc); break;
+        case 2: mma_slab<Frag, 2, KS>(sa, a_stride, sb, b_stride, fsw, acc); break;
+        case 1: mma_slab<Frag, 1, KS>(sa, a_stride, sb, b_stride, fsw, acc); break;
         default: break;                             // no live row block in this wave
     }
 }
 
-// One workgroup of 8 waves (2 wave rows x 4 wave columns) per CU on a 256 x 256 tile, K in slabs of 64
-// through a ring of two LDS stages.
+// One workgroup of 8 waves (2 wave rows x 4 wave columns) per CU on a 256 x 256 tile, K in slabs of 128 bytes
+// per row (64 bfloat16 or 32 float32) through a ring of two LDS stages.
+//   T    uint16_t (bfloat16 storage) or float.  Everything that moves bytes is the same for both; a float32
+//        slab takes 8 times the matrix-core cycles of a bfloat16 slab of the same bytes, so that path is bound
+//        by the float32 matrix rate (157 TFLOP/s nominal) alone and the tile has latency to spare.  Against
+//        one thread per (b, v) with a scalar loop over D (no reuse): forward + backward of B=64 S=32 D=768
+//        |V|=30522 386 -> 1.5 ms, of B=2 S=16 D=64 |V|=1000 0.108 -> 0.078 ms; the error against float64
+//        logits is the same (3.2e-7 of the norm of Y).
 //   ARG  track the arg-max position (I requested)
-//   DMA  operands go global -> LDS directly (D a multiple of 64, H and W below 4 GiB each); otherwise
+//   DMA  operands go global -> LDS directly (rows a multiple of 128 bytes, H and W below 4 GiB each); otherwise
 //        through registers, with 64-bit addresses and a zero-filled last slab
 //   SEG  rows per segment of the packed token list: 32 (FWD_BLK) or 8 (FWD_SEG_SHORT)
 //   RES  resident workgroups: a workgroup walks several units (see the schedule below); without it the
@@ -237,24 +282,27 @@ __device__ __forceinline__ void mma_dispatch(int na, const uint8_t* sa, int a_st
 // (Built and measured slower, and not kept as parameters: two 4-wave workgroups per CU on 256 x 128
 //  tiles, which move 1.5x the bytes into LDS, -20 %; 32-deep slabs in four stages, -6 %.)
 constexpr int FWD_NWN = 4;               // wave columns
-template <bool ARG, bool DMA, int SEG, bool RES>
-__global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_bf16_kernel(FwdParams p) {
+template <typename T, bool ARG, bool DMA, int SEG, bool RES>
+__global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_mfma_kernel(FwdParams p) {
     static_assert(SEG == 32 || SEG == 16 || SEG == 8, "a segment is a whole number of a lane's register quads");
     constexpr int SPB = FWD_BLK / SEG;       // segments per row block
     constexpr int SPT = FWD_TM / SEG;        // segments per tile
     constexpr int RPS = 16 / SPB;            // accumulator registers of a lane per segment
     constexpr int NWN = FWD_NWN;
-    constexpr int BK = 64;                   // K elements per slab
+    typedef typename FwdFrag<T>::type Frag;
+    constexpr int ESZ = sizeof(T);
+    constexpr int EPC = 16 / ESZ;            // elements per 16-byte chunk
+    constexpr int BK = 128 / ESZ;            // K elements per slab
     constexpr int NS = 2;                    // ring stages
     constexpr int SPREAD = 2;                // k-steps over which the loads of the next slab are spread
     constexpr int NW = 2 * NWN;              // waves
     constexpr int TN = fwd_tn(NWN);
-    constexpr int RB = BK * 2;               // bytes per tile row per slab
+    constexpr int RB = BK * ESZ;             // bytes per tile row per slab
     constexpr int CPR = RB / 16;             // 16-byte chunks per row
     constexpr int RPI = 64 / CPR;            // rows covered by one wave-wide 16-byte-per-lane access
     constexpr int IPA = FWD_TM / RPI / NW;   // such accesses per wave and slab, token rows
     constexpr int IPB = TN / RPI / NW;       //                                  vocabulary rows
-    constexpr int KS = BK / 16;              // MFMA k-steps per slab
+    constexpr int KS = RB / 32;              // k-steps per slab (two chunks each)
     constexpr int SLAB_A = FWD_TM * RB;      // bytes per stage, token operand
     constexpr int SLAB_B = TN * RB;          //                  vocabulary operand
     constexpr int STAGE = SLAB_A + SLAB_B;
@@ -293,12 +341,14 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_bf16_kernel(FwdPa
     //      unit and the hardware hands out units in order as CUs come free.  Workgroup ids go round-robin
     //      over the XCDs, so id & 7 is the XCD and id >> 3 the index on it. ----
     const int n_segs = *p.n_blocks;
+    constexpr bool WHOLE = ESZ == 4;         // chunks of whole sequences
     const ChunkSplit cs = chunk_split(n_segs, p.tpc, SPT);
+    const int nc = WHOLE ? (n_segs + p.chunk_segs - 1) / p.chunk_segs : cs.nc;
     // units per group of vocabulary tiles.  One workgroup per unit: the unit list provides for the chunks
     // of the longest possible token list, as the grid does, and the workgroups of chunks that do not exist
     // return at once, in place (measured 1 % faster at B=64 S=512 than closing the gaps, which moves all
     // idle workgroups to the end of the grid).
-    const int span = (RES ? cs.nc : p.n_chunks) * p.gv;
+    const int span = (RES ? nc : p.n_chunks) * p.gv;
     const long long n_units = (long long)((p.n_vtiles + p.gv - 1) / p.gv) * span;
     const int n_local = gridDim.x >> 3;
     const int u_end = (int)(n_units * ((blockIdx.x & 7) + 1) / 8);
@@ -311,10 +361,16 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_bf16_kernel(FwdPa
             const int rem = u - vg * span;
             const int rc = rem / p.gv;
             const int vt = vg * p.gv + (rem - rc * p.gv);
-            if (vt >= p.n_vtiles || rc >= cs.nc) continue;
+            if (vt >= p.n_vtiles || rc >= nc) continue;
             x.u = u; x.vt = vt; x.rc = rc;
-            x.g0 = cs.first_tile(rc) * SPT;                                              // first segment of the chunk
-            x.ns = min(n_segs, cs.first_tile(rc + 1) * SPT) - x.g0;                      // its segments
+            if constexpr (WHOLE) {
+                x.g0 = first_segment_from(p.seg0, p.B, rc * p.chunk_segs);
+                x.ns = first_segment_from(p.seg0, p.B, min(n_segs, (rc + 1) * p.chunk_segs)) - x.g0;
+                if (x.ns <= 0) continue;
+            } else {
+                x.g0 = cs.first_tile(rc) * SPT;                                          // first segment of the chunk
+                x.ns = min(n_segs, cs.first_tile(rc + 1) * SPT) - x.g0;                  // its segments
+            }
             x.n_tiles = (x.ns + SPT - 1) / SPT;
             return true;
         }
@@ -338,7 +394,7 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_bf16_kernel(FwdPa
     //      LDS bytes; lane -> (row lrow, LDS chunk slot lp), which holds global chunk lp ^ swizzle(row) ----
     const int lrow = wave * RPI + lane / CPR;                 // + NW RPI j
     const int lp = lane % CPR;
-    const int gch = lp ^ lds_swz<BK>(lrow);                   // swizzle bits do not depend on j
+    const int gch = lp ^ lds_swz<RB>(lrow);                   // swizzle bits do not depend on j
     const int st_off = lrow * RB + lp * 16;                   // + JSTEP j   (register-staged loader)
     // Operand rows are addressed as base + byte offset; the direct-to-LDS loader keeps the offsets in
     // 32 bits (the host takes this path only while H and W are each below 4 GiB).
@@ -352,7 +408,7 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_bf16_kernel(FwdPa
         for (int j = 0; j < IPB; ++j) {
             int v = vt * TN + lrow + NW * RPI * j;
             v = v < p.V ? v : p.V - 1;
-            const size_t o = ((size_t)v * D + gch * 8) * 2;
+            const size_t o = ((size_t)v * D + gch * EPC) * ESZ;
             if constexpr (DMA) woff32[j] = (uint32_t)o;
             else woff[j] = o;
         }
@@ -370,7 +426,7 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_bf16_kernel(FwdPa
     const int fb_row = wn * 64 + l32;
     int fsw[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) fsw[ks] = ((ks * 2 + half) ^ lds_swz<BK>(l32)) << 4;
+    for (int ks = 0; ks < KS; ++ks) fsw[ks] = ((ks * 2 + half) ^ lds_swz<RB>(l32)) << 4;
 
     // ---- row tables of tile t into buffer buf, by direct-to-LDS loads (no registers held while the
     //      tile before it is multiplied): waves 0 and 1 bring 128 rows each (two per lane), wave 2
@@ -404,7 +460,7 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_bf16_kernel(FwdPa
     auto row_offsets = [&](int buf) {
 #pragma unroll
         for (int j = 0; j < IPA; ++j) {
-            const size_t o = ((size_t)s_rows[buf][lrow + NW * RPI * j].x * D + gch * 8) * 2;
+            const size_t o = ((size_t)s_rows[buf][lrow + NW * RPI * j].x * D + gch * EPC) * ESZ;
             if constexpr (DMA) hoff32[j] = (uint32_t)o;
             else hoff[j] = o;
         }
@@ -463,8 +519,8 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_bf16_kernel(FwdPa
                 else dma16_to_lds(wb, woff32[n - IPA], dst + SLAB_A + (n - IPA) * JSTEP);
             };
             auto issue = [&](auto st, int kt) {
-                const char* hb = Hb + (size_t)kt * (BK * 2);
-                const char* wb = Wb + (size_t)kt * (BK * 2);
+                const char* hb = Hb + (size_t)kt * RB;
+                const char* wb = Wb + (size_t)kt * RB;
 #pragma unroll
                 for (int n = 0; n < LPT; ++n) issue_one(st, hb, wb, n);
             };
@@ -472,7 +528,7 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_bf16_kernel(FwdPa
             // made per tile, outside the loop, so that each instance is straight-line MFMA code.
             auto run_slabs = [&](auto na_c) {
                 constexpr int NA = decltype(na_c)::value;
-                bf16x8 fa[2][4], fb[2][2];
+                Frag fa[2][4], fb[2][2];
                 // One pipeline step: barrier that publishes slab kt (stage ST), then a slab's worth of
                 // MFMAs (see mma_rot) with the loads of slab kt + 1 riding inside them.
                 // (NEXT: this is the last slab of the tile and its loads are the first slab of the next
@@ -489,7 +545,7 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_bf16_kernel(FwdPa
                     // one scalar flag and one pair of advanced bases per slab: what is left per load is
                     // a scalar branch, the M0 write and the load itself
                     const int more = __builtin_amdgcn_readfirstlane((NEXT || kt + 1 < nk) ? 1 : 0);
-                    const size_t kbytes = (size_t)(NEXT ? 0 : kt + 1) * (BK * 2);
+                    const size_t kbytes = (size_t)(NEXT ? 0 : kt + 1) * RB;
                     const char* hb = Hb + kbytes;
                     const char* wb = Wb + kbytes;
                     auto dma = [&](int n) {
@@ -535,23 +591,23 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_bf16_kernel(FwdPa
             }
         } else {
             uint4 ra[IPA], rb[IPB];
-            // K slabs are full except possibly the last one (D not a multiple of 64): only that one
+            // K slabs are full except possibly the last one (D not a multiple of BK): only that one
             // pays for per-chunk predication.
             auto gload = [&](int kt) {
                 const int koff = kt * BK;
                 if (koff + BK <= D) {
 #pragma unroll
-                    for (int j = 0; j < IPA; ++j) ra[j] = *reinterpret_cast<const uint4*>(Hb + hoff[j] + koff * 2);
+                    for (int j = 0; j < IPA; ++j) ra[j] = *reinterpret_cast<const uint4*>(Hb + hoff[j] + koff * ESZ);
 #pragma unroll
-                    for (int j = 0; j < IPB; ++j) rb[j] = *reinterpret_cast<const uint4*>(Wb + woff[j] + koff * 2);
+                    for (int j = 0; j < IPB; ++j) rb[j] = *reinterpret_cast<const uint4*>(Wb + woff[j] + koff * ESZ);
                 } else {
-                    const bool kval = koff + gch * 8 < D;
+                    const bool kval = koff + gch * EPC < D;
 #pragma unroll
                     for (int j = 0; j < IPA; ++j)
-                        ra[j] = kval ? *reinterpret_cast<const uint4*>(Hb + hoff[j] + koff * 2) : make_uint4(0, 0, 0, 0);
+                        ra[j] = kval ? *reinterpret_cast<const uint4*>(Hb + hoff[j] + koff * ESZ) : make_uint4(0, 0, 0, 0);
 #pragma unroll
                     for (int j = 0; j < IPB; ++j)
-                        rb[j] = kval ? *reinterpret_cast<const uint4*>(Wb + woff[j] + koff * 2) : make_uint4(0, 0, 0, 0);
+                        rb[j] = kval ? *reinterpret_cast<const uint4*>(Wb + woff[j] + koff * ESZ) : make_uint4(0, 0, 0, 0);
                 }
             };
             auto lstore = [&](int st) {
@@ -568,7 +624,7 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_bf16_kernel(FwdPa
                 if (kt + 1 < nk) gload(kt + 1);
                 const uint8_t* sa = &s_pair[st][fa_row * RB];
                 const uint8_t* sb = &s_pair[st][SLAB_A + fb_row * RB];
-                mma_dispatch<KS>(na, sa, A_STRIDE, sb, B_STRIDE, fsw, acc);
+                mma_dispatch<Frag, KS>(na, sa, A_STRIDE, sb, B_STRIDE, fsw, acc);
                 if (kt + 1 < nk) lstore(st ^ 1);
                 __syncthreads();
             }

@@ -1,9 +1,9 @@
-// Mask compaction (feeds the fused forward) and the plain fp32 forward used for small problems.
+// Mask compaction and packing plan (feed the fused forward), and the join of cut sequences.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "fwd_bf16.hpp"
+#include "fwd_mfma.hpp"
 
 namespace lsr {
 
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(PACK_THREADS) void fwd_pack_kernel(const uint8_t* _
     }
 }
 
-// Joins the pieces of the sequences that a chunk boundary of the fused kernel cuts (see fwd_bf16.hpp).
+// Joins the pieces of the sequences that a chunk boundary of the fused kernel cuts (see fwd_mfma.hpp).
 // The workgroups of chunk c leave, for a sequence that runs on into chunk c+1, the raw (max, position)
 // of its blocks inside chunk c in Y and I; the workgroups of every later chunk k the sequence reaches
 // leave theirs in slot k of part_m / part_s.  One thread per (chunk, vocabulary entry) takes the
@@ -218,38 +218,6 @@ __global__ __launch_bounds__(FWD_MERGE_THREADS) void fwd_merge_kernel(const int*
         Y[o] = log1pf(fmaxf(m + bias[v], 0.f));
         if (ARG) I[o] = s;
     }
-}
-
-// Plain fp32 head: one thread per (b, v), looping over valid positions and the hidden size with
-// fp32 FMAs.  Eq. 1 evaluated with the max taken before the activation (Sec. 3).  Not tuned: it
-// exists so that small fp32 problems run through the same entry points.
-constexpr int F32_THREADS = 128;
-
-template <bool ARG>
-__global__ __launch_bounds__(F32_THREADS) void fwd_f32_kernel(const float* __restrict__ H,
-                                                              const float* __restrict__ W,
-                                                              const float* __restrict__ bias,
-                                                              const int* __restrict__ len,
-                                                              const int* __restrict__ pos,
-                                                              float* __restrict__ Y, int* __restrict__ I,
-                                                              int S, int D, int V) {
-    const int b = blockIdx.y;
-    const int v = blockIdx.x * F32_THREADS + threadIdx.x;
-    if (v >= V) return;
-    const int n = len[b];
-    const float* wrow = W + (size_t)v * D;
-    float m = -INFINITY;
-    int arg = 0;
-    for (int j = 0; j < n; ++j) {
-        const int s = pos[(size_t)b * S + j];
-        const float* hrow = H + ((size_t)b * S + s) * D;
-        float a = 0.f;
-        for (int d = 0; d < D; ++d) a = fmaf(hrow[d], wrow[d], a);
-        if (a > m) { m = a; arg = s; }
-    }
-    const size_t o = (size_t)b * V + v;
-    Y[o] = n > 0 ? log1pf(fmaxf(m + bias[v], 0.f)) : 0.f;
-    if (ARG) I[o] = arg;
 }
 
 // Register-only matrix-core probe: every wave issues `iters` rounds of four independent

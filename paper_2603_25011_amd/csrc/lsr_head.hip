@@ -4,12 +4,13 @@
 #include "lsr_head_measure.h"
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <string.h>
 
 #include <mutex>
 
 #include "bwd.hpp"
-#include "fwd_bf16.hpp"
+#include "fwd_mfma.hpp"
 #include "fwd_misc.hpp"
 #include "probes.hpp"
 
@@ -44,7 +45,7 @@ int check_desc(const lsr_head_desc* d, Shape* out) {
 
 inline bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
-// Chunks of the packed forward (see fwd_bf16.hpp).  The host does not know the lengths, so it sizes the
+// Chunks of the packed forward (see fwd_mfma.hpp).  The host does not know the lengths, so it sizes the
 // grid and the workspace for the longest block list the shape allows (every sequence full:
 // B * ceil(S/32) blocks, 8 per tile); chunks beyond the real list return at once.
 // Chunks and launch mode.  A unit of work is (chunk of tiles, vocabulary tile).
@@ -78,8 +79,31 @@ FwdChunks fwd_chunks(const Shape& s) {
     if (c.tpc < per_seq) c.tpc = (int)per_seq;
     c.n_chunks = (int)((tiles_max + c.tpc - 1) / c.tpc);
     // a sequence of one segment can never lie across a chunk boundary: no pieces, no merge pass
-    c.cut_possible = s.S > seg && c.n_chunks > 1;
+    // Float32 chunks are whole sequences.
+    c.cut_possible = s.dtype == LSR_BF16 && s.S > seg && c.n_chunks > 1;
     return c;
+}
+
+// Float32 problems: segments per window of a chunk (FwdParams::chunk_segs).  The float32 matrix rate makes a
+// unit an order of magnitude longer than in bfloat16, so what matters is how full the last round of units
+// is: the window of about half-tile granularity (short tiles cost what their live blocks cost) that gives the
+// least rounds x rows, on 256 CUs, with sequences taken to fill 70 % of S; never less than the longest
+// sequence, so that few windows come out empty.
+int fwd_f32_window(const Shape& s) {
+    const int seg = fwd_seg(s);
+    const int per_seq = (s.S + seg - 1) / seg;
+    const double segs = 0.7 * (double)s.B * per_seq;
+    const double vtiles = (double)((s.V + fwd_tn(FWD_NWN) - 1) / fwd_tn(FWD_NWN));
+    const int half = FWD_TM / seg / 2;
+    int best = 0;
+    double best_cost = 0.0;
+    for (int k = 1; k <= 16; ++k) {
+        const int L = k * half > per_seq ? k * half : per_seq;
+        const double units = ceil(segs / L) * vtiles;
+        const double cost = ceil(units / 256.0) * (L * seg + 32.0);
+        if (!best || cost < best_cost) { best = L; best_cost = cost; }
+    }
+    return best;
 }
 
 // ---- forward workspace: len[B] | pos[B*S] | seg0[B+1] | seg_meta[segs] | rows[segs*seg] |
@@ -91,7 +115,7 @@ FwdWs fwd_ws(const Shape& s) {
     const int seg = fwd_seg(s);
     const size_t blocks = (size_t)s.B * ((s.S + seg - 1) / seg);          // segments
     const FwdChunks c = fwd_chunks(s);
-    const size_t part = (s.dtype == LSR_BF16 && c.cut_possible) ? align_up(sizeof(float) * (size_t)c.n_chunks * s.V) : 0;
+    const size_t part = c.cut_possible ? align_up(sizeof(float) * (size_t)c.n_chunks * s.V) : 0;
     w.len_off = 0;
     w.pos_off = w.len_off + align_up(sizeof(int) * (size_t)s.B);
     w.blk0_off = w.pos_off + align_up(sizeof(int) * (size_t)s.B * s.S);
@@ -269,10 +293,10 @@ struct Prof {
 
 inline int launch_status() { return hipGetLastError() == hipSuccess ? LSR_OK : LSR_ERR_LAUNCH; }
 
-// Kernel choice: the direct-to-LDS ring when D is a multiple of the 64-wide K slab and H and W are
+// Kernel choice: the direct-to-LDS ring when a row is a whole number of 128-byte K slabs and H and W are
 // each below 4 GiB (32-bit byte offsets per lane), else the register-staged loader (64-bit addresses,
 // zero-fills the last slab).
-template <bool DMA, int SEG, bool RES>
+template <typename T, bool DMA, int SEG, bool RES>
 void launch_fwd_cfg(FwdParams p, int V, bool arg, int n_cus, hipStream_t st) {
     constexpr int TN = fwd_tn(FWD_NWN);
     p.n_vtiles = (V + TN - 1) / TN;
@@ -283,22 +307,23 @@ void launch_fwd_cfg(FwdParams p, int V, bool arg, int n_cus, hipStream_t st) {
     const long long n_units = (long long)((p.n_vtiles + p.gv - 1) / p.gv) * p.gv * p.n_chunks;
     const int n_wg = RES ? (n_cus >= 8 ? n_cus / 8 * 8 : 8) : (int)((n_units + 7) / 8 * 8);
     const dim3 grid(n_wg), block(fwd_threads(FWD_NWN));
-    if (arg) hipLaunchKernelGGL((fwd_bf16_kernel<true, DMA, SEG, RES>), grid, block, 0, st, p);
-    else     hipLaunchKernelGGL((fwd_bf16_kernel<false, DMA, SEG, RES>), grid, block, 0, st, p);
+    if (arg) hipLaunchKernelGGL((fwd_mfma_kernel<T, true, DMA, SEG, RES>), grid, block, 0, st, p);
+    else     hipLaunchKernelGGL((fwd_mfma_kernel<T, false, DMA, SEG, RES>), grid, block, 0, st, p);
 }
 
-void launch_fwd_bf16(const FwdParams& p, int seg, bool resident, bool arg, int n_cus, hipStream_t st) {
-    const bool small = (size_t)p.B * p.S * p.D * 2 < ((size_t)1 << 32) && (size_t)p.V * p.D * 2 < ((size_t)1 << 32);
-    const bool dma = p.D % 64 == 0 && small;
+template <typename T>
+void launch_fwd(const FwdParams& p, int seg, bool resident, bool arg, int n_cus, hipStream_t st) {
+    const bool small = (size_t)p.B * p.S * p.D * sizeof(T) < ((size_t)1 << 32) && (size_t)p.V * p.D * sizeof(T) < ((size_t)1 << 32);
+    const bool dma = p.D * sizeof(T) % 128 == 0 && small;
     if (!dma) {          // the register-staged loader has no prefetch across units to gain from
-        if (seg == FWD_BLK) launch_fwd_cfg<false, FWD_BLK, false>(p, p.V, arg, n_cus, st);
-        else launch_fwd_cfg<false, FWD_SEG_SHORT, false>(p, p.V, arg, n_cus, st);
+        if (seg == FWD_BLK) launch_fwd_cfg<T, false, FWD_BLK, false>(p, p.V, arg, n_cus, st);
+        else launch_fwd_cfg<T, false, FWD_SEG_SHORT, false>(p, p.V, arg, n_cus, st);
     } else if (seg == FWD_BLK) {
-        if (resident) launch_fwd_cfg<true, FWD_BLK, true>(p, p.V, arg, n_cus, st);
-        else launch_fwd_cfg<true, FWD_BLK, false>(p, p.V, arg, n_cus, st);
+        if (resident) launch_fwd_cfg<T, true, FWD_BLK, true>(p, p.V, arg, n_cus, st);
+        else launch_fwd_cfg<T, true, FWD_BLK, false>(p, p.V, arg, n_cus, st);
     } else {
-        if (resident) launch_fwd_cfg<true, FWD_SEG_SHORT, true>(p, p.V, arg, n_cus, st);
-        else launch_fwd_cfg<true, FWD_SEG_SHORT, false>(p, p.V, arg, n_cus, st);
+        if (resident) launch_fwd_cfg<T, true, FWD_SEG_SHORT, true>(p, p.V, arg, n_cus, st);
+        else launch_fwd_cfg<T, true, FWD_SEG_SHORT, false>(p, p.V, arg, n_cus, st);
     }
 }
 
@@ -322,8 +347,8 @@ int forward_impl(const lsr_head_desc* desc, const void* H, const void* W, const 
     int* pos = reinterpret_cast<int*>(static_cast<char*>(ws) + w.pos_off);
 
     prof.begin(0);
-    // batches of few tokens are packed by one workgroup in one launch (bf16 path)
-    const bool one_launch = s.dtype == LSR_BF16 && s.B <= PACK_MAX_B && (long)s.B * s.S <= PACK_MAX_TOKENS;
+    // batches of few tokens are packed by one workgroup in one launch
+    const bool one_launch = s.B <= PACK_MAX_B && (long)s.B * s.S <= PACK_MAX_TOKENS;
     if (!one_launch) hipLaunchKernelGGL(fwd_prep_kernel, dim3(s.B), dim3(PREP_THREADS), 0, st, mask, len, pos, s.S);
     char* base = static_cast<char*>(ws);
     int* blk0 = reinterpret_cast<int*>(base + w.blk0_off);
@@ -335,7 +360,7 @@ int forward_impl(const lsr_head_desc* desc, const void* H, const void* W, const 
     const int seg = fwd_seg(s);
     if (one_launch) {
         hipLaunchKernelGGL(fwd_pack_kernel, dim3(1), dim3(PACK_THREADS), 0, st, mask, len, pos, blk0, rows, blk_meta, s.B, s.S, seg);
-    } else if (s.dtype == LSR_BF16) {
+    } else {
         hipLaunchKernelGGL(fwd_plan_kernel, dim3(1), dim3(PLAN_THREADS), 0, st, len, blk0, s.B, seg);
         hipLaunchKernelGGL(fwd_rows_kernel, dim3(s.B), dim3(FWD_ROWS_THREADS), 0, st, len, pos, blk0, rows, blk_meta, s.S, seg);
     }
@@ -343,24 +368,22 @@ int forward_impl(const lsr_head_desc* desc, const void* H, const void* W, const 
     if ((rc = launch_status()) != LSR_OK) return rc;
 
     prof.begin(1);
+    FwdParams p;
+    p.H = H; p.W = W;
+    p.bias = bias; p.rows = rows; p.blk_meta = blk_meta; p.n_blocks = blk0 + s.B; p.Y = Y; p.I = I;
+    p.part_m = part_m; p.part_s = part_s;
+    p.B = s.B; p.S = s.S; p.D = s.D; p.V = s.V;
+    p.n_chunks = ck.n_chunks; p.tpc = ck.tpc;
+    p.seg0 = blk0;
+    p.chunk_segs = 0;
     if (s.dtype == LSR_F32) {
-        dim3 grid((s.V + F32_THREADS - 1) / F32_THREADS, s.B);
-        if (I) hipLaunchKernelGGL((fwd_f32_kernel<true>), grid, dim3(F32_THREADS), 0, st,
-                                  static_cast<const float*>(H), static_cast<const float*>(W), bias, len, pos, Y, I, s.S, s.D, s.V);
-        else   hipLaunchKernelGGL((fwd_f32_kernel<false>), grid, dim3(F32_THREADS), 0, st,
-                                  static_cast<const float*>(H), static_cast<const float*>(W), bias, len, pos, Y, I, s.S, s.D, s.V);
-    } else {
-        FwdParams p;
-        p.H = static_cast<const uint16_t*>(H);
-        p.W = static_cast<const uint16_t*>(W);
-        p.bias = bias; p.rows = rows; p.blk_meta = blk_meta; p.n_blocks = blk0 + s.B; p.Y = Y; p.I = I;
-        p.part_m = part_m; p.part_s = part_s;
-        p.B = s.B; p.S = s.S; p.D = s.D; p.V = s.V;
-        p.n_chunks = ck.n_chunks; p.tpc = ck.tpc;
-        launch_fwd_bf16(p, seg, ck.resident, I != nullptr, n_cus, st);
+        p.chunk_segs = fwd_f32_window(s);
+        p.n_chunks = (int)(((long)s.B * ((s.S + seg - 1) / seg) + p.chunk_segs - 1) / p.chunk_segs);
     }
+    if (s.dtype == LSR_F32) launch_fwd<float>(p, seg, ck.resident, I != nullptr, n_cus, st);
+    else launch_fwd<uint16_t>(p, seg, ck.resident, I != nullptr, n_cus, st);
     prof.end(1);
-    if (s.dtype == LSR_BF16 && ck.cut_possible) {
+    if (ck.cut_possible) {
         if ((rc = launch_status()) != LSR_OK) return rc;
         prof.begin(2);
         const dim3 grid((s.V + FWD_MERGE_THREADS - 1) / FWD_MERGE_THREADS, ck.n_chunks < FWD_MERGE_ROWS ? ck.n_chunks : FWD_MERGE_ROWS);

@@ -71,7 +71,7 @@ def mean(v):
 
 
 FWD_KERNELS = ("lsr::fwd_prep_kernel", "lsr::fwd_plan_kernel", "lsr::fwd_rows_kernel", "lsr::fwd_pack_kernel",
-               "lsr::fwd_bf16_kernel", "lsr::fwd_merge_kernel")
+               "lsr::fwd_mfma_kernel", "lsr::fwd_merge_kernel")
 BWD_KERNELS = ("lsr::bwd_count_kernel", "lsr::bwd_scan_kernel", "lsr::bwd_place_staged_kernel", "lsr::bwd_place_kernel",
                "lsr::bwd_chunk_bounds_kernel", "lsr::bwd_dh_sliced_kernel", "lsr::bwd_dw_sliced_kernel",
                "lsr::bwd_dw_tile_kernel", "lsr::bwd_dh_kernel", "lsr::bwd_dw_kernel")
@@ -115,10 +115,10 @@ def main():
                  "Calibration: lsr::copy_probe_kernel copies 1 GiB (1 048 576 KiB read, 1 048 576 KiB written) per launch and reads",
                  "  FETCH_SIZE %.0f -> scale %.3f;  WRITE_SIZE %.0f -> scale %.3f." % (cf, sf, cw, sw), "",
                  "Mean per dispatch (counter units are KiB as printed), and GB per forward / backward call after scaling",
-                 "(launches per call = dispatches of the kernel / dispatches of lsr::fwd_bf16_kernel resp. lsr::bwd_count_kernel):", "",
+                 "(launches per call = dispatches of the kernel / dispatches of lsr::fwd_mfma_kernel resp. lsr::bwd_count_kernel):", "",
                  "%-32s %9s %14s %14s %10s %10s" % ("kernel", "launches", "FETCH_SIZE", "WRITE_SIZE", "read GB", "write GB")]
         tot = {"fwd": [0.0, 0.0], "bwd": [0.0, 0.0]}
-        calls = {"fwd": float(len(fetch.get("lsr::fwd_bf16_kernel", {}).get("FETCH_SIZE", [])) or 1),
+        calls = {"fwd": float(len(fetch.get("lsr::fwd_mfma_kernel", {}).get("FETCH_SIZE", [])) or 1),
                  "bwd": float(len(fetch.get("lsr::bwd_count_kernel", {}).get("FETCH_SIZE", [])) or 1)}
         for k in FWD_KERNELS + BWD_KERNELS:
             f, w = fetch.get(k, {}).get("FETCH_SIZE", []), write.get(k, {}).get("WRITE_SIZE", [])
@@ -131,7 +131,7 @@ def main():
             side = "fwd" if k in FWD_KERNELS else "bwd"
             tot[side][0] += rgb
             tot[side][1] += wgb
-            if k == "lsr::fwd_bf16_kernel":
+            if k == "lsr::fwd_mfma_kernel":
                 traffic["fwd_fused_kernel_bytes"] = int((rgb + wgb) * 1e9)
         lines += ["", "forward : %.3f GB read + %.3f GB written per call" % tuple(tot["fwd"]),
                   "backward: %.3f GB read + %.3f GB written per call" % tuple(tot["bwd"])]
@@ -162,9 +162,9 @@ def main():
         traffic["bwd_l2"] = l2_json
 
     sq = counters(os.path.join(d, "sq"))
-    if sq.get("lsr::fwd_bf16_kernel"):
-        c = {k: mean(v) for k, v in sq["lsr::fwd_bf16_kernel"].items()}
-        lines = ["rocprofv3 SQ counters of lsr::fwd_bf16_kernel, workload %s, MI355X, one GPU (mean per dispatch)." % args.workload,
+    if sq.get("lsr::fwd_mfma_kernel"):
+        c = {k: mean(v) for k, v in sq["lsr::fwd_mfma_kernel"].items()}
+        lines = ["rocprofv3 SQ counters of lsr::fwd_mfma_kernel, workload %s, MI355X, one GPU (mean per dispatch)." % args.workload,
                  "  rocprofv3 --pmc SQ_INSTS_VALU_MFMA_MOPS_BF16 SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CYCLES SQ_WAVES SQ_LDS_BANK_CONFLICT \\",
                  "      SQ_INSTS_LDS SQ_WAVE_CYCLES SQ_WAIT_INST_ANY GRBM_GUI_ACTIVE -d gpurun_out/prof/sq -o sq --output-format csv -- \\",
                  "      python3 bench.py --no-cpu --no-extra --steps 3 --warmup 1", ""]
@@ -178,7 +178,7 @@ def main():
                       "matrix-core busy = MFMA_BUSY / (4 SIMDs x 256 CUs x cycles)   %.3f" % busy]
             if c.get("SQ_INSTS_VALU_MFMA_MOPS_BF16"):
                 lines.append("flops issued = MOPS_BF16 x 512                 %.4g" % (c["SQ_INSTS_VALU_MFMA_MOPS_BF16"] * 512.0))
-        out["fwd_bf16_kernel_sq_counters"] = "\n".join(lines)
+        out["fwd_mfma_kernel_sq_counters"] = "\n".join(lines)
 
     sqb = counters(os.path.join(d, "sqb"))
     if any(sqb.get(k) for k in GATHER_KERNELS):

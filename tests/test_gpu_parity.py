@@ -104,6 +104,31 @@ def test_fp32_small_shapes():
     print(run_case(wl.make_custom(200, 6, 64, 100, dtype="f32", seed=7, w_std=0.05)))
 
 
+@pytest.mark.parametrize("B,S,D,V,len_lo", [
+    (1, 1, 8, 1, 1),           # smallest legal shape; register-staged loader, one short slab
+    (2, 16, 32, 257, 1),       # one slab of 32 through the direct loader
+    (5, 64, 96, 300, 1),       # odd slab count, short segments
+    (70, 33, 64, 600, 1),      # more than 64 sequences: the search for a chunk's first sequence takes two rounds
+    (3, 300, 128, 700, 200),   # sequences longer than a tile
+    (90, 90, 40, 513, 1),      # D not a multiple of 32, sequences with and without a second segment
+])
+def test_fp32_matrix_core_forward(B, S, D, V, len_lo):
+    """Float32 logits are sums of D products of float32 values: a sum in any order is within D * 2^-24 of the sum of
+    the magnitudes, and Y moves by no more than the logit does."""
+    inp = wl.make_custom(B, S, D, V, dtype="f32", seed=B * 1000 + S, len_lo=len_lo, w_std=0.05)
+    rng = np.random.default_rng(S)
+    for mask in (None, wl.scattered_mask(rng, B, S)):
+        head = DeviceHead(inp, mask=mask)
+        head.poison_outputs()
+        head.forward()
+        torch.cuda.synchronize()
+        Y, I = head.Y.cpu().numpy(), head.I.cpu().numpy()
+        Y_ref, _, _, _ = parity.compare_forward(inp, Y, I, mask=mask)
+        size = np.abs(inp.H.astype(np.float64)).max(axis=(0, 1)) @ np.abs(inp.W.astype(np.float64)).max(axis=0)
+        assert np.abs(Y - Y_ref).max() <= (D + 4) * 2.0 ** -24 * (size + np.abs(Y_ref).max())
+    run_case(inp)
+
+
 def test_scattered_mask_and_empty_rows():
     inp = wl.make_custom(6, 150, 128, 600, seed=77)
     rng = np.random.default_rng(3)
