@@ -514,6 +514,8 @@ __global__ __launch_bounds__(ROW_THREADS) void bwd_dw_kernel(const T* __restrict
 // ---------------------------------------------------------------------------------------------
 constexpr int DWS_COLS = 64;
 constexpr int DH_NLD = 4;                 // gathers in flight per lane of the sliced dH gather
+// threads per workgroup: one bucket if WPB > 1 waves share it, else four waves of BPW buckets each
+constexpr int dh_threads(int wpb) { return wpb > 1 ? 64 * wpb : 256; }
 constexpr int PERM_SLACK = 256;           // entries the workspace keeps behind the sorted lists (see bwd_dh_sliced_kernel)
 
 // Slices owned by XCDs.  Workgroup ids go round-robin over the chip's 8 XCDs (id & 7), each with an L2
@@ -723,8 +725,8 @@ __global__ __launch_bounds__(256) void bwd_chunk_bounds_kernel(const int* __rest
     bounds[idx] = lo;
 }
 
-template <typename T, int BPW, typename OT, bool OFF32>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void bwd_dh_sliced_kernel(const T* __restrict__ W,
+template <typename T, int BPW, int WPB, typename OT, bool OFF32>
+__global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu(8, 8))) void bwd_dh_sliced_kernel(const T* __restrict__ W,
                                                             const int* __restrict__ bounds,
                                                             const uint2* __restrict__ perm,
                                                             const float* prev_sum, OT* dH, int add_dst, int write_all,
@@ -738,6 +740,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     constexpr int NLD = DH_NLD;                // gathers in flight per lane (8: more registers, fewer
                                                // waves; C5 2.83 -> 3.71 ms)
     static_assert(2 * G <= PERM_SLACK, "entries read behind the end of a list stay inside the slack");
+    static_assert(WPB == 1 || BPW == 1, "either several buckets per wave or several waves per bucket");
+    constexpr int BLK = G * WPB;               // entries between a wave's consecutive blocks
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     int dc, g;
@@ -755,16 +759,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     // fastest, the empty buckets behind the end of each sequence recur with a period that can leave
     // some engines with twice the work of others.
     const int b = g % B;
-    const int s = ((g / B) * 4 + wave) * BPW + lane / G;
+    const int s = WPB > 1 ? g / B : ((g / B) * 4 + wave) * BPW + lane / G;
     const bool live = s < S;
     const int bq = live ? b * S + s : 0;
     const size_t bi = n_vc == 1 ? (size_t)b * (S + 1) + s : (size_t)bq * (n_vc + 1) + vc;
     const int beg = live ? bounds[bi] : 0;
     const int end = live ? bounds[bi + 1] : 0;
-    if (!write_all && !__any(beg < end)) return;      // nothing of this chunk in any bucket of the wave
+    if (!write_all && !__any(beg < end)) return;      // nothing of this chunk in any bucket of the wave (WPB > 1: of the workgroup)
     const int col0 = dc * DWS_COLS + (lane % LPR) * N;
     const int sub = (lane % G) / LPR;
-    const bool writer = live && sub == 0 && (write_all || beg < end);
+    const bool writer = live && sub == 0 && (write_all || beg < end) && (WPB == 1 || wave == 0);
     const size_t o = (size_t)bq * D + col0;
     float acc[N];
 #pragma unroll
@@ -801,10 +805,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     const uint32_t col_bytes = (uint32_t)col0 * (uint32_t)sizeof(T);
     const int li = lane % G;                   // lane within its bucket
     const int src0 = (lane - li + sub) * 4;    // bpermute address of the lane holding entry `sub` of the block
-    const uint2* pe = pl + beg + li;           // this lane's entry of the current block
+    int left = end - beg - (WPB > 1 ? wave * G : 0);                // entries from the block's start to the end of the list
+    const uint2* pe = pl + beg + li + (WPB > 1 && left > 0 ? wave * G : 0);      // this lane's entry of the current block
     uint2 cur = *pe;
-    for (int left = end - beg; left > 0; left -= G) {               // entries from the block's start to the end of the list
-        pe += G;
+    for (; left > 0; left -= BLK) {
+        // with several waves per bucket only a block that exists is requested (BLK entries may be more than the slack)
+        pe += WPB == 1 || left > BLK ? BLK : 0;
         const uint2 nxt = *pe;
         __builtin_amdgcn_sched_barrier(0);                          // the next block is requested first
         const int v_first = __builtin_amdgcn_ds_bpermute((lane - li) * 4, (int)cur.x);      // the block's first entry: inside the list
@@ -845,6 +851,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     for (int off = LPR; off < G; off <<= 1)
 #pragma unroll
         for (int i = 0; i < N; ++i) acc[i] += __shfl_xor(acc[i], off);
+    if constexpr (WPB > 1) {
+        // the waves' sums, added in wave order (the exit above is taken by all waves of a bucket or by none)
+        __shared__ __attribute__((aligned(16))) float s_sum[WPB][DWS_COLS];
+        if (sub == 0 && wave > 0) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) s_sum[wave][(lane % LPR) * N + i] = acc[i];
+        }
+        __syncthreads();
+        if (!writer) return;
+#pragma unroll
+        for (int w = 1; w < WPB; ++w)
+#pragma unroll
+            for (int i = 0; i < N; ++i) acc[i] += s_sum[w][(lane % LPR) * N + i];
+    }
     if (writer) {
 #pragma unroll
         for (int i = 0; i < N / 4; ++i)

@@ -199,6 +199,30 @@ int dh_buckets_per_wave(const Shape& s, int n_vc) {
     return bpw;
 }
 
+// Waves that share a bucket of the sliced dH gather (then one bucket per workgroup, else four waves with buckets
+// of their own).  One wave per long list leaves the launch waiting for its longest lists (a sequence of 4 tokens
+// has |V| / 4 entries per bucket), and the chip half empty where buckets are few; a wave more per bucket costs
+// about 0.2 ns of launch and prologue also where the bucket turns out empty (padding, sparse gradients).
+// List lengths as estimated above, in the time of bfloat16 entries (a float32 row piece takes twice the lanes).
+// Measured (dH us with 1 / 2 / 4 / 8 waves; waves at one per bucket, estimated entries per bucket and chunk):
+// B=100 S=24 D=384 |V|=60000 (14k, 1786) 538 / 420 / 308 / 281; B=24 S=50 D=512 |V|=120000 (10k, 857) 438 / 367 /
+// 294 / 250; B=10 S=60 D=768 |V|=200000 (7k, 680) 361 / 317 / 292 / 324; B=60 S=40 D=768 |V|=200000 (29k, 1020)
+// 2046 / 1675 / 1174 / 1241; B=30 S=80 D=256 |V|=25000 (10k, 446) 54 / 39 / 32 / 45; float32 B=64 S=32 D=768
+// |V|=30522 (25k, 681) 865 / 537 / 421 / 344; B=32 S=128 D=1024 |V|=30522 (66k, 341) 200 / 144 / 169 / 291;
+// B=256 S=32 D=768 |V|=30522 (98k, 1363) 910 / 659 / 626 / 830, with one gradient in twenty 63 / 86 / 142 / 301;
+// B=64 S=100 D=768 |V|=50000 (77k, 357) 305 / 294 / 381 / 618, with one in twenty 70 / 107 / 192; B=150 S=60 D=768 |V|=40000 (108k, 476) 482 / 474 / 567 /
+// 880; B=16 S=256 |V|=250002 (49k, 174) 602 / 602 / 743; B=12 S=300 |V|=100000 (43k, 159) 175 / 195 / 291;
+// B=200 S=100 D=768 |V|=30522 (240k, 436) 481 / 501 / 602; B=250 S=60 D=1024 |V|=100000 (240k, 595) 2513 / 2519 / 2828,
+// with one in twenty 442 / 626 / 1142.
+// From 64k waves on what long lists win is no more than what sparse gradients lose.
+int dh_waves_per_bucket(const Shape& s, int n_vc) {
+    const double list = (double)s.V / ((0.7 * s.S > 1.0 ? 0.7 * s.S : 1.0) * n_vc) * (s.dtype == LSR_F32 ? 2.0 : 1.0);
+    const long long waves = (long long)s.B * s.S * (s.D / DWS_COLS);
+    if (waves <= 4096 && list >= 64.0) return 4;           // latency alone (B=2 S=16 D=64 |V|=1000: 16 -> 6.4 us)
+    if (list < 256.0 || waves > 65536) return 1;
+    return waves > 32768 ? 2 : (list >= 1024.0 ? 8 : 4);
+}
+
 // Sequences per launch of the sliced dW gather.  The gather is L2-resident while the H slice of the
 // sequences in flight (rows x 64 columns) is about 4 MB; larger batches are cut into chunks of
 // consecutive sequences, each launch adding to dW (8*|V|*D bytes re-read and re-written per extra
@@ -422,17 +446,20 @@ void launch_dw(int cpt, dim3 grid, size_t lds, hipStream_t st, const T* H, const
 
 // One launch of the sliced dH gather (vocabulary chunk vc) / of the sliced dW gather (sequences b0 .. b0+nb-1).
 template <typename T, typename OT>
-void launch_dh_sliced(int bpw, dim3 grid, hipStream_t st, const T* W, const int* bounds, const uint2* perm, const float* prev,
+void launch_dh_sliced(int bpw, int wpb, dim3 grid, hipStream_t st, const T* W, const int* bounds, const uint2* perm, const float* prev,
                       OT* dst, int add_dst, int write_all, const Shape& s, int n_groups, int n_vc, int vc, bool xcd_own) {
     // 32-bit byte offsets into W (one multiply-add of 24-bit factors per gather) where W allows them
     const bool off32 = (size_t)s.V * s.D * sizeof(T) <= 0xffffffffull && s.V <= (1 << 24) && (size_t)s.D * sizeof(T) < (1u << 24);
-#define LSR_DH2(BPW, O32) hipLaunchKernelGGL((bwd_dh_sliced_kernel<T, BPW, OT, O32>), grid, dim3(256), 0, st, W, bounds, perm, prev, dst, \
-                                             add_dst, write_all, s.B, s.S, s.D, s.V, n_groups, n_vc, vc, xcd_own ? 1 : 0)
-#define LSR_DH(BPW) do { if (off32) LSR_DH2(BPW, true); else LSR_DH2(BPW, false); } while (0)
-    if (bpw == 1) LSR_DH(1);
-    else if (bpw == 2) LSR_DH(2);
-    else if (bpw == 4 || sizeof(T) == 4) LSR_DH(4);      // a float row piece takes 16 lanes: at most four buckets per wave
-    else if constexpr (sizeof(T) == 2) LSR_DH(8);
+#define LSR_DH2(BPW, WPB, O32) hipLaunchKernelGGL((bwd_dh_sliced_kernel<T, BPW, WPB, OT, O32>), grid, dim3(dh_threads(WPB)), 0, st, W, bounds, \
+                                                  perm, prev, dst, add_dst, write_all, s.B, s.S, s.D, s.V, n_groups, n_vc, vc, xcd_own ? 1 : 0)
+#define LSR_DH(BPW, WPB) do { if (off32) LSR_DH2(BPW, WPB, true); else LSR_DH2(BPW, WPB, false); } while (0)
+    if (wpb == 8) LSR_DH(1, 8);
+    else if (wpb == 4) LSR_DH(1, 4);
+    else if (wpb == 2) LSR_DH(1, 2);
+    else if (bpw == 1) LSR_DH(1, 1);
+    else if (bpw == 2) LSR_DH(2, 1);
+    else if (bpw == 4 || sizeof(T) == 4) LSR_DH(4, 1);   // a float row piece takes 16 lanes: at most four buckets per wave
+    else if constexpr (sizeof(T) == 2) LSR_DH(8, 1);
 #undef LSR_DH
 #undef LSR_DH2
 }
@@ -527,7 +554,7 @@ struct BwdLaunch {
     int cpt;                 // 16-byte chunks per thread of the whole-row kernels
     bool staged_place;       // the bucket sort places through LDS
     bool dh_sliced;          // column-sliced dH gather (D a multiple of 64)
-    int bpw, dh_groups;      // buckets per wave and workgroups per slice of the sliced dH gather
+    int bpw, wpb, dh_groups; // buckets per wave, waves per bucket and workgroups per slice of the sliced dH gather
     int dw_vt;               // rows of the dW staging tile: sliced gather if dw_sliced, else whole-row kernel
     bool dw_sliced;
     int dw_bc, dw_ndc, dw_slice_groups, dw_vtiles;
@@ -562,7 +589,8 @@ int plan_backward(const Shape& s, const BwdWs& w, BwdLaunch* L) {
     L->staged_place = s.S <= PLACE_MAX_S && w.seg_len <= PLACE_MAX_SEG;      // plan[3] of lsr_head_plan
     L->dh_sliced = s.D % DWS_COLS == 0;
     L->bpw = L->dh_sliced ? dh_buckets_per_wave(s, w.n_vc) : 0;
-    L->dh_groups = L->dh_sliced ? s.B * ((s.S + 4 * L->bpw - 1) / (4 * L->bpw)) : 0;
+    L->wpb = L->dh_sliced ? dh_waves_per_bucket(s, w.n_vc) : 1;
+    L->dh_groups = !L->dh_sliced ? 0 : L->wpb > 1 ? s.B * s.S : s.B * ((s.S + 4 * L->bpw - 1) / (4 * L->bpw));
     if ((long long)L->dh_groups * (s.D / DWS_COLS) > 0x7fffffffll) return LSR_ERR_SHAPE;
     L->dh_xcd_own = L->dh_sliced && dh_slices_owned(s);
     if (L->dh_xcd_own && xcd_slice_grid(s.D / DWS_COLS, L->dh_groups, 1) > 0x7fffffffll) return LSR_ERR_SHAPE;
@@ -700,16 +728,16 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
                     // partial sums live in dH itself; the first chunk of a fresh result writes every bucket
                     float* d = reinterpret_cast<float*>(dH);
                     const bool fresh = vc == 0 && !accumulate;
-                    launch_dh_sliced<T, float>(L.bpw, grid, st, W, bounds, perm, fresh ? nullptr : d, d, 0, fresh ? 1 : 0, s, L.dh_groups,
+                    launch_dh_sliced<T, float>(L.bpw, L.wpb, grid, st, W, bounds, perm, fresh ? nullptr : d, d, 0, fresh ? 1 : 0, s, L.dh_groups,
                                                w.n_vc, vc, L.dh_xcd_own);
                 } else if (w.n_vc == 1) {
-                    launch_dh_sliced<T, OT>(L.bpw, grid, st, W, bounds, perm, nullptr, dH, accumulate, accumulate ? 0 : 1, s, L.dh_groups,
+                    launch_dh_sliced<T, OT>(L.bpw, L.wpb, grid, st, W, bounds, perm, nullptr, dH, accumulate, accumulate ? 0 : 1, s, L.dh_groups,
                                             w.n_vc, vc, L.dh_xcd_own);
                 } else if (!last) {
-                    launch_dh_sliced<T, float>(L.bpw, grid, st, W, bounds, perm, vc > 0 ? stage : nullptr, stage, 0, vc == 0 ? 1 : 0, s,
+                    launch_dh_sliced<T, float>(L.bpw, L.wpb, grid, st, W, bounds, perm, vc > 0 ? stage : nullptr, stage, 0, vc == 0 ? 1 : 0, s,
                                                L.dh_groups, w.n_vc, vc, L.dh_xcd_own);
                 } else {
-                    launch_dh_sliced<T, OT>(L.bpw, grid, st, W, bounds, perm, stage, dH, accumulate, 1, s, L.dh_groups, w.n_vc, vc, L.dh_xcd_own);
+                    launch_dh_sliced<T, OT>(L.bpw, L.wpb, grid, st, W, bounds, perm, stage, dH, accumulate, 1, s, L.dh_groups, w.n_vc, vc, L.dh_xcd_own);
                 }
             }
         } else {

@@ -86,6 +86,19 @@ def test_large_batches_whole_row_dw_beside_sliced_dh(B, S, D, V):
     print(run_case(inp))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,S,D,V,dy_keep", [
+    (3, 10, 64, 1000, None),       # four waves per bucket, few buckets; lists of one or two 64-entry blocks per wave
+    (2, 5, 64, 3000, 0.02),        # ... lists shorter than a block: waves without entries
+    (100, 24, 128, 60000, None),   # eight waves per bucket, two vocabulary chunks
+    (100, 24, 128, 40000, 0.05),
+    (40, 30, 256, 9000, None),     # four waves per bucket
+    (3300, 10, 64, 2000, None),    # two waves per bucket (33 000 waves at one)
+])
+def test_dh_lists_shared_by_waves(B, S, D, V, dy_keep, dtype):
+    print(run_case(wl.make_custom(B, S, D, V, dtype=dtype, seed=B + S, len_lo=1, dy_keep=dy_keep)))
+
+
 def test_forward_beyond_the_backward_length_limit():
     # S above 8192 is forward-only
     inp = wl.make_custom(2, 9000, 64, 40, seed=31, len_lo=8000, backward=False)
