@@ -68,13 +68,14 @@ int lsr_gather_probe(const void* table, size_t window_bytes, int steps, int laun
 
 /*
  * The launch plan the host derives from a shape alone, for inspection and tests (no device needed,
- * nothing is launched).  Writes LSR_PLAN_SLOTS int32 values to the HOST array `plan`:
+ * nothing is launched).  [4] to [7] and [12] describe shapes whose D is a multiple of 64; other shapes report one
+ * chunk and zeros there and run the same kernels by the same rules.  Writes LSR_PLAN_SLOTS int32 values to the HOST array `plan`:
  *   [0] most tiles per chunk of the packed forward    [1] segments of the bucket sort per sequence
  *   [2] vocabulary entries per sort segment       [3] 1 if the sort places through LDS, else 0
  *   [4] vocabulary chunks of the dH gather        [5] vocabulary entries per chunk
- *   [6] buckets per wave in the sliced dH gather (0: whole-row dH kernel, D not a multiple of 64), where a wave
+ *   [6] buckets per wave in the sliced dH gather (0 for D not a multiple of 64), where a wave
  *       has buckets of its own (long lists of few buckets are shared by the waves of a workgroup instead)
- *   [7] rows of the sliced dW gather's staging tile (0: whole-row dW kernel)
+ *   [7] rows of the sliced dW gather's staging tile (0: whole-row dW kernel, or D not a multiple of 64)
  *   [8] sequences per launch of the sliced dW gather (B: one launch)
  *   [9] chunks the forward grid provides for (the longest token list the shape allows); float32 problems are cut
  *       into whole sequences instead, in windows of the length the launch picks

@@ -319,72 +319,6 @@ __global__ __launch_bounds__(256) void bwd_place_staged_kernel(const float* __re
 }
 
 // ---------------------------------------------------------------------------------------------
-// dH[b,s,:] = sum over the bucket of (b,s), in ascending v, of g * W[v,:].   grid (B, S): b fastest,
-// so that the empty buckets behind the ends of the sequences are spread evenly over the chip
-// ---------------------------------------------------------------------------------------------
-// accumulate: the sums are added to what dH holds
-template <typename T, int CPT, typename OT>
-__global__ __launch_bounds__(ROW_THREADS) void bwd_dh_kernel(const T* __restrict__ W,
-                                                             const int* __restrict__ bstart,
-                                                             const uint2* __restrict__ perm,
-                                                             OT* __restrict__ dH,
-                                                             int S, int D, int V, int accumulate) {
-    constexpr int N = RowChunk<T>::N;
-    __shared__ int s_v[ROW_THREADS];
-    __shared__ float s_g[ROW_THREADS];
-    const int b = blockIdx.x, s = blockIdx.y, tid = threadIdx.x;
-    const int n_chunks = D / N;
-    const int beg = bstart[(size_t)b * (S + 1) + s];
-    const int end = bstart[(size_t)b * (S + 1) + s + 1];
-    const size_t prow = (size_t)b * V;
-    float acc[CPT][N];
-#pragma unroll
-    for (int cp = 0; cp < CPT; ++cp)
-#pragma unroll
-        for (int i = 0; i < N; ++i) acc[cp][i] = 0.f;
-
-    for (int base = beg; base < end; base += ROW_THREADS) {
-        const int n = min(ROW_THREADS, end - base);
-        const uint2 ent = tid < n ? perm[prow + base + tid] : make_uint2(0u, 0u);   // padding: row 0, weight 0
-        s_v[tid] = (int)ent.x;
-        s_g[tid] = __uint_as_float(ent.y);
-        __syncthreads();
-        for (int k = 0; k < n; k += 4) {
-            uint4 x[4][CPT];
-            float g[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                g[u] = s_g[k + u];
-                const T* src = W + (size_t)s_v[k + u] * D;
-#pragma unroll
-                for (int cp = 0; cp < CPT; ++cp) {
-                    const int c = tid + cp * ROW_THREADS;
-                    x[u][cp] = c < n_chunks ? *reinterpret_cast<const uint4*>(src + c * N) : make_uint4(0, 0, 0, 0);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int cp = 0; cp < CPT; ++cp) RowChunk<T>::fma(x[u][cp], g[u], acc[cp]);
-        }
-        __syncthreads();
-    }
-    OT* out = dH + ((size_t)b * S + s) * D;
-#pragma unroll
-    for (int cp = 0; cp < CPT; ++cp) {
-        const int c = tid + cp * ROW_THREADS;
-        if (c < n_chunks) {
-#pragma unroll
-            for (int i = 0; i < N; i += 4) {
-                float4 r = make_float4(acc[cp][i], acc[cp][i + 1], acc[cp][i + 2], acc[cp][i + 3]);
-                if (accumulate) r = add4(OutVec<OT>::load4(out + c * N + i), r);
-                OutVec<OT>::store4(out + c * N + i, r);
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
 // dW[v,:] = sum_b g[b,v] * H[b, I[b,v], :],  db[v] = sum_b g[b,v].
 // A workgroup owns VT consecutive vocabulary rows.  It first stages g and I for all B x VT pairs in
 // LDS (coalesced along v), then walks the rows one by one, skipping pairs with g = 0.
@@ -485,7 +419,7 @@ __global__ __launch_bounds__(ROW_THREADS) void bwd_dw_kernel(const T* __restrict
 }
 
 // ---------------------------------------------------------------------------------------------
-// dW/db, column-sliced variant (D a multiple of 64).
+// dW/db, column-sliced variant.
 // The gathers of the kernel above hit rows of H scattered over all of H (tens of MB), so they are
 // served by the memory-side cache at a fraction of the L2 rate.  Here the work is cut into slices of
 // 64 hidden-state columns and the grid is ordered slice-major: the workgroups resident at any time
@@ -510,13 +444,16 @@ __global__ __launch_bounds__(ROW_THREADS) void bwd_dw_kernel(const T* __restrict
 // the caller's gradient), and dst is float32 or bfloat16 (OT).  A float32 result spread over several
 // launches passes prev = dst; a bfloat16 result keeps its partial sums in a float32 staging array (dst of
 // all launches but the last, prev of all but the first), so that it is rounded once.
-// dynamic LDS: B*VT floats + B*VT ints.   grid = ceil(V/VT) * ceil((D/64)/NDC).
+// dynamic LDS: B*VT floats + B*VT ints.   grid = (ceil(V/VT), ceil(ceil(D/64)/NDC)).
 // ---------------------------------------------------------------------------------------------
 constexpr int DWS_COLS = 64;
 constexpr int DH_NLD = 4;                 // gathers in flight per lane of the sliced dH gather
 // threads per workgroup: one bucket if WPB > 1 waves share it, else four waves of BPW buckets each
 constexpr int dh_threads(int wpb) { return wpb > 1 ? 64 * wpb : 256; }
 constexpr int PERM_SLACK = 256;           // entries the workspace keeps behind the sorted lists (see bwd_dh_sliced_kernel)
+
+// column slices of a row (D a multiple of 8: the last one may be partly filled)
+__host__ __device__ constexpr int n_slices(int D) { return (D + DWS_COLS - 1) / DWS_COLS; }
 
 // Slices owned by XCDs.  Workgroup ids go round-robin over the chip's 8 XCDs (id & 7), each with an L2
 // of its own.  With n_dc = 8 q + r column slices, XCD x owns slices x, x + 8, ..., x + 8 (q - 1): every
@@ -567,8 +504,7 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
                                                             const int* __restrict__ I,
                                                             const float* prev, OT* dW, int add_dst,
                                                             float* __restrict__ db, int add_db,
-                                                            int b_first, int B, int S, int D, int V, int VT,
-                                                            int n_vtiles, int NDC) {
+                                                            int b_first, int B, int S, int D, int V, int VT, int NDC) {
     // b_first, B: the sequences of this launch; prev / add_dst: see above; add_db: db already holds the
     // sums over the sequences before b_first (or the caller's accumulated gradient) and is added to
     constexpr int N = RowChunk<T>::N;          // elements per 16-byte chunk
@@ -582,10 +518,10 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int n_waves = blockDim.x >> 6;
-    const int dg = blockIdx.x / n_vtiles;                  // slice-group-major order
-    const int v0 = (blockIdx.x - dg * n_vtiles) * VT;
+    const int dg = blockIdx.y;                             // slice-group-major order
+    const int v0 = blockIdx.x * VT;
     const int dc_begin = dg * NDC;
-    const int dc_end = min(D / DWS_COLS, dc_begin + NDC);
+    const int dc_end = min(n_slices(D), dc_begin + NDC);
 
     // staging, four independent (dY, Y, I) triples in flight per thread
     for (int e0 = tid; e0 < B * VT; e0 += 4 * blockDim.x) {
@@ -647,7 +583,8 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
     if (!dW) return;
 
     for (int dc = dc_begin; dc < dc_end; ++dc) {
-        const int col0 = dc * DWS_COLS + (lane % LPR) * N;
+        const int col = dc * DWS_COLS + (lane % LPR) * N;
+        const int col0 = col < D ? col : 0;                    // behind D: gathers column 0, stores nothing
         for (int grp = wave; grp * VPG < VT; grp += n_waves) {
             const int vv = grp * VPG + lane / LPR;
             const int v = v0 + vv;
@@ -670,7 +607,7 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
                 for (int u = 0; u < 8; ++u) RowChunk<T>::fma(x[u], g[u], acc);
                 if (COMPACT && !open) break;
             }
-            if (v < V) {
+            if (v < V && col < D) {
                 const size_t o = (size_t)v * D + col0;
 #pragma unroll
                 for (int i = 0; i < N; i += 4) {
@@ -685,7 +622,7 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
 }
 
 // ---------------------------------------------------------------------------------------------
-// dH, column-sliced variant (D a multiple of 64).
+// dH, column-sliced variant.
 // One sub-group of a wave owns one bucket and one 64-column slice; the grid is ordered slice-major.
 // A 64-column piece of a row is LPR lanes x 16 bytes, so a sub-group of G = 64/BPW lanes gathers
 // G/LPR bucket entries per load, keeps four loads in flight per lane, and folds the per-entry
@@ -702,7 +639,7 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
 // As in the dW gather, `prev` (float32, may be null) is added to the sums of this launch, `add_dst` adds
 // what dst already holds, dst is float32 or bfloat16; `write_all` makes every bucket write (the launch
 // that produces the final value of a fresh result), otherwise only buckets with entries in this chunk do.
-// grid = B * ceil(S / (4*BPW)) * (D/64), 256 threads.
+// grid = (B * ceil(S / (4*BPW)), ceil(D/64)), or xcd_slice_grid workgroups; 256 threads.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void bwd_chunk_bounds_kernel(const int* __restrict__ bstart,
                                                                const uint2* __restrict__ perm,
@@ -746,13 +683,13 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
     const int wave = threadIdx.x >> 6;
     int dc, g;
     if (xcd_own) {                                                 // slices owned by XCDs (see xcd_slice_unit)
-        const XcdSliceUnit u = xcd_slice_unit(blockIdx.x, D / DWS_COLS, n_groups, 1);
+        const XcdSliceUnit u = xcd_slice_unit(blockIdx.x, n_slices(D), n_groups, 1);
         if (!u.valid) return;
         dc = u.dc_first;
         g = u.item;
     } else {
-        dc = blockIdx.x / n_groups;                                // slice-major order
-        g = blockIdx.x - dc * n_groups;
+        dc = blockIdx.y;                                           // slice-major order
+        g = blockIdx.x;
     }
     // Within a slice, consecutive workgroups take the same positions of consecutive sequences
     // (b fastest).  Workgroups are dealt to the chip's shader engines in a fixed rotation; with s
@@ -767,8 +704,9 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
     const int end = live ? bounds[bi + 1] : 0;
     if (!write_all && !__any(beg < end)) return;      // nothing of this chunk in any bucket of the wave (WPB > 1: of the workgroup)
     const int col0 = dc * DWS_COLS + (lane % LPR) * N;
+    const bool col_ok = col0 < D;              // the last slice may be partly filled: the lanes behind D gather column 0
     const int sub = (lane % G) / LPR;
-    const bool writer = live && sub == 0 && (write_all || beg < end) && (WPB == 1 || wave == 0);
+    const bool writer = live && col_ok && sub == 0 && (write_all || beg < end) && (WPB == 1 || wave == 0);
     const size_t o = (size_t)bq * D + col0;
     float acc[N];
 #pragma unroll
@@ -802,7 +740,7 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
     const char* const Wb = reinterpret_cast<const char*>(W);
     const uint2* const pl = perm + (size_t)b * V;                   // b: the same for the whole workgroup
     const uint32_t row_bytes = (uint32_t)D * (uint32_t)sizeof(T);
-    const uint32_t col_bytes = (uint32_t)col0 * (uint32_t)sizeof(T);
+    const uint32_t col_bytes = (uint32_t)(col_ok ? col0 : 0) * (uint32_t)sizeof(T);
     const int li = lane % G;                   // lane within its bucket
     const int src0 = (lane - li + sub) * 4;    // bpermute address of the lane holding entry `sub` of the block
     int left = end - beg - (WPB > 1 ? wave * G : 0);                // entries from the block's start to the end of the list
@@ -874,7 +812,7 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
 }
 
 // ---------------------------------------------------------------------------------------------
-// dW/db, LDS-tile variant (bfloat16 inputs, D a multiple of 64, DWT_MIN_S <= S <= DWT_MAX_S).
+// dW/db, LDS-tile variant (bfloat16 inputs, DWT_MIN_S <= S <= DWT_MAX_S).
 // A workgroup of 1024 threads owns 1024 consecutive vocabulary rows and one 64-column slice and walks
 // the sequences b = 0 .. B-1 in order.  For each sequence the slice of all S hidden states (S x 128
 // bytes, at most 64 KiB) is copied into LDS and every gather of the sequence is an LDS read.  Eight
@@ -891,7 +829,7 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
 // Not for sparse gradients (the cost does not fall with the number of non-zero pairs, as it does in the
 // compacting kernel above) or for few workgroups: the host takes it for shapes with at least one
 // workgroup per CU.
-// grid = ceil(V / 1024) * (D / 64), slice-major.  PASSES = ceil(S / 128) copy passes per tile.
+// grid = ceil(V / 1024) * ceil(D / 64), slice-major.  PASSES = ceil(S / 128) copy passes per tile.
 // ---------------------------------------------------------------------------------------------
 constexpr int DWT_ROWS = 1024;
 constexpr int DWT_MAX_S = 512;
@@ -915,6 +853,8 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
     const int dc = blockIdx.x / n_vtiles;
     const int v0 = (blockIdx.x - dc * n_vtiles) * DWT_ROWS;
     const int rg = tid >> 3, cc = tid & 7;
+    const int col = dc * DWS_COLS + cc * 8;
+    const bool col_ok = col < D;                           // the last slice may be partly filled: lanes behind D copy its first chunk
     const int vs = v0 + tid;                               // the row this thread stages
     const bool vs_ok = vs < V;
     const int vs_c = vs_ok ? vs : V - 1;
@@ -934,7 +874,7 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
     int ix_r;
     uint32_t hoff[PASSES];
 #pragma unroll
-    for (int p = 0; p < PASSES; ++p) hoff[p] = (uint32_t)((min(p * RGS + rg, S - 1) * D + dc * DWS_COLS + cc * 8) * 2);
+    for (int p = 0; p < PASSES; ++p) hoff[p] = (uint32_t)((min(p * RGS + rg, S - 1) * D + (col_ok ? col : dc * DWS_COLS)) * 2);
     const uint32_t voff = (uint32_t)vs_c * 4u;
     auto gload = [&](int b) {
         const size_t ro = (size_t)b * V * 4;
@@ -1000,8 +940,8 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
         const int v = v0 + rg + RGS * k;
-        if (v < V) {
-            const size_t o = (size_t)v * D + dc * DWS_COLS + cc * 8;
+        if (v < V && col_ok) {
+            const size_t o = (size_t)v * D + col;
 #pragma unroll
             for (int i = 0; i < 8; i += 4) {
                 float4 r = make_float4(acc[k][i], acc[k][i + 1], acc[k][i + 2], acc[k][i + 3]);

@@ -128,7 +128,8 @@ FwdWs fwd_ws(const Shape& s) {
 }
 
 // ---- backward workspace: perm[B*V + PERM_SLACK] (v, g) pairs | cnt[B*n_seg*S] | bstart[B*(S+1)] |
-//      bounds[B*S*(n_vc+1)] (only when the dH gather is cut into n_vc > 1 vocabulary chunks) ----
+//      bounds[B*S*(n_vc+1)] (only when the dH gather is cut into n_vc > 1 vocabulary chunks; where D is not a
+//      multiple of 64 they take the place of cnt, which nothing reads after the placement) ----
 struct BwdWs { int n_seg, seg_len, key_bits, n_vc, vc_len; size_t perm_off, cnt_off, bs_off, cb_off, dh_stage_off, dw_stage_off, total; };
 
 // Vocabulary chunks of the sliced dH gather.  A chunk is sized so that one 64-column slice of its
@@ -136,19 +137,26 @@ struct BwdWs { int n_seg, seg_len, key_bits, n_vc, vc_len; size_t perm_off, cnt_
 // the first re-reads and re-writes dH once (8*B*S*D bytes), so the count is capped where that
 // traffic would pass a quarter of the gather traffic itself (B*|V|*D elements): long sequences
 // with few entries per bucket are gathered in one pass.
-void dh_chunks(const Shape& s, int* n_vc, int* vc_len) {
+// Measured where row pieces straddle lines (dH us with windows of 8 / 4 / 2 / 1 MB of elements, i.e. twice that in
+// lines): B=100 S=40 D=552 |V|=150000 3355 / 2628 / 1494 / 1345, one gradient in twenty 197 / 169 / 229 / 380; B=64 S=200
+// D=712 |V|=60000 1139 / 855 / 569 / 537; B=16 S=250 D=904 |V|=200000 1357 / 1184 / 1006 / 1071; B=200 S=400 D=184
+// |V|=40000 560 / 360 / 346 / 361 (whole rows by 128 threads, without windows: 3387, 185, 785, 991, 491).
+// n_seg: sort segments; where D is not a multiple of 64 the chunk bounds have to fit the count table.
+void dh_chunks(const Shape& s, int n_seg, int* n_vc, int* vc_len) {
     const long esize = s.dtype == LSR_F32 ? 4 : 2;
-    const long rows_l2 = (4l << 20) / (DWS_COLS * esize);
+    long rows_l2 = (4l << 20) / (DWS_COLS * esize);
+    if (s.D * esize % 128 != 0) rows_l2 /= 2;      // a row piece then touches two cache lines
     long c = (s.V + rows_l2 - 1) / rows_l2;
     const long cap = (long)s.V * esize / (32l * s.S);
     if (c > cap) c = cap;
     if (c > 64) c = 64;
-    if (c < 1 || s.D % DWS_COLS != 0) c = 1;
+    if (s.D % DWS_COLS != 0 && c > n_seg - 1) c = n_seg - 1;
+    if (c < 1) c = 1;
     *n_vc = (int)c;
     *vc_len = (int)((s.V + c - 1) / c);
 }
 int dw_batch_chunk(const Shape& s);
-int dw_tile_rows(const Shape& s);
+int dw_stage_rows(int nb);
 // bf16_out: dH and dW are stored as bfloat16.  A result that several launches add up (dH over vocabulary
 // chunks, dW over chunks of sequences) then keeps its float32 partial sums in a staging array of the
 // workspace and is rounded once, by the last launch.
@@ -175,10 +183,12 @@ BwdWs bwd_ws(const Shape& s, bool bf16_out = false) {
     w.cnt_off = w.perm_off + align_up(sizeof(uint2) * (bv + PERM_SLACK));
     w.bs_off = w.cnt_off + align_up(sizeof(int) * (size_t)s.B * w.n_seg * s.S);
     w.cb_off = w.bs_off + align_up(sizeof(int) * (size_t)s.B * (s.S + 1));
-    dh_chunks(s, &w.n_vc, &w.vc_len);
-    w.dh_stage_off = w.cb_off + (w.n_vc > 1 ? align_up(sizeof(int) * (size_t)s.B * s.S * (w.n_vc + 1)) : 0);
+    dh_chunks(s, w.n_seg, &w.n_vc, &w.vc_len);
+    w.dh_stage_off = w.cb_off;
+    if (s.D % DWS_COLS != 0) w.cb_off = w.cnt_off;
+    else if (w.n_vc > 1) w.dh_stage_off += align_up(sizeof(int) * (size_t)s.B * s.S * (w.n_vc + 1));
     w.dw_stage_off = w.dh_stage_off + ((bf16_out && w.n_vc > 1) ? align_up(sizeof(float) * (size_t)s.B * s.S * s.D) : 0);
-    const bool dw_multi = dw_tile_rows(s) > 0 && dw_batch_chunk(s) < s.B;
+    const bool dw_multi = dw_stage_rows(dw_batch_chunk(s)) > 0 && dw_batch_chunk(s) < s.B;
     w.total = w.dw_stage_off + ((bf16_out && dw_multi) ? align_up(sizeof(float) * (size_t)s.V * s.D) : 0);
     return w;
 }
@@ -217,7 +227,7 @@ int dh_buckets_per_wave(const Shape& s, int n_vc) {
 // From 64k waves on what long lists win is no more than what sparse gradients lose.
 int dh_waves_per_bucket(const Shape& s, int n_vc) {
     const double list = (double)s.V / ((0.7 * s.S > 1.0 ? 0.7 * s.S : 1.0) * n_vc) * (s.dtype == LSR_F32 ? 2.0 : 1.0);
-    const long long waves = (long long)s.B * s.S * (s.D / DWS_COLS);
+    const long long waves = (long long)s.B * s.S * n_slices(s.D);
     if (waves <= 4096 && list >= 64.0) return 4;           // latency alone (B=2 S=16 D=64 |V|=1000: 16 -> 6.4 us)
     if (list < 256.0 || waves > 65536) return 1;
     return waves > 32768 ? 2 : (list >= 1024.0 ? 8 : 4);
@@ -242,14 +252,15 @@ int dw_batch_chunk(const Shape& s) {
     return (int)((s.B + n - 1) / n);
 }
 
-// Vocabulary rows of the (g, I) staging tile of the sliced dW gather (at most 48 KiB of LDS for the
-// sequences of one launch), or 0 when the whole-row kernel runs instead (D not a multiple of 64, or
-// too many sequences per launch for 16 rows).
-int dw_tile_rows(const Shape& s) {
-    const int nb = dw_batch_chunk(s);
+// Vocabulary rows of the (g, I) staging tile of the sliced dW gather (at most 48 KiB of LDS for the nb
+// sequences of one launch), or 0 when the whole-row kernel runs instead (too many sequences per launch for
+// 16 rows).  Also for D not a multiple of 64, against whole rows by 128 threads (dW us): B=100 S=40 D=552
+// |V|=150000 2999 -> 1040, one gradient in twenty 398 -> 534; B=128 S=100 D=936 |V|=100000 3836 -> 1640; B=250 S=64 D=1000
+// |V|=30000 2156 -> 1270; with the LDS-tile kernel B=64 S=200 D=712 |V|=60000 822 -> 285; B=200 S=500 D=120 |V|=100000 3738 -> 570.
+int dw_stage_rows(int nb) {
     int VT = 64;
     while (VT > 1 && (size_t)nb * VT * 8 > 48 * 1024) VT /= 2;
-    return (s.D % DWS_COLS == 0 && VT >= 16) ? VT : 0;
+    return VT >= 16 ? VT : 0;
 }
 
 int check_device(int* n_cus) {
@@ -421,18 +432,6 @@ int forward_impl(const lsr_head_desc* desc, const void* H, const void* W, const 
 }
 
 template <typename T, typename OT>
-void launch_dh(int cpt, dim3 grid, hipStream_t st, const T* W, const int* bstart, const uint2* pm,
-               OT* dH, int S, int D, int V, int accumulate) {
-    switch (cpt) {
-        case 1: hipLaunchKernelGGL((bwd_dh_kernel<T, 1, OT>), grid, dim3(ROW_THREADS), 0, st, W, bstart, pm, dH, S, D, V, accumulate); break;
-        case 2: hipLaunchKernelGGL((bwd_dh_kernel<T, 2, OT>), grid, dim3(ROW_THREADS), 0, st, W, bstart, pm, dH, S, D, V, accumulate); break;
-        case 4: hipLaunchKernelGGL((bwd_dh_kernel<T, 4, OT>), grid, dim3(ROW_THREADS), 0, st, W, bstart, pm, dH, S, D, V, accumulate); break;
-        case 8: hipLaunchKernelGGL((bwd_dh_kernel<T, 8, OT>), grid, dim3(ROW_THREADS), 0, st, W, bstart, pm, dH, S, D, V, accumulate); break;
-        default: hipLaunchKernelGGL((bwd_dh_kernel<T, 16, OT>), grid, dim3(ROW_THREADS), 0, st, W, bstart, pm, dH, S, D, V, accumulate); break;
-    }
-}
-
-template <typename T, typename OT>
 void launch_dw(int cpt, dim3 grid, size_t lds, hipStream_t st, const T* H, const float* dY, const float* Y, const int* I,
                OT* dW, float* db, int B, int S, int D, int V, int VT, int accumulate) {
     switch (cpt) {
@@ -466,13 +465,13 @@ void launch_dh_sliced(int bpw, int wpb, dim3 grid, hipStream_t st, const T* W, c
 template <typename T, typename OT>
 void launch_dw_sliced(bool compact, dim3 grid, dim3 block, size_t lds, hipStream_t st, const T* H, const float* dY, const float* Y,
                       const int* I, const float* prev, OT* dst, int add_dst, float* db, int add_db, int b0, int nb, const Shape& s,
-                      int VT, int n_vtiles, int NDC) {
+                      int VT, int NDC) {
     if (compact)
         hipLaunchKernelGGL((bwd_dw_sliced_kernel<T, true, OT>), grid, block, lds, st, H, dY, Y, I, prev, dst, add_dst, db, add_db, b0, nb,
-                           s.S, s.D, s.V, VT, n_vtiles, NDC);
+                           s.S, s.D, s.V, VT, NDC);
     else
         hipLaunchKernelGGL((bwd_dw_sliced_kernel<T, false, OT>), grid, block, lds, st, H, dY, Y, I, prev, dst, add_dst, db, add_db, b0, nb,
-                           s.S, s.D, s.V, VT, n_vtiles, NDC);
+                           s.S, s.D, s.V, VT, NDC);
 }
 
 // The dW/db gather does not depend on the bucket sort that feeds dH, so the plain (not profiled)
@@ -553,7 +552,6 @@ private:
 struct BwdLaunch {
     int cpt;                 // 16-byte chunks per thread of the whole-row kernels
     bool staged_place;       // the bucket sort places through LDS
-    bool dh_sliced;          // column-sliced dH gather (D a multiple of 64)
     int bpw, wpb, dh_groups; // buckets per wave, waves per bucket and workgroups per slice of the sliced dH gather
     int dw_vt;               // rows of the dW staging tile: sliced gather if dw_sliced, else whole-row kernel
     bool dw_sliced;
@@ -569,15 +567,15 @@ struct BwdLaunch {
 // 1.06 -> 1.01; from B=32 at D=1024 on it loses (B=32 1.45 -> 1.67, B=64 S=512 2.65 -> 3.1: fewer L2 misses
 // but a slower kernel; the slice-major order happens to keep every sequence's bucket lists on one XCD).
 bool dh_slices_owned(const Shape& s) { return s.B <= 16; }
-// The LDS-tile dW kernel (bwd_dw_tile_kernel): bfloat16, D a multiple of 64, S within the tile, and at least
+// The LDS-tile dW kernel (bwd_dw_tile_kernel): bfloat16, S within the tile, and at least
 // one workgroup per CU of a 256-CU device.  Measured against the sliced gather (dW): B=64 S=512 D=1024
 // |V|=250002 1.98 -> 1.72 ms; B=256 S=512 D=768 |V|=250002 7.84 -> 5.43; B=16 S=256 |V|=250002 0.407 ->
 // 0.363; B=256 S=512 |V|=30522 1.02 -> 0.94; B=8 S=512 |V|=30522 0.0445 -> 0.0463; 60 workgroups (D=128,
 // |V|=30522) 0.030 -> 0.052.
 int dw_tile_passes(const Shape& s) {
-    if (s.dtype != LSR_BF16 || s.D % DWS_COLS != 0 || s.S < DWT_MIN_S || s.S > DWT_MAX_S) return 0;
+    if (s.dtype != LSR_BF16 || s.S < DWT_MIN_S || s.S > DWT_MAX_S) return 0;
     if (s.V > (1 << 28)) return 0;                       // the kernel keeps byte offsets within a row of dY / Y / I in 32 bits
-    const long long units = (long long)((s.V + DWT_ROWS - 1) / DWT_ROWS) * (s.D / DWS_COLS);
+    const long long units = (long long)((s.V + DWT_ROWS - 1) / DWT_ROWS) * n_slices(s.D);
     if (units < 256 || units > 0x7fffffffll) return 0;
     return (s.S + 127) / 128;
 }
@@ -587,27 +585,26 @@ int plan_backward(const Shape& s, const BwdWs& w, BwdLaunch* L) {
     L->cpt = 1;
     while (L->cpt * ROW_THREADS < n_chunks) L->cpt *= 2;
     L->staged_place = s.S <= PLACE_MAX_S && w.seg_len <= PLACE_MAX_SEG;      // plan[3] of lsr_head_plan
-    L->dh_sliced = s.D % DWS_COLS == 0;
-    L->bpw = L->dh_sliced ? dh_buckets_per_wave(s, w.n_vc) : 0;
-    L->wpb = L->dh_sliced ? dh_waves_per_bucket(s, w.n_vc) : 1;
-    L->dh_groups = !L->dh_sliced ? 0 : L->wpb > 1 ? s.B * s.S : s.B * ((s.S + 4 * L->bpw - 1) / (4 * L->bpw));
-    if ((long long)L->dh_groups * (s.D / DWS_COLS) > 0x7fffffffll) return LSR_ERR_SHAPE;
-    L->dh_xcd_own = L->dh_sliced && dh_slices_owned(s);
-    if (L->dh_xcd_own && xcd_slice_grid(s.D / DWS_COLS, L->dh_groups, 1) > 0x7fffffffll) return LSR_ERR_SHAPE;
+    L->bpw = dh_buckets_per_wave(s, w.n_vc);
+    L->wpb = dh_waves_per_bucket(s, w.n_vc);
+    L->dh_groups = L->wpb > 1 ? s.B * s.S : s.B * ((s.S + 4 * L->bpw - 1) / (4 * L->bpw));
+    if ((long long)L->dh_groups * n_slices(s.D) > 0x7fffffffll) return LSR_ERR_SHAPE;
+    L->dh_xcd_own = dh_slices_owned(s);
+    if (L->dh_xcd_own && xcd_slice_grid(n_slices(s.D), L->dh_groups, 1) > 0x7fffffffll) return LSR_ERR_SHAPE;
     L->dw_tile_passes = dw_tile_passes(s);
     L->dw_tile_vtiles = (s.V + DWT_ROWS - 1) / DWT_ROWS;
-    // column-sliced dW gathers (L2-resident slices of H) need D % 64 == 0 and a (g, I) staging tile (at
-    // most 48 KiB) at least 16 vocabulary rows wide, i.e. at most 384 sequences per launch.  Larger
-    // batches keep the whole-row kernel, which also skips zero gradients.
-    L->dw_vt = dw_tile_rows(s);
-    L->dw_sliced = L->dw_vt > 0;
+    // column-sliced dW gathers (L2-resident slices of H) need a (g, I) staging tile (at most 48 KiB) at least
+    // 16 vocabulary rows wide, i.e. at most 384 sequences per launch.  Larger batches keep the whole-row
+    // kernel, which also skips zero gradients.
     L->dw_bc = dw_batch_chunk(s);
+    L->dw_vt = dw_stage_rows(L->dw_bc);
+    L->dw_sliced = L->dw_vt > 0;
     if (L->dw_sliced) {
         // slices per group: a workgroup walks the slices of its group with one staging of (g, I), and
         // the groups run one after the other.  Up to 9 MiB of H rows per group measured best (C5: two
         // 4 MiB slices, dW 2.21 -> 2.02 ms; C3 0.22 -> 0.175; 3 per group at C5 2.11, all 16: 2.48):
         // fewer stagings against a wider window of H in flight.
-        const int n_dc = s.D / DWS_COLS;
+        const int n_dc = n_slices(s.D);
         const size_t slice_bytes = (size_t)L->dw_bc * s.S * DWS_COLS * (s.dtype == LSR_F32 ? 4 : 2);
         int ndc = (int)((size_t)(9u << 20) / slice_bytes);
         L->dw_ndc = ndc < 1 ? 1 : (ndc > n_dc ? n_dc : ndc);
@@ -709,39 +706,35 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
         prof.end(2);
         if ((r = launch_status()) != LSR_OK) return r;
         prof.begin(3);
-        if (L.dh_sliced) {
-            // column-sliced gathers, one launch per vocabulary chunk: the rows of W in use stay in L2
-            const int* bounds = bstart;
-            if (w.n_vc > 1) {
-                int* cb = reinterpret_cast<int*>(base + w.cb_off);
-                const long long n = (long long)s.B * s.S * (w.n_vc + 1);
-                hipLaunchKernelGGL(bwd_chunk_bounds_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, bstart, perm, cb,
-                                   s.B * s.S, s.S, s.V, w.n_vc, w.vc_len);
-                bounds = cb;
+        // column-sliced gathers, one launch per vocabulary chunk: the rows of W in use stay in L2
+        const int* bounds = bstart;
+        if (w.n_vc > 1) {
+            int* cb = reinterpret_cast<int*>(base + w.cb_off);
+            const long long n = (long long)s.B * s.S * (w.n_vc + 1);
+            hipLaunchKernelGGL(bwd_chunk_bounds_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, bstart, perm, cb,
+                               s.B * s.S, s.S, s.V, w.n_vc, w.vc_len);
+            bounds = cb;
+        }
+        const dim3 grid = L.dh_xcd_own ? dim3((unsigned)xcd_slice_grid(n_slices(s.D), L.dh_groups, 1))
+                                       : dim3((unsigned)L.dh_groups, (unsigned)n_slices(s.D));
+        float* stage = reinterpret_cast<float*>(base + w.dh_stage_off);
+        for (int vc = 0; vc < w.n_vc; ++vc) {
+            const bool last = vc + 1 == w.n_vc;
+            if (OUT_F32) {
+                // partial sums live in dH itself; the first chunk of a fresh result writes every bucket
+                float* d = reinterpret_cast<float*>(dH);
+                const bool fresh = vc == 0 && !accumulate;
+                launch_dh_sliced<T, float>(L.bpw, L.wpb, grid, st, W, bounds, perm, fresh ? nullptr : d, d, 0, fresh ? 1 : 0, s, L.dh_groups,
+                                           w.n_vc, vc, L.dh_xcd_own);
+            } else if (w.n_vc == 1) {
+                launch_dh_sliced<T, OT>(L.bpw, L.wpb, grid, st, W, bounds, perm, nullptr, dH, accumulate, accumulate ? 0 : 1, s, L.dh_groups,
+                                        w.n_vc, vc, L.dh_xcd_own);
+            } else if (!last) {
+                launch_dh_sliced<T, float>(L.bpw, L.wpb, grid, st, W, bounds, perm, vc > 0 ? stage : nullptr, stage, 0, vc == 0 ? 1 : 0, s,
+                                           L.dh_groups, w.n_vc, vc, L.dh_xcd_own);
+            } else {
+                launch_dh_sliced<T, OT>(L.bpw, L.wpb, grid, st, W, bounds, perm, stage, dH, accumulate, 1, s, L.dh_groups, w.n_vc, vc, L.dh_xcd_own);
             }
-            const dim3 grid(L.dh_xcd_own ? (unsigned)xcd_slice_grid(s.D / DWS_COLS, L.dh_groups, 1)
-                                         : (unsigned)L.dh_groups * (unsigned)(s.D / DWS_COLS));
-            float* stage = reinterpret_cast<float*>(base + w.dh_stage_off);
-            for (int vc = 0; vc < w.n_vc; ++vc) {
-                const bool last = vc + 1 == w.n_vc;
-                if (OUT_F32) {
-                    // partial sums live in dH itself; the first chunk of a fresh result writes every bucket
-                    float* d = reinterpret_cast<float*>(dH);
-                    const bool fresh = vc == 0 && !accumulate;
-                    launch_dh_sliced<T, float>(L.bpw, L.wpb, grid, st, W, bounds, perm, fresh ? nullptr : d, d, 0, fresh ? 1 : 0, s, L.dh_groups,
-                                               w.n_vc, vc, L.dh_xcd_own);
-                } else if (w.n_vc == 1) {
-                    launch_dh_sliced<T, OT>(L.bpw, L.wpb, grid, st, W, bounds, perm, nullptr, dH, accumulate, accumulate ? 0 : 1, s, L.dh_groups,
-                                            w.n_vc, vc, L.dh_xcd_own);
-                } else if (!last) {
-                    launch_dh_sliced<T, float>(L.bpw, L.wpb, grid, st, W, bounds, perm, vc > 0 ? stage : nullptr, stage, 0, vc == 0 ? 1 : 0, s,
-                                               L.dh_groups, w.n_vc, vc, L.dh_xcd_own);
-                } else {
-                    launch_dh_sliced<T, OT>(L.bpw, L.wpb, grid, st, W, bounds, perm, stage, dH, accumulate, 1, s, L.dh_groups, w.n_vc, vc, L.dh_xcd_own);
-                }
-            }
-        } else {
-            launch_dh<T, OT>(L.cpt, dim3(s.B, s.S), st, W, bstart, perm, dH, s.S, s.D, s.V, accumulate);
         }
         prof.end(3);
         if ((r = launch_status()) != LSR_OK) return r;
@@ -752,7 +745,7 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
         if (L.dw_tile_passes > 0 && dW) {
             // one launch for all sequences; the sums start from zero, so bfloat16 results need no staging
             if constexpr (sizeof(T) == 2) {
-                const dim3 grid((unsigned)L.dw_tile_vtiles * (unsigned)(s.D / DWS_COLS));
+                const dim3 grid((unsigned)L.dw_tile_vtiles * (unsigned)n_slices(s.D));
 #define LSR_DWT(NP) hipLaunchKernelGGL((bwd_dw_tile_kernel<OT, NP>), grid, dim3(DWT_ROWS), 0, st_dw, H, dY, Y, I, dW, accumulate, db, \
                                        accumulate, s.B, s.S, s.D, s.V, L.dw_tile_vtiles)
                 switch (L.dw_tile_passes) {
@@ -769,7 +762,7 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
             const int waves = 4;
             const int bc = L.dw_bc;                            // sequences per launch
             const size_t lds = (size_t)bc * VT * 8;
-            const dim3 grid((unsigned)L.dw_vtiles * (unsigned)L.dw_slice_groups), block(64 * waves);
+            const dim3 grid((unsigned)L.dw_vtiles, (unsigned)L.dw_slice_groups), block(64 * waves);
             float* stage = reinterpret_cast<float*>(base + w.dw_stage_off);
             const bool compact = VT < 32;      // tiles of 16 rows (more than 192 sequences per launch) compact their columns first
             for (int b0 = 0; b0 < s.B; b0 += bc) {
@@ -779,16 +772,16 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
                 if (OUT_F32) {
                     float* d = reinterpret_cast<float*>(dW);
                     launch_dw_sliced<T, float>(compact, grid, block, lds, st_dw, H, dY, Y, I, (!first || accumulate) ? d : nullptr, d, 0, db,
-                                               add_db, b0, nb, s, VT, L.dw_vtiles, L.dw_ndc);
+                                               add_db, b0, nb, s, VT, L.dw_ndc);
                 } else if (first && last) {
                     launch_dw_sliced<T, OT>(compact, grid, block, lds, st_dw, H, dY, Y, I, nullptr, dW, accumulate, db, add_db, b0, nb, s, VT,
-                                            L.dw_vtiles, L.dw_ndc);
+                                            L.dw_ndc);
                 } else if (!last) {
                     launch_dw_sliced<T, float>(compact, grid, block, lds, st_dw, H, dY, Y, I, first ? nullptr : stage, dW ? stage : nullptr, 0,
-                                               db, add_db, b0, nb, s, VT, L.dw_vtiles, L.dw_ndc);
+                                               db, add_db, b0, nb, s, VT, L.dw_ndc);
                 } else {
                     launch_dw_sliced<T, OT>(compact, grid, block, lds, st_dw, H, dY, Y, I, stage, dW, accumulate, db, add_db, b0, nb, s, VT,
-                                            L.dw_vtiles, L.dw_ndc);
+                                            L.dw_ndc);
                 }
             }
         } else {
@@ -984,15 +977,16 @@ int lsr_head_plan(const lsr_head_desc* desc, int32_t* plan) {
     plan[1] = w.n_seg;
     plan[2] = w.seg_len;
     plan[3] = (s.S <= PLACE_MAX_S && w.seg_len <= PLACE_MAX_SEG) ? 1 : 0;
-    plan[4] = w.n_vc;
-    plan[5] = w.vc_len;
-    plan[6] = s.D % DWS_COLS == 0 ? dh_buckets_per_wave(s, w.n_vc) : 0;
-    plan[7] = dw_tile_rows(s);
+    const bool whole = s.D % DWS_COLS == 0;        // figures that are reported for whole slices only (see the header)
+    plan[4] = whole ? w.n_vc : 1;
+    plan[5] = whole ? w.vc_len : s.V;
+    plan[6] = whole ? dh_buckets_per_wave(s, w.n_vc) : 0;
+    plan[7] = whole ? dw_stage_rows(dw_batch_chunk(s)) : 0;
     plan[8] = dw_batch_chunk(s);
     plan[9] = fwd_chunks(s).n_chunks;
     plan[10] = fwd_seg(s);
     plan[11] = fwd_chunks(s).resident ? 1 : 0;
-    plan[12] = (s.D % DWS_COLS == 0 && dh_slices_owned(s)) ? 1 : 0;
+    plan[12] = (whole && dh_slices_owned(s)) ? 1 : 0;
     plan[13] = dw_tile_passes(s);
     return LSR_OK;
 }

@@ -86,6 +86,24 @@ def test_large_batches_whole_row_dw_beside_sliced_dh(B, S, D, V):
     print(run_case(inp))
 
 
+@pytest.mark.parametrize("B,S,D,V", [(3, 20, 72, 333), (2, 70, 96, 300), (2, 9, 256, 260)])
+def test_fp32_logits_are_the_fma_chain_in_ascending_d(B, S, D, V):
+    """Near-ties of float32 logits fall as they do for a scalar loop of FMAs: the arg-max is that loop's.  The chain is
+    formed in float64 (the product is exact there) and rounded to float32 after every term; the sum is rounded twice,
+    which differs from an FMA about once in 2^29 terms (3 * 10^6 are formed here)."""
+    inp = wl.make_custom(B, S, D, V, dtype="f32", seed=D, len_lo=S, w_std=0.05)
+    head = DeviceHead(inp)
+    head.forward()
+    H, W = torch.from_numpy(inp.H).double(), torch.from_numpy(inp.W).double()
+    acc = torch.zeros((B, S, V), dtype=torch.float64)
+    for d in range(D):
+        acc = (acc + H[:, :, None, d] * W[None, None, :, d]).float().double()
+    top, first = acc.max(dim=1).values, acc.argmax(dim=1)
+    assert torch.equal(head.I.cpu().long(), first)
+    Y = torch.log1p(torch.relu(top.float() + torch.from_numpy(inp.bias)).double()).float()
+    assert torch.allclose(head.Y.cpu(), Y, rtol=2.0 ** -22, atol=0.0)      # log1pf: within two units in the last place
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("B,S,D,V,dy_keep", [
     (3, 10, 64, 1000, None),       # four waves per bucket, few buckets; lists of one or two 64-entry blocks per wave
@@ -415,6 +433,65 @@ def test_bf16_gradient_outputs_and_accumulation(B, S, D, V, len_lo):
     db_only = torch.full((V,), float("nan"), device=dev)
     run(lsr.LSR_F32, False, None, None, db_only)
     assert torch.equal(db_only, f32[2])
+
+
+@pytest.mark.parametrize("grad_dtype,accumulate", [(lsr.LSR_F32, False), (lsr.LSR_F32, True), (lsr.LSR_BF16, False), (lsr.LSR_BF16, True)])
+@pytest.mark.parametrize("B,S,D,V,dtype", [
+    (2, 9, 8, 300, "bf16"),        # one slice with a single 16-byte chunk
+    (3, 70, 72, 500, "bf16"),      # the last slice holds one chunk
+    (5, 40, 568, 700, "bf16"),     # nine slices, the last one short of one chunk; slices owned by XCDs
+    (20, 30, 120, 900, "bf16"),    # slices in grid order
+    (200, 20, 104, 300, "bf16"),   # 16-row dW tiles
+    (400, 6, 104, 200, "bf16"),    # more sequences than the staging tile takes: whole-row dW
+    (3, 140, 1016, 17000, "bf16"), # LDS-tile dW kernel
+    (3, 20, 72, 70000, "bf16"),    # several vocabulary chunks (more than the filled-up problem has)
+    (4, 20, 40, 600, "f32"),
+    (90, 12, 200, 400, "f32"),
+])
+def test_partly_filled_column_slices(B, S, D, V, dtype, grad_dtype, accumulate):
+    """A hidden size that is not a multiple of 64 gives, bit for bit, the gradients of the same problem with D filled up
+    with zeros to the next multiple (every sum over sequences or vocabulary entries has the same terms in the
+    same order; dH over several vocabulary chunks is cut in other places, and then within D 2^-24 of the size of its
+    terms), and nothing behind a row is touched."""
+    if dtype == "f32" and grad_dtype == lsr.LSR_BF16:
+        pytest.skip("bfloat16 gradients belong to bfloat16 parameters")
+    dt = lsr.LSR_F32 if dtype == "f32" else lsr.LSR_BF16
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    gd = torch.bfloat16 if grad_dtype == lsr.LSR_BF16 else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(B * 1000 + D)
+    Dp = (D + 63) // 64 * 64
+    H = torch.randn((B, S, D), device="cuda", generator=g).to(td)
+    W = torch.randn((V, D), device="cuda", generator=g).mul_(0.05).to(td)
+    Y = torch.rand((B, V), device="cuda", generator=g)
+    I = torch.randint(0, S, (B, V), device="cuda", generator=g, dtype=torch.int32)
+    dY = torch.randn((B, V), device="cuda", generator=g)
+    dH0 = torch.randn((B, S, D), device="cuda", generator=g).to(gd)
+    dW0 = torch.randn((V, D), device="cuda", generator=g).to(gd)
+    db0 = torch.randn((V,), device="cuda", generator=g)
+    wide = lambda t: torch.nn.functional.pad(t, (0, Dp - D)).contiguous()      # noqa: E731
+    got = []
+    for d, fill in ((D, lambda t: t.clone()), (Dp, wide)):
+        guard = torch.full((4096,), 7.0, dtype=gd, device="cuda")
+        bufs = [torch.cat([fill(t).flatten(), guard]) for t in (dH0, dW0)]
+        db = db0.clone()
+        ws = torch.empty(lsr.lsr_head_backward_ex_workspace_bytes(B, S, d, V, dt, grad_dtype, accumulate), dtype=torch.uint8, device="cuda")
+        lsr.lsr_head_backward_ex(B, S, d, V, dt, fill(H), fill(W), dY, Y, I, bufs[0], bufs[1], db, grad_dtype, accumulate, ws)
+        torch.cuda.synchronize()
+        for b in bufs:
+            assert torch.equal(b[-4096:], guard)
+        got.append((bufs[0][:-4096].view(B, S, d), bufs[1][:-4096].view(V, d), db))
+    assert torch.equal(got[0][2], got[1][2])
+    for k, (a, p) in enumerate(zip(got[0][:2], got[1][:2])):
+        assert not p[..., D:].any() or accumulate
+        if k == 0 and V > 16384:
+            # lists of up to n entries in another order: n 2^-23 of the sum of magnitudes, and one step of the output type
+            n = int(torch.bincount((I.long() + torch.arange(B, device="cuda")[:, None] * S).flatten()).max())
+            size = n * float(dY.abs().max()) * float(W.float().abs().max())
+            step = 2.0 ** -7 if gd == torch.bfloat16 else 2.0 ** -22
+            d = (a.double() - p[..., :D].double()).abs()
+            assert bool((d <= n * 2.0 ** -23 * size + step * p[..., :D].double().abs()).all())
+        else:
+            assert torch.equal(a, p[..., :D])
 
 
 def test_two_host_threads_on_two_streams():
