@@ -17,7 +17,13 @@ class _LsrHead(torch.autograd.Function):
             raise TypeError("lsr_head: H and W must both be bfloat16 or both float32")
         H, W = H.contiguous(), W.contiguous()
         bias = bias.contiguous().float()
-        mask = (mask != 0).to(torch.uint8).contiguous()
+        # the library takes any non-zero byte for a valid token: one-byte masks go in as they are
+        if mask.dtype == torch.bool:
+            mask = mask.contiguous().view(torch.uint8)
+        elif mask.dtype == torch.uint8:
+            mask = mask.contiguous()
+        else:
+            mask = (mask != 0).to(torch.uint8).contiguous()
         B, S, D = H.shape
         V = W.shape[0]
         dt = lsr.LSR_BF16 if H.dtype == torch.bfloat16 else lsr.LSR_F32
@@ -28,6 +34,7 @@ class _LsrHead(torch.autograd.Function):
         ctx.save_for_backward(H, W, Y, I)
         ctx.shape = (B, S, D, V, dt)
         ctx.mark_non_differentiable(I)
+        ctx.set_materialize_grads(False)      # no zeros for the gradient that I does not have
         return Y, I
 
     @staticmethod
@@ -35,8 +42,8 @@ class _LsrHead(torch.autograd.Function):
         H, W, Y, I = ctx.saved_tensors
         B, S, D, V, dt = ctx.shape
         need_h, need_w, need_b = ctx.needs_input_grad[0], ctx.needs_input_grad[1], ctx.needs_input_grad[2]
-        dY = dY.contiguous().float()
         dev = H.device
+        dY = torch.zeros((B, V), dtype=torch.float32, device=dev) if dY is None else dY.contiguous().float()
         # the library stores dH and dW in the parameters' own dtype (float32 sums, rounded once)
         dH = torch.empty((B, S, D), dtype=H.dtype, device=dev) if need_h else None
         dW = torch.empty((V, D), dtype=W.dtype, device=dev) if need_w else None

@@ -101,7 +101,7 @@ def _ptr(t) -> Optional[int]:
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
