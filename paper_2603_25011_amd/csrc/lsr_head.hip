@@ -476,11 +476,20 @@ void launch_dw_sliced(bool compact, dim3 grid, dim3 block, size_t lds, hipStream
 
 // The dW/db gather does not depend on the bucket sort that feeds dH, so the plain (not profiled)
 // backward can run it on an auxiliary stream beside the dH chain: fork after the caller's prior
-// work, join before returning control of the caller's stream.  Measured: the overlap shortens the
-// backward while the gathers are small (B=256 S=32 |V|=30522: 0.42 -> 0.30 ms; B=16 S=256
-// |V|=250002: 1.56 -> 1.47 ms) and lengthens it once they stream tens of GB (B=64 S=512
-// |V|=250002: 7.2 -> 7.7 ms, the two kernels evict each other's L2-resident slices), so it is used
-// up to AUX_MAX_GATHER_BYTES of worst-case gather traffic (2 * B * |V| rows of D elements).
+// work, join before returning control of the caller's stream.  The fork and the join cost the host about 30 us
+// (two event records, two waits), and two gathers at a time help while they leave each other's windows in L2:
+//   - up to AUX_MIN_GATHER_BYTES of worst-case gather traffic (2 * B * |V| rows of D elements) the host's time is
+//     the longer one (forward and backward, us, without -> with: B=2 S=16 D=64 |V|=1000 float32 42.6 -> 52.1; B=10 S=60
+//     D=512 |V|=10000 float32, 0.41 GB, 177 -> 172; B=13 S=197 D=312 |V|=31091, 0.5 GB, 193 -> 182);
+//   - up to AUX_MAX_GATHER_BYTES it always pays (B=30 S=80 D=256 |V|=25000 153 -> 130; B=64 S=100 D=768 |V|=50000 1016 ->
+//     933; B=16 S=256 |V|=250002 1807 -> 1740);
+//   - beyond, where a 64-column slice of H is at most 1 MiB (B=256 S=32 D=768 |V|=30522 2402 -> 2038, with one gradient in
+//     twenty 609 -> 579; B=60 S=40 D=768 |V|=200000 2763 -> 2652) or dW gathers from LDS and dH has one window (B=256
+//     S=512 D=768 |V|=30522 6757 -> 6409); not otherwise (B=200 S=100 D=768 |V|=30522 1845 -> 2049; B=256 S=100 D=1024 |V|=30522
+//     3634 -> 4107; B=128 S=100 D=936 |V|=100000 6229 -> 7135; B=64 S=512 D=1024 |V|=250002 13.29 -> 13.37 ms).
+constexpr double AUX_MIN_GATHER_BYTES = 100e6;
+constexpr double AUX_MAX_GATHER_BYTES = 16e9;
+constexpr size_t AUX_SMALL_SLICE_BYTES = 1u << 20;
 //
 // The lane (one stream, one fork and one join event per device, default priority, non-blocking with
 // respect to the null stream) is created by the first backward on that device and kept until the
@@ -491,7 +500,6 @@ void launch_dw_sliced(bool compact, dim3 grid, dim3 block, size_t lds, hipStream
 // a wait always refers to the record made by the same call (a stream wait binds to the event's most
 // recent record at the time of the wait call).  Only enqueueing is serialised; the device work of
 // two callers still overlaps as their streams allow, except that their dW gathers share one lane.
-constexpr double AUX_MAX_GATHER_BYTES = 16e9;
 struct AuxLane {
     std::mutex mu;
     hipStream_t stream = nullptr;
@@ -658,7 +666,9 @@ int backward_impl(const lsr_head_desc* desc, const void* H, const void* W, const
 
     // fork: dW/db on the auxiliary stream, the dH chain on the caller's
     const double gather_bytes = 2.0 * s.B * s.V * s.D * (s.dtype == LSR_F32 ? 4 : 2);
-    const bool overlap = !prof.on && dH && (dW || db) && gather_bytes <= AUX_MAX_GATHER_BYTES;
+    const size_t h_slice = (size_t)s.B * s.S * DWS_COLS * (s.dtype == LSR_F32 ? 4 : 2);
+    const bool apart = gather_bytes <= AUX_MAX_GATHER_BYTES || h_slice <= AUX_SMALL_SLICE_BYTES || (L.dw_tile_passes > 0 && dW && w.n_vc == 1);
+    const bool overlap = !prof.on && dH && (dW || db) && gather_bytes >= AUX_MIN_GATHER_BYTES && apart;
     AuxFork lane(overlap ? aux_lane_of_current_device() : nullptr, st);
     const hipStream_t st_dw = lane.side();
 

@@ -533,6 +533,43 @@ def test_two_host_threads_on_two_streams():
                 assert np.array_equal(a, b_)
 
 
+def test_two_host_threads_whose_backwards_fork():
+    """Problems large enough that the dW gather goes to the library's shared auxiliary stream (0.12 GB and more of
+    worst-case gathers): calls of two threads on two streams give, bit for bit, what each gives alone."""
+    import threading
+    inps = [wl.make_custom(20, 40, 256, 6000, seed=111, len_lo=3), wl.make_custom(17, 60, 320, 6100, seed=112, len_lo=1)]
+    outs = lambda h: [t.clone() for t in (h.Y, h.I, h.dH, h.dW, h.db)]      # noqa: E731
+    heads = [DeviceHead(i) for i in inps]
+    alone = []
+    for h, inp in zip(heads, inps):
+        h.forward()
+        h.backward()
+        torch.cuda.synchronize()
+        alone.append(outs(h))
+    torch.cuda.synchronize()
+    errors = []
+
+    def worker(k):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                for _ in range(20):
+                    heads[k].poison_outputs()
+                    heads[k].forward()
+                    heads[k].backward()
+                    stream.synchronize()
+                    assert all(torch.equal(a, b) for a, b in zip(outs(heads[k]), alone[k]))
+        except BaseException as exc:      # surfaced in the main thread
+            errors.append((k, repr(exc)))
+
+    threads = [threading.Thread(target=worker, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+
+
 def test_mfma_probe_reports_a_plausible_rate():
     from paper_2603_25011_amd import binding as b
     sink = torch.zeros(1, dtype=torch.float32, device="cuda:0")
