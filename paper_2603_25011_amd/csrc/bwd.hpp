@@ -18,6 +18,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "lds_dma.hpp"
 
 namespace lsr {
@@ -429,13 +431,15 @@ __global__ __launch_bounds__(ROW_THREADS) void bwd_dw_kernel(const T* __restrict
 // A row piece is 64 elements = LPR lanes x 16 bytes; a wave therefore serves 64/LPR vocabulary
 // rows at once, walks the sequences that have a gradient for them with eight gathers in flight per
 // lane, and writes one 64-column piece of each dW row.  Summation order over b is fixed.
-// COMPACT (used for the narrow tiles of large batches, where sequences are short and gradients often
-// sparse): after staging, each column of the (g, I) tile is compacted in place to its non-zero
-// entries, in ascending b (one wave per column, ballot ranking) and closed by a zero, so that sparse
-// gradients cost what they hold; element (b, vv) of the tile then sits at word
-// b*VT + (vv ^ (b % VT)), so that staging (lanes along vv), compaction (lanes along b) and the gather
-// (eight columns per wave) all spread over the LDS banks.  Without it the tile is plain row-major
-// and every b is visited (measured 7 % faster on dense gradients).   VT a power of two.
+// A tile in which fewer than half of the pairs have a gradient is compacted after staging: each column of the (g, I)
+// tile in place to its non-zero entries, in ascending b (one wave per column, ballot ranking), closed by a
+// zero, so that sparse gradients cost what they hold; the sums are the same either way (same terms, same order).
+// With one gradient in twenty (dW us, compacted or not): B=64 S=100 D=768 |V|=50000 226 -> 85; B=167 S=62 D=648
+// |V|=66407 704 -> 249; B=100 S=24 D=384 |V|=60000 185 -> 63; dense ones are unchanged within 2 %.
+// SWZ (16-row tiles, of which a workgroup of a large batch compacts many narrow columns): element (b, vv) sits at
+// word b*VT + (vv ^ (b % VT)), so that the compaction's column reads spread over the LDS banks (B=250 S=60 D=1024
+// |V|=100000, one in twenty, 747 -> 717 us).  On wider tiles the address arithmetic costs more than the bank
+// conflicts (about 1 us per workgroup), and a word of padding per row costs a workgroup per CU.   VT a power of two.
 // When the H slice of the whole batch (B*S rows x 128 bytes) is larger than L2, the host launches
 // the kernel once per chunk of consecutive sequences (b_first, B = sequences of the chunk); later
 // launches add to dW and db, which keeps the order of the sums fixed.
@@ -444,7 +448,7 @@ __global__ __launch_bounds__(ROW_THREADS) void bwd_dw_kernel(const T* __restrict
 // the caller's gradient), and dst is float32 or bfloat16 (OT).  A float32 result spread over several
 // launches passes prev = dst; a bfloat16 result keeps its partial sums in a float32 staging array (dst of
 // all launches but the last, prev of all but the first), so that it is rounded once.
-// dynamic LDS: B*VT floats + B*VT ints.   grid = (ceil(V/VT), ceil(ceil(D/64)/NDC)).
+// dynamic LDS: B*VT floats + B*VT ints.   256 threads, grid = (ceil(V/VT), ceil(ceil(D/64)/NDC)).
 // ---------------------------------------------------------------------------------------------
 constexpr int DWS_COLS = 64;
 constexpr int DH_NLD = 4;                 // gathers in flight per lane of the sliced dH gather
@@ -497,7 +501,7 @@ __host__ __device__ inline XcdSliceUnit xcd_slice_unit(unsigned id, int n_dc, in
     return u;
 }
 
-template <typename T, bool COMPACT, typename OT>
+template <typename T, bool SWZ, typename OT>
 __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict__ H,
                                                             const float* __restrict__ dY,
                                                             const float* __restrict__ Y,
@@ -513,7 +517,7 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
     extern __shared__ int s_dyn[];
     float* s_g = reinterpret_cast<float*>(s_dyn);          // [B][VT]
     int* s_i = s_dyn + (size_t)B * VT;                     // [B][VT]  token row b*S + I[b,v]
-    auto at = [VT](int b, int vv) { return COMPACT ? b * VT + (vv ^ (b & (VT - 1))) : b * VT + vv; };
+    auto at = [VT](int b, int vv) { return b * VT + (SWZ ? vv ^ (b & (VT - 1)) : vv); };
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
@@ -523,6 +527,8 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
     const int dc_begin = dg * NDC;
     const int dc_end = min(n_slices(D), dc_begin + NDC);
 
+    __shared__ int s_nz[4];                                // pairs with a gradient that each wave has staged
+    int nz = 0;
     // staging, four independent (dY, Y, I) triples in flight per thread
     for (int e0 = tid; e0 < B * VT; e0 += 4 * blockDim.x) {
         float dy[4], y[4];
@@ -540,20 +546,24 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int e = e0 + u * blockDim.x;
+            const float g = gate_grad(dy[u], y[u]);
+            nz += __popcll(__ballot(g != 0.f));            // no gradient behind the end of the tile (dy = 0)
             if (e < B * VT) {
                 const int bb = e / VT, vv = e - bb * VT;
-                s_g[at(bb, vv)] = gate_grad(dy[u], y[u]);
+                s_g[at(bb, vv)] = g;
                 s_i[at(bb, vv)] = (b_first + bb) * S + clamp_pos(ix[u], S);
             }
         }
     }
+    if (lane == 0) s_nz[wave] = nz;
     __syncthreads();
+    const bool compact = 2 * (s_nz[0] + s_nz[1] + s_nz[2] + s_nz[3]) < B * min(VT, V - v0);
 
     // compaction: column vv keeps its non-zero entries, in ascending b, at rows 0..n-1, and a zero at
     // row n if n < B.  A chunk of 64 rows is read before any of it is written and lands at or below
     // where it was read, so this works in place.
     const unsigned long long lt = (1ull << lane) - 1ull;
-    for (int vv = wave; COMPACT && vv < VT; vv += n_waves) {
+    for (int vv = wave; compact && vv < VT; vv += n_waves) {
         int n = 0;
         for (int b0 = 0; b0 < B; b0 += 64) {
             const int b = b0 + lane;
@@ -569,13 +579,13 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
         }
         if (lane == 0 && n < B) s_g[at(n, vv)] = 0.f;
     }
-    if (COMPACT) __syncthreads();
+    if (compact) __syncthreads();
 
     if (db && dg == 0 && tid < VT && v0 + tid < V) {           // fixed-order sum over b
         float sum = add_db ? db[v0 + tid] : 0.f;
         for (int k = 0; k < B; ++k) {
             const float g = s_g[at(k, tid)];
-            if (COMPACT && g == 0.f) break;
+            if (compact && g == 0.f) break;
             sum += g;
         }
         db[v0 + tid] = sum;
@@ -591,22 +601,27 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
             float acc[N];
 #pragma unroll
             for (int i = 0; i < N; ++i) acc[i] = 0.f;
-            for (int k0 = 0; k0 < B; k0 += 8) {
-                float g[8];
-                uint4 x[8];
-                bool open = true;                                // false behind the closing zero
+            auto gather = [&](auto compacted) {
+                constexpr bool C = decltype(compacted)::value;
+                for (int k0 = 0; k0 < B; k0 += 8) {
+                    float g[8];
+                    uint4 x[8];
+                    bool open = true;                            // false behind the closing zero of a compacted column
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int k = k0 + u;
-                    g[u] = (open && k < B) ? s_g[at(k, vv)] : 0.f;
-                    if (COMPACT) open = g[u] != 0.f;
-                    x[u] = make_uint4(0, 0, 0, 0);
-                    if (g[u] != 0.f) x[u] = *reinterpret_cast<const uint4*>(H + (size_t)s_i[at(k, vv)] * D + col0);
+                    for (int u = 0; u < 8; ++u) {
+                        const int k = k0 + u;
+                        g[u] = (open && k < B) ? s_g[at(k, vv)] : 0.f;
+                        if (C) open = g[u] != 0.f;
+                        x[u] = make_uint4(0, 0, 0, 0);
+                        if (g[u] != 0.f) x[u] = *reinterpret_cast<const uint4*>(H + (size_t)s_i[at(k, vv)] * D + col0);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) RowChunk<T>::fma(x[u], g[u], acc);
+                    if (C && !open) break;
                 }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) RowChunk<T>::fma(x[u], g[u], acc);
-                if (COMPACT && !open) break;
-            }
+            };
+            if (compact) gather(std::true_type{});
+            else gather(std::false_type{});
             if (v < V && col < D) {
                 const size_t o = (size_t)v * D + col0;
 #pragma unroll

@@ -463,10 +463,10 @@ void launch_dh_sliced(int bpw, int wpb, dim3 grid, hipStream_t st, const T* W, c
 #undef LSR_DH2
 }
 template <typename T, typename OT>
-void launch_dw_sliced(bool compact, dim3 grid, dim3 block, size_t lds, hipStream_t st, const T* H, const float* dY, const float* Y,
+void launch_dw_sliced(dim3 grid, dim3 block, size_t lds, hipStream_t st, const T* H, const float* dY, const float* Y,
                       const int* I, const float* prev, OT* dst, int add_dst, float* db, int add_db, int b0, int nb, const Shape& s,
                       int VT, int NDC) {
-    if (compact)
+    if (VT < 32)
         hipLaunchKernelGGL((bwd_dw_sliced_kernel<T, true, OT>), grid, block, lds, st, H, dY, Y, I, prev, dst, add_dst, db, add_db, b0, nb,
                            s.S, s.D, s.V, VT, NDC);
     else
@@ -774,23 +774,22 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
             const size_t lds = (size_t)bc * VT * 8;
             const dim3 grid((unsigned)L.dw_vtiles, (unsigned)L.dw_slice_groups), block(64 * waves);
             float* stage = reinterpret_cast<float*>(base + w.dw_stage_off);
-            const bool compact = VT < 32;      // tiles of 16 rows (more than 192 sequences per launch) compact their columns first
             for (int b0 = 0; b0 < s.B; b0 += bc) {
                 const int nb = s.B - b0 < bc ? s.B - b0 : bc;
                 const bool first = b0 == 0, last = b0 + bc >= s.B;
                 const int add_db = (!first || accumulate) ? 1 : 0;
                 if (OUT_F32) {
                     float* d = reinterpret_cast<float*>(dW);
-                    launch_dw_sliced<T, float>(compact, grid, block, lds, st_dw, H, dY, Y, I, (!first || accumulate) ? d : nullptr, d, 0, db,
+                    launch_dw_sliced<T, float>(grid, block, lds, st_dw, H, dY, Y, I, (!first || accumulate) ? d : nullptr, d, 0, db,
                                                add_db, b0, nb, s, VT, L.dw_ndc);
                 } else if (first && last) {
-                    launch_dw_sliced<T, OT>(compact, grid, block, lds, st_dw, H, dY, Y, I, nullptr, dW, accumulate, db, add_db, b0, nb, s, VT,
+                    launch_dw_sliced<T, OT>(grid, block, lds, st_dw, H, dY, Y, I, nullptr, dW, accumulate, db, add_db, b0, nb, s, VT,
                                             L.dw_ndc);
                 } else if (!last) {
-                    launch_dw_sliced<T, float>(compact, grid, block, lds, st_dw, H, dY, Y, I, first ? nullptr : stage, dW ? stage : nullptr, 0,
+                    launch_dw_sliced<T, float>(grid, block, lds, st_dw, H, dY, Y, I, first ? nullptr : stage, dW ? stage : nullptr, 0,
                                                db, add_db, b0, nb, s, VT, L.dw_ndc);
                 } else {
-                    launch_dw_sliced<T, OT>(compact, grid, block, lds, st_dw, H, dY, Y, I, stage, dW, accumulate, db, add_db, b0, nb, s, VT,
+                    launch_dw_sliced<T, OT>(grid, block, lds, st_dw, H, dY, Y, I, stage, dW, accumulate, db, add_db, b0, nb, s, VT,
                                             L.dw_ndc);
                 }
             }
