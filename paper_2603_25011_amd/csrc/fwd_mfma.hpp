@@ -124,7 +124,8 @@ struct FwdParams {
     const float* bias;
     const int2* rows;        // [n_segs * SEG] per packed row: (row of H = b*S + s, position s)
     const int* blk_meta;     // [n_segs] sequence index b, ORed with FWD_META_LAST / _EMPTY / _FIRST
-    const int* n_blocks;     // n_segs: length of the segment list (written by the planning pass)
+    const int* n_blocks;     // n_segs: length of the segment list (written by the planning pass); the B entries in
+                             // front of it are the first segments of the sequences
     float* Y;
     int* I;                  // may be null
     float* part_m;           // [n_chunks][V] pieces of sequences that begin in an earlier chunk
@@ -132,9 +133,7 @@ struct FwdParams {
     int B, S, D, V;
     int n_vtiles;            // ceil(V / tile columns)
     int n_chunks;            // chunks the grid provides for (from the longest block list the shape allows)
-    int tpc;                 // most tiles per chunk
-    const int* seg0;         // [B + 1] first segment of every sequence (float32: chunks of whole sequences)
-    int chunk_segs;          // float32: segments per window of a chunk
+    int tpc;                 // most tiles per chunk; float32: segments per window of a chunk
     int gv;                  // vocabulary tiles per L2-sharing group
 };
 
@@ -359,7 +358,7 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_mfma_kernel(FwdPa
     const int n_segs = *p.n_blocks;
     constexpr bool WHOLE = ESZ == 4;         // chunks of whole sequences
     const ChunkSplit cs = chunk_split(n_segs, p.tpc, SPT);
-    const int nc = WHOLE ? (n_segs + p.chunk_segs - 1) / p.chunk_segs : cs.nc;
+    const int nc = WHOLE ? (n_segs + p.tpc - 1) / p.tpc : cs.nc;
     // units per group of vocabulary tiles.  One workgroup per unit: the unit list provides for the chunks
     // of the longest possible token list, as the grid does, and the workgroups of chunks that do not exist
     // return at once, in place (measured 1 % faster at B=64 S=512 than closing the gaps, which moves all
@@ -380,8 +379,8 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_mfma_kernel(FwdPa
             if (vt >= p.n_vtiles || rc >= nc) continue;
             x.u = u; x.vt = vt; x.rc = rc;
             if constexpr (WHOLE) {
-                x.g0 = first_segment_from(p.seg0, p.B, rc * p.chunk_segs);
-                x.ns = first_segment_from(p.seg0, p.B, min(n_segs, (rc + 1) * p.chunk_segs)) - x.g0;
+                x.g0 = first_segment_from(p.n_blocks - p.B, p.B, rc * p.tpc);
+                x.ns = first_segment_from(p.n_blocks - p.B, p.B, min(n_segs, (rc + 1) * p.tpc)) - x.g0;
                 if (x.ns <= 0) continue;
             } else {
                 x.g0 = cs.first_tile(rc) * SPT;                                          // first segment of the chunk

@@ -84,7 +84,7 @@ FwdChunks fwd_chunks(const Shape& s) {
     return c;
 }
 
-// Float32 problems: segments per window of a chunk (FwdParams::chunk_segs).  The float32 matrix rate makes a
+// Float32 problems: segments per window of a chunk (FwdParams::tpc).  The float32 matrix rate makes a
 // unit an order of magnitude longer than in bfloat16, so what matters is how full the last round of units
 // is: the window of about half-tile granularity (short tiles cost what their live blocks cost) that gives the
 // least rounds x rows, on 256 CUs, with sequences taken to fill 70 % of S; never less than the longest
@@ -409,11 +409,9 @@ int forward_impl(const lsr_head_desc* desc, const void* H, const void* W, const 
     p.part_m = part_m; p.part_s = part_s;
     p.B = s.B; p.S = s.S; p.D = s.D; p.V = s.V;
     p.n_chunks = ck.n_chunks; p.tpc = ck.tpc;
-    p.seg0 = blk0;
-    p.chunk_segs = 0;
     if (s.dtype == LSR_F32) {
-        p.chunk_segs = fwd_f32_window(s);
-        p.n_chunks = (int)(((long)s.B * ((s.S + seg - 1) / seg) + p.chunk_segs - 1) / p.chunk_segs);
+        p.tpc = fwd_f32_window(s);
+        p.n_chunks = (int)(((long)s.B * ((s.S + seg - 1) / seg) + p.tpc - 1) / p.tpc);
     }
     if (s.dtype == LSR_F32) launch_fwd<float>(p, seg, ck.resident, I != nullptr, n_cus, st);
     else launch_fwd<uint16_t>(p, seg, ck.resident, I != nullptr, n_cus, st);
