@@ -676,7 +676,9 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_mfma_kernel(FwdPa
 #pragma unroll
                         for (int r = 1; r < RPS - 1; r += 2)
                             m = __builtin_fmaxf(__builtin_fmaxf(m, acc[i][c][r0 + r]), acc[i][c][r0 + r + 1]);
-                        m = __builtin_fmaxf(m, acc[i][c][r0 + RPS - 1]);
+                        // (never NaN: where all of them are, -inf leaves the choice to the other half-wave
+                        // and to the other segments; the constant rides in the last three-way maximum)
+                        m = __builtin_fmaxf(__builtin_fmaxf(m, acc[i][c][r0 + RPS - 1]), -INFINITY);
                         // e: row of that register within the block, for half-wave 0 (constants per register)
                         int e = acc_row(0, r0 + RPS - 1, 0);
                         if (ARG) {

@@ -160,6 +160,27 @@ def test_fp32_matrix_core_forward(B, S, D, V, len_lo):
     run_case(inp)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,S,D,V", [(5, 24, 64, 300), (3, 100, 72, 300), (2, 300, 64, 520)])      # 8-row segments, 32-row segments, several tiles
+def test_nan_tokens_are_never_selected(B, S, D, V, dtype):
+    """A token whose hidden state holds a NaN has NaN logits; the maximum and its position are those of the other tokens.
+    The patterns leave one half-wave of a segment (rows 0..3 of every eight, or 4..7), whole segments, whole tiles or
+    whole sequences without a number; a sequence of NaN tokens only gives Y = 0, I = 0."""
+    inp = wl.make_custom(B, S, D, V, dtype=dtype, seed=S, len_lo=S, w_std=0.05)
+    s = np.arange(S)
+    for bad in (s % 8 < 4, s % 8 >= 4, s % 4 != 2, (s // 8) % 2 == 0, s < min(S - 1, 260), s >= 1, s >= 0):
+        head = DeviceHead(inp)
+        head.H[:, torch.from_numpy(np.nonzero(bad)[0]).cuda(), 3] = float("nan")
+        head.poison_outputs()
+        head.forward()
+        torch.cuda.synchronize()
+        Y, I = head.Y.cpu().numpy(), head.I.cpu().numpy()
+        keep = np.broadcast_to(~bad, (B, S)).astype(np.uint8)
+        parity.compare_forward(inp, Y, I, mask=keep)      # as if the NaN tokens were masked
+        if bad.all():
+            assert not Y.any() and not I.any()
+
+
 def test_scattered_mask_and_empty_rows():
     inp = wl.make_custom(6, 150, 128, 600, seed=77)
     rng = np.random.default_rng(3)
