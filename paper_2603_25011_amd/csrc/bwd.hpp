@@ -76,6 +76,24 @@ template <> struct OutVec<uint16_t> {
 };
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 
+// A float32 sum that carries what its additions round off (the two-sum of Knuth, TAOCP vol. 2, 4.2.2), so that the value
+// is rounded once.  db is summed this way: against float64, in units of the norm of db, a plain loop over B = 13 / 64 / 256
+// sequences is off by 7.0e-8 / 1.5e-7 / 2.9e-7, the 64-lane butterfly of the whole-row kernel by 5.2e-8 / 6.7e-8 / 7.8e-8,
+// this by 2.5e-8, and by 4.0e-8 / 7.4e-8 where four / sixteen launches each round the db they hand on.
+struct Sum32 {
+    float s, e;
+    __device__ __forceinline__ void add(float x) {
+        const float t = s + x;
+        const float b = t - s;
+        e += (s - (t - b)) + (x - b);
+        s = t;
+    }
+    __device__ __forceinline__ float value() const {
+        const float r = s + e;
+        return r == r ? r : s;               // an infinite sum has no rounding error (e is NaN then)
+    }
+};
+
 // ---------------------------------------------------------------------------------------------
 // Stable bucketing of the non-zero (b,v) pairs by position s.
 // The vocabulary is cut into n_seg segments of seg_len entries; (b, segment) is the unit of work.
@@ -559,6 +577,25 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
     __syncthreads();
     const bool compact = 2 * (s_nz[0] + s_nz[1] + s_nz[2] + s_nz[3]) < B * min(VT, V - v0);
 
+    // db: every wave sums the columns that it compacts below (so it has read them before), 256 / VT lanes per
+    // column, each every (256 / VT)-th sequence; fixed order
+    if (db && dg == 0) {
+        const int cols = VT / n_waves;
+        const int part = lane / cols;
+        const int vv = wave + n_waves * (lane - part * cols);
+        Sum32 sum = {0.f, 0.f};
+        for (int k = part; k < B; k += 64 / cols) sum.add(s_g[at(k, vv)]);
+        for (int off = cols; off < 64; off <<= 1) {
+            const float other = __shfl_xor(sum.s, off), err = __shfl_xor(sum.e, off);
+            sum.add(other);
+            sum.e += err;
+        }
+        if (part == 0 && v0 + vv < V) {
+            if (add_db) sum.add(db[v0 + vv]);
+            db[v0 + vv] = sum.value();
+        }
+    }
+
     // compaction: column vv keeps its non-zero entries, in ascending b, at rows 0..n-1, and a zero at
     // row n if n < B.  A chunk of 64 rows is read before any of it is written and lands at or below
     // where it was read, so this works in place.
@@ -580,16 +617,6 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
         if (lane == 0 && n < B) s_g[at(n, vv)] = 0.f;
     }
     if (compact) __syncthreads();
-
-    if (db && dg == 0 && tid < VT && v0 + tid < V) {           // fixed-order sum over b
-        float sum = add_db ? db[v0 + tid] : 0.f;
-        for (int k = 0; k < B; ++k) {
-            const float g = s_g[at(k, tid)];
-            if (compact && g == 0.f) break;
-            sum += g;
-        }
-        db[v0 + tid] = sum;
-    }
     if (!dW) return;
 
     for (int dc = dc_begin; dc < dc_end; ++dc) {
@@ -879,7 +906,8 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
     for (int k = 0; k < RPT; ++k)
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[k][i] = 0.f;
-    float db_acc = (db && dc == 0 && add_db && vs_ok) ? db[vs] : 0.f;
+    const bool sum_db = db && dc == 0;
+    Sum32 db_sum = {(sum_db && add_db && vs_ok) ? db[vs] : 0.f, 0.f};
 
     // The loads of a sequence are straight-line code (clamped addresses instead of predicates) and nothing
     // looks at their results before stage(), so that they stay in flight while the sequence before is
@@ -908,7 +936,7 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
     };
     auto stage = [&](int buf, bool count) {
         const float g = vs_ok ? gate_grad(dy_r, y_r) : 0.f;
-        db_acc += count ? g : 0.f;
+        if (sum_db && count) db_sum.add(g);
         s_go[buf][tid] = make_float2(g, __int_as_float((g != 0.f ? clamp_pos(ix_r, S) : DWT_MAX_S) * ROW_B));
     };
     if (tid < 16) *reinterpret_cast<uint4*>(&s_tile[tid >> 3][DWT_MAX_S * ROW_B + (tid & 7) * 16]) = make_uint4(0, 0, 0, 0);
@@ -950,7 +978,7 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
         wait_vmcnt<0>();                               // the tile has landed
         __syncthreads();
     }
-    if (db && dc == 0 && vs_ok) db[vs] = db_acc;
+    if (sum_db && vs_ok) db[vs] = db_sum.value();
     if (!dW) return;
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {

@@ -515,6 +515,53 @@ def test_partly_filled_column_slices(B, S, D, V, dtype, grad_dtype, accumulate):
             assert torch.equal(a, p[..., :D])
 
 
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("B,S,D,V,dtype", [
+    (13, 40, 72, 300, "bf16"),        # 64-row staging tiles
+    (160, 20, 72, 300, "f32"),        # 32-row tiles
+    (256, 20, 200, 300, "bf16"),      # 16-row tiles
+    (300, 512, 72, 9000, "bf16"),     # several launches, each of which rounds the db it hands on; S above 128 but too few tiles
+    (256, 130, 1032, 15400, "bf16"),  # LDS-tile kernel
+    (256, 130, 1024, 16400, "bf16"),
+    (90, 600, 1032, 10000, "f32"),
+])
+def test_db_is_rounded_once_per_launch(B, S, D, V, dtype, accumulate):
+    """db = sum of dY where Y is tiny (exp(-Y) = 1): every launch rounds its running sum once, to within 2^-24 of its size;
+    the carried rounding errors are themselves rounded (B 2^-47 of the sum of magnitudes).  With one gradient in ten too,
+    which the sliced kernel compacts; infinities come out as in a plain sum."""
+    dt = lsr.LSR_F32 if dtype == "f32" else lsr.LSR_BF16
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(B + V)
+    H = torch.zeros((B, S, D), device="cuda", dtype=td)
+    W = torch.zeros((V, D), device="cuda", dtype=td)
+    Y = torch.full((B, V), 1e-30, device="cuda")
+    I = torch.zeros((B, V), device="cuda", dtype=torch.int32)
+    plan = lsr.lsr_head_plan(B, S, D, V, dt)
+    per_launch = {True: B if plan["dw_lds_tile_passes"] else plan["dw_sequences_per_launch"], False: plan["dw_sequences_per_launch"]}
+    db0 = torch.randn((V,), device="cuda", generator=g)
+    ws = torch.empty(lsr.lsr_head_backward_ex_workspace_bytes(B, S, D, V, dt), dtype=torch.uint8, device="cuda")
+    dW = torch.zeros((V, D), device="cuda")
+    for keep in (1.0, 0.1):
+        dY = torch.randn((B, V), device="cuda", generator=g) * (torch.rand((B, V), device="cuda", generator=g) < keep)
+        start = db0.double() if accumulate else torch.zeros(V, device="cuda", dtype=torch.float64)
+        run = torch.cat([start[None], dY.double()]).cumsum(dim=0)
+        for want_dw in (True, False):
+            per = per_launch[want_dw]
+            ends = run[[min(b + per, B) for b in range(0, B, per)]]      # the running sum after each launch
+            bound = 2.0 ** -24 * ends.abs().sum(dim=0) + B * 2.0 ** -47 * (start.abs() + dY.double().abs().sum(dim=0))
+            db = db0.clone()
+            lsr.lsr_head_backward_ex(B, S, D, V, dt, H, W, dY, Y, I, None, dW if want_dw else None, db, lsr.LSR_F32, accumulate, ws)
+            assert bool(((db.double() - run[-1]).abs() <= bound).all())
+    dY[B // 2, 5] = float("inf")
+    dY[B - 1, 6] = float("-inf")
+    dY[0, 7], dY[B - 1, 7] = float("inf"), float("-inf")
+    db = db0.clone()
+    lsr.lsr_head_backward_ex(B, S, D, V, dt, H, W, dY, Y, I, None, None, db, lsr.LSR_F32, accumulate, ws)
+    assert db[5] == float("inf") and db[6] == float("-inf") and bool(db[7].isnan()) and bool(db[8:].isfinite().all())
+    lsr.lsr_head_backward_ex(B, S, D, V, dt, H, W, dY, Y, I, None, dW, db, lsr.LSR_F32, False, ws)
+    assert db[5] == float("inf") and db[6] == float("-inf") and bool(db[7].isnan()) and bool(db[8:].isfinite().all())
+
+
 def test_two_host_threads_on_two_streams():
     """Two host threads call forward + backward concurrently, each on its own stream, buffers and small
     problem (small problems fork the dW gather onto the library's shared auxiliary stream).  Every call
