@@ -68,26 +68,31 @@ int lsr_gather_probe(const void* table, size_t window_bytes, int steps, int laun
 
 /*
  * The launch plan the host derives from a shape alone, for inspection and tests (no device needed,
- * nothing is launched).  [4] to [7] and [12] describe shapes whose D is a multiple of 64; other shapes report one
- * chunk and zeros there and run the same kernels by the same rules.  Writes LSR_PLAN_SLOTS int32 values to the HOST array `plan`:
+ * nothing is launched).  Writes LSR_PLAN_SLOTS int32 values to the HOST array `plan`; lsr_head_plan_ex writes the first
+ * `slots` of LSR_PLAN_EX_SLOTS values (LSR_ERR_SHAPE if slots < 1):
  *   [0] most tiles per chunk of the packed forward    [1] segments of the bucket sort per sequence
  *   [2] vocabulary entries per sort segment       [3] 1 if the sort places through LDS, else 0
  *   [4] vocabulary chunks of the dH gather        [5] vocabulary entries per chunk
- *   [6] buckets per wave in the sliced dH gather (0 for D not a multiple of 64), where a wave
- *       has buckets of its own (long lists of few buckets are shared by the waves of a workgroup instead)
- *   [7] rows of the sliced dW gather's staging tile (0: whole-row dW kernel, or D not a multiple of 64)
+ *   [6] buckets per wave in the dH gather, where waves have buckets of their own ([14] = 1)
+ *   [7] rows of the sliced dW gather's staging tile (0: whole-row dW kernel)
  *   [8] sequences per launch of the sliced dW gather (B: one launch)
- *   [9] chunks the forward grid provides for (the longest token list the shape allows); float32 problems are cut
- *       into whole sequences instead, in windows of the length the launch picks
+ *   [9] chunks the forward grid provides for (the longest token list the shape allows)
  *   [10] rows per segment of the packed token list (32, or 8 for batches of short sequences)
- *   [11] 1 if the forward runs one resident workgroup per CU over its units (shallow problems), else 0
- *   [12] 1 if the column slices of the sliced dH gather are owned by XCDs (small batches), else 0
+ *   [11] 1 if the forward runs one resident workgroup per CU over its units (shallow problems whose rows are a
+ *        multiple of 128 bytes, H and W below 4 GiB each), else 0
+ *   [12] 1 if the column slices of the dH gather are owned by XCDs (small batches), else 0
  *   [13] copy passes per tile of the LDS-tile dW kernel (ceil(S / 128)), 0 when the gathers of [7] / [8] run
  *        instead (the kernel applies to bfloat16 shapes with 128 <= S <= 512 and enough vocabulary rows to
  *        give every CU a workgroup; it also needs dW to be requested)
+ *   [14] waves that share a bucket of the dH gather (1: none, see [6])
+ *   [15] float32: segments of the packed token list per window of a chunk (a chunk holds the sequences that begin in
+ *        its window); 0 for bfloat16, whose chunks are [0] tiles long
+ *   [16] 1 if dW and db run on the library's auxiliary stream beside dH where all three are requested
  */
 #define LSR_PLAN_SLOTS 14
 int lsr_head_plan(const lsr_head_desc* desc, int32_t* plan);
+#define LSR_PLAN_EX_SLOTS 17
+int lsr_head_plan_ex(const lsr_head_desc* desc, int32_t* plan, int slots);
 
 #ifdef __cplusplus
 }

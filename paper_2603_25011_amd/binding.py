@@ -67,6 +67,8 @@ def load_library():
     lib.lsr_head_forward_profiled.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, sz, vp, fp]
     lib.lsr_head_plan.restype = ctypes.c_int
     lib.lsr_head_plan.argtypes = [dp, ctypes.POINTER(ctypes.c_int32)]
+    lib.lsr_head_plan_ex.restype = ctypes.c_int
+    lib.lsr_head_plan_ex.argtypes = [dp, ctypes.POINTER(ctypes.c_int32), ctypes.c_int]
     lib.lsr_mfma_peak_probe.restype = ctypes.c_int
     lib.lsr_mfma_peak_probe.argtypes = [ctypes.c_int64, ctypes.c_int, vp, ctypes.POINTER(ctypes.c_double), vp]
     lib.lsr_copy_probe.restype = ctypes.c_int
@@ -172,14 +174,14 @@ def lsr_head_forward_profiled(B, S, D, V, hw_dtype, H, W, bias, mask, Y, I, work
 LSR_PLAN_FIELDS = ("fwd_tiles_per_chunk", "sort_segments", "sort_segment_len", "sort_places_through_lds",
                    "dh_chunks", "dh_chunk_len", "dh_buckets_per_wave", "dw_tile_rows", "dw_sequences_per_launch",
                    "fwd_chunks", "fwd_segment_rows", "fwd_resident_workgroups", "dh_slices_owned_by_xcd",
-                   "dw_lds_tile_passes")
+                   "dw_lds_tile_passes", "dh_waves_per_bucket", "fwd_window_segments", "dw_beside_dh")
 
 
 def lsr_head_plan(B, S, D, V, hw_dtype):
     """The host's launch plan for a shape, as a dict (no device needed)."""
     d = _desc(B, S, D, V, hw_dtype)
     out = (ctypes.c_int32 * len(LSR_PLAN_FIELDS))()
-    _check(load_library().lsr_head_plan(ctypes.byref(d), out))
+    _check(load_library().lsr_head_plan_ex(ctypes.byref(d), out, len(LSR_PLAN_FIELDS)))
     return dict(zip(LSR_PLAN_FIELDS, (int(x) for x in out)))
 
 

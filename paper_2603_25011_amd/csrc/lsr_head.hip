@@ -66,20 +66,40 @@ inline bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) &
 // (B=256, S=32, lengths 4..32: 8192 packed rows with 32-row segments, 5 400 with 8-row segments).
 int fwd_seg(const Shape& s) { return s.S <= FWD_SEG_SHORT_MAX_S ? FWD_SEG_SHORT : FWD_BLK; }
 
-struct FwdChunks { int tpc, n_chunks; bool cut_possible, resident; };
+// Kernel choice: the direct-to-LDS ring when a row is a whole number of 128-byte K slabs and H and W are
+// each below 4 GiB (32-bit byte offsets per lane), else the register-staged loader (64-bit addresses,
+// zero-fills the last slab).
+bool fwd_direct(const Shape& s) {
+    const size_t row = (size_t)s.D * (s.dtype == LSR_F32 ? 4 : 2);
+    return row % 128 == 0 && (size_t)s.B * s.S * row < ((size_t)1 << 32) && (size_t)s.V * row < ((size_t)1 << 32);
+}
+
+// tpc: most tiles per chunk; window: float32 only, segments per window of a chunk (chunks are whole sequences, see
+// fwd_f32_window); n_chunks: chunks the grid provides for
+int fwd_f32_window(const Shape& s);
+struct FwdChunks { int tpc, window, n_chunks; bool cut_possible, direct, resident; };
 FwdChunks fwd_chunks(const Shape& s) {
     const int seg = fwd_seg(s);
     const long segs_max = (long)s.B * ((s.S + seg - 1) / seg);
     const long tiles_max = (segs_max * seg + FWD_TM - 1) / FWD_TM;
     FwdChunks c;
     const double units1 = 0.7 * (double)tiles_max * (double)((s.V + 255) / 256) / 256.0;      // per workgroup at one tile per chunk
-    c.resident = units1 < 24.0;
-    c.tpc = c.resident ? 1 : 4;
+    const bool shallow = units1 < 24.0;
+    c.tpc = shallow ? 1 : 4;
     const long per_seq = (tiles_max + s.B - 1) / s.B;
     if (c.tpc < per_seq) c.tpc = (int)per_seq;
+    c.window = 0;
     c.n_chunks = (int)((tiles_max + c.tpc - 1) / c.tpc);
+    if (s.dtype == LSR_F32) {
+        c.window = fwd_f32_window(s);
+        c.n_chunks = (int)((segs_max + c.window - 1) / c.window);
+        const long longest = c.window - 1 + (s.S + seg - 1) / seg;        // segments of the sequences that begin in a window
+        c.tpc = (int)(((longest < segs_max ? longest : segs_max) * seg + FWD_TM - 1) / FWD_TM);
+    }
+    // the register-staged loader has no prefetch across units to gain from residency
+    c.direct = fwd_direct(s);
+    c.resident = shallow && c.direct;
     // a sequence of one segment can never lie across a chunk boundary: no pieces, no merge pass
-    // Float32 chunks are whole sequences.
     c.cut_possible = s.dtype == LSR_BF16 && s.S > seg && c.n_chunks > 1;
     return c;
 }
@@ -328,9 +348,6 @@ struct Prof {
 
 inline int launch_status() { return hipGetLastError() == hipSuccess ? LSR_OK : LSR_ERR_LAUNCH; }
 
-// Kernel choice: the direct-to-LDS ring when a row is a whole number of 128-byte K slabs and H and W are
-// each below 4 GiB (32-bit byte offsets per lane), else the register-staged loader (64-bit addresses,
-// zero-fills the last slab).
 template <typename T, bool DMA, int SEG, bool RES>
 void launch_fwd_cfg(FwdParams p, int V, bool arg, int n_cus, hipStream_t st) {
     constexpr int TN = fwd_tn(FWD_NWN);
@@ -347,10 +364,8 @@ void launch_fwd_cfg(FwdParams p, int V, bool arg, int n_cus, hipStream_t st) {
 }
 
 template <typename T>
-void launch_fwd(const FwdParams& p, int seg, bool resident, bool arg, int n_cus, hipStream_t st) {
-    const bool small = (size_t)p.B * p.S * p.D * sizeof(T) < ((size_t)1 << 32) && (size_t)p.V * p.D * sizeof(T) < ((size_t)1 << 32);
-    const bool dma = p.D * sizeof(T) % 128 == 0 && small;
-    if (!dma) {          // the register-staged loader has no prefetch across units to gain from
+void launch_fwd(const FwdParams& p, int seg, bool direct, bool resident, bool arg, int n_cus, hipStream_t st) {
+    if (!direct) {
         if (seg == FWD_BLK) launch_fwd_cfg<T, false, FWD_BLK, false>(p, p.V, arg, n_cus, st);
         else launch_fwd_cfg<T, false, FWD_SEG_SHORT, false>(p, p.V, arg, n_cus, st);
     } else if (seg == FWD_BLK) {
@@ -408,13 +423,9 @@ int forward_impl(const lsr_head_desc* desc, const void* H, const void* W, const 
     p.bias = bias; p.rows = rows; p.blk_meta = blk_meta; p.n_blocks = blk0 + s.B; p.Y = Y; p.I = I;
     p.part_m = part_m; p.part_s = part_s;
     p.B = s.B; p.S = s.S; p.D = s.D; p.V = s.V;
-    p.n_chunks = ck.n_chunks; p.tpc = ck.tpc;
-    if (s.dtype == LSR_F32) {
-        p.tpc = fwd_f32_window(s);
-        p.n_chunks = (int)(((long)s.B * ((s.S + seg - 1) / seg) + p.tpc - 1) / p.tpc);
-    }
-    if (s.dtype == LSR_F32) launch_fwd<float>(p, seg, ck.resident, I != nullptr, n_cus, st);
-    else launch_fwd<uint16_t>(p, seg, ck.resident, I != nullptr, n_cus, st);
+    p.n_chunks = ck.n_chunks; p.tpc = s.dtype == LSR_F32 ? ck.window : ck.tpc;
+    if (s.dtype == LSR_F32) launch_fwd<float>(p, seg, ck.direct, ck.resident, I != nullptr, n_cus, st);
+    else launch_fwd<uint16_t>(p, seg, ck.direct, ck.resident, I != nullptr, n_cus, st);
     prof.end(1);
     if (ck.cut_possible) {
         if ((rc = launch_status()) != LSR_OK) return rc;
@@ -585,6 +596,13 @@ int dw_tile_passes(const Shape& s) {
     if (units < 256 || units > 0x7fffffffll) return 0;
     return (s.S + 127) / 128;
 }
+// Whether dW/db run on the auxiliary stream beside dH (see AUX_MIN_GATHER_BYTES).
+bool dw_beside_dh(const Shape& s, int n_vc, bool want_dw) {
+    const double gather_bytes = 2.0 * s.B * s.V * s.D * (s.dtype == LSR_F32 ? 4 : 2);
+    const size_t h_slice = (size_t)s.B * s.S * DWS_COLS * (s.dtype == LSR_F32 ? 4 : 2);
+    const bool apart = gather_bytes <= AUX_MAX_GATHER_BYTES || h_slice <= AUX_SMALL_SLICE_BYTES || (dw_tile_passes(s) > 0 && want_dw && n_vc == 1);
+    return gather_bytes >= AUX_MIN_GATHER_BYTES && apart;
+}
 int plan_backward(const Shape& s, const BwdWs& w, BwdLaunch* L) {
     const int chunk_elems = s.dtype == LSR_F32 ? 4 : 8;
     const int n_chunks = s.D / chunk_elems;
@@ -663,10 +681,7 @@ int backward_impl(const lsr_head_desc* desc, const void* H, const void* W, const
     char* base = static_cast<char*>(ws);
 
     // fork: dW/db on the auxiliary stream, the dH chain on the caller's
-    const double gather_bytes = 2.0 * s.B * s.V * s.D * (s.dtype == LSR_F32 ? 4 : 2);
-    const size_t h_slice = (size_t)s.B * s.S * DWS_COLS * (s.dtype == LSR_F32 ? 4 : 2);
-    const bool apart = gather_bytes <= AUX_MAX_GATHER_BYTES || h_slice <= AUX_SMALL_SLICE_BYTES || (L.dw_tile_passes > 0 && dW && w.n_vc == 1);
-    const bool overlap = !prof.on && dH && (dW || db) && gather_bytes >= AUX_MIN_GATHER_BYTES && apart;
+    const bool overlap = !prof.on && dH && (dW || db) && dw_beside_dh(s, w.n_vc, dW != nullptr);
     AuxFork lane(overlap ? aux_lane_of_current_device() : nullptr, st);
     const hipStream_t st_dw = lane.side();
 
@@ -974,29 +989,25 @@ int lsr_gather_probe(const void* table, size_t window_bytes, int steps, int laun
     return LSR_OK;
 }
 
-int lsr_head_plan(const lsr_head_desc* desc, int32_t* plan) {
+int lsr_head_plan_ex(const lsr_head_desc* desc, int32_t* plan, int slots) {
     Shape s;
     const int rc = check_desc(desc, &s);
     if (rc != LSR_OK) return rc;
     if (!plan) return LSR_ERR_NULL;
+    if (slots < 1) return LSR_ERR_SHAPE;
+    const FwdChunks f = fwd_chunks(s);
     const BwdWs w = bwd_ws(s);
-    plan[0] = fwd_chunks(s).tpc;
-    plan[1] = w.n_seg;
-    plan[2] = w.seg_len;
-    plan[3] = (s.S <= PLACE_MAX_S && w.seg_len <= PLACE_MAX_SEG) ? 1 : 0;
-    const bool whole = s.D % DWS_COLS == 0;        // figures that are reported for whole slices only (see the header)
-    plan[4] = whole ? w.n_vc : 1;
-    plan[5] = whole ? w.vc_len : s.V;
-    plan[6] = whole ? dh_buckets_per_wave(s, w.n_vc) : 0;
-    plan[7] = whole ? dw_stage_rows(dw_batch_chunk(s)) : 0;
-    plan[8] = dw_batch_chunk(s);
-    plan[9] = fwd_chunks(s).n_chunks;
-    plan[10] = fwd_seg(s);
-    plan[11] = fwd_chunks(s).resident ? 1 : 0;
-    plan[12] = (whole && dh_slices_owned(s)) ? 1 : 0;
-    plan[13] = dw_tile_passes(s);
+    const int32_t all[LSR_PLAN_EX_SLOTS] = {
+        f.tpc, w.n_seg, w.seg_len, (s.S <= PLACE_MAX_S && w.seg_len <= PLACE_MAX_SEG) ? 1 : 0,
+        w.n_vc, w.vc_len, dh_buckets_per_wave(s, w.n_vc), dw_stage_rows(dw_batch_chunk(s)),
+        dw_batch_chunk(s), f.n_chunks, fwd_seg(s), f.resident ? 1 : 0,
+        dh_slices_owned(s) ? 1 : 0, dw_tile_passes(s), dh_waves_per_bucket(s, w.n_vc), f.window,
+        dw_beside_dh(s, w.n_vc, true) ? 1 : 0};
+    for (int i = 0; i < slots && i < LSR_PLAN_EX_SLOTS; ++i) plan[i] = all[i];
     return LSR_OK;
 }
+
+int lsr_head_plan(const lsr_head_desc* desc, int32_t* plan) { return lsr_head_plan_ex(desc, plan, LSR_PLAN_SLOTS); }
 
 const char* lsr_status_string(int status) {
     switch (status) {

@@ -23,7 +23,8 @@ def test_plans_of_the_benchmark_shapes():
     assert p == {"fwd_tiles_per_chunk": 4, "fwd_chunks": 32, "fwd_segment_rows": 32, "fwd_resident_workgroups": 0,
                  "sort_segments": 64, "sort_segment_len": 3968, "sort_places_through_lds": 1,
                  "dh_chunks": 8, "dh_chunk_len": 31251, "dh_buckets_per_wave": 2, "dw_tile_rows": 64,
-                 "dw_sequences_per_launch": 64, "dh_slices_owned_by_xcd": 0, "dw_lds_tile_passes": 4}
+                 "dw_sequences_per_launch": 64, "dh_slices_owned_by_xcd": 0, "dw_lds_tile_passes": 4,
+                 "dh_waves_per_bucket": 1, "fwd_window_segments": 0, "dw_beside_dh": 0}
     p = lsr.lsr_head_plan(16, 256, 768, 250002, lsr.LSR_BF16)           # C4: longer buckets, one per wave
     assert (p["dh_chunks"], p["dh_buckets_per_wave"], p["dw_tile_rows"]) == (8, 1, 64)
     # a small batch: dH slices owned by XCDs; S = 256: the LDS-tile dW kernel with two copy passes per tile
@@ -45,8 +46,15 @@ def test_plans_of_the_benchmark_shapes():
     assert lsr.lsr_head_plan(17, 128, 768, 30522, lsr.LSR_BF16)["dh_slices_owned_by_xcd"] == 0
     p = lsr.lsr_head_plan(256, 512, 768, 250002, lsr.LSR_BF16)          # a batch whose H slice is 4x L2: four dW launches
     assert (p["dw_sequences_per_launch"], p["dw_tile_rows"]) == (64, 64)
-    p = lsr.lsr_head_plan(3, 40, 200, 900, lsr.LSR_BF16)                # D not a multiple of 64: whole-row kernels
-    assert (p["dh_buckets_per_wave"], p["dw_tile_rows"], p["dh_chunks"]) == (0, 0, 1)
+    # D not a multiple of 64: the same sliced kernels; windows of half the rows (a row piece touches two cache lines)
+    p = lsr.lsr_head_plan(3, 40, 200, 900, lsr.LSR_BF16)
+    assert (p["dh_buckets_per_wave"], p["dw_tile_rows"], p["dh_chunks"], p["fwd_resident_workgroups"]) == (4, 64, 1, 0)      # 32 entries per bucket: four buckets per wave
+    p = lsr.lsr_head_plan(40, 200, 712, 60000, lsr.LSR_BF16)
+    assert (p["dh_chunks"], p["dh_chunk_len"], p["dw_lds_tile_passes"], p["dw_beside_dh"]) == (4, 15000, 2, 1)
+    # float32: windows of whole sequences; a single query runs without the auxiliary stream
+    p = lsr.lsr_head_plan(64, 32, 768, 30522, lsr.LSR_F32)
+    assert (p["fwd_window_segments"], p["fwd_chunks"], p["fwd_segment_rows"]) == (96, 3, 8)
+    assert lsr.lsr_head_plan(2, 16, 64, 1000, lsr.LSR_F32)["dw_beside_dh"] == 0
 
 
 def test_plan_invariants_on_random_shapes():
@@ -69,24 +77,33 @@ def test_plan_invariants_on_random_shapes():
                 assert p["sort_places_through_lds"] == 0
             c, clen = p["dh_chunks"], p["dh_chunk_len"]
             assert 1 <= c <= 64 and c * clen >= V and (c - 1) * clen < V
-            if D % 64 != 0:
-                assert c == 1 and p["dh_buckets_per_wave"] == 0 and p["dw_tile_rows"] == 0
-            else:
-                assert p["dh_buckets_per_wave"] in ((1, 2, 4) if dt == lsr.LSR_F32 else (1, 2, 4, 8))
-                assert c == 1 or c <= V * esize // (32 * S)      # re-reading dH stays below a quarter of the gathers
-                assert c == 1 or clen * 64 * esize <= (4 << 20) or c == 64 or c == V * esize // (32 * S)
-                rows, nb = p["dw_tile_rows"], p["dw_sequences_per_launch"]
-                assert 1 <= nb <= B and (B + nb - 1) // nb <= 16
-                assert rows in (0, 16, 32, 64) and nb * rows * 8 <= 48 * 1024
-                assert (rows == 0) == (nb * 16 * 8 > 48 * 1024)
-                # several launches only where rows of H are reused often, and few enough that re-reading dW stays small
-                assert nb == B or (V >= 16 * S and (B + nb - 1) // nb <= min(16, 1 + B * esize // 32))
+            assert p["dh_buckets_per_wave"] in ((1, 2, 4) if dt == lsr.LSR_F32 else (1, 2, 4, 8))
+            assert p["dh_waves_per_bucket"] in (1, 2, 4, 8)
+            assert c == 1 or c <= V * esize // (32 * S)      # re-reading dH stays below a quarter of the gathers
+            ragged = D % 64 != 0
+            window = (4 << 20) // (2 if D * esize % 128 != 0 else 1)
+            if ragged:
+                # the chunk bounds (c + 1 per bucket) take the place of the counts, which the placement read last
+                assert c == 1 or B * S * (c + 1) <= B * n_seg * S
+            assert c == 1 or clen * 64 * esize <= window or c == 64 or c == V * esize // (32 * S) or (ragged and c == n_seg - 1)
+            rows, nb = p["dw_tile_rows"], p["dw_sequences_per_launch"]
+            assert 1 <= nb <= B and (B + nb - 1) // nb <= 16
+            assert rows in (0, 16, 32, 64) and nb * rows * 8 <= 48 * 1024
+            assert (rows == 0) == (nb * 16 * 8 > 48 * 1024)
+            # several launches only where rows of H are reused often, and few enough that re-reading dW stays small
+            assert nb == B or (V >= 16 * S and (B + nb - 1) // nb <= min(16, 1 + B * esize // 32))
             seg = p["fwd_segment_rows"]
             assert seg == (8 if S <= 64 else 32)
             segs = B * ((S + seg - 1) // seg)
             tiles_max = (segs * seg + 255) // 256
             assert p["fwd_tiles_per_chunk"] >= 1 and p["fwd_chunks"] <= B
-            assert (p["fwd_chunks"] - 1) * p["fwd_tiles_per_chunk"] < tiles_max <= p["fwd_chunks"] * p["fwd_tiles_per_chunk"]
+            if dt == lsr.LSR_BF16:
+                assert (p["fwd_chunks"] - 1) * p["fwd_tiles_per_chunk"] < tiles_max <= p["fwd_chunks"] * p["fwd_tiles_per_chunk"]
+            else:
+                # windows cover the longest list; the last sequence that begins in one may run on behind it
+                win, per_seq = p["fwd_window_segments"], (S + seg - 1) // seg
+                assert (p["fwd_chunks"] - 1) * win < segs <= p["fwd_chunks"] * win and win >= per_seq
+                assert p["fwd_tiles_per_chunk"] * 256 >= min(segs, win + per_seq - 1) * seg
             # forward workspace: O(B*S) tables, plus one (max, position) slot per chunk and vocabulary entry
             # where a chunk boundary can fall inside a sequence (bf16 path, S above one block)
             fw = lsr.lsr_head_workspace_bytes(B, S, D, V, dt, False)
@@ -95,7 +112,7 @@ def test_plan_invariants_on_random_shapes():
             assert tables + parts <= fw <= tables + parts + 8 * 256
             # the backward workspace holds what the plan implies
             # (the sorted (v, g) lists are followed by 256 entries of slack that the dH gather may read, never write)
-            need = 8 * (B * V + 256) + 4 * B * n_seg * S + 4 * B * (S + 1) + (4 * B * S * (c + 1) if c > 1 else 0)
+            need = 8 * (B * V + 256) + 4 * B * n_seg * S + 4 * B * (S + 1) + (4 * B * S * (c + 1) if c > 1 and not ragged else 0)
             if S <= 8192 and B <= 6144:
                 ws = lsr.lsr_head_workspace_bytes(B, S, D, V, dt, True)
                 assert need <= ws <= need + 4 * 256
@@ -108,3 +125,7 @@ def test_plan_argument_errors(lib):
     bad = binding._desc(2, 16, 60, 1000, lsr.LSR_BF16)
     assert lib.lsr_head_plan(ctypes.byref(bad), out) == 2
     assert lib.lsr_head_plan(None, out) == 1
+    assert lib.lsr_head_plan_ex(ctypes.byref(d), out, 0) == 2
+    out[14] = out[15] = -5
+    assert lib.lsr_head_plan(ctypes.byref(d), out) == 0 and out[13] >= 0      # the first 14 values and nothing behind them
+    assert list(out)[14:] == [-5, -5]
