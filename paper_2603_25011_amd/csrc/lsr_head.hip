@@ -123,6 +123,11 @@ int fwd_f32_window(const Shape& s) {
         const double cost = ceil(units / 256.0) * (L * seg + 32.0);
         if (!best || cost < best_cost) { best = L; best_cost = cost; }
     }
+    // one workgroup of fwd_threads(FWD_NWN) threads per (window, vocabulary tile, in groups of FWD_GV_COLS columns), at most
+    // 2^32 - 1 threads in a launch (a single window always fits)
+    const long long max_units = (0xffffffffll / fwd_threads(FWD_NWN)) / 8 * 8;
+    const long long groups = ((long long)s.V + FWD_GV_COLS - 1) / FWD_GV_COLS * (FWD_GV_COLS / fwd_tn(FWD_NWN));
+    while (groups * (((long long)s.B * per_seq + best - 1) / best) > max_units) best *= 2;
     return best;
 }
 

@@ -129,3 +129,17 @@ def test_plan_argument_errors(lib):
     out[14] = out[15] = -5
     assert lib.lsr_head_plan(ctypes.byref(d), out) == 0 and out[13] >= 0      # the first 14 values and nothing behind them
     assert list(out)[14:] == [-5, -5]
+
+
+def test_float32_forward_grids_stay_launchable():
+    """A launch holds fewer than 2^32 threads: 512 per (chunk, tile of 256 vocabulary entries), in groups of four tiles.
+    With two sequences and half of the largest B * |V| each window would otherwise be one sequence: 2^23 workgroups."""
+    for B in (1, 2, 3, 5, 8, 16, 100, 1000, 65535):
+        for S in (1, 8, 64, 65, 512, 4096, 32768):
+            for V in ((2 ** 31 - 1) // B, 2 ** 30 // B, 2 ** 26 // B + 1, 256):
+                V = min(V, 2 ** 31 - 4097)
+                if B * S >= 2 ** 31 or V < 1:
+                    continue
+                p = lsr.lsr_head_plan(B, S, 8, V, lsr.LSR_F32)
+                tiles = ((V + 255) // 256 + 3) // 4 * 4
+                assert (tiles * p["fwd_chunks"] + 7) // 8 * 8 * 512 < 2 ** 32, (B, S, V)
