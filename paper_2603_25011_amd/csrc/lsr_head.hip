@@ -182,6 +182,7 @@ void dh_chunks(const Shape& s, int n_seg, int* n_vc, int* vc_len) {
 }
 int dw_batch_chunk(const Shape& s);
 int dw_stage_rows(int nb);
+int dw_tile_passes(const Shape& s);
 // bf16_out: dH and dW are stored as bfloat16.  A result that several launches add up (dH over vocabulary
 // chunks, dW over chunks of sequences) then keeps its float32 partial sums in a staging array of the
 // workspace and is rounded once, by the last launch.
@@ -213,7 +214,8 @@ BwdWs bwd_ws(const Shape& s, bool bf16_out = false) {
     if (s.D % DWS_COLS != 0) w.cb_off = w.cnt_off;
     else if (w.n_vc > 1) w.dh_stage_off += align_up(sizeof(int) * (size_t)s.B * s.S * (w.n_vc + 1));
     w.dw_stage_off = w.dh_stage_off + ((bf16_out && w.n_vc > 1) ? align_up(sizeof(float) * (size_t)s.B * s.S * s.D) : 0);
-    const bool dw_multi = dw_stage_rows(dw_batch_chunk(s)) > 0 && dw_batch_chunk(s) < s.B;
+    // (the LDS-tile kernel takes one launch, and without dW nothing is staged)
+    const bool dw_multi = dw_tile_passes(s) == 0 && dw_stage_rows(dw_batch_chunk(s)) > 0 && dw_batch_chunk(s) < s.B;
     w.total = w.dw_stage_off + ((bf16_out && dw_multi) ? align_up(sizeof(float) * (size_t)s.V * s.D) : 0);
     return w;
 }

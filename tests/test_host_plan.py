@@ -143,3 +143,17 @@ def test_float32_forward_grids_stay_launchable():
                 p = lsr.lsr_head_plan(B, S, 8, V, lsr.LSR_F32)
                 tiles = ((V + 255) // 256 + 3) // 4 * 4
                 assert (tiles * p["fwd_chunks"] + 7) // 8 * 8 * 512 < 2 ** 32, (B, S, V)
+
+
+def test_bfloat16_gradients_are_staged_only_where_several_launches_add_up():
+    """Beside the float32 workspace: B*S*D floats where dH takes several vocabulary chunks, |V|*D floats where the sliced
+    dW gather takes several launches; none for the LDS-tile dW kernel, which takes one."""
+    for B, S, D, V in ((256, 512, 1000, 100000), (256, 512, 768, 250002), (64, 512, 1024, 250002), (300, 100, 768, 30522),
+                       (260, 1024, 72, 30522), (16, 64, 128, 30522), (256, 512, 1000, 30522)):
+        p = lsr.lsr_head_plan(B, S, D, V, lsr.LSR_BF16)
+        extra = (lsr.lsr_head_backward_ex_workspace_bytes(B, S, D, V, lsr.LSR_BF16, lsr.LSR_BF16)
+                 - lsr.lsr_head_workspace_bytes(B, S, D, V, lsr.LSR_BF16, True))
+        want = 4 * B * S * D if p["dh_chunks"] > 1 else 0
+        if p["dw_tile_rows"] > 0 and p["dw_sequences_per_launch"] < B and p["dw_lds_tile_passes"] == 0:
+            want += 4 * V * D
+        assert want <= extra <= want + 2 * 256, (B, S, D, V)
