@@ -681,7 +681,8 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
 // As in the dW gather, `prev` (float32, may be null) is added to the sums of this launch, `add_dst` adds
 // what dst already holds, dst is float32 or bfloat16; `write_all` makes every bucket write (the launch
 // that produces the final value of a fresh result), otherwise only buckets with entries in this chunk do.
-// grid = (B * ceil(S / (4*BPW)), ceil(D/64)), or xcd_slice_grid workgroups; 256 threads.
+// grid = (B, ceil(S / (4*BPW)), ceil(D/64)), 256 threads, or (B, S, ceil(D/64)), 64 * WPB threads, where the WPB waves of
+// a workgroup share one bucket; xcd_slice_grid workgroups instead of either where XCDs own the slices.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void bwd_chunk_bounds_kernel(const int* __restrict__ bstart,
                                                                const uint2* __restrict__ perm,
@@ -730,21 +731,26 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
         dc = u.dc_first;
         g = u.item;
     } else {
-        dc = blockIdx.y;                                           // slice-major order
-        g = blockIdx.x;
+        dc = blockIdx.z;                                           // slice-major order
+        g = 0;
     }
     // Within a slice, consecutive workgroups take the same positions of consecutive sequences
     // (b fastest).  Workgroups are dealt to the chip's shader engines in a fixed rotation; with s
     // fastest, the empty buckets behind the end of each sequence recur with a period that can leave
     // some engines with twice the work of others.
-    const int b = g % B;
-    const int s = WPB > 1 ? g / B : ((g / B) * 4 + wave) * BPW + lane / G;
+    const int sg = xcd_own ? g / B : (int)blockIdx.y;
+    const int b = xcd_own ? g - sg * B : (int)blockIdx.x;
+    const int s = WPB > 1 ? sg : (sg * 4 + wave) * BPW + lane / G;
     const bool live = s < S;
     const int bq = live ? b * S + s : 0;
     const size_t bi = n_vc == 1 ? (size_t)b * (S + 1) + s : (size_t)bq * (n_vc + 1) + vc;
     const int beg = live ? bounds[bi] : 0;
     const int end = live ? bounds[bi + 1] : 0;
     if (!write_all && !__any(beg < end)) return;      // nothing of this chunk in any bucket of the wave (WPB > 1: of the workgroup)
+    // A shared bucket of at most one block of entries is the first wave's alone: the others leave at once, and nobody
+    // waits at the barrier below (all waves of the workgroup see the same list).
+    const bool alone = WPB > 1 && end - beg <= G;
+    if (alone && wave > 0) return;
     const int col0 = dc * DWS_COLS + (lane % LPR) * N;
     const bool col_ok = col0 < D;              // the last slice may be partly filled: the lanes behind D gather column 0
     const int sub = (lane % G) / LPR;
@@ -827,12 +833,14 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
         }
         cur = nxt;
     }
+    if (__any(beg < end)) {
 #pragma unroll
-    for (int off = LPR; off < G; off <<= 1)
+        for (int off = LPR; off < G; off <<= 1)
 #pragma unroll
-        for (int i = 0; i < N; ++i) acc[i] += __shfl_xor(acc[i], off);
-    if constexpr (WPB > 1) {
-        // the waves' sums, added in wave order (the exit above is taken by all waves of a bucket or by none)
+            for (int i = 0; i < N; ++i) acc[i] += __shfl_xor(acc[i], off);
+    }
+    if (WPB > 1 && !alone) {
+        // the waves' sums, added in wave order (the exits above leave all waves of a bucket or the first one)
         __shared__ __attribute__((aligned(16))) float s_sum[WPB][DWS_COLS];
         if (sub == 0 && wave > 0) {
 #pragma unroll

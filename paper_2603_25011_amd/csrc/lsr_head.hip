@@ -238,26 +238,29 @@ int dh_buckets_per_wave(const Shape& s, int n_vc) {
 
 // Waves that share a bucket of the sliced dH gather (then one bucket per workgroup, else four waves with buckets
 // of their own).  One wave per long list leaves the launch waiting for its longest lists (a sequence of 4 tokens
-// has |V| / 4 entries per bucket), and the chip half empty where buckets are few; a wave more per bucket costs
-// about 0.2 ns of launch and prologue also where the bucket turns out empty (padding, sparse gradients).
+// has |V| / 4 entries per bucket) and the chip half empty where buckets are few.  The price is paid where the lists turn
+// out short, which the host cannot know: sparse gradients launch the same waves, and all but the first of a bucket of at
+// most 64 entries leave at once (0.05 to 0.2 ns each).  The lines lie where one gradient in twenty costs about 3 % of a step.
+// Forward and backward, us, one wave per bucket -> as chosen here, for dense gradients; one in five; one in twenty (D=768
+// |V|=30522 where not said; in brackets the waves of a launch at one per bucket, x launches, and the estimated list):
+//   4  B=64 S=32 (25k, 1363) 594 -> 462; 268 -> 259; 202 -> 200 (8 waves: 450; 272; 236).  float32 1576 -> 1216; 883 -> 848;
+//      749 -> 736.  B=32 S=64 (25k, 681) 359 -> 297; 216 -> 208; 172 -> 170.  B=100 S=24 D=384 |V|=60000 (14k x 2, 1786) 916 ->
+//      694; 412 -> 376; 303 -> 304.  B=24 S=50 D=512 |V|=120000 (10k x 4, 857) 793 -> 644; 398 -> 379; 317 -> 319.  B=128 S=24
+//      D=512 (25k, 1817) 652 -> 534; 320 -> 302; 239 -> 247
+//   2  B=32 S=128 D=1024 (66k, 341) 489 -> 446; 337 -> 343; 303 -> 313.  B=48 S=128 D=1024 (74k, 341) 517 -> 475; 366 -> 375;
+//      340 -> 343.  B=16 S=128 (25k, 341) 234 -> 227; 183 -> 184; 174 -> 174.  B=128 S=40 (61k, 1090) 975 -> 863; 463 -> 439;
+//      341 -> 348 (4 waves: 801; 447; 355).  B=60 S=40 |V|=200000 (29k x 7, 1020) 3448 -> 3062; 1470 -> 1412; 1085 -> 1093
+//   1  (two waves instead) B=64 S=100 |V|=50000 (77k x 2, 357), backward 566 -> 550; -; 176 -> 197.  B=40 S=100 |V|=50000 (48k x 2, 357)
+//      623 -> 590; 383 -> 381; 325 -> 333.  B=256 S=32 (98k, 1363), dH 904 -> 647; 187 -> 153; 61 -> 75 and the backward, where
+//      it runs beside dW, 1677 -> 1753; -; 254 -> 257.  B=20 S=200 |V|=60000 (48k x 4, 107) 537 -> 510; 410 -> 414; 370 -> 377
 // List lengths as estimated above, in the time of bfloat16 entries (a float32 row piece takes twice the lanes).
-// Measured (dH us with 1 / 2 / 4 / 8 waves; waves at one per bucket, estimated entries per bucket and chunk):
-// B=100 S=24 D=384 |V|=60000 (14k, 1786) 538 / 420 / 308 / 281; B=24 S=50 D=512 |V|=120000 (10k, 857) 438 / 367 /
-// 294 / 250; B=10 S=60 D=768 |V|=200000 (7k, 680) 361 / 317 / 292 / 324; B=60 S=40 D=768 |V|=200000 (29k, 1020)
-// 2046 / 1675 / 1174 / 1241; B=30 S=80 D=256 |V|=25000 (10k, 446) 54 / 39 / 32 / 45; float32 B=64 S=32 D=768
-// |V|=30522 (25k, 681) 865 / 537 / 421 / 344; B=32 S=128 D=1024 |V|=30522 (66k, 341) 200 / 144 / 169 / 291;
-// B=256 S=32 D=768 |V|=30522 (98k, 1363) 910 / 659 / 626 / 830, with one gradient in twenty 63 / 86 / 142 / 301;
-// B=64 S=100 D=768 |V|=50000 (77k, 357) 305 / 294 / 381 / 618, with one in twenty 70 / 107 / 192; B=150 S=60 D=768 |V|=40000 (108k, 476) 482 / 474 / 567 /
-// 880; B=16 S=256 |V|=250002 (49k, 174) 602 / 602 / 743; B=12 S=300 |V|=100000 (43k, 159) 175 / 195 / 291;
-// B=200 S=100 D=768 |V|=30522 (240k, 436) 481 / 501 / 602; B=250 S=60 D=1024 |V|=100000 (240k, 595) 2513 / 2519 / 2828,
-// with one in twenty 442 / 626 / 1142.
-// From 64k waves on what long lists win is no more than what sparse gradients lose.
 int dh_waves_per_bucket(const Shape& s, int n_vc) {
     const double list = (double)s.V / ((0.7 * s.S > 1.0 ? 0.7 * s.S : 1.0) * n_vc) * (s.dtype == LSR_F32 ? 2.0 : 1.0);
-    const long long waves = (long long)s.B * s.S * n_slices(s.D);
-    if (waves <= 4096 && list >= 64.0) return 4;           // latency alone (B=2 S=16 D=64 |V|=1000: 16 -> 6.4 us)
-    if (list < 256.0 || waves > 65536) return 1;
-    return waves > 32768 ? 2 : (list >= 1024.0 ? 8 : 4);
+    const long long waves = (long long)s.B * s.S * n_slices(s.D);      // per launch, at one per bucket
+    if (waves <= 4096 && list >= 64.0) return 4;                       // latency alone (B=2 S=16 D=64 |V|=1000: 16 -> 6.4 us)
+    if (list < 256.0) return 1;
+    if (waves * n_vc > 80000) return list >= 512.0 && waves <= 80000 ? 2 : 1;
+    return waves * n_vc <= 16384 || (waves <= 32768 && list >= 512.0) ? 4 : 2;
 }
 
 // Sequences per launch of the sliced dW gather.  The gather is L2-resident while the H slice of the
@@ -468,8 +471,7 @@ void launch_dh_sliced(int bpw, int wpb, dim3 grid, hipStream_t st, const T* W, c
 #define LSR_DH2(BPW, WPB, O32) hipLaunchKernelGGL((bwd_dh_sliced_kernel<T, BPW, WPB, OT, O32>), grid, dim3(dh_threads(WPB)), 0, st, W, bounds, \
                                                   perm, prev, dst, add_dst, write_all, s.B, s.S, s.D, s.V, n_groups, n_vc, vc, xcd_own ? 1 : 0)
 #define LSR_DH(BPW, WPB) do { if (off32) LSR_DH2(BPW, WPB, true); else LSR_DH2(BPW, WPB, false); } while (0)
-    if (wpb == 8) LSR_DH(1, 8);
-    else if (wpb == 4) LSR_DH(1, 4);
+    if (wpb == 4) LSR_DH(1, 4);
     else if (wpb == 2) LSR_DH(1, 2);
     else if (bpw == 1) LSR_DH(1, 1);
     else if (bpw == 2) LSR_DH(2, 1);
@@ -746,7 +748,7 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
             bounds = cb;
         }
         const dim3 grid = L.dh_xcd_own ? dim3((unsigned)xcd_slice_grid(n_slices(s.D), L.dh_groups, 1))
-                                       : dim3((unsigned)L.dh_groups, (unsigned)n_slices(s.D));
+                                       : dim3((unsigned)s.B, (unsigned)(L.dh_groups / s.B), (unsigned)n_slices(s.D));
         float* stage = reinterpret_cast<float*>(base + w.dh_stage_off);
         for (int vc = 0; vc < w.n_vc; ++vc) {
             const bool last = vc + 1 == w.n_vc;

@@ -108,13 +108,64 @@ def test_fp32_logits_are_the_fma_chain_in_ascending_d(B, S, D, V):
 @pytest.mark.parametrize("B,S,D,V,dy_keep", [
     (3, 10, 64, 1000, None),       # four waves per bucket, few buckets; lists of one or two 64-entry blocks per wave
     (2, 5, 64, 3000, 0.02),        # ... lists shorter than a block: waves without entries
-    (100, 24, 128, 60000, None),   # eight waves per bucket, two vocabulary chunks
+    (100, 24, 128, 60000, None),   # four waves per bucket, two vocabulary chunks
     (100, 24, 128, 40000, 0.05),
     (40, 30, 256, 9000, None),     # four waves per bucket
     (3300, 10, 64, 2000, None),    # two waves per bucket (33 000 waves at one)
 ])
 def test_dh_lists_shared_by_waves(B, S, D, V, dy_keep, dtype):
     print(run_case(wl.make_custom(B, S, D, V, dtype=dtype, seed=B + S, len_lo=1, dy_keep=dy_keep)))
+
+
+def dh_in_float64(B, S, V, g, I, W):
+    """dH = sum of g W over the entries of each bucket, and the sum of the magnitudes, in float64 (one sequence at a time)."""
+    D = W.shape[1]
+    out, size = (torch.zeros((B, S, D), dtype=torch.float64, device="cuda") for _ in range(2))
+    Wd = W.double()
+    for b in range(B):
+        t = g[b].double()[:, None] * Wd
+        out[b].index_add_(0, I[b].long(), t)
+        size[b].index_add_(0, I[b].long(), t.abs())
+    return out, size
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,S,D,V,waves", [
+    (2, 16, 64, 2500, 4),
+    (3, 9, 72, 40000, 4),          # several vocabulary chunks, the last slice partly filled
+    (48, 20, 1024, 8000, 4),       # slices in grid order
+    (75, 48, 1024, 9500, 2),
+])
+def test_shared_lists_around_one_block(B, S, D, V, waves, dtype):
+    """Lists of 0, 1, 63, 64, 65, 127, ... entries where waves share a bucket: up to 64 entries are the first wave's alone.
+    Y is so small that g = dY.  Every addition rounds to 2^-24 of a sum that the magnitudes bound: a lane adds a list in
+    chains of at most ceil(n / 4) entries, then joins lanes and waves."""
+    dt = lsr.LSR_F32 if dtype == "f32" else lsr.LSR_BF16
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    if dtype == "bf16":
+        assert lsr.lsr_head_plan(B, S, D, V, dt)["dh_waves_per_bucket"] == waves
+    g = torch.Generator(device="cuda").manual_seed(V)
+    sizes = [0, 1, 63, 64, 65, 127, 128, 129, 255, 256, 257]
+    I = torch.empty((B, V), dtype=torch.int32, device="cuda")
+    for b in range(B):
+        n = [sizes[(b + s) % len(sizes)] for s in range(S - 1)]
+        lists = torch.repeat_interleave(torch.arange(S, device="cuda"), torch.tensor(n + [V - sum(n)], device="cuda").clamp(min=0))[:V]
+        I[b] = lists[torch.randperm(V, device="cuda", generator=g)].int()
+    W = torch.randn((V, D), device="cuda", generator=g).mul_(0.05).to(td)
+    H = torch.zeros((B, S, D), device="cuda", dtype=td)
+    Y = torch.full((B, V), 1e-30, device="cuda")
+    for keep in (1.0, 0.3):
+        dY = torch.randn((B, V), device="cuda", generator=g) * (torch.rand((B, V), device="cuda", generator=g) < keep)
+        for accumulate in (False, True):
+            dH0 = torch.randn((B, S, D), device="cuda", generator=g)
+            dH = dH0.clone()
+            ws = torch.empty(lsr.lsr_head_backward_ex_workspace_bytes(B, S, D, V, dt), dtype=torch.uint8, device="cuda")
+            lsr.lsr_head_backward_ex(B, S, D, V, dt, H, W, dY, Y, I, dH, None, None, lsr.LSR_F32, accumulate, ws)
+            want, size = dh_in_float64(B, S, V, dY, I, W)
+            if accumulate:
+                want, size = want + dH0.double(), size + dH0.double().abs()
+            n = torch.zeros((B, S), device="cuda", dtype=torch.float64).scatter_add_(1, I.long(), torch.ones((B, V), device="cuda", dtype=torch.float64))
+            assert bool(((dH.double() - want).abs() <= (n[:, :, None] / 4 + 16) * 2.0 ** -24 * size).all())
 
 
 def test_forward_beyond_the_backward_length_limit():

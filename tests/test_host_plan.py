@@ -51,6 +51,12 @@ def test_plans_of_the_benchmark_shapes():
     assert (p["dh_buckets_per_wave"], p["dw_tile_rows"], p["dh_chunks"], p["fwd_resident_workgroups"]) == (4, 64, 1, 0)      # 32 entries per bucket: four buckets per wave
     p = lsr.lsr_head_plan(40, 200, 712, 60000, lsr.LSR_BF16)
     assert (p["dh_chunks"], p["dh_chunk_len"], p["dw_lds_tile_passes"], p["dw_beside_dh"]) == (4, 15000, 2, 1)
+    # waves that share a list: surplus waves cost sparse gradients a few per cent at most
+    waves = {(64, 32, 768, 30522): 4, (100, 24, 384, 60000): 4, (4, 64, 768, 30522): 4, (32, 128, 1024, 30522): 2, (128, 40, 768, 30522): 2,
+             (60, 40, 768, 200000): 2, (64, 100, 768, 50000): 1, (256, 32, 768, 30522): 1, (250, 60, 1024, 100000): 1}
+    for shape, n in waves.items():
+        assert lsr.lsr_head_plan(*shape, lsr.LSR_BF16)["dh_waves_per_bucket"] == n, shape
+    assert lsr.lsr_head_plan(64, 32, 768, 30522, lsr.LSR_F32)["dh_waves_per_bucket"] == 4
     # float32: windows of whole sequences; a single query runs without the auxiliary stream
     p = lsr.lsr_head_plan(64, 32, 768, 30522, lsr.LSR_F32)
     assert (p["fwd_window_segments"], p["fwd_chunks"], p["fwd_segment_rows"]) == (96, 3, 8)
@@ -78,7 +84,7 @@ def test_plan_invariants_on_random_shapes():
             c, clen = p["dh_chunks"], p["dh_chunk_len"]
             assert 1 <= c <= 64 and c * clen >= V and (c - 1) * clen < V
             assert p["dh_buckets_per_wave"] in ((1, 2, 4) if dt == lsr.LSR_F32 else (1, 2, 4, 8))
-            assert p["dh_waves_per_bucket"] in (1, 2, 4, 8)
+            assert p["dh_waves_per_bucket"] in (1, 2, 4)
             assert c == 1 or c <= V * esize // (32 * S)      # re-reading dH stays below a quarter of the gathers
             ragged = D % 64 != 0
             window = (4 << 20) // (2 if D * esize % 128 != 0 else 1)
