@@ -73,7 +73,8 @@ int lsr_gather_probe(const void* table, size_t window_bytes, int steps, int laun
  *   [0] most tiles per chunk of the packed forward    [1] segments of the bucket sort per sequence
  *   [2] vocabulary entries per sort segment       [3] 1 if the sort places through LDS, else 0
  *   [4] vocabulary chunks of the dH gather        [5] vocabulary entries per chunk
- *   [6] buckets per wave in the dH gather, where waves have buckets of their own ([14] = 1)
+ *   [6] buckets per wave in the sliced dH gather, where waves have buckets of their own ([14] = 1); 0: whole-row dH kernel
+ *       (D not a multiple of 64 and above 720 or with long sequences)
  *   [7] rows of the sliced dW gather's staging tile (0: whole-row dW kernel)
  *   [8] sequences per launch of the sliced dW gather (B: one launch)
  *   [9] chunks the forward grid provides for (the longest token list the shape allows)

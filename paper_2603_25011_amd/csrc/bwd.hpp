@@ -77,7 +77,7 @@ template <> struct OutVec<uint16_t> {
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 
 // A float32 sum that carries what its additions round off (the two-sum of Knuth, TAOCP vol. 2, 4.2.2), so that the value
-// is rounded once.  db is summed this way: against float64, in units of the norm of db, a plain loop over B = 13 / 64 / 256
+// is rounded once.  The sliced and the LDS-tile dW kernels sum db this way: against float64, in units of the norm of db, a plain loop over B = 13 / 64 / 256
 // sequences is off by 7.0e-8 / 1.5e-7 / 2.9e-7, the 64-lane butterfly of the whole-row kernel by 5.2e-8 / 6.7e-8 / 7.8e-8,
 // this by 2.5e-8, and by 4.0e-8 / 7.4e-8 where four / sixteen launches each round the db they hand on.
 struct Sum32 {
@@ -339,6 +339,74 @@ __global__ __launch_bounds__(256) void bwd_place_staged_kernel(const float* __re
 }
 
 // ---------------------------------------------------------------------------------------------
+// dH, whole rows (D not a multiple of 64, see sliced_gathers in lsr_head.hip).
+// dH[b,s,:] = sum over the bucket of (b,s), in ascending v, of g * W[v,:].   grid (B, S): b fastest,
+// so that the empty buckets behind the ends of the sequences are spread evenly over the chip
+// ---------------------------------------------------------------------------------------------
+// accumulate: the sums are added to what dH holds
+template <typename T, int CPT, typename OT>
+__global__ __launch_bounds__(ROW_THREADS) void bwd_dh_kernel(const T* __restrict__ W,
+                                                             const int* __restrict__ bstart,
+                                                             const uint2* __restrict__ perm,
+                                                             OT* __restrict__ dH,
+                                                             int S, int D, int V, int accumulate) {
+    constexpr int N = RowChunk<T>::N;
+    __shared__ int s_v[ROW_THREADS];
+    __shared__ float s_g[ROW_THREADS];
+    const int b = blockIdx.x, s = blockIdx.y, tid = threadIdx.x;
+    const int n_chunks = D / N;
+    const int beg = bstart[(size_t)b * (S + 1) + s];
+    const int end = bstart[(size_t)b * (S + 1) + s + 1];
+    const size_t prow = (size_t)b * V;
+    float acc[CPT][N];
+#pragma unroll
+    for (int cp = 0; cp < CPT; ++cp)
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[cp][i] = 0.f;
+
+    for (int base = beg; base < end; base += ROW_THREADS) {
+        const int n = min(ROW_THREADS, end - base);
+        const uint2 ent = perm[prow + base + min(tid, n - 1)];      // padding: the last row of the list, weight 0
+        s_v[tid] = (int)ent.x;
+        s_g[tid] = tid < n ? __uint_as_float(ent.y) : 0.f;
+        __syncthreads();
+        for (int k = 0; k < n; k += 4) {
+            uint4 x[4][CPT];
+            float g[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                g[u] = s_g[k + u];
+                const T* src = W + (size_t)s_v[k + u] * D;
+#pragma unroll
+                for (int cp = 0; cp < CPT; ++cp) {
+                    const int c = tid + cp * ROW_THREADS;
+                    x[u][cp] = c < n_chunks ? *reinterpret_cast<const uint4*>(src + c * N) : make_uint4(0, 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int cp = 0; cp < CPT; ++cp) RowChunk<T>::fma(x[u][cp], g[u], acc[cp]);
+        }
+        __syncthreads();
+    }
+    OT* out = dH + ((size_t)b * S + s) * D;
+#pragma unroll
+    for (int cp = 0; cp < CPT; ++cp) {
+        const int c = tid + cp * ROW_THREADS;
+        if (c < n_chunks) {
+#pragma unroll
+            for (int i = 0; i < N; i += 4) {
+                float4 r = make_float4(acc[cp][i], acc[cp][i + 1], acc[cp][i + 2], acc[cp][i + 3]);
+                if (accumulate) r = add4(OutVec<OT>::load4(out + c * N + i), r);
+                OutVec<OT>::store4(out + c * N + i, r);
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// dW/db, whole rows (D not a multiple of 64 or large batches, see plan_backward).
 // dW[v,:] = sum_b g[b,v] * H[b, I[b,v], :],  db[v] = sum_b g[b,v].
 // A workgroup owns VT consecutive vocabulary rows.  It first stages g and I for all B x VT pairs in
 // LDS (coalesced along v), then walks the rows one by one, skipping pairs with g = 0.
@@ -390,19 +458,18 @@ __global__ __launch_bounds__(ROW_THREADS) void bwd_dw_kernel(const T* __restrict
             const float gl = bl < B ? s_g[bl * VT + vv] : 0.f;
             gsum += gl;
             unsigned long long nz = dW ? __ballot(gl != 0.f) : 0ull;       // same in both waves
+            int bb = 0;
             while (nz) {
                 uint4 x[4][CPT];
                 float g[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    // take the next non-zero pair, or repeat a harmless one with weight 0
-                    const int bit = nz ? __builtin_ctzll(nz) : 0;
+                    // take the next non-zero pair, or repeat the last one (a row that is used anyway) with weight 0
                     const bool have = nz != 0;
-                    nz = have ? nz & (nz - 1) : 0;
-                    const int bb = bb0 + bit;
+                    bb = have ? bb0 + __builtin_ctzll(nz) : bb;
+                    nz &= nz - 1;
                     g[u] = have ? s_g[bb * VT + vv] : 0.f;
-                    const int idx = have ? s_i[bb * VT + vv] : 0;
-                    const T* src = H + ((size_t)(have ? bb : 0) * S + idx) * D;
+                    const T* src = H + ((size_t)bb * S + s_i[bb * VT + vv]) * D;
 #pragma unroll
                     for (int cp = 0; cp < CPT; ++cp) {
                         const int c = tid + cp * ROW_THREADS;
@@ -862,7 +929,7 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
 }
 
 // ---------------------------------------------------------------------------------------------
-// dW/db, LDS-tile variant (bfloat16 inputs, DWT_MIN_S <= S <= DWT_MAX_S).
+// dW/db, LDS-tile variant (bfloat16 inputs, D a multiple of 64, DWT_MIN_S <= S <= DWT_MAX_S).
 // A workgroup of 1024 threads owns 1024 consecutive vocabulary rows and one 64-column slice and walks
 // the sequences b = 0 .. B-1 in order.  For each sequence the slice of all S hidden states (S x 128
 // bytes, at most 64 KiB) is copied into LDS and every gather of the sequence is an LDS read.  Eight
@@ -879,7 +946,7 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
 // Not for sparse gradients (the cost does not fall with the number of non-zero pairs, as it does in the
 // compacting kernel above) or for few workgroups: the host takes it for shapes with at least one
 // workgroup per CU.
-// grid = ceil(V / 1024) * ceil(D / 64), slice-major.  PASSES = ceil(S / 128) copy passes per tile.
+// grid = ceil(V / 1024) * (D / 64), slice-major.  PASSES = ceil(S / 128) copy passes per tile.
 // ---------------------------------------------------------------------------------------------
 constexpr int DWT_ROWS = 1024;
 constexpr int DWT_MAX_S = 512;
@@ -903,8 +970,6 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
     const int dc = blockIdx.x / n_vtiles;
     const int v0 = (blockIdx.x - dc * n_vtiles) * DWT_ROWS;
     const int rg = tid >> 3, cc = tid & 7;
-    const int col = dc * DWS_COLS + cc * 8;
-    const bool col_ok = col < D;                           // the last slice may be partly filled: lanes behind D copy its first chunk
     const int vs = v0 + tid;                               // the row this thread stages
     const bool vs_ok = vs < V;
     const int vs_c = vs_ok ? vs : V - 1;
@@ -925,7 +990,7 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
     int ix_r;
     uint32_t hoff[PASSES];
 #pragma unroll
-    for (int p = 0; p < PASSES; ++p) hoff[p] = (uint32_t)((min(p * RGS + rg, S - 1) * D + (col_ok ? col : dc * DWS_COLS)) * 2);
+    for (int p = 0; p < PASSES; ++p) hoff[p] = (uint32_t)((min(p * RGS + rg, S - 1) * D + dc * DWS_COLS + cc * 8) * 2);
     const uint32_t voff = (uint32_t)vs_c * 4u;
     auto gload = [&](int b) {
         const size_t ro = (size_t)b * V * 4;
@@ -991,8 +1056,8 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
         const int v = v0 + rg + RGS * k;
-        if (v < V && col_ok) {
-            const size_t o = (size_t)v * D + col;
+        if (v < V) {
+            const size_t o = (size_t)v * D + dc * DWS_COLS + cc * 8;
 #pragma unroll
             for (int i = 0; i < 8; i += 4) {
                 float4 r = make_float4(acc[k][i], acc[k][i + 1], acc[k][i + 2], acc[k][i + 3]);

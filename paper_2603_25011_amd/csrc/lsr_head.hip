@@ -152,6 +152,27 @@ FwdWs fwd_ws(const Shape& s) {
     return w;
 }
 
+// Column-sliced gathers (dH and dW), or whole rows by one workgroup each.  Slices gather what L2 holds, at the price of a pass
+// over every list per slice and vocabulary chunk, whatever the list holds.  Where rows are a multiple of 64 columns that
+// always paid; where they are not, pieces of rows straddle cache lines (reads and writes) and sparse gradients, which
+// the host cannot see, ran up to 2.6 times slower in slices.  Backward, us, whole rows -> slices, for dense
+// gradients; one in five; one in twenty (|V|=30522 where not said):
+//   sliced: B=100 S=40 D=552 |V|=150000 6486 -> 2595; 1643 -> 921; 732 -> 577.  B=167 S=62 D=648 |V|=66407 5966 -> 2377; 1509 -> 858;
+//     666 -> 555.  B=64 S=64 D=456 623 -> 347; 183 -> 144; 104 -> 106.  B=256 S=32 D=600 3861 -> 2026; 940 -> 621; 380 -> 278.
+//     float32 B=32 S=64 D=712 840 -> 488; 220 -> 169; 101 -> 105.  Few waves: B=13 S=197 D=312 |V|=31091 172 -> 108; 84 -> 60;
+//     71 -> 57.  B=16 S=100 D=456 |V|=60000 434 -> 240; 138 -> 108; 81 -> 86.  B=4 S=512 D=200 |V|=50000 141 -> 100; 75 -> 69; 62 -> 65
+//     (dH alone loses where it has many waves: B=167 S=62 with one in twenty 195 -> 293)
+//   whole rows: B=64 S=200 D=712 |V|=60000 1509 -> 1137; 373 -> 452; 172 -> 261.  B=45 S=110 D=680 |V|=70000 1270 -> 844; 331 -> 335;
+//     156 -> 224.  B=16 S=250 D=904 |V|=200000 1385 -> 1586; 504 -> 806; 372 -> 547.  B=128 S=100 D=936 |V|=100000 7433 -> 4173;
+//     1840 -> 1531; 771 -> 892.  B=64 S=64 D=776 |V|=60000 1473 -> 1077; 364 -> 376; 161 -> 251.  B=8 S=128 D=968 236 -> 145; 89 -> 90;
+//     70 -> 76.  float32 B=64 S=24 D=904 |V|=30000 1610 -> 1028; 388 -> 358; 146 -> 163, B=16 S=128 D=328 |V|=20000 175 -> 187; 84 -> 79;
+//     69 -> 62.  B=30 S=3000 D=312 |V|=60000 474 -> 584; 215 -> 271; 197 -> 236
+bool sliced_gathers(const Shape& s) {
+    if (s.D % DWS_COLS == 0) return true;
+    const long long waves = (long long)s.B * s.S * n_slices(s.D);
+    return s.D <= 720 && (s.S <= 64 || (s.dtype == LSR_BF16 && waves <= 16384));
+}
+
 // ---- backward workspace: perm[B*V + PERM_SLACK] (v, g) pairs | cnt[B*n_seg*S] | bstart[B*(S+1)] |
 //      bounds[B*S*(n_vc+1)] (only when the dH gather is cut into n_vc > 1 vocabulary chunks; where D is not a
 //      multiple of 64 they take the place of cnt, which nothing reads after the placement) ----
@@ -162,26 +183,26 @@ struct BwdWs { int n_seg, seg_len, key_bits, n_vc, vc_len; size_t perm_off, cnt_
 // the first re-reads and re-writes dH once (8*B*S*D bytes), so the count is capped where that
 // traffic would pass a quarter of the gather traffic itself (B*|V|*D elements): long sequences
 // with few entries per bucket are gathered in one pass.
-// Measured where row pieces straddle lines (dH us with windows of 8 / 4 / 2 / 1 MB of elements, i.e. twice that in
-// lines): B=100 S=40 D=552 |V|=150000 3355 / 2628 / 1494 / 1345, one gradient in twenty 197 / 169 / 229 / 380; B=64 S=200
-// D=712 |V|=60000 1139 / 855 / 569 / 537; B=16 S=250 D=904 |V|=200000 1357 / 1184 / 1006 / 1071; B=200 S=400 D=184
-// |V|=40000 560 / 360 / 346 / 361 (whole rows by 128 threads, without windows: 3387, 185, 785, 991, 491).
+// Where row pieces straddle cache lines a window of half the rows takes the same lines.  Backward, us, whole -> half windows, for
+// dense gradients; one in twenty: B=100 S=40 D=552 |V|=150000 3738 -> 2595; 520 -> 577, B=256 S=32 D=600 |V|=30522 2762 -> 2026;
+// 289 -> 278, B=64 S=64 D=456 |V|=30522 405 -> 347; 89 -> 106, B=64 S=32 D=200 |V|=60000 430 -> 346; 107 -> 114; not for longer
+// sequences (B=13 S=197 D=312 |V|=31091 108 -> 108; 57 -> 64) or few waves (B=2 S=64 D=328 |V|=30522 58 -> 66; 49 -> 57).
 // n_seg: sort segments; where D is not a multiple of 64 the chunk bounds have to fit the count table.
 void dh_chunks(const Shape& s, int n_seg, int* n_vc, int* vc_len) {
     const long esize = s.dtype == LSR_F32 ? 4 : 2;
     long rows_l2 = (4l << 20) / (DWS_COLS * esize);
-    if (s.D * esize % 128 != 0) rows_l2 /= 2;      // a row piece then touches two cache lines
+    if (s.D * esize % 128 != 0 && s.S <= 64 && (long long)s.B * s.S * n_slices(s.D) > 4096) rows_l2 /= 2;
     long c = (s.V + rows_l2 - 1) / rows_l2;
     const long cap = (long)s.V * esize / (32l * s.S);
     if (c > cap) c = cap;
     if (c > 64) c = 64;
     if (s.D % DWS_COLS != 0 && c > n_seg - 1) c = n_seg - 1;
-    if (c < 1) c = 1;
+    if (c < 1 || !sliced_gathers(s)) c = 1;
     *n_vc = (int)c;
     *vc_len = (int)((s.V + c - 1) / c);
 }
 int dw_batch_chunk(const Shape& s);
-int dw_stage_rows(int nb);
+int dw_stage_rows(const Shape& s);
 int dw_tile_passes(const Shape& s);
 // bf16_out: dH and dW are stored as bfloat16.  A result that several launches add up (dH over vocabulary
 // chunks, dW over chunks of sequences) then keeps its float32 partial sums in a staging array of the
@@ -215,7 +236,7 @@ BwdWs bwd_ws(const Shape& s, bool bf16_out = false) {
     else if (w.n_vc > 1) w.dh_stage_off += align_up(sizeof(int) * (size_t)s.B * s.S * (w.n_vc + 1));
     w.dw_stage_off = w.dh_stage_off + ((bf16_out && w.n_vc > 1) ? align_up(sizeof(float) * (size_t)s.B * s.S * s.D) : 0);
     // (the LDS-tile kernel takes one launch, and without dW nothing is staged)
-    const bool dw_multi = dw_tile_passes(s) == 0 && dw_stage_rows(dw_batch_chunk(s)) > 0 && dw_batch_chunk(s) < s.B;
+    const bool dw_multi = dw_tile_passes(s) == 0 && dw_stage_rows(s) > 0 && dw_batch_chunk(s) < s.B;
     w.total = w.dw_stage_off + ((bf16_out && dw_multi) ? align_up(sizeof(float) * (size_t)s.V * s.D) : 0);
     return w;
 }
@@ -230,6 +251,7 @@ BwdWs bwd_ws(const Shape& s, bool bf16_out = false) {
 // lengths (85; 60) 0.91 / 0.75 / 0.79 / 0.90; B=256 S=512 |V|=250002, full lengths (87; 61) 9.3 / 8.0 / 7.7 /
 // 8.6; B=128 S=8192 |V|=30522 (5; 4) 4.4 / 2.4 / 1.55 / 1.37.
 int dh_buckets_per_wave(const Shape& s, int n_vc) {
+    if (!sliced_gathers(s)) return 0;
     const double per_bucket = (double)s.V / ((0.7 * s.S > 1.0 ? 0.7 * s.S : 1.0) * n_vc);
     int bpw = per_bucket >= 128.0 ? 1 : (per_bucket >= 48.0 ? 2 : (per_bucket >= 12.0 ? 4 : 8));
     if (s.dtype == LSR_F32 && bpw > 4) bpw = 4;      // a float row piece takes 16 lanes
@@ -255,6 +277,7 @@ int dh_buckets_per_wave(const Shape& s, int n_vc) {
 //      it runs beside dW, 1677 -> 1753; -; 254 -> 257.  B=20 S=200 |V|=60000 (48k x 4, 107) 537 -> 510; 410 -> 414; 370 -> 377
 // List lengths as estimated above, in the time of bfloat16 entries (a float32 row piece takes twice the lanes).
 int dh_waves_per_bucket(const Shape& s, int n_vc) {
+    if (!sliced_gathers(s)) return 1;
     const double list = (double)s.V / ((0.7 * s.S > 1.0 ? 0.7 * s.S : 1.0) * n_vc) * (s.dtype == LSR_F32 ? 2.0 : 1.0);
     const long long waves = (long long)s.B * s.S * n_slices(s.D);      // per launch, at one per bucket
     if (waves <= 4096 && list >= 64.0) return 4;                       // latency alone (B=2 S=16 D=64 |V|=1000: 16 -> 6.4 us)
@@ -282,15 +305,14 @@ int dw_batch_chunk(const Shape& s) {
     return (int)((s.B + n - 1) / n);
 }
 
-// Vocabulary rows of the (g, I) staging tile of the sliced dW gather (at most 48 KiB of LDS for the nb
-// sequences of one launch), or 0 when the whole-row kernel runs instead (too many sequences per launch for
-// 16 rows).  Also for D not a multiple of 64, against whole rows by 128 threads (dW us): B=100 S=40 D=552
-// |V|=150000 2999 -> 1040, one gradient in twenty 398 -> 534; B=128 S=100 D=936 |V|=100000 3836 -> 1640; B=250 S=64 D=1000
-// |V|=30000 2156 -> 1270; with the LDS-tile kernel B=64 S=200 D=712 |V|=60000 822 -> 285; B=200 S=500 D=120 |V|=100000 3738 -> 570.
-int dw_stage_rows(int nb) {
+// Vocabulary rows of the (g, I) staging tile of the sliced dW gather (at most 48 KiB of LDS for the sequences of
+// one launch), or 0 when the whole-row kernel runs instead (see sliced_gathers, or too many sequences per launch for
+// 16 rows).
+int dw_stage_rows(const Shape& s) {
+    const int nb = dw_batch_chunk(s);
     int VT = 64;
     while (VT > 1 && (size_t)nb * VT * 8 > 48 * 1024) VT /= 2;
-    return VT >= 16 ? VT : 0;
+    return VT >= 16 && sliced_gathers(s) ? VT : 0;
 }
 
 int check_device(int* n_cus) {
@@ -451,6 +473,18 @@ int forward_impl(const lsr_head_desc* desc, const void* H, const void* W, const 
 }
 
 template <typename T, typename OT>
+void launch_dh(int cpt, dim3 grid, hipStream_t st, const T* W, const int* bstart, const uint2* pm,
+               OT* dH, int S, int D, int V, int accumulate) {
+    switch (cpt) {
+        case 1: hipLaunchKernelGGL((bwd_dh_kernel<T, 1, OT>), grid, dim3(ROW_THREADS), 0, st, W, bstart, pm, dH, S, D, V, accumulate); break;
+        case 2: hipLaunchKernelGGL((bwd_dh_kernel<T, 2, OT>), grid, dim3(ROW_THREADS), 0, st, W, bstart, pm, dH, S, D, V, accumulate); break;
+        case 4: hipLaunchKernelGGL((bwd_dh_kernel<T, 4, OT>), grid, dim3(ROW_THREADS), 0, st, W, bstart, pm, dH, S, D, V, accumulate); break;
+        case 8: hipLaunchKernelGGL((bwd_dh_kernel<T, 8, OT>), grid, dim3(ROW_THREADS), 0, st, W, bstart, pm, dH, S, D, V, accumulate); break;
+        default: hipLaunchKernelGGL((bwd_dh_kernel<T, 16, OT>), grid, dim3(ROW_THREADS), 0, st, W, bstart, pm, dH, S, D, V, accumulate); break;
+    }
+}
+
+template <typename T, typename OT>
 void launch_dw(int cpt, dim3 grid, size_t lds, hipStream_t st, const T* H, const float* dY, const float* Y, const int* I,
                OT* dW, float* db, int B, int S, int D, int V, int VT, int accumulate) {
     switch (cpt) {
@@ -578,6 +612,7 @@ private:
 struct BwdLaunch {
     int cpt;                 // 16-byte chunks per thread of the whole-row kernels
     bool staged_place;       // the bucket sort places through LDS
+    bool dh_sliced;          // column-sliced dH gather, else whole rows
     int bpw, wpb, dh_groups; // buckets per wave, waves per bucket and workgroups per slice of the sliced dH gather
     int dw_vt;               // rows of the dW staging tile: sliced gather if dw_sliced, else whole-row kernel
     bool dw_sliced;
@@ -592,16 +627,16 @@ struct BwdLaunch {
 // owned): B=8 S=512 |V|=30522 0.062 -> 0.047 ms; B=16 S=256 |V|=250002 0.88 -> 0.73; B=32 S=256 |V|=250002
 // 1.06 -> 1.01; from B=32 at D=1024 on it loses (B=32 1.45 -> 1.67, B=64 S=512 2.65 -> 3.1: fewer L2 misses
 // but a slower kernel; the slice-major order happens to keep every sequence's bucket lists on one XCD).
-bool dh_slices_owned(const Shape& s) { return s.B <= 16; }
-// The LDS-tile dW kernel (bwd_dw_tile_kernel): bfloat16, S within the tile, and at least
+bool dh_slices_owned(const Shape& s) { return sliced_gathers(s) && s.B <= 16; }
+// The LDS-tile dW kernel (bwd_dw_tile_kernel): bfloat16, D a multiple of 64, S within the tile, and at least
 // one workgroup per CU of a 256-CU device.  Measured against the sliced gather (dW): B=64 S=512 D=1024
 // |V|=250002 1.98 -> 1.72 ms; B=256 S=512 D=768 |V|=250002 7.84 -> 5.43; B=16 S=256 |V|=250002 0.407 ->
 // 0.363; B=256 S=512 |V|=30522 1.02 -> 0.94; B=8 S=512 |V|=30522 0.0445 -> 0.0463; 60 workgroups (D=128,
 // |V|=30522) 0.030 -> 0.052.
 int dw_tile_passes(const Shape& s) {
-    if (s.dtype != LSR_BF16 || s.S < DWT_MIN_S || s.S > DWT_MAX_S) return 0;
+    if (s.dtype != LSR_BF16 || s.D % DWS_COLS != 0 || s.S < DWT_MIN_S || s.S > DWT_MAX_S) return 0;
     if (s.V > (1 << 28)) return 0;                       // the kernel keeps byte offsets within a row of dY / Y / I in 32 bits
-    const long long units = (long long)((s.V + DWT_ROWS - 1) / DWT_ROWS) * n_slices(s.D);
+    const long long units = (long long)((s.V + DWT_ROWS - 1) / DWT_ROWS) * (s.D / DWS_COLS);
     if (units < 256 || units > 0x7fffffffll) return 0;
     return (s.S + 127) / 128;
 }
@@ -609,7 +644,7 @@ int dw_tile_passes(const Shape& s) {
 bool dw_beside_dh(const Shape& s, int n_vc, bool want_dw) {
     const double gather_bytes = 2.0 * s.B * s.V * s.D * (s.dtype == LSR_F32 ? 4 : 2);
     const size_t h_slice = (size_t)s.B * s.S * DWS_COLS * (s.dtype == LSR_F32 ? 4 : 2);
-    const bool apart = gather_bytes <= AUX_MAX_GATHER_BYTES || h_slice <= AUX_SMALL_SLICE_BYTES || (dw_tile_passes(s) > 0 && want_dw && n_vc == 1);
+    const bool apart = gather_bytes <= AUX_MAX_GATHER_BYTES || (sliced_gathers(s) && h_slice <= AUX_SMALL_SLICE_BYTES) || (dw_tile_passes(s) > 0 && want_dw && n_vc == 1);
     return gather_bytes >= AUX_MIN_GATHER_BYTES && apart;
 }
 int plan_backward(const Shape& s, const BwdWs& w, BwdLaunch* L) {
@@ -618,19 +653,20 @@ int plan_backward(const Shape& s, const BwdWs& w, BwdLaunch* L) {
     L->cpt = 1;
     while (L->cpt * ROW_THREADS < n_chunks) L->cpt *= 2;
     L->staged_place = s.S <= PLACE_MAX_S && w.seg_len <= PLACE_MAX_SEG;      // plan[3] of lsr_head_plan
+    L->dh_sliced = sliced_gathers(s);
     L->bpw = dh_buckets_per_wave(s, w.n_vc);
     L->wpb = dh_waves_per_bucket(s, w.n_vc);
-    L->dh_groups = L->wpb > 1 ? s.B * s.S : s.B * ((s.S + 4 * L->bpw - 1) / (4 * L->bpw));
+    L->dh_groups = !L->dh_sliced ? 0 : (L->wpb > 1 ? s.B * s.S : s.B * ((s.S + 4 * L->bpw - 1) / (4 * L->bpw)));
     if ((long long)L->dh_groups * n_slices(s.D) > 0x7fffffffll) return LSR_ERR_SHAPE;
     L->dh_xcd_own = dh_slices_owned(s);
     if (L->dh_xcd_own && xcd_slice_grid(n_slices(s.D), L->dh_groups, 1) > 0x7fffffffll) return LSR_ERR_SHAPE;
     L->dw_tile_passes = dw_tile_passes(s);
     L->dw_tile_vtiles = (s.V + DWT_ROWS - 1) / DWT_ROWS;
     // column-sliced dW gathers (L2-resident slices of H) need a (g, I) staging tile (at most 48 KiB) at least
-    // 16 vocabulary rows wide, i.e. at most 384 sequences per launch.  Larger batches keep the whole-row
+    // 16 vocabulary rows wide, i.e. at most 384 sequences per launch.  Larger batches take the whole-row
     // kernel, which also skips zero gradients.
     L->dw_bc = dw_batch_chunk(s);
-    L->dw_vt = dw_stage_rows(L->dw_bc);
+    L->dw_vt = dw_stage_rows(s);
     L->dw_sliced = L->dw_vt > 0;
     if (L->dw_sliced) {
         // slices per group: a workgroup walks the slices of its group with one staging of (g, I), and
@@ -738,34 +774,38 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
         prof.end(2);
         if ((r = launch_status()) != LSR_OK) return r;
         prof.begin(3);
-        // column-sliced gathers, one launch per vocabulary chunk: the rows of W in use stay in L2
-        const int* bounds = bstart;
-        if (w.n_vc > 1) {
-            int* cb = reinterpret_cast<int*>(base + w.cb_off);
-            const long long n = (long long)s.B * s.S * (w.n_vc + 1);
-            hipLaunchKernelGGL(bwd_chunk_bounds_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, bstart, perm, cb,
-                               s.B * s.S, s.S, s.V, w.n_vc, w.vc_len);
-            bounds = cb;
-        }
-        const dim3 grid = L.dh_xcd_own ? dim3((unsigned)xcd_slice_grid(n_slices(s.D), L.dh_groups, 1))
-                                       : dim3((unsigned)s.B, (unsigned)(L.dh_groups / s.B), (unsigned)n_slices(s.D));
-        float* stage = reinterpret_cast<float*>(base + w.dh_stage_off);
-        for (int vc = 0; vc < w.n_vc; ++vc) {
-            const bool last = vc + 1 == w.n_vc;
-            if (OUT_F32) {
-                // partial sums live in dH itself; the first chunk of a fresh result writes every bucket
-                float* d = reinterpret_cast<float*>(dH);
-                const bool fresh = vc == 0 && !accumulate;
-                launch_dh_sliced<T, float>(L.bpw, L.wpb, grid, st, W, bounds, perm, fresh ? nullptr : d, d, 0, fresh ? 1 : 0, s, L.dh_groups,
-                                           w.n_vc, vc, L.dh_xcd_own);
-            } else if (w.n_vc == 1) {
-                launch_dh_sliced<T, OT>(L.bpw, L.wpb, grid, st, W, bounds, perm, nullptr, dH, accumulate, accumulate ? 0 : 1, s, L.dh_groups,
-                                        w.n_vc, vc, L.dh_xcd_own);
-            } else if (!last) {
-                launch_dh_sliced<T, float>(L.bpw, L.wpb, grid, st, W, bounds, perm, vc > 0 ? stage : nullptr, stage, 0, vc == 0 ? 1 : 0, s,
-                                           L.dh_groups, w.n_vc, vc, L.dh_xcd_own);
-            } else {
-                launch_dh_sliced<T, OT>(L.bpw, L.wpb, grid, st, W, bounds, perm, stage, dH, accumulate, 1, s, L.dh_groups, w.n_vc, vc, L.dh_xcd_own);
+        if (!L.dh_sliced) {
+            launch_dh<T, OT>(L.cpt, dim3(s.B, s.S), st, W, bstart, perm, dH, s.S, s.D, s.V, accumulate);
+        } else {
+            // column-sliced gathers, one launch per vocabulary chunk: the rows of W in use stay in L2
+            const int* bounds = bstart;
+            if (w.n_vc > 1) {
+                int* cb = reinterpret_cast<int*>(base + w.cb_off);
+                const long long n = (long long)s.B * s.S * (w.n_vc + 1);
+                hipLaunchKernelGGL(bwd_chunk_bounds_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, bstart, perm, cb,
+                                   s.B * s.S, s.S, s.V, w.n_vc, w.vc_len);
+                bounds = cb;
+            }
+            const dim3 grid = L.dh_xcd_own ? dim3((unsigned)xcd_slice_grid(n_slices(s.D), L.dh_groups, 1))
+                                           : dim3((unsigned)s.B, (unsigned)(L.dh_groups / s.B), (unsigned)n_slices(s.D));
+            float* stage = reinterpret_cast<float*>(base + w.dh_stage_off);
+            for (int vc = 0; vc < w.n_vc; ++vc) {
+                const bool last = vc + 1 == w.n_vc;
+                if (OUT_F32) {
+                    // partial sums live in dH itself; the first chunk of a fresh result writes every bucket
+                    float* d = reinterpret_cast<float*>(dH);
+                    const bool fresh = vc == 0 && !accumulate;
+                    launch_dh_sliced<T, float>(L.bpw, L.wpb, grid, st, W, bounds, perm, fresh ? nullptr : d, d, 0, fresh ? 1 : 0, s, L.dh_groups,
+                                               w.n_vc, vc, L.dh_xcd_own);
+                } else if (w.n_vc == 1) {
+                    launch_dh_sliced<T, OT>(L.bpw, L.wpb, grid, st, W, bounds, perm, nullptr, dH, accumulate, accumulate ? 0 : 1, s, L.dh_groups,
+                                            w.n_vc, vc, L.dh_xcd_own);
+                } else if (!last) {
+                    launch_dh_sliced<T, float>(L.bpw, L.wpb, grid, st, W, bounds, perm, vc > 0 ? stage : nullptr, stage, 0, vc == 0 ? 1 : 0, s,
+                                               L.dh_groups, w.n_vc, vc, L.dh_xcd_own);
+                } else {
+                    launch_dh_sliced<T, OT>(L.bpw, L.wpb, grid, st, W, bounds, perm, stage, dH, accumulate, 1, s, L.dh_groups, w.n_vc, vc, L.dh_xcd_own);
+                }
             }
         }
         prof.end(3);
@@ -777,7 +817,7 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
         if (L.dw_tile_passes > 0 && dW) {
             // one launch for all sequences; the sums start from zero, so bfloat16 results need no staging
             if constexpr (sizeof(T) == 2) {
-                const dim3 grid((unsigned)L.dw_tile_vtiles * (unsigned)n_slices(s.D));
+                const dim3 grid((unsigned)L.dw_tile_vtiles * (unsigned)(s.D / DWS_COLS));
 #define LSR_DWT(NP) hipLaunchKernelGGL((bwd_dw_tile_kernel<OT, NP>), grid, dim3(DWT_ROWS), 0, st_dw, H, dY, Y, I, dW, accumulate, db, \
                                        accumulate, s.B, s.S, s.D, s.V, L.dw_tile_vtiles)
                 switch (L.dw_tile_passes) {
@@ -1008,7 +1048,7 @@ int lsr_head_plan_ex(const lsr_head_desc* desc, int32_t* plan, int slots) {
     const BwdWs w = bwd_ws(s);
     const int32_t all[LSR_PLAN_EX_SLOTS] = {
         f.tpc, w.n_seg, w.seg_len, (s.S <= PLACE_MAX_S && w.seg_len <= PLACE_MAX_SEG) ? 1 : 0,
-        w.n_vc, w.vc_len, dh_buckets_per_wave(s, w.n_vc), dw_stage_rows(dw_batch_chunk(s)),
+        w.n_vc, w.vc_len, dh_buckets_per_wave(s, w.n_vc), dw_stage_rows(s),
         dw_batch_chunk(s), f.n_chunks, fwd_seg(s), f.resident ? 1 : 0,
         dh_slices_owned(s) ? 1 : 0, dw_tile_passes(s), dh_waves_per_bucket(s, w.n_vc), f.window,
         dw_beside_dh(s, w.n_vc, true) ? 1 : 0};

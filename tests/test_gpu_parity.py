@@ -120,19 +120,20 @@ def test_dh_lists_shared_by_waves(B, S, D, V, dy_keep, dtype):
 def dh_in_float64(B, S, V, g, I, W):
     """dH = sum of g W over the entries of each bucket, and the sum of the magnitudes, in float64 (one sequence at a time)."""
     D = W.shape[1]
-    out, size = (torch.zeros((B, S, D), dtype=torch.float64, device="cuda") for _ in range(2))
-    Wd = W.double()
+    out, size = (torch.empty((B, S, D), dtype=torch.float64, device="cuda") for _ in range(2))
+    Wd, Wa = W.double(), W.double().abs()
     for b in range(B):
-        t = g[b].double()[:, None] * Wd
-        out[b].index_add_(0, I[b].long(), t)
-        size[b].index_add_(0, I[b].long(), t.abs())
+        m = torch.zeros((S, V), dtype=torch.float64, device="cuda")
+        m[I[b].long(), torch.arange(V, device="cuda")] = g[b].double()
+        out[b] = m @ Wd
+        size[b] = m.abs() @ Wa
     return out, size
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("B,S,D,V,waves", [
     (2, 16, 64, 2500, 4),
-    (3, 9, 72, 40000, 4),          # several vocabulary chunks, the last slice partly filled
+    (3, 9, 72, 34000, 4),          # several vocabulary chunks, the last slice partly filled
     (48, 20, 1024, 8000, 4),       # slices in grid order
     (75, 48, 1024, 9500, 2),
 ])
@@ -156,12 +157,12 @@ def test_shared_lists_around_one_block(B, S, D, V, waves, dtype):
     Y = torch.full((B, V), 1e-30, device="cuda")
     for keep in (1.0, 0.3):
         dY = torch.randn((B, V), device="cuda", generator=g) * (torch.rand((B, V), device="cuda", generator=g) < keep)
+        want, size = dh_in_float64(B, S, V, dY, I, W)
         for accumulate in (False, True):
             dH0 = torch.randn((B, S, D), device="cuda", generator=g)
             dH = dH0.clone()
             ws = torch.empty(lsr.lsr_head_backward_ex_workspace_bytes(B, S, D, V, dt), dtype=torch.uint8, device="cuda")
             lsr.lsr_head_backward_ex(B, S, D, V, dt, H, W, dY, Y, I, dH, None, None, lsr.LSR_F32, accumulate, ws)
-            want, size = dh_in_float64(B, S, V, dY, I, W)
             if accumulate:
                 want, size = want + dH0.double(), size + dH0.double().abs()
             n = torch.zeros((B, S), device="cuda", dtype=torch.float64).scatter_add_(1, I.long(), torch.ones((B, V), device="cuda", dtype=torch.float64))
@@ -515,16 +516,23 @@ def test_bf16_gradient_outputs_and_accumulation(B, S, D, V, len_lo):
     (20, 30, 120, 900, "bf16"),    # slices in grid order
     (200, 20, 104, 300, "bf16"),   # 16-row dW tiles
     (400, 6, 104, 200, "bf16"),    # more sequences than the staging tile takes: whole-row dW
-    (3, 140, 1016, 17000, "bf16"), # LDS-tile dW kernel
-    (3, 20, 72, 70000, "bf16"),    # several vocabulary chunks (more than the filled-up problem has)
+    (3, 140, 712, 17000, "bf16"),  # the filled-up problem takes the LDS-tile dW kernel
+    (3, 20, 72, 70000, "bf16"),    # several vocabulary chunks
+    (30, 64, 200, 70000, "bf16"),  # ... of half the rows (more than the filled-up problem has)
     (4, 20, 40, 600, "f32"),
     (90, 12, 200, 400, "f32"),
+    (6, 24, 104, 40000, "f32"),    # several vocabulary chunks
+    (4, 60, 728, 500, "bf16"),     # whole rows, 91 of 128 threads
+    (3, 12, 1032, 3000, "bf16"),   # whole rows, two chunks per thread
+    (70, 80, 200, 2100, "bf16"),   # whole rows for their length
+    (3, 66, 40, 700, "f32"),
 ])
-def test_partly_filled_column_slices(B, S, D, V, dtype, grad_dtype, accumulate):
-    """A hidden size that is not a multiple of 64 gives, bit for bit, the gradients of the same problem with D filled up
-    with zeros to the next multiple (every sum over sequences or vocabulary entries has the same terms in the
-    same order; dH over several vocabulary chunks is cut in other places, and then within D 2^-24 of the size of its
-    terms), and nothing behind a row is touched."""
+def test_hidden_sizes_that_are_no_multiple_of_64(B, S, D, V, dtype, grad_dtype, accumulate):
+    """dH and dW against float64 sums: a sum of n terms in any order is within (n + 16) 2^-24 of the sum of their magnitudes
+    (16: the joins of lanes, waves and chunks, and what it is accumulated onto), and a bfloat16 result within half a step of
+    its size more.  Nothing behind a row is touched.  Where a problem takes slices, dW and db are, bit for bit, those of the
+    same problem with D filled up with zeros to the next multiple of 64 (every sum has the same terms in the same
+    order), and so is dH where both are cut into the same vocabulary chunks."""
     if dtype == "f32" and grad_dtype == lsr.LSR_BF16:
         pytest.skip("bfloat16 gradients belong to bfloat16 parameters")
     dt = lsr.LSR_F32 if dtype == "f32" else lsr.LSR_BF16
@@ -534,9 +542,9 @@ def test_partly_filled_column_slices(B, S, D, V, dtype, grad_dtype, accumulate):
     Dp = (D + 63) // 64 * 64
     H = torch.randn((B, S, D), device="cuda", generator=g).to(td)
     W = torch.randn((V, D), device="cuda", generator=g).mul_(0.05).to(td)
-    Y = torch.rand((B, V), device="cuda", generator=g)
+    Y = torch.full((B, V), 1e-30, device="cuda")              # exp(-Y) = 1: the gradient of a pair is dY
     I = torch.randint(0, S, (B, V), device="cuda", generator=g, dtype=torch.int32)
-    dY = torch.randn((B, V), device="cuda", generator=g)
+    dY = torch.randn((B, V), device="cuda", generator=g) * (torch.rand((B, V), device="cuda", generator=g) < 0.7)
     dH0 = torch.randn((B, S, D), device="cuda", generator=g).to(gd)
     dW0 = torch.randn((V, D), device="cuda", generator=g).to(gd)
     db0 = torch.randn((V,), device="cuda", generator=g)
@@ -552,18 +560,55 @@ def test_partly_filled_column_slices(B, S, D, V, dtype, grad_dtype, accumulate):
         for b in bufs:
             assert torch.equal(b[-4096:], guard)
         got.append((bufs[0][:-4096].view(B, S, d), bufs[1][:-4096].view(V, d), db))
-    assert torch.equal(got[0][2], got[1][2])
-    for k, (a, p) in enumerate(zip(got[0][:2], got[1][:2])):
-        assert not p[..., D:].any() or accumulate
-        if k == 0 and V > 16384:
-            # lists of up to n entries in another order: n 2^-23 of the sum of magnitudes, and one step of the output type
-            n = int(torch.bincount((I.long() + torch.arange(B, device="cuda")[:, None] * S).flatten()).max())
-            size = n * float(dY.abs().max()) * float(W.float().abs().max())
-            step = 2.0 ** -7 if gd == torch.bfloat16 else 2.0 ** -22
-            d = (a.double() - p[..., :D].double()).abs()
-            assert bool((d <= n * 2.0 ** -23 * size + step * p[..., :D].double().abs()).all())
-        else:
-            assert torch.equal(a, p[..., :D])
+
+    dH, size_H = dh_in_float64(B, S, V, dY, I, W)
+    dW, size_W = (torch.zeros((V, D), dtype=torch.float64, device="cuda") for _ in range(2))
+    n_H = torch.zeros((B, S), device="cuda", dtype=torch.float64)
+    n_H.scatter_add_(1, I.long(), (dY != 0).double())
+    for b in range(B):
+        t = dY[b].double()[:, None] * H[b].double()[I[b].long()]
+        dW += t
+        size_W += t.abs()
+    n_W = (dY != 0).sum(dim=0).double()
+    half_step = 2.0 ** -8 if gd == torch.bfloat16 else 0.0      # eight significant bits: steps of 2^-7 between 1 and 2
+    for mine, want, size, n, old in ((got[0][0], dH, size_H, n_H[:, :, None], dH0), (got[0][1], dW, size_W, n_W[:, None], dW0)):
+        if accumulate:
+            want, size = want + old.double(), size + old.double().abs()
+        bound = (n + 16) * 2.0 ** -24 * size
+        assert bool(((mine.double() - want).abs() <= bound + half_step * (want.abs() + bound)).all())
+
+    plan, plan_p = (lsr.lsr_head_plan(B, S, d, V, dt) for d in (D, Dp))
+    if plan["dh_buckets_per_wave"] > 0:
+        same_cut = all(plan[k] == plan_p[k] for k in ("dh_chunks", "dh_chunk_len", "dh_buckets_per_wave", "dh_waves_per_bucket"))
+        for k, (a, p) in enumerate(zip(got[0][:2], got[1][:2])):
+            if k == 1 or same_cut:
+                assert torch.equal(a, p[..., :D])
+        if plan["dw_sequences_per_launch"] >= B:
+            assert torch.equal(got[0][2], got[1][2])
+
+
+@pytest.mark.parametrize("B,S,D,V,dtype", [
+    (6, 40, 64, 500, "bf16"), (6, 40, 72, 500, "bf16"), (6, 40, 728, 500, "bf16"), (6, 70, 72, 500, "f32"), (450, 5, 64, 300, "bf16")])
+def test_rows_without_a_gradient_may_hold_nan(B, S, D, V, dtype):
+    """Rows of H and W that no gradient points at stay out of every sum (also the first rows, which a gather could
+    take to fill up a round): slices, whole rows, and whole-row dW beside sliced dH."""
+    dt = lsr.LSR_F32 if dtype == "f32" else lsr.LSR_BF16
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(D)
+    H = torch.randn((B, S, D), device="cuda", generator=g).to(td)
+    W = torch.randn((V, D), device="cuda", generator=g).to(td)
+    Y = torch.rand((B, V), device="cuda", generator=g)
+    I = torch.randint(1, S, (B, V), device="cuda", generator=g, dtype=torch.int32)
+    dY = torch.randn((B, V), device="cuda", generator=g)
+    bad = [0, 7, V - 1]
+    dY[:, bad] = 0.0
+    H[:, 0] = float("nan")
+    W[bad] = float("inf")
+    dH, dW, db = torch.empty((B, S, D), device="cuda"), torch.empty((V, D), device="cuda"), torch.empty((V,), device="cuda")
+    ws = torch.empty(lsr.lsr_head_workspace_bytes(B, S, D, V, dt, True), dtype=torch.uint8, device="cuda")
+    lsr.lsr_head_backward(B, S, D, V, dt, H, W, dY, Y, I, dH, dW, db, ws)
+    assert bool(dH.isfinite().all()) and bool(dW.isfinite().all()) and bool(db.isfinite().all())
+    assert not dH[:, 0].any() and not dW[bad].any() and not db[bad].any()
 
 
 @pytest.mark.parametrize("accumulate", [False, True])
@@ -571,15 +616,18 @@ def test_partly_filled_column_slices(B, S, D, V, dtype, grad_dtype, accumulate):
     (13, 40, 72, 300, "bf16"),        # 64-row staging tiles
     (160, 20, 72, 300, "f32"),        # 32-row tiles
     (256, 20, 200, 300, "bf16"),      # 16-row tiles
-    (300, 512, 72, 9000, "bf16"),     # several launches, each of which rounds the db it hands on; S above 128 but too few tiles
-    (256, 130, 1032, 15400, "bf16"),  # LDS-tile kernel
-    (256, 130, 1024, 16400, "bf16"),
-    (90, 600, 1032, 10000, "f32"),
+    (300, 512, 64, 9000, "bf16"),     # several launches, each of which rounds the db it hands on; S above 128 but too few tiles
+    (256, 130, 1024, 16400, "bf16"),  # LDS-tile kernel
+    (90, 600, 1024, 10000, "f32"),
+    (256, 130, 1032, 900, "bf16"),    # whole rows, one launch
+    (400, 70, 72, 500, "f32"),
+    (500, 9, 128, 333, "bf16"),
 ])
 def test_db_is_rounded_once_per_launch(B, S, D, V, dtype, accumulate):
     """db = sum of dY where Y is tiny (exp(-Y) = 1): every launch rounds its running sum once, to within 2^-24 of its size;
-    the carried rounding errors are themselves rounded (B 2^-47 of the sum of magnitudes).  With one gradient in ten too,
-    which the sliced kernel compacts; infinities come out as in a plain sum."""
+    the carried rounding errors are themselves rounded (B 2^-47 of the sum of magnitudes).  The whole-row kernel adds every
+    64th sequence in a lane and joins the lanes in six steps, each rounded to 2^-24 of a sum that the magnitudes bound.  With
+    one gradient in ten too, which the sliced kernel compacts; infinities come out as in a plain sum."""
     dt = lsr.LSR_F32 if dtype == "f32" else lsr.LSR_BF16
     td = torch.float32 if dtype == "f32" else torch.bfloat16
     g = torch.Generator(device="cuda").manual_seed(B + V)
@@ -588,7 +636,8 @@ def test_db_is_rounded_once_per_launch(B, S, D, V, dtype, accumulate):
     Y = torch.full((B, V), 1e-30, device="cuda")
     I = torch.zeros((B, V), device="cuda", dtype=torch.int32)
     plan = lsr.lsr_head_plan(B, S, D, V, dt)
-    per_launch = {True: B if plan["dw_lds_tile_passes"] else plan["dw_sequences_per_launch"], False: plan["dw_sequences_per_launch"]}
+    sliced = plan["dw_sequences_per_launch"] if plan["dw_tile_rows"] > 0 else B
+    per_launch = {True: B if plan["dw_lds_tile_passes"] else sliced, False: sliced}
     db0 = torch.randn((V,), device="cuda", generator=g)
     ws = torch.empty(lsr.lsr_head_backward_ex_workspace_bytes(B, S, D, V, dt), dtype=torch.uint8, device="cuda")
     dW = torch.zeros((V, D), device="cuda")
@@ -599,7 +648,10 @@ def test_db_is_rounded_once_per_launch(B, S, D, V, dtype, accumulate):
         for want_dw in (True, False):
             per = per_launch[want_dw]
             ends = run[[min(b + per, B) for b in range(0, B, per)]]      # the running sum after each launch
-            bound = 2.0 ** -24 * ends.abs().sum(dim=0) + B * 2.0 ** -47 * (start.abs() + dY.double().abs().sum(dim=0))
+            size = start.abs() + dY.double().abs().sum(dim=0)
+            bound = 2.0 ** -24 * ends.abs().sum(dim=0) + B * 2.0 ** -47 * size
+            if plan["dw_tile_rows"] == 0:
+                bound = ((B + 63) // 64 + 7) * 2.0 ** -24 * size
             db = db0.clone()
             lsr.lsr_head_backward_ex(B, S, D, V, dt, H, W, dY, Y, I, None, dW if want_dw else None, db, lsr.LSR_F32, accumulate, ws)
             assert bool(((db.double() - run[-1]).abs() <= bound).all())

@@ -46,11 +46,18 @@ def test_plans_of_the_benchmark_shapes():
     assert lsr.lsr_head_plan(17, 128, 768, 30522, lsr.LSR_BF16)["dh_slices_owned_by_xcd"] == 0
     p = lsr.lsr_head_plan(256, 512, 768, 250002, lsr.LSR_BF16)          # a batch whose H slice is 4x L2: four dW launches
     assert (p["dw_sequences_per_launch"], p["dw_tile_rows"]) == (64, 64)
-    # D not a multiple of 64: the same sliced kernels; windows of half the rows (a row piece touches two cache lines)
+    # D not a multiple of 64: sliced kernels for short sequences and small problems ...
     p = lsr.lsr_head_plan(3, 40, 200, 900, lsr.LSR_BF16)
     assert (p["dh_buckets_per_wave"], p["dw_tile_rows"], p["dh_chunks"], p["fwd_resident_workgroups"]) == (4, 64, 1, 0)      # 32 entries per bucket: four buckets per wave
-    p = lsr.lsr_head_plan(40, 200, 712, 60000, lsr.LSR_BF16)
-    assert (p["dh_chunks"], p["dh_chunk_len"], p["dw_lds_tile_passes"], p["dw_beside_dh"]) == (4, 15000, 2, 1)
+    p = lsr.lsr_head_plan(100, 40, 552, 150000, lsr.LSR_BF16)           # windows of half the rows: row pieces straddle cache lines
+    assert (p["dh_chunks"], p["dh_chunk_len"], p["dw_tile_rows"], p["dw_lds_tile_passes"], p["dw_beside_dh"]) == (10, 15000, 32, 0, 1)
+    p = lsr.lsr_head_plan(13, 197, 312, 31091, lsr.LSR_BF16)
+    assert (p["dh_chunks"], p["dh_buckets_per_wave"], p["dw_tile_rows"], p["dw_lds_tile_passes"]) == (1, 1, 64, 0)
+    # ... and whole rows elsewhere: slices cost sparse gradients too much there
+    for shape in ((40, 200, 712, 60000), (64, 64, 776, 60000), (30, 3000, 312, 60000), (16, 250, 904, 200000)):
+        p = lsr.lsr_head_plan(*shape, lsr.LSR_BF16)
+        assert (p["dh_chunks"], p["dh_buckets_per_wave"], p["dh_waves_per_bucket"], p["dw_tile_rows"], p["dw_lds_tile_passes"]) == (1, 0, 1, 0, 0)
+    assert lsr.lsr_head_plan(5, 100, 72, 900, lsr.LSR_F32)["dh_buckets_per_wave"] == 0
     # waves that share a list: surplus waves cost sparse gradients a few per cent at most
     waves = {(64, 32, 768, 30522): 4, (100, 24, 384, 60000): 4, (4, 64, 768, 30522): 4, (32, 128, 1024, 30522): 2, (128, 40, 768, 30522): 2,
              (60, 40, 768, 200000): 2, (64, 100, 768, 50000): 1, (256, 32, 768, 30522): 1, (250, 60, 1024, 100000): 1}
@@ -68,7 +75,7 @@ def test_plan_invariants_on_random_shapes():
     for _ in range(3000):
         B = int(rng.choice([1, 2, 7, 16, 64, 192, 193, 256, 384, 385, 1000, 6144]))
         S = int(rng.choice([1, 5, 32, 33, 512, 1024, 1025, 4096, 8192]))
-        D = int(rng.choice([8, 64, 72, 128, 768, 1024, 4096]))
+        D = int(rng.choice([8, 64, 72, 128, 712, 728, 768, 1024, 4096]))
         V = int(rng.choice([1, 63, 512, 4097, 30522, 32769, 65536, 250002, 1000003]))
         if B * V >= 2 ** 31 or B * S >= 2 ** 31:
             continue
@@ -83,21 +90,25 @@ def test_plan_invariants_on_random_shapes():
                 assert p["sort_places_through_lds"] == 0
             c, clen = p["dh_chunks"], p["dh_chunk_len"]
             assert 1 <= c <= 64 and c * clen >= V and (c - 1) * clen < V
-            assert p["dh_buckets_per_wave"] in ((1, 2, 4) if dt == lsr.LSR_F32 else (1, 2, 4, 8))
-            assert p["dh_waves_per_bucket"] in (1, 2, 4)
-            assert c == 1 or c <= V * esize // (32 * S)      # re-reading dH stays below a quarter of the gathers
             ragged = D % 64 != 0
-            window = (4 << 20) // (2 if D * esize % 128 != 0 else 1)
-            if ragged:
-                # the chunk bounds (c + 1 per bucket) take the place of the counts, which the placement read last
-                assert c == 1 or B * S * (c + 1) <= B * n_seg * S
-            assert c == 1 or clen * 64 * esize <= window or c == 64 or c == V * esize // (32 * S) or (ragged and c == n_seg - 1)
             rows, nb = p["dw_tile_rows"], p["dw_sequences_per_launch"]
             assert 1 <= nb <= B and (B + nb - 1) // nb <= 16
-            assert rows in (0, 16, 32, 64) and nb * rows * 8 <= 48 * 1024
-            assert (rows == 0) == (nb * 16 * 8 > 48 * 1024)
             # several launches only where rows of H are reused often, and few enough that re-reading dW stays small
             assert nb == B or (V >= 16 * S and (B + nb - 1) // nb <= min(16, 1 + B * esize // 32))
+            assert p["dh_waves_per_bucket"] in (1, 2, 4)
+            whole_rows = p["dh_buckets_per_wave"] == 0
+            if whole_rows:
+                assert ragged and (S > 64 or D > 720) and c == 1 and rows == 0 and p["dh_waves_per_bucket"] == 1
+                assert p["dh_slices_owned_by_xcd"] == 0 and p["dw_lds_tile_passes"] == 0
+            else:
+                assert p["dh_buckets_per_wave"] in ((1, 2, 4) if dt == lsr.LSR_F32 else (1, 2, 4, 8))
+                assert c == 1 or c <= V * esize // (32 * S)      # re-reading dH stays below a quarter of the gathers
+                if ragged:
+                    # the chunk bounds (c + 1 per bucket) take the place of the counts, which the placement read last
+                    assert c == 1 or B * S * (c + 1) <= B * n_seg * S
+                assert c == 1 or clen * 64 * esize <= (4 << 20) or c == 64 or c == V * esize // (32 * S) or (ragged and c == n_seg - 1)
+                assert rows in (0, 16, 32, 64) and nb * rows * 8 <= 48 * 1024
+                assert (rows == 0) == (nb * 16 * 8 > 48 * 1024)
             seg = p["fwd_segment_rows"]
             assert seg == (8 if S <= 64 else 32)
             segs = B * ((S + seg - 1) // seg)
