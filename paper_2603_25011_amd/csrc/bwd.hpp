@@ -516,11 +516,11 @@ __global__ __launch_bounds__(ROW_THREADS) void bwd_dw_kernel(const T* __restrict
 // A row piece is 64 elements = LPR lanes x 16 bytes; a wave therefore serves 64/LPR vocabulary
 // rows at once, walks the sequences that have a gradient for them with eight gathers in flight per
 // lane, and writes one 64-column piece of each dW row.  Summation order over b is fixed.
+// (No LDS beside the tile: sixteen bytes for a count of the pairs cost B=250 S=60 D=1024 one of five workgroups per CU,
+// dW 4114 -> 4525 us.)
 // A tile in which fewer than half of the pairs have a gradient is compacted after staging: each column of the (g, I)
 // tile in place to its non-zero entries, in ascending b (one wave per column, ballot ranking), closed by a
 // zero, so that sparse gradients cost what they hold; the sums are the same either way (same terms, same order).
-// With one gradient in twenty (dW us, compacted or not): B=64 S=100 D=768 |V|=50000 226 -> 85; B=167 S=62 D=648
-// |V|=66407 704 -> 249; B=100 S=24 D=384 |V|=60000 185 -> 63; dense ones are unchanged within 2 %.
 // SWZ (16-row tiles, of which a workgroup of a large batch compacts many narrow columns): element (b, vv) sits at
 // word b*VT + (vv ^ (b % VT)), so that the compaction's column reads spread over the LDS banks (B=250 S=60 D=1024
 // |V|=100000, one in twenty, 747 -> 717 us).  On wider tiles the address arithmetic costs more than the bank
@@ -599,7 +599,7 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
     constexpr int N = RowChunk<T>::N;          // elements per 16-byte chunk
     constexpr int LPR = DWS_COLS / N;          // lanes per row piece
     constexpr int VPG = 64 / LPR;              // vocabulary rows a wave serves at once
-    extern __shared__ int s_dyn[];
+    extern __shared__ __attribute__((aligned(16))) int s_dyn[];
     float* s_g = reinterpret_cast<float*>(s_dyn);          // [B][VT]
     int* s_i = s_dyn + (size_t)B * VT;                     // [B][VT]  token row b*S + I[b,v]
     auto at = [VT](int b, int vv) { return b * VT + (SWZ ? vv ^ (b & (VT - 1)) : vv); };
@@ -612,8 +612,6 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
     const int dc_begin = dg * NDC;
     const int dc_end = min(n_slices(D), dc_begin + NDC);
 
-    __shared__ int s_nz[4];                                // pairs with a gradient that each wave has staged
-    int nz = 0;
     // staging, four independent (dY, Y, I) triples in flight per thread
     for (int e0 = tid; e0 < B * VT; e0 += 4 * blockDim.x) {
         float dy[4], y[4];
@@ -631,18 +629,22 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int e = e0 + u * blockDim.x;
-            const float g = gate_grad(dy[u], y[u]);
-            nz += __popcll(__ballot(g != 0.f));            // no gradient behind the end of the tile (dy = 0)
             if (e < B * VT) {
                 const int bb = e / VT, vv = e - bb * VT;
-                s_g[at(bb, vv)] = g;
+                s_g[at(bb, vv)] = gate_grad(dy[u], y[u]);
                 s_i[at(bb, vv)] = (b_first + bb) * S + clamp_pos(ix[u], S);
             }
         }
     }
-    if (lane == 0) s_nz[wave] = nz;
     __syncthreads();
-    const bool compact = 2 * (s_nz[0] + s_nz[1] + s_nz[2] + s_nz[3]) < B * min(VT, V - v0);
+    // how many of 1024 pairs spread over the tile have a gradient (the same for all waves)
+    int nz = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float4 q = reinterpret_cast<const float4*>(s_g)[((j * 64 + lane) * (B * VT / 4)) >> 8];
+        nz += __popcll(__ballot(q.x != 0.f)) + __popcll(__ballot(q.y != 0.f)) + __popcll(__ballot(q.z != 0.f)) + __popcll(__ballot(q.w != 0.f));
+    }
+    const bool compact = nz < 512;
 
     // db: every wave sums the columns that it compacts below (so it has read them before), 256 / VT lanes per
     // column, each every (256 / VT)-th sequence; fixed order
