@@ -518,9 +518,18 @@ __global__ __launch_bounds__(ROW_THREADS) void bwd_dw_kernel(const T* __restrict
 // lane, and writes one 64-column piece of each dW row.  Summation order over b is fixed.
 // (No LDS beside the tile: sixteen bytes for a count of the pairs cost B=250 S=60 D=1024 one of five workgroups per CU,
 // dW 4114 -> 4525 us.)
-// A tile in which fewer than half of the pairs have a gradient is compacted after staging: each column of the (g, I)
+// A tile is compacted after staging where few enough of its pairs have a gradient: each column of the (g, I)
 // tile in place to its non-zero entries, in ascending b (one wave per column, ballot ranking), closed by a
 // zero, so that sparse gradients cost what they hold; the sums are the same either way (same terms, same order).
+// dW us, without / with compaction, by the share of pairs that have a gradient:
+//   16-row tiles (below 31/32)       1.0             0.98            0.95            0.85            0.55            0.25
+//     B=256 S=32 D=768 |V|=30522     1058 / 1063     1053 / 1043     1052 / 1017     1054 / 937      1038 / 662      989 / 368
+//     B=384 S=32 D=768 |V|=30522     2055 / 2089     2080 / 2072     2051 / 2012     2063 / 1818     2055 / 1262     1932 / 683
+//     B=250 S=64 D=1000 |V|=30000    1489 / 1534     1483 / 1490     1475 / 1459     1451 / 1339     1415 / 970      1350 / 564
+//   wider tiles (below one half)     0.95            0.85            0.7             0.55            0.4             0.25
+//     B=64 S=100 D=768 |V|=50000     282 / 305       281 / 293       295 / 272       274 / 226       266 / 189       258 / 147
+//     B=167 S=62 D=648 |V|=66407     1005 / 1104     982 / 1033      958 / 901       931 / 758       911 / 612       881 / 453
+//     B=100 S=40 D=768 |V|=50000     434 / 460       425 / 422       417 / 369       414 / 317       401 / 261       388 / 187
 // SWZ (16-row tiles, of which a workgroup of a large batch compacts many narrow columns): element (b, vv) sits at
 // word b*VT + (vv ^ (b % VT)), so that the compaction's column reads spread over the LDS banks (B=250 S=60 D=1024
 // |V|=100000, one in twenty, 747 -> 717 us).  On wider tiles the address arithmetic costs more than the bank
@@ -644,7 +653,7 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
         const float4 q = reinterpret_cast<const float4*>(s_g)[((j * 64 + lane) * (B * VT / 4)) >> 8];
         nz += __popcll(__ballot(q.x != 0.f)) + __popcll(__ballot(q.y != 0.f)) + __popcll(__ballot(q.z != 0.f)) + __popcll(__ballot(q.w != 0.f));
     }
-    const bool compact = nz < 512;
+    const bool compact = nz < (SWZ ? 992 : 512);
 
     // db: every wave sums the columns that it compacts below (so it has read them before), 256 / VT lanes per
     // column, each every (256 / VT)-th sequence; fixed order
