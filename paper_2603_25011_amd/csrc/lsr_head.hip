@@ -532,13 +532,19 @@ void launch_dw_sliced(dim3 grid, dim3 block, size_t lds, hipStream_t st, const T
 // (two event records, two waits), and two gathers at a time help while they leave each other's windows in L2:
 //   - up to AUX_MIN_GATHER_BYTES of worst-case gather traffic (2 * B * |V| rows of D elements) the host's time is
 //     the longer one (forward and backward, us, without -> with: B=2 S=16 D=64 |V|=1000 float32 42.6 -> 52.1; B=10 S=60
-//     D=512 |V|=10000 float32, 0.41 GB, 177 -> 172; B=13 S=197 D=312 |V|=31091, 0.5 GB, 193 -> 182);
-//   - up to AUX_MAX_GATHER_BYTES it always pays (B=30 S=80 D=256 |V|=25000 153 -> 130; B=64 S=100 D=768 |V|=50000 1016 ->
-//     933; B=16 S=256 |V|=250002 1807 -> 1740);
-//   - beyond, where a 64-column slice of H is at most 1 MiB (B=256 S=32 D=768 |V|=30522 2402 -> 2038, with one gradient in
-//     twenty 609 -> 579; B=60 S=40 D=768 |V|=200000 2763 -> 2652) or dW gathers from LDS and dH has one window (B=256
-//     S=512 D=768 |V|=30522 6757 -> 6409); not otherwise (B=200 S=100 D=768 |V|=30522 1845 -> 2049; B=256 S=100 D=1024 |V|=30522
-//     3634 -> 4107; B=128 S=100 D=936 |V|=100000 6229 -> 7135; B=64 S=512 D=1024 |V|=250002 13.29 -> 13.37 ms).
+//     D=512 |V|=10000 float32, 0.41 GB, 177 -> 172; B=13 S=197 D=312 |V|=31091, 0.5 GB, 193 -> 182; backward alone B=4 S=64
+//     D=512 |V|=20000, 0.16 GB, 55 -> 59, B=8 S=32 |V|=8000, 0.2 GB, 70 -> 71, B=2 S=128 |V|=30522, 0.19 GB, 64 -> 68);
+//   - up to AUX_MAX_GATHER_BYTES it pays nearly everywhere (backward, dense; one gradient in twenty: B=30 S=80 D=256 |V|=25000
+//     101 -> 87; 62 -> 61, B=64 S=100 D=768 |V|=50000 646 -> 579; 195 -> 176, B=24 S=400 |V|=100000 674 -> 626; 411 -> 363,
+//     B=16 S=256 |V|=250002 1026 -> 988; 581 -> 566; but B=256 S=512 D=384 |V|=30522 955 -> 985; 463 -> 371);
+//   - beyond, where dW gathers from L2 and a 64-column slice of H is at most 1 MiB (B=256 S=24 |V|=60000 3958 -> 3656; 510 -> 448,
+//     B=128 S=64 |V|=60000 1374 -> 1316; 300 -> 270; still so at 1.25 MiB, B=256 S=40 1843 -> 1670; 296 -> 264, no longer at
+//     1.6, B=200 S=64 |V|=40000 1479 -> 1511; 344 -> 317, or 2.5, B=200 S=100 1845 -> 2049), or from LDS and dH has one window
+//     (B=256 S=512 6757 -> 6409 with the forward, B=128 S=512 D=1024 1075 -> 994; 737 -> 637, B=200 S=256 1124 -> 1008; 752 -> 618,
+//     B=256 S=128 D=1024 1530 -> 1517; 780 -> 746).  With several windows a dW that gathers from LDS gains or loses beside dH
+//     (B=60 S=128 D=1024 |V|=80000 1069 -> 1109; 575 -> 596, B=40 S=200 D=1024 |V|=130000 1356 -> 1361; 705 -> 712, B=16 S=512 D=1024
+//     |V|=250002 1507 -> 1567; 834 -> 829, B=128 S=512 |V|=50000 1461 -> 1361; 1003 -> 933, B=64 S=512 D=1024 |V|=250002 13.29 ->
+//     13.37 ms with the forward), so it runs behind (D=768 |V|=30522 where not said).
 constexpr double AUX_MIN_GATHER_BYTES = 100e6;
 constexpr double AUX_MAX_GATHER_BYTES = 16e9;
 constexpr size_t AUX_SMALL_SLICE_BYTES = 1u << 20;
@@ -644,7 +650,8 @@ int dw_tile_passes(const Shape& s) {
 bool dw_beside_dh(const Shape& s, int n_vc, bool want_dw) {
     const double gather_bytes = 2.0 * s.B * s.V * s.D * (s.dtype == LSR_F32 ? 4 : 2);
     const size_t h_slice = (size_t)s.B * s.S * DWS_COLS * (s.dtype == LSR_F32 ? 4 : 2);
-    const bool apart = gather_bytes <= AUX_MAX_GATHER_BYTES || (sliced_gathers(s) && h_slice <= AUX_SMALL_SLICE_BYTES) || (dw_tile_passes(s) > 0 && want_dw && n_vc == 1);
+    const bool tile = dw_tile_passes(s) > 0 && want_dw;      // dW gathers from LDS
+    const bool apart = gather_bytes <= AUX_MAX_GATHER_BYTES || (tile ? n_vc == 1 : sliced_gathers(s) && h_slice <= AUX_SMALL_SLICE_BYTES);
     return gather_bytes >= AUX_MIN_GATHER_BYTES && apart;
 }
 int plan_backward(const Shape& s, const BwdWs& w, BwdLaunch* L) {

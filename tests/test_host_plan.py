@@ -58,6 +58,11 @@ def test_plans_of_the_benchmark_shapes():
         p = lsr.lsr_head_plan(*shape, lsr.LSR_BF16)
         assert (p["dh_chunks"], p["dh_buckets_per_wave"], p["dh_waves_per_bucket"], p["dw_tile_rows"], p["dw_lds_tile_passes"]) == (1, 0, 1, 0, 0)
     assert lsr.lsr_head_plan(5, 100, 72, 900, lsr.LSR_F32)["dh_buckets_per_wave"] == 0
+    # dW beside dH: from 0.1 GB of gathers on; beyond 16 GB for small slices of H, or from LDS beside a single dH window
+    beside = {(64, 512, 1024, 250002): 0, (256, 512, 768, 30522): 1, (128, 512, 1024, 30522): 1, (60, 128, 1024, 80000): 0, (256, 32, 768, 30522): 1,
+              (128, 64, 768, 60000): 1, (200, 64, 768, 40000): 0, (128, 100, 936, 100000): 0, (16, 256, 768, 250002): 1, (1, 32, 768, 1000): 0}
+    for shape, yes in beside.items():
+        assert lsr.lsr_head_plan(*shape, lsr.LSR_BF16)["dw_beside_dh"] == yes, shape
     # waves that share a list: surplus waves cost sparse gradients a few per cent at most
     waves = {(64, 32, 768, 30522): 4, (100, 24, 384, 60000): 4, (4, 64, 768, 30522): 4, (32, 128, 1024, 30522): 2, (128, 40, 768, 30522): 2,
              (60, 40, 768, 200000): 2, (64, 100, 768, 50000): 1, (256, 32, 768, 30522): 1, (250, 60, 1024, 100000): 1}
