@@ -537,9 +537,10 @@ void launch_dw_sliced(dim3 grid, dim3 block, size_t lds, hipStream_t st, const T
 //   - up to AUX_MAX_GATHER_BYTES it pays nearly everywhere (backward, dense; one gradient in twenty: B=30 S=80 D=256 |V|=25000
 //     101 -> 87; 62 -> 61, B=64 S=100 D=768 |V|=50000 646 -> 579; 195 -> 176, B=24 S=400 |V|=100000 674 -> 626; 411 -> 363,
 //     B=16 S=256 |V|=250002 1026 -> 988; 581 -> 566; but B=256 S=512 D=384 |V|=30522 955 -> 985; 463 -> 371);
-//   - beyond, where dW gathers from L2 and a 64-column slice of H is at most 1 MiB (B=256 S=24 |V|=60000 3958 -> 3656; 510 -> 448,
-//     B=128 S=64 |V|=60000 1374 -> 1316; 300 -> 270; still so at 1.25 MiB, B=256 S=40 1843 -> 1670; 296 -> 264, no longer at
-//     1.6, B=200 S=64 |V|=40000 1479 -> 1511; 344 -> 317, or 2.5, B=200 S=100 1845 -> 2049), or from LDS and dH has one window
+//   - beyond, where dW gathers from L2 and a 64-column slice of H is at most 1.375 MiB (at 0.75 MiB, B=256 S=24 |V|=60000, 3958 ->
+//     3656; 510 -> 448, at 1, B=128 S=64 |V|=60000, 1374 -> 1316; 300 -> 270, at 1.25, B=256 S=40, 1843 -> 1670; 296 -> 264, at 1.5,
+//     B=256 S=48, 1818 -> 1750; 305 -> 271, at 1.56, B=200 S=64 |V|=40000, 1479 -> 1511; 344 -> 317, at 2.5, B=200 S=100, 1845 -> 2049),
+//     or from LDS and dH has one window
 //     (B=256 S=512 6757 -> 6409 with the forward, B=128 S=512 D=1024 1075 -> 994; 737 -> 637, B=200 S=256 1124 -> 1008; 752 -> 618,
 //     B=256 S=128 D=1024 1530 -> 1517; 780 -> 746).  With several windows a dW that gathers from LDS gains or loses beside dH
 //     (B=60 S=128 D=1024 |V|=80000 1069 -> 1109; 575 -> 596, B=40 S=200 D=1024 |V|=130000 1356 -> 1361; 705 -> 712, B=16 S=512 D=1024
@@ -547,7 +548,7 @@ void launch_dw_sliced(dim3 grid, dim3 block, size_t lds, hipStream_t st, const T
 //     13.37 ms with the forward), so it runs behind (D=768 |V|=30522 where not said).
 constexpr double AUX_MIN_GATHER_BYTES = 100e6;
 constexpr double AUX_MAX_GATHER_BYTES = 16e9;
-constexpr size_t AUX_SMALL_SLICE_BYTES = 1u << 20;
+constexpr size_t AUX_SMALL_SLICE_BYTES = 11u << 17;      // 1.375 MiB
 //
 // The lane (one stream, one fork and one join event per device, default priority, non-blocking with
 // respect to the null stream) is created by the first backward on that device and kept until the

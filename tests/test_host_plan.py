@@ -60,7 +60,7 @@ def test_plans_of_the_benchmark_shapes():
     assert lsr.lsr_head_plan(5, 100, 72, 900, lsr.LSR_F32)["dh_buckets_per_wave"] == 0
     # dW beside dH: from 0.1 GB of gathers on; beyond 16 GB for small slices of H, or from LDS beside a single dH window
     beside = {(64, 512, 1024, 250002): 0, (256, 512, 768, 30522): 1, (128, 512, 1024, 30522): 1, (60, 128, 1024, 80000): 0, (256, 32, 768, 30522): 1,
-              (128, 64, 768, 60000): 1, (200, 64, 768, 40000): 0, (128, 100, 936, 100000): 0, (16, 256, 768, 250002): 1, (1, 32, 768, 1000): 0}
+              (128, 64, 768, 60000): 1, (200, 64, 768, 40000): 0, (256, 40, 768, 30522): 1, (256, 46, 768, 30522): 0, (128, 100, 936, 100000): 0, (16, 256, 768, 250002): 1, (1, 32, 768, 1000): 0}
     for shape, yes in beside.items():
         assert lsr.lsr_head_plan(*shape, lsr.LSR_BF16)["dw_beside_dh"] == yes, shape
     # waves that share a list: surplus waves cost sparse gradients a few per cent at most
