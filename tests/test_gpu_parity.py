@@ -344,6 +344,43 @@ def test_autograd_wrapper_matches_direct_calls():
     assert torch.equal(b2.grad, head.db)
 
 
+def test_autograd_wrapper_masks_and_missing_gradients():
+    """Masks of one byte per token go to the library as they are: any non-zero byte is a valid token, at any address and
+    stride.  An output gradient that autograd leaves out counts as zero.  Calls go to the current stream."""
+    from paper_2603_25011_amd.autograd import lsr_head
+    inp = wl.make_custom(3, 37, 64, 300, seed=5, len_lo=4)
+    head = DeviceHead(inp)
+    H, W, bias = head.H, head.W, head.bias
+    want = lsr_head(H, W, bias, head.mask)
+    odd = torch.zeros((4, 37), dtype=torch.uint8, device="cuda")
+    odd[1:] = head.mask * 255                                   # rows begin at odd addresses
+    strided = torch.zeros((3, 74), dtype=torch.uint8, device="cuda")
+    strided[:, ::2] = head.mask * 7
+    for mask in (head.mask != 0, odd[1:], strided[:, ::2], head.mask.long() * 256, head.mask.float()):
+        assert all(torch.equal(a, b) for a, b in zip(lsr_head(H, W, bias, mask), want))
+
+    class Dropped(torch.autograd.Function):
+        @staticmethod
+        def forward(ctx, y):
+            return y.clone()
+
+        @staticmethod
+        def backward(ctx, _grad):
+            return None
+
+    leaves = [t.clone().requires_grad_(True) for t in (H, W, bias)]
+    Y, I = lsr_head(*leaves, head.mask)
+    assert not I.requires_grad
+    Dropped.apply(Y).sum().backward()
+    for t in leaves:
+        assert t.grad is None or (t.grad.dtype == t.dtype and not t.grad.any())
+
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert lsr._stream(None) == side.cuda_stream
+    assert lsr._stream(None) == torch.cuda.current_stream().cuda_stream
+
+
 def test_random_shapes_and_masks():
     """Two dozen seeded random problems: odd sizes, D from the smallest legal value up, masks of any
     density with empty sequences mixed in, both loaders (D a multiple of 64 or not)."""
@@ -667,7 +704,7 @@ def test_db_is_rounded_once_per_launch(B, S, D, V, dtype, accumulate):
 
 def test_two_host_threads_on_two_streams():
     """Two host threads call forward + backward concurrently, each on its own stream, buffers and small
-    problem (small problems fork the dW gather onto the library's shared auxiliary stream).  Every call
+    problem (too small for the library's shared auxiliary stream: the next test's are not).  Every call
     of both threads must match the oracle."""
     import threading
     inps = [wl.make_custom(6, 70, 128, 900, seed=101, len_lo=3), wl.make_custom(9, 33, 64, 1500, seed=102, len_lo=1)]
