@@ -76,24 +76,6 @@ template <> struct OutVec<uint16_t> {
 };
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 
-// A float32 sum that carries what its additions round off (the two-sum of Knuth, TAOCP vol. 2, 4.2.2), so that the value
-// is rounded once.  The sliced and the LDS-tile dW kernels sum db this way: against float64, in units of the norm of db, a plain loop over B = 13 / 64 / 256
-// sequences is off by 7.0e-8 / 1.5e-7 / 2.9e-7, the 64-lane butterfly of the whole-row kernel by 5.2e-8 / 6.7e-8 / 7.8e-8,
-// this by 2.5e-8, and by 4.0e-8 / 7.4e-8 where four / sixteen launches each round the db they hand on.
-struct Sum32 {
-    float s, e;
-    __device__ __forceinline__ void add(float x) {
-        const float t = s + x;
-        const float b = t - s;
-        e += (s - (t - b)) + (x - b);
-        s = t;
-    }
-    __device__ __forceinline__ float value() const {
-        const float r = s + e;
-        return r == r ? r : s;               // an infinite sum has no rounding error (e is NaN then)
-    }
-};
-
 // ---------------------------------------------------------------------------------------------
 // Stable bucketing of the non-zero (b,v) pairs by position s.
 // The vocabulary is cut into n_seg segments of seg_len entries; (b, segment) is the unit of work.
@@ -656,22 +638,18 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
     const bool compact = nz < (SWZ ? 992 : 512);
 
     // db: every wave sums the columns that it compacts below (so it has read them before), 256 / VT lanes per
-    // column, each every (256 / VT)-th sequence; fixed order
+    // column, each every (256 / VT)-th sequence, in float64, rounded once per launch.  Against float64, in units of the norm of
+    // db, a float32 loop over B = 13 / 64 / 256 sequences is off by 7.0e-8 / 1.5e-7 / 2.9e-7, the 64-lane butterfly of the
+    // whole-row kernel by 5.2e-8 / 6.7e-8 / 7.8e-8, this by 2.5e-8, and by 4.0e-8 / 7.4e-8 where four / sixteen launches each
+    // round the db they hand on.
     if (db && dg == 0) {
         const int cols = VT / n_waves;
         const int part = lane / cols;
         const int vv = wave + n_waves * (lane - part * cols);
-        Sum32 sum = {0.f, 0.f};
-        for (int k = part; k < B; k += 64 / cols) sum.add(s_g[at(k, vv)]);
-        for (int off = cols; off < 64; off <<= 1) {
-            const float other = __shfl_xor(sum.s, off), err = __shfl_xor(sum.e, off);
-            sum.add(other);
-            sum.e += err;
-        }
-        if (part == 0 && v0 + vv < V) {
-            if (add_db) sum.add(db[v0 + vv]);
-            db[v0 + vv] = sum.value();
-        }
+        double sum = 0.0;
+        for (int k = part; k < B; k += 64 / cols) sum += (double)s_g[at(k, vv)];
+        for (int off = cols; off < 64; off <<= 1) sum += __shfl_xor(sum, off);
+        if (part == 0 && v0 + vv < V) db[v0 + vv] = (float)(add_db ? (double)db[v0 + vv] + sum : sum);
     }
 
     // compaction: column vv keeps its non-zero entries, in ascending b, at rows 0..n-1, and a zero at
@@ -990,8 +968,7 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
     for (int k = 0; k < RPT; ++k)
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[k][i] = 0.f;
-    const bool sum_db = db && dc == 0;
-    Sum32 db_sum = {(sum_db && add_db && vs_ok) ? db[vs] : 0.f, 0.f};
+    double db_acc = (db && dc == 0 && add_db && vs_ok) ? (double)db[vs] : 0.0;      // rounded once, as in the kernel above
 
     // The loads of a sequence are straight-line code (clamped addresses instead of predicates) and nothing
     // looks at their results before stage(), so that they stay in flight while the sequence before is
@@ -1020,7 +997,7 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
     };
     auto stage = [&](int buf, bool count) {
         const float g = vs_ok ? gate_grad(dy_r, y_r) : 0.f;
-        if (sum_db && count) db_sum.add(g);
+        db_acc += count ? (double)g : 0.0;
         s_go[buf][tid] = make_float2(g, __int_as_float((g != 0.f ? clamp_pos(ix_r, S) : DWT_MAX_S) * ROW_B));
     };
     if (tid < 16) *reinterpret_cast<uint4*>(&s_tile[tid >> 3][DWT_MAX_S * ROW_B + (tid & 7) * 16]) = make_uint4(0, 0, 0, 0);
@@ -1062,7 +1039,7 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
         wait_vmcnt<0>();                               // the tile has landed
         __syncthreads();
     }
-    if (sum_db && vs_ok) db[vs] = db_sum.value();
+    if (db && dc == 0 && vs_ok) db[vs] = (float)db_acc;
     if (!dW) return;
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {

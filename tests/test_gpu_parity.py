@@ -662,7 +662,7 @@ def test_rows_without_a_gradient_may_hold_nan(B, S, D, V, dtype):
 ])
 def test_db_is_rounded_once_per_launch(B, S, D, V, dtype, accumulate):
     """db = sum of dY where Y is tiny (exp(-Y) = 1): every launch rounds its running sum once, to within 2^-24 of its size;
-    the carried rounding errors are themselves rounded (B 2^-47 of the sum of magnitudes).  The whole-row kernel adds every
+    the float64 sums behind it are off by less (B 2^-47 of the sum of magnitudes).  The whole-row kernel adds every
     64th sequence in a lane and joins the lanes in six steps, each rounded to 2^-24 of a sum that the magnitudes bound.  With
     one gradient in ten too, which the sliced kernel compacts; infinities come out as in a plain sum."""
     dt = lsr.LSR_F32 if dtype == "f32" else lsr.LSR_BF16
