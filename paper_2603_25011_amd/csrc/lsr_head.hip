@@ -274,7 +274,9 @@ int dh_buckets_per_wave(const Shape& s, int n_vc) {
 //      341 -> 348 (4 waves: 801; 447; 355).  B=60 S=40 |V|=200000 (29k x 7, 1020) 3448 -> 3062; 1470 -> 1412; 1085 -> 1093
 //   1  (two waves instead) B=64 S=100 |V|=50000 (77k x 2, 357), backward 566 -> 550; -; 176 -> 197.  B=40 S=100 |V|=50000 (48k x 2, 357)
 //      623 -> 590; 383 -> 381; 325 -> 333.  B=256 S=32 (98k, 1363), dH 904 -> 647; 187 -> 153; 61 -> 75 and the backward, where
-//      it runs beside dW, 1677 -> 1753; -; 254 -> 257.  B=20 S=200 |V|=60000 (48k x 4, 107) 537 -> 510; 410 -> 414; 370 -> 377
+//      it runs beside dW, 1677 -> 1753; -; 254 -> 257.  B=20 S=200 |V|=60000 (48k x 2, 214) 537 -> 510; 410 -> 414; 370 -> 377
+// dH alone has no dW to hide the surplus behind: with one gradient in twenty B=10 S=60 |V|=200000 110 -> 128, B=32 S=128 D=1024 55 -> 62,
+// B=60 S=40 |V|=200000 267 -> 271, B=24 S=50 D=512 |V|=120000 89 -> 86.
 // List lengths as estimated above, in the time of bfloat16 entries (a float32 row piece takes twice the lanes).
 int dh_waves_per_bucket(const Shape& s, int n_vc) {
     if (!sliced_gathers(s)) return 1;
