@@ -10,6 +10,7 @@
 #include <mutex>
 
 #include "bwd.hpp"
+#include "fwd_few.hpp"
 #include "fwd_mfma.hpp"
 #include "fwd_misc.hpp"
 #include "probes.hpp"
@@ -72,6 +73,23 @@ int fwd_seg(const Shape& s) { return s.S <= FWD_SEG_SHORT_MAX_S ? FWD_SEG_SHORT 
 bool fwd_direct(const Shape& s) {
     const size_t row = (size_t)s.D * (s.dtype == LSR_F32 ? 4 : 2);
     return row % 128 == 0 && (size_t)s.B * s.S * row < ((size_t)1 << 32) && (size_t)s.V * row < ((size_t)1 << 32);
+}
+
+// Calls of few tokens go through one launch of their own (fwd_few_kernel), where the hidden states fit the LDS.  Forward, us,
+// packing and tile kernel -> one launch, all tokens valid (D=768 |V|=30522 bfloat16 where not said):
+//   one round of workgroups (|V| <= 32768 on 256 CUs), up to 16 sequences: B=1 S=32 22.1 -> 13.4, S=64 21.9 -> 17.3, D=2048 38.5 ->
+//     28.1, B=8 S=8 24.6 -> 21.7, B=16 S=4 29.4 -> 25.3, B=1 S=16 D=384 14.1 -> 7.8, B=2 S=16 D=64 |V|=1000 11.3 -> 5.8; float32 B=1
+//     S=32 38.6 -> 30.6, B=8 S=8 D=384 |V|=20000 39.4 -> 30.2, B=2 S=16 D=64 |V|=1000 13.9 -> 6.9
+//   many rounds with long rows, which keep the loads of W going beside the sums: B=1 S=32 |V|=250002 97 -> 83, D=1024 115 -> 98,
+//     |V|=160000 56 -> 44, B=8 S=8 |V|=160000 69.7 -> 69.2, B=1 S=16 D=512 |V|=250002 57.6 -> 47.4
+//   not: two or three rounds (B=4 S=16 |V|=40000 24.6 -> 27.6, B=1 S=32 |V|=60000 25.1 -> 26.1, |V|=119547 40.2 -> 40.2), many rounds of
+//     short rows (B=1 S=64 D=384 |V|=119547 29.5 -> 33.5, B=8 S=8 D=128 |V|=250002 43 -> 58) or in float32 (B=1 S=16 D=512 |V|=250002
+//     121 -> 134), more sequences (the lanes of a column take them one after the other: B=64 S=1 45.6 -> 51.1)
+bool fwd_few(const Shape& s) {
+    const long tokens = (long)s.B * s.S;
+    if (tokens > FEW_MAX_TOKENS || few_lds((int)tokens, s.D * (s.dtype == LSR_F32 ? 4 : 2)) > FEW_LDS) return false;
+    if (s.V <= 256 * FEW_COLS) return s.B <= 16;
+    return s.dtype == LSR_BF16 && s.V >= 131072 && s.D >= 512 && s.B <= 8;
 }
 
 // tpc: most tiles per chunk; window: float32 only, segments per window of a chunk (chunks are whole sequences, see
@@ -411,6 +429,19 @@ void launch_fwd(const FwdParams& p, int seg, bool direct, bool resident, bool ar
     }
 }
 
+template <typename T>
+void launch_few(const Shape& s, const void* H, const void* W, const float* bias, const uint8_t* mask, float* Y, int32_t* I, int n_cus,
+                hipStream_t st) {
+    const int row_bytes = s.D * (int)sizeof(T);
+    const int n_tiles = (s.V + FEW_COLS - 1) / FEW_COLS;
+    const dim3 grid(n_tiles < n_cus ? n_tiles : n_cus);
+#define LSR_FEW(ARG) hipLaunchKernelGGL((fwd_few_kernel<T, ARG>), grid, dim3(FEW_THREADS), 0, st, static_cast<const T*>(H), \
+                                        static_cast<const T*>(W), bias, mask, Y, I, s.B, s.S, s.D, s.V, few_stride(row_bytes), n_tiles)
+    if (I) LSR_FEW(true);
+    else LSR_FEW(false);
+#undef LSR_FEW
+}
+
 int forward_impl(const lsr_head_desc* desc, const void* H, const void* W, const float* bias,
                  const uint8_t* mask, float* Y, int32_t* I, void* ws, size_t ws_bytes, hipStream_t st,
                  Prof& prof) {
@@ -427,6 +458,13 @@ int forward_impl(const lsr_head_desc* desc, const void* H, const void* W, const 
     if (rc != LSR_OK) return rc;
 
     prof.stream = st;
+    if (fwd_few(s)) {
+        prof.begin(1);
+        if (s.dtype == LSR_F32) launch_few<float>(s, H, W, bias, mask, Y, I, n_cus, st);
+        else launch_few<uint16_t>(s, H, W, bias, mask, Y, I, n_cus, st);
+        prof.end(1);
+        return launch_status();
+    }
     int* len = reinterpret_cast<int*>(static_cast<char*>(ws) + w.len_off);
     int* pos = reinterpret_cast<int*>(static_cast<char*>(ws) + w.pos_off);
 
@@ -1061,7 +1099,7 @@ int lsr_head_plan_ex(const lsr_head_desc* desc, int32_t* plan, int slots) {
         w.n_vc, w.vc_len, dh_buckets_per_wave(s, w.n_vc), dw_stage_rows(s),
         dw_batch_chunk(s), f.n_chunks, fwd_seg(s), f.resident ? 1 : 0,
         dh_slices_owned(s) ? 1 : 0, dw_tile_passes(s), dh_waves_per_bucket(s, w.n_vc), f.window,
-        dw_beside_dh(s, w.n_vc, true) ? 1 : 0};
+        dw_beside_dh(s, w.n_vc, true) ? 1 : 0, fwd_few(s) ? 1 : 0};
     for (int i = 0; i < slots && i < LSR_PLAN_EX_SLOTS; ++i) plan[i] = all[i];
     return LSR_OK;
 }

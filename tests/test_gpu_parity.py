@@ -212,6 +212,42 @@ def test_fp32_matrix_core_forward(B, S, D, V, len_lo):
     run_case(inp)
 
 
+@pytest.mark.parametrize("B,S,D,V,dtype", [
+    (1, 1, 8, 1, "bf16"),          # one token, half a k-step, one vocabulary entry
+    (1, 64, 768, 32768, "bf16"),   # two row blocks at the largest token count; the widest vocabulary of one round
+    (1, 64, 768, 32769, "bf16"),   # one entry more: the tile kernel
+    (16, 4, 72, 129, "bf16"),      # odd number of 16-byte chunks; a ragged second workgroup; the most sequences
+    (3, 11, 264, 640, "bf16"),     # 33 tokens: the second row block holds one; one k-step behind a batch of loads
+    (2, 32, 512, 128, "f32"),      # four batches of loads, one workgroup
+    (5, 7, 20 * 8, 200, "f32"),
+    (8, 8, 512, 131100, "bf16"),   # workgroups that walk several tiles of the vocabulary, the last one ragged
+    (1, 9, 1032, 131072, "bf16"),
+])
+def test_calls_of_few_tokens(B, S, D, V, dtype):
+    """The one-launch forward.  Products are exact in float32, so a logit is within D * 2^-24 of the sum of the
+    magnitudes, and Y moves by no more than the logit does.  Scattered masks, an empty sequence, and the same result
+    without the index."""
+    inp = wl.make_custom(B, S, D, V, dtype=dtype, seed=B * 100 + S, w_std=0.05, backward=False)
+    rng = np.random.default_rng(D)
+    m2 = wl.scattered_mask(rng, B, S)
+    if B > 1:
+        m2[1, :] = 0
+    size = np.abs(inp.H.astype(np.float64)).max(axis=(0, 1)) @ np.abs(inp.W.astype(np.float64)).max(axis=0)
+    for mask in (None, m2):
+        ys = []
+        for want_index in (True, False):
+            head = DeviceHead(inp, mask=mask, want_index=want_index)
+            head.poison_outputs()
+            head.forward()
+            torch.cuda.synchronize()
+            ys.append(head.Y.cpu().numpy())
+            if want_index:
+                I = head.I.cpu().numpy()
+        Y_ref, _, _, _ = parity.compare_forward(inp, ys[0], I, mask=mask, v_chunk=16384)
+        assert np.array_equal(ys[0], ys[1])
+        assert np.abs(ys[0] - Y_ref).max() <= (D + 4) * 2.0 ** -24 * (size + np.abs(Y_ref).max())
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("B,S,D,V", [(5, 24, 64, 300), (3, 100, 72, 300), (2, 300, 64, 520)])      # 8-row segments, 32-row segments, several tiles
 def test_nan_tokens_are_never_selected(B, S, D, V, dtype):
