@@ -81,40 +81,97 @@ __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(
 // The vocabulary is cut into n_seg segments of seg_len entries; (b, segment) is the unit of work.
 // ---------------------------------------------------------------------------------------------
 
+// Exclusive prefix sum over the 64 * NW threads of a workgroup: shuffles within each wave, then the sums of the waves in
+// front; *total is the sum of all.  s_wave: NW ints, free again after the next barrier.  (One thread that walks 256
+// partial sums in LDS takes 7 us: it waits for LDS at every step.)
+template <int NW>
+__device__ __forceinline__ int exclusive_scan(int x, int* s_wave, int* total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int incl = x;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int up = __shfl_up(incl, off);
+        incl += lane >= off ? up : 0;
+    }
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const int t = s_wave[w];
+        before += w < wave ? t : 0;
+        all += t;
+    }
+    *total = all;
+    return before + incl - x;
+}
+
+// Rank of a lane among the lanes of its wave with the same key, and how many there are: one ballot per key bit.
+// The rank keeps the order of the lanes, so a bucket filled step by step ends up sorted by v (stable).
+struct LaneGroup { int rank, size; };
+__device__ __forceinline__ LaneGroup same_key_lanes(int key, bool active, int key_bits) {
+    unsigned long long same = __ballot(active);
+    for (int bit = 0; bit < key_bits; ++bit) {
+        const bool one = (key >> bit) & 1;
+        const unsigned long long bm = __ballot(active && one);
+        same &= one ? bm : ~bm;
+    }
+    return {(int)__popcll(same & ((1ull << (threadIdx.x & 63)) - 1ull)), (int)__popcll(same)};
+}
+
 // cnt[b][seg][s] = number of v in the segment with g != 0 and I[b,v] = s.
-__global__ __launch_bounds__(256) void bwd_count_kernel(const float* __restrict__ dY,
-                                                        const float* __restrict__ Y,
-                                                        const int* __restrict__ I,
-                                                        int* __restrict__ cnt,
-                                                        int S, int V, int n_seg, int seg_len) {
+// Four triples in flight per thread, and 1024 threads where segments are few, as long sequences have them: such a launch
+// waits for memory alone (B=32 S=8192 |V|=30522 137 -> 9 us; B=64 S=512 |V|=250002, 256 threads, 50 -> 36).
+constexpr int SORT_MAX_THREADS = 1024;
+__global__ __launch_bounds__(SORT_MAX_THREADS) void bwd_count_kernel(const float* __restrict__ dY,
+                                                                     const float* __restrict__ Y,
+                                                                     const int* __restrict__ I,
+                                                                     int* __restrict__ cnt,
+                                                                     int S, int V, int n_seg, int seg_len) {
     extern __shared__ int s_hist[];
-    const int seg = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-    for (int s = tid; s < S; s += 256) s_hist[s] = 0;
+    const int seg = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, nt = blockDim.x;
+    for (int s = tid; s < S; s += nt) s_hist[s] = 0;
     __syncthreads();
     const int vbeg = seg * seg_len;
-    const int vend = min(V, vbeg + seg_len);
+    const int vend = vbeg + min(V - vbeg, seg_len);
     const size_t row = (size_t)b * V;
-    for (int v = vbeg + tid; v < vend; v += 256) {
-        const float g = gate_grad(dY[row + v], Y[row + v]);
-        if (g != 0.f) atomicAdd(&s_hist[clamp_pos(I[row + v], S)], 1);
+    for (int v0 = vbeg + tid; v0 < vend; v0 += 4 * nt) {
+        float dy[4], y[4];
+        int ix[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int v = v0 + u * nt;
+            const bool ok = v < vend;
+            dy[u] = ok ? dY[row + v] : 0.f;
+            y[u] = ok ? Y[row + v] : 0.f;
+            ix[u] = ok ? I[row + v] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (gate_grad(dy[u], y[u]) != 0.f) atomicAdd(&s_hist[clamp_pos(ix[u], S)], 1);
     }
     __syncthreads();
     int* out = cnt + ((size_t)b * n_seg + seg) * S;
-    for (int s = tid; s < S; s += 256) out[s] = s_hist[s];
+    for (int s = tid; s < S; s += nt) out[s] = s_hist[s];
 }
 
 // Per b: cnt[b][seg][s] becomes the number of earlier-segment entries of bucket s, and
 // bstart[b][0..S] the exclusive prefix of the bucket sizes (bstart[b][S] = non-zero pairs of row b).
-__global__ __launch_bounds__(256) void bwd_scan_kernel(int* __restrict__ cnt, int* __restrict__ bstart,
-                                                       int S, int n_seg) {
-    extern __shared__ int s_tot[];          // [S] bucket sizes, then [256] partials
-    int* s_part = s_tot + S;
+// A thread owns one bucket of every NT: its loads and stores are coalesced, and the prefix over the buckets goes
+// NT at a time (B=2 S=16 4.5 -> 2.5 us, B=64 S=512 with 64 segments 15 -> 10).
+template <int NT>
+__global__ __launch_bounds__(NT) void bwd_scan_kernel(int* __restrict__ cnt, int* __restrict__ bstart,
+                                                      int S, int n_seg) {
+    __shared__ int s_wave[2][NT / 64];
     const int b = blockIdx.x, tid = threadIdx.x;
-    for (int s = tid; s < S; s += 256) {
+    int* out = bstart + (size_t)b * (S + 1);
+    int base = 0;
+    for (int s0 = 0, it = 0; s0 < S; s0 += NT, ++it) {
+        const int s = s0 + tid;
         int run = 0;
         // eight segments at a time: the loads of a batch are all issued before the first store,
         // which the compiler cannot do by itself (loads and stores go to the same array)
-        for (int seg0 = 0; seg0 < n_seg; seg0 += 8) {
+        for (int seg0 = 0; s < S && seg0 < n_seg; seg0 += 8) {
             int c[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u)
@@ -125,83 +182,99 @@ __global__ __launch_bounds__(256) void bwd_scan_kernel(int* __restrict__ cnt, in
                 run += c[u];
             }
         }
-        s_tot[s] = run;
+        int total;
+        const int before = exclusive_scan<NT / 64>(run, s_wave[it & 1], &total);
+        if (s < S) out[s] = base + before;
+        base += total;
     }
-    __syncthreads();
-    const int per = (S + 255) / 256;
-    const int lo = min(S, tid * per), hi = min(S, lo + per);
-    int sum = 0;
-    for (int s = lo; s < hi; ++s) sum += s_tot[s];
-    s_part[tid] = sum;
-    __syncthreads();
-    if (tid == 0) {
-        int run = 0;
-        for (int t = 0; t < 256; ++t) { const int c = s_part[t]; s_part[t] = run; run += c; }
-        bstart[(size_t)b * (S + 1) + S] = run;
-    }
-    __syncthreads();
-    int run = s_part[tid];
-    int* out = bstart + (size_t)b * (S + 1);
-    for (int s = lo; s < hi; ++s) { out[s] = run; run += s_tot[s]; }
+    if (tid == 0) out[S] = base;
 }
 
-// One wave per (b, segment) walks its entries in ascending v, 64 at a time.  Lanes holding the
-// same position find each other with one ballot per key bit; the rank among them keeps the order
-// of v, so every bucket ends up sorted by v (stable) and the later sums have a fixed order.
-__global__ __launch_bounds__(64) void bwd_place_kernel(const float* __restrict__ dY,
-                                                       const float* __restrict__ Y,
-                                                       const int* __restrict__ I,
-                                                       const int* __restrict__ cnt,
-                                                       const int* __restrict__ bstart,
-                                                       uint2* __restrict__ perm,
-                                                       int S, int V, int n_seg, int seg_len, int key_bits) {
-    extern __shared__ int s_off[];          // [S] next free slot of each bucket
-    const int seg = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
+// Placement: PLACE_WAVES waves per (b, segment), each with a consecutive piece of the segment.  A wave first counts its
+// pairs per bucket (LDS atomics); the counts of the waves in front of it and of the segments in front then give it a slot
+// of its own in every bucket, and it walks its piece in ascending v, 64 at a time, without looking at the other waves.
+// Lanes holding the same position find each other by ballots (same_key_lanes), so every bucket ends up sorted by v
+// and the later sums have a fixed order.  What bounds it are the ballots and dependent LDS accesses of each step, so steps must not
+// wait for one another (waves that took turns behind a barrier per 64 pairs: with LDS staging B=2 S=16 |V|=1000 8.4 ->
+// 5.0 us, B=13 S=197 |V|=31091 11.4 -> 8.0, B=256 S=512 |V|=30522 82 -> 72, B=64 S=512 |V|=250002 157 -> 165;
+// without, from one wave per workgroup, B=32 S=8192 |V|=30522 230 -> 65).
+constexpr int PLACE_WAVES = 4;
+
+// Long sequences: every pair is stored straight to its bucket.   dynamic LDS: PLACE_WAVES * S ints
+__global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_kernel(const float* __restrict__ dY,
+                                                                     const float* __restrict__ Y,
+                                                                     const int* __restrict__ I,
+                                                                     const int* __restrict__ cnt,
+                                                                     const int* __restrict__ bstart,
+                                                                     uint2* __restrict__ perm,
+                                                                     int S, int V, int n_seg, int seg_len, int key_bits) {
+    extern __shared__ int s_place[];        // [PLACE_WAVES][S] counts, then the next free slot of each bucket
+    const int seg = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    int* const s_off = s_place + wave * S;
     const int* c0 = cnt + ((size_t)b * n_seg + seg) * S;
     const int* b0 = bstart + (size_t)b * (S + 1);
-    for (int s = lane; s < S; s += 64) s_off[s] = b0[s] + c0[s];
+    for (int s = tid; s < PLACE_WAVES * S; s += 64 * PLACE_WAVES) s_place[s] = 0;
     __syncthreads();
-    const int vbeg = seg * seg_len;
-    const int vend = min(V, vbeg + seg_len);
+    const int piece = (seg_len / 64 + PLACE_WAVES - 1) / PLACE_WAVES * 64;       // (seg_len is a multiple of 64)
+    const int vseg = seg * seg_len, n = min(V - vseg, seg_len);
+    const int vbeg = vseg + min(n, wave * piece), vend = vseg + min(n, (wave + 1) * piece);
     const size_t row = (size_t)b * V;
-    const unsigned long long lt = (1ull << lane) - 1ull;
-    // the next 64 entries are requested before the current ones are ranked (the ranking has two
-    // barriers and would otherwise expose a full memory latency per step)
-    float n_dy = 0.f, n_y = 0.f;
-    int n_i = 0;
-    auto request = [&](int base) {
-        const int v = base + lane;
-        const bool ok = v < vend;
-        n_dy = ok ? dY[row + v] : 0.f;
-        n_y = ok ? Y[row + v] : 0.f;
-        n_i = ok ? I[row + v] : 0;
+    float dy[4], y[4];
+    int ix[4];
+    auto request = [&](int base) {          // four steps of 64
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int v = base + u * 64 + lane;
+            const bool ok = v < vend;
+            dy[u] = ok ? dY[row + v] : 0.f;
+            y[u] = ok ? Y[row + v] : 0.f;
+            ix[u] = ok ? I[row + v] : 0;
+        }
     };
+    for (int base = vbeg; base < vend; base += 256) {
+        request(base);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (gate_grad(dy[u], y[u]) != 0.f) atomicAdd(&s_off[clamp_pos(ix[u], S)], 1);
+    }
     request(vbeg);
-    for (int base = vbeg; base < vend; base += 64) {
-        const int v = base + lane;
-        const float g = gate_grad(n_dy, n_y);      // 0 for lanes past the end (dy = 0, y = 0)
-        const int key = clamp_pos(n_i, S);
-        request(base + 64);
-        const bool active = g != 0.f;
-        unsigned long long same = __ballot(active);
-        for (int bit = 0; bit < key_bits; ++bit) {
-            const bool one = (key >> bit) & 1;
-            const unsigned long long bm = __ballot(active && one);
-            same &= one ? bm : ~bm;
+    __syncthreads();
+    for (int s = tid; s < S; s += 64 * PLACE_WAVES) {
+        int at = b0[s] + c0[s];
+#pragma unroll
+        for (int w = 0; w < PLACE_WAVES; ++w) {
+            const int c = s_place[w * S + s];
+            s_place[w * S + s] = at;
+            at += c;
         }
-        const int rank = __popcll(same & lt);
-        const int group = __popcll(same);
-        int dest = 0;
-        if (active) {
-            dest = s_off[key] + rank;
-            perm[row + dest] = make_uint2((unsigned)v, __float_as_uint(g));      // one 8-byte scattered store
+    }
+    __syncthreads();
+    for (int base = vbeg; base < vend; base += 256) {
+        float g[4];
+        int key[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            g[u] = gate_grad(dy[u], y[u]);      // 0 for lanes past the end (dy = 0, y = 0)
+            key[u] = clamp_pos(ix[u], S);
         }
-        // The workgroup is a single wave: its LDS instructions execute in program order for all lanes,
-        // so the read of s_off above precedes this update and the update precedes the next step's
-        // read.  wave_barrier only pins that order for the compiler; no hardware barrier is needed.
-        __builtin_amdgcn_wave_barrier();
-        if (active && rank == group - 1) s_off[key] = dest + 1;
-        __builtin_amdgcn_wave_barrier();
+        // the next four steps are requested before the current ones are ranked
+        request(base + 256);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool active = g[u] != 0.f;
+            const LaneGroup lg = same_key_lanes(key[u], active, key_bits);
+            int dest = 0;
+            if (active) {
+                dest = s_off[key[u]] + lg.rank;
+                perm[row + dest] = make_uint2((unsigned)(base + u * 64 + lane), __float_as_uint(g[u]));      // one 8-byte scattered store
+            }
+            // LDS instructions of one wave execute in program order for all lanes, so the read of s_off above precedes
+            // this update and the update precedes the next step's read.  wave_barrier only pins that order for the compiler.
+            __builtin_amdgcn_wave_barrier();
+            if (active && lg.rank == lg.size - 1) s_off[key[u]] = dest + 1;
+            __builtin_amdgcn_wave_barrier();
+        }
     }
 }
 
@@ -209,114 +282,102 @@ __global__ __launch_bounds__(64) void bwd_place_kernel(const float* __restrict__
 // The kernel above stores every (v, g) pair straight to its bucket: the 64 stores of a step go to some
 // fifty buckets, and with thousands of (b, segment) waves in flight every bucket's line leaves L2
 // between two stores to it (measured at C5: 0.48 GB written for 0.13 GB of pairs).  Here a workgroup
-// of four waves first sorts its whole segment by bucket in LDS and then writes it out in sorted order:
+// first sorts its whole segment by bucket in LDS and then writes it out in sorted order:
 // the pairs a bucket receives from this segment (about a dozen at C5) leave as one contiguous run.
-//   1. per bucket, the pairs of this segment (difference of two rows of the scanned count table) and
-//      their exclusive prefix = first local slot; s_delta = first global slot - first local slot;
-//   2. steps of 256 pairs: ballot ranking inside each wave as above, then the four waves take their
-//      slots one after the other (wave order = ascending v, so the order inside a bucket is kept);
-//   3. local slot k goes to global slot k + s_delta[bucket of k].
-// A staged pair is (v - vbeg) | bucket << 12 and g.   dynamic LDS: 2*S ints + seg_len pairs.
+//   1. every wave loads its piece of the segment, keeps (g, bucket) in registers and counts per bucket;
+//   2. exclusive prefix over buckets and waves = first local slot of each (bucket, wave); s_delta = first global
+//      slot of the bucket - its first local slot;
+//   3. steps of 64 pairs per wave: ballot ranking, staging;
+//   4. local slot k goes to global slot k + s_delta[bucket of k].
+// A staged pair is (v - vbeg) | bucket << 12 and g.   dynamic LDS: (PLACE_WAVES + 1) * S ints + seg_len pairs.
+// STEPS: steps of 64 per wave, at least seg_len / (64 * PLACE_WAVES).
 // ---------------------------------------------------------------------------------------------
 constexpr int PLACE_MAX_S = 1024;
 constexpr int PLACE_MAX_SEG = 4096;
 
-__global__ __launch_bounds__(256) void bwd_place_staged_kernel(const float* __restrict__ dY,
+template <int STEPS>
+__global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_staged_kernel(const float* __restrict__ dY,
                                                                const float* __restrict__ Y,
                                                                const int* __restrict__ I,
                                                                const int* __restrict__ cnt,
                                                                const int* __restrict__ bstart,
                                                                uint2* __restrict__ perm,
                                                                int S, int V, int n_seg, int seg_len, int key_bits) {
-    extern __shared__ int s_place[];
-    int* s_next = s_place;                  // [S] next free local slot of each bucket
-    int* s_delta = s_place + S;             // [S] global slot - local slot
-    uint2* s_stage = reinterpret_cast<uint2*>(s_place + 2 * S);     // [seg_len]
-    __shared__ int s_part[256];
+    constexpr int NT = 64 * PLACE_WAVES;
+    extern __shared__ __attribute__((aligned(16))) int s_place[];
+    uint2* s_stage = reinterpret_cast<uint2*>(s_place);             // [seg_len]
+    int* s_next = s_place + 2 * seg_len;    // [PLACE_WAVES][S] counts, then the next free local slot of each bucket
+    int* s_delta = s_next + PLACE_WAVES * S;                        // [S] global slot - local slot
+    __shared__ int s_wave[PLACE_WAVES];
     const int seg = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
+    int* const s_mine = s_next + wave * S;
     const int* c0 = cnt + ((size_t)b * n_seg + seg) * S;
     const int* b0 = bstart + (size_t)b * (S + 1);
-    const bool last_seg = seg + 1 == n_seg;
 
-    // 1. counts of this segment, exclusive prefix over the buckets
-    const int per = (S + 255) / 256;
+    // 1. this wave's piece
+    const int piece = (seg_len / 64 + PLACE_WAVES - 1) / PLACE_WAVES * 64;       // (seg_len is a multiple of 64)
+    const int vseg = seg * seg_len, n = min(V - vseg, seg_len);
+    const int vbeg = vseg + min(n, wave * piece), vend = vseg + min(n, (wave + 1) * piece);
+    const size_t row = (size_t)b * V;
+    float g[STEPS];
+    int key[STEPS];
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+        const int v = vbeg + i * 64 + lane;
+        const bool ok = v < vend;
+        const float dy = ok ? dY[row + v] : 0.f;
+        const float y = ok ? Y[row + v] : 0.f;
+        key[i] = ok ? clamp_pos(I[row + v], S) : 0;
+        g[i] = gate_grad(dy, y);                // 0 for lanes past the end (dy = 0, y = 0)
+    }
+    for (int s = tid; s < PLACE_WAVES * S; s += NT) s_next[s] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i)
+        if (g[i] != 0.f) atomicAdd(&s_mine[key[i]], 1);
+    __syncthreads();
+
+    // 2. slots
+    const int per = (S + NT - 1) / NT;
     const int lo = min(S, tid * per), hi = min(S, lo + per);
     int sum = 0;
+    for (int s = lo; s < hi; ++s)
+#pragma unroll
+        for (int w = 0; w < PLACE_WAVES; ++w) sum += s_next[w * S + s];
+    int total;
+    int run = exclusive_scan<PLACE_WAVES>(sum, s_wave, &total);
     for (int s = lo; s < hi; ++s) {
-        const int earlier = c0[s];
-        const int upto = last_seg ? b0[s + 1] - b0[s] : c0[S + s];      // next segment's row, or the bucket size
-        s_next[s] = upto - earlier;
-        s_delta[s] = b0[s] + earlier;
-        sum += upto - earlier;
-    }
-    s_part[tid] = sum;
-    __syncthreads();
-    if (tid == 0) {
-        int run = 0;
-        for (int t = 0; t < 256; ++t) { const int c = s_part[t]; s_part[t] = run; run += c; }
-    }
-    __syncthreads();
-    int run = s_part[tid];
-    for (int s = lo; s < hi; ++s) {
-        const int c = s_next[s];
-        s_next[s] = run;
-        s_delta[s] -= run;
-        run += c;
-    }
-    __shared__ int s_total;
-    if (tid == 255) s_total = run;          // the last thread ends on the pairs of the whole segment
-    __syncthreads();
-
-    // 2. rank and stage
-    const int vbeg = seg * seg_len;
-    const int vend = min(V, vbeg + seg_len);
-    const size_t row = (size_t)b * V;
-    const unsigned long long lt = (1ull << lane) - 1ull;
-    float n_dy = 0.f, n_y = 0.f;
-    int n_i = 0;
-    auto request = [&](int base) {
-        const int v = base + tid;
-        const bool ok = v < vend;
-        n_dy = ok ? dY[row + v] : 0.f;
-        n_y = ok ? Y[row + v] : 0.f;
-        n_i = ok ? I[row + v] : 0;
-    };
-    request(vbeg);
-    for (int base = vbeg; base < vend; base += 256) {
-        const int v = base + tid;
-        const float g = gate_grad(n_dy, n_y);      // 0 for threads past the end (dy = 0, y = 0)
-        const int key = clamp_pos(n_i, S);
-        request(base + 256);
-        const bool active = g != 0.f;
-        unsigned long long same = __ballot(active);
-        for (int bit = 0; bit < key_bits; ++bit) {
-            const bool one = (key >> bit) & 1;
-            const unsigned long long bm = __ballot(active && one);
-            same &= one ? bm : ~bm;
-        }
-        const int rank = __popcll(same & lt);
-        const int group = __popcll(same);
-        for (int w = 0; w < 4; ++w) {
-            if (wave == w) {
-                int slot = 0;
-                if (active) {
-                    slot = s_next[key] + rank;
-                    s_stage[slot] = make_uint2((unsigned)(v - vbeg) | ((unsigned)key << 12), __float_as_uint(g));
-                }
-                __builtin_amdgcn_wave_barrier();     // LDS operations of one wave execute in program order
-                if (active && rank == group - 1) s_next[key] = slot + 1;
-            }
-            __syncthreads();
+        s_delta[s] = b0[s] + c0[s] - run;
+#pragma unroll
+        for (int w = 0; w < PLACE_WAVES; ++w) {
+            const int c = s_next[w * S + s];
+            s_next[w * S + s] = run;
+            run += c;
         }
     }
+    __syncthreads();
 
-    // 3. sorted write-out
-    const int total = s_total;
-    for (int k = tid; k < total; k += 256) {
+    // 3. rank and stage
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+        const bool active = g[i] != 0.f;
+        const LaneGroup lg = same_key_lanes(key[i], active, key_bits);
+        int slot = 0;
+        if (active) {
+            slot = s_mine[key[i]] + lg.rank;
+            s_stage[slot] = make_uint2((unsigned)(vbeg - vseg + i * 64 + lane) | ((unsigned)key[i] << 12), __float_as_uint(g[i]));
+        }
+        __builtin_amdgcn_wave_barrier();         // LDS operations of one wave execute in program order
+        if (active && lg.rank == lg.size - 1) s_mine[key[i]] = slot + 1;
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+
+    // 4. sorted write-out
+    for (int k = tid; k < total; k += NT) {
         const uint2 e = s_stage[k];
-        const int key = (int)(e.x >> 12);
-        perm[row + k + s_delta[key]] = make_uint2((unsigned)vbeg + (e.x & 4095u), e.y);
+        perm[row + k + s_delta[e.x >> 12]] = make_uint2((unsigned)vseg + (e.x & 4095u), e.y);
     }
 }
 

@@ -805,20 +805,30 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
     if (dH) {
         const dim3 seg_grid(w.n_seg, s.B);
         prof.begin(0);
-        hipLaunchKernelGGL(bwd_count_kernel, seg_grid, dim3(256), sizeof(int) * s.S, st, dY, Y, I, cnt, s.S, s.V, w.n_seg, w.seg_len);
+        // few segments (long sequences, small problems): more threads per workgroup instead
+        const int count_threads = (long long)s.B * w.n_seg < 512 ? SORT_MAX_THREADS : 256;
+        hipLaunchKernelGGL(bwd_count_kernel, seg_grid, dim3(count_threads), sizeof(int) * s.S, st, dY, Y, I, cnt, s.S, s.V, w.n_seg, w.seg_len);
         prof.end(0);
         if ((r = launch_status()) != LSR_OK) return r;
         prof.begin(1);
-        hipLaunchKernelGGL(bwd_scan_kernel, dim3(s.B), dim3(256), sizeof(int) * (s.S + 256), st, cnt, bstart, s.S, w.n_seg);
+        if (s.S > 256) hipLaunchKernelGGL(bwd_scan_kernel<1024>, dim3(s.B), dim3(1024), 0, st, cnt, bstart, s.S, w.n_seg);
+        else hipLaunchKernelGGL(bwd_scan_kernel<256>, dim3(s.B), dim3(256), 0, st, cnt, bstart, s.S, w.n_seg);
         prof.end(1);
         if ((r = launch_status()) != LSR_OK) return r;
         prof.begin(2);
-        if (L.staged_place)
-            hipLaunchKernelGGL(bwd_place_staged_kernel, seg_grid, dim3(256), sizeof(int) * 2 * s.S + sizeof(uint2) * w.seg_len, st,
-                               dY, Y, I, cnt, bstart, perm, s.S, s.V, w.n_seg, w.seg_len, w.key_bits);
-        else
-            hipLaunchKernelGGL(bwd_place_kernel, seg_grid, dim3(64), sizeof(int) * s.S, st, dY, Y, I, cnt, bstart, perm,
+        const dim3 place_block(64 * PLACE_WAVES);
+        if (L.staged_place) {
+            const size_t lds = sizeof(int) * (PLACE_WAVES + 1) * s.S + sizeof(uint2) * w.seg_len;
+#define LSR_PLACE(STEPS) hipLaunchKernelGGL(bwd_place_staged_kernel<STEPS>, seg_grid, place_block, lds, st, dY, Y, I, cnt, bstart, perm, s.S, \
+                                            s.V, w.n_seg, w.seg_len, w.key_bits)
+            if (w.seg_len <= 4 * 64 * PLACE_WAVES) LSR_PLACE(4);
+            else if (w.seg_len <= 8 * 64 * PLACE_WAVES) LSR_PLACE(8);
+            else LSR_PLACE(16);
+#undef LSR_PLACE
+        } else {
+            hipLaunchKernelGGL(bwd_place_kernel, seg_grid, place_block, sizeof(int) * PLACE_WAVES * s.S, st, dY, Y, I, cnt, bstart, perm,
                                s.S, s.V, w.n_seg, w.seg_len, w.key_bits);
+        }
         prof.end(2);
         if ((r = launch_status()) != LSR_OK) return r;
         prof.begin(3);

@@ -821,3 +821,16 @@ def test_mfma_probe_reports_a_plausible_rate():
     print(f"register-only bf16 MFMA rate: {tf:.0f} TFLOP/s")
     assert 800.0 < tf < 2600.0          # between a third of and just above the nominal 2.5 PFLOP/s
     assert float(sink.item()) == 0.0    # nothing is ever stored
+
+
+@pytest.mark.parametrize("B,S,D,V,dy_keep", [
+    (2, 3, 64, 63, None),          # one step of one wave; the other waves of the placement have nothing
+    (3, 257, 64, 4097, None),      # the prefix over the buckets takes two rounds of 256 threads, or one of 1024
+    (2, 1024, 64, 9000, 0.3),      # the longest sequences that place through LDS, short last piece
+    (2, 1025, 64, 9001, None),     # the first that do not
+    (1, 8192, 64, 25000, 0.9),     # the longest of all: four tables of 8192 buckets
+    (2, 40, 64, 16384 + 1, None),  # a last segment of few entries
+])
+def test_bucket_sort_pieces(B, S, D, V, dy_keep):
+    """Sizes at which the pieces that the waves of the bucket sort take, and its prefix sums, end."""
+    print(run_case(wl.make_custom(B, S, D, V, seed=B * 7 + S, len_lo=max(1, S // 2), dy_keep=dy_keep)))
