@@ -106,65 +106,65 @@ __global__ __launch_bounds__(FWD_ROWS_THREADS) void fwd_rows_kernel(const int* _
 // dependent launches cost more than the work in them (B=32 S=256: 15.6 -> 11.6 us, B=16 S=256: 13.5 ->
 // 9.8 us; with hundreds of sequences the waves' one-sequence-at-a-time loop loses: B=256 S=32 13.5 ->
 // 21.8 us, B=64 S=512 24 -> 37 us).  Wave w serves sequences w, w + 16, ...: it compacts the
-// mask row (ballot + popcount), and after the workgroup-wide prefix sum of the block counts writes the
-// row table and block records of the same sequences (its own earlier stores, program order).
+// mask row (ballot + popcount) into LDS, and after the prefix sum of the block counts writes the
+// row table and block records of the same sequences.  What bounds it is latency, so PACK_U mask entries per lane are in
+// flight at a time, every wave forms the prefix sum for itself by shuffles (one barrier), and positions stay in LDS (against one
+// entry in flight, a prefix sum of 1024 partials and positions through memory: B=32 S=256 9.0 -> 4.9 us, B=8 S=512 7.4 -> 4.8).
 constexpr int PACK_THREADS = 1024;
 constexpr int PACK_MAX_B = 64;
 constexpr int PACK_MAX_TOKENS = 16384;
+constexpr int PACK_U = 8;
 
-__global__ __launch_bounds__(PACK_THREADS) void fwd_pack_kernel(const uint8_t* __restrict__ mask, int* __restrict__ len,
-                                                                 int* __restrict__ pos, int* __restrict__ blk0,
+__global__ __launch_bounds__(PACK_THREADS) void fwd_pack_kernel(const uint8_t* __restrict__ mask, int* __restrict__ blk0,
                                                                  int2* __restrict__ rows, int* __restrict__ blk_meta,
                                                                  int B, int S, int seg) {
     __shared__ int s_len[PACK_MAX_B];
-    __shared__ int s_blk0[PACK_MAX_B + 1];
-    __shared__ int s_part[PACK_THREADS];
+    __shared__ uint16_t s_pos[PACK_MAX_TOKENS];      // [B][S] valid positions, ascending
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int NW = PACK_THREADS / 64;
     // 1. compaction
     for (int b = wave; b < B; b += NW) {
         const uint8_t* mrow = mask + (size_t)b * S;
-        int* prow = pos + (size_t)b * S;
+        uint16_t* prow = s_pos + b * S;
         int base = 0;
-        for (int s0 = 0; s0 < S; s0 += 64) {
-            const int s = s0 + lane;
-            const bool flag = s < S && mrow[s] != 0;
-            const unsigned long long bal = __ballot(flag);
-            if (flag) prow[base + __popcll(bal & ((1ull << lane) - 1ull))] = s;
-            base += __popcll(bal);
+        for (int s0 = 0; s0 < S; s0 += 64 * PACK_U) {
+            uint8_t m[PACK_U];
+#pragma unroll
+            for (int u = 0; u < PACK_U; ++u) {
+                const int s = s0 + u * 64 + lane;
+                m[u] = s < S ? mrow[s] : (uint8_t)0;
+            }
+#pragma unroll
+            for (int u = 0; u < PACK_U; ++u) {
+                const unsigned long long bal = __ballot(m[u] != 0);
+                if (m[u] != 0) prow[base + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)(s0 + u * 64 + lane);
+                base += __popcll(bal);
+            }
         }
-        if (lane == 0) { s_len[b] = base; len[b] = base; }
+        if (lane == 0) s_len[b] = base;
     }
     __syncthreads();
-    // 2. exclusive prefix sum of the block counts: consecutive sequences per thread, then the partials
-    const int per = (B + PACK_THREADS - 1) / PACK_THREADS;
-    const int lo = min(B, tid * per), hi = min(B, lo + per);
-    int sum = 0;
-    for (int b = lo; b < hi; ++b) sum += max(1, (s_len[b] + seg - 1) / seg);
-    s_part[tid] = sum;
-    __syncthreads();
-    for (int off = 1; off < PACK_THREADS; off <<= 1) {
-        const int add = tid >= off ? s_part[tid - off] : 0;
-        __syncthreads();
-        s_part[tid] += add;
-        __syncthreads();
+    // 2. exclusive prefix sum of the block counts: lane b holds sequence b
+    static_assert(PACK_MAX_B <= 64, "one wave holds all sequences");
+    const int mine = lane < B ? max(1, (s_len[lane] + seg - 1) / seg) : 0;
+    int incl = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int up = __shfl_up(incl, off);
+        incl += lane >= off ? up : 0;
     }
-    int run = s_part[tid] - sum;
-    for (int b = lo; b < hi; ++b) {
-        s_blk0[b] = run;
-        blk0[b] = run;
-        run += max(1, (s_len[b] + seg - 1) / seg);
+    if (wave == 0 && lane < B) {
+        blk0[lane] = incl - mine;
+        if (lane == B - 1) blk0[B] = incl;
     }
-    if (tid == PACK_THREADS - 1) { s_blk0[B] = s_part[tid]; blk0[B] = s_part[tid]; }
-    __syncthreads();
     // 3. row table and block records
     for (int b = wave; b < B; b += NW) {
         const int n = s_len[b];
-        const int g0 = s_blk0[b];
-        const int nblk = s_blk0[b + 1] - g0;
-        const int* prow = pos + (size_t)b * S;
+        const int g0 = __shfl(incl - mine, b);
+        const int nblk = __shfl(mine, b);
+        const uint16_t* prow = s_pos + b * S;
         for (int k = lane; k < nblk * seg; k += 64) {
-            const int s = n > 0 ? prow[k < n ? k : n - 1] : 0;
+            const int s = n > 0 ? (int)prow[k < n ? k : n - 1] : 0;
             rows[(size_t)g0 * seg + k] = make_int2(b * S + s, s);
         }
         for (int k = lane; k < nblk; k += 64)
@@ -179,11 +179,18 @@ __global__ __launch_bounds__(PACK_THREADS) void fwd_pack_kernel(const uint8_t* _
 // leave theirs in slot k of part_m / part_s.  One thread per (chunk, vocabulary entry) takes the
 // pieces in order (later pieces hold higher positions, so an equal maximum keeps the earlier
 // position), applies bias, ReLU and log1p (F4) and overwrites Y and I with the final values.
-// grid (ceil(V/256), up to FWD_MERGE_ROWS): a workgroup walks the chunks y, y + gridDim.y, ... (most end
+// grid (ceil(V/256), fwd_merge_rows): a workgroup walks the chunks y, y + gridDim.y, ... (most end
 // with a whole sequence and cost one table read).  tpc = most tiles per chunk, spt = segments per tile
 // (ChunkSplit); blk0 and blk_meta are the segment tables.
 constexpr int FWD_MERGE_THREADS = 256;
-constexpr int FWD_MERGE_ROWS = 4;
+// Rows of the grid: each chunk is a chain of dependent reads, so narrow vocabularies spread the chunks over more workgroups (4 ->
+// 32 rows: B=32 S=256 |V|=30522 9.1 -> 7.5 us, B=256 S=512 12.4 -> 9.3); with a thousand workgroups per row four are enough (B=64
+// S=512 |V|=250002 38.8 -> 46.5).
+inline int fwd_merge_rows(int vgroups, int n_chunks) {
+    int rows = 4096 / vgroups;
+    rows = rows < 4 ? 4 : (rows > 32 ? 32 : rows);
+    return n_chunks < rows ? n_chunks : rows;
+}
 
 template <bool ARG>
 __global__ __launch_bounds__(FWD_MERGE_THREADS) void fwd_merge_kernel(const int* __restrict__ blk0,

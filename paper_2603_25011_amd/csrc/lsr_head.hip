@@ -481,7 +481,7 @@ int forward_impl(const lsr_head_desc* desc, const void* H, const void* W, const 
     const FwdChunks ck = fwd_chunks(s);
     const int seg = fwd_seg(s);
     if (one_launch) {
-        hipLaunchKernelGGL(fwd_pack_kernel, dim3(1), dim3(PACK_THREADS), 0, st, mask, len, pos, blk0, rows, blk_meta, s.B, s.S, seg);
+        hipLaunchKernelGGL(fwd_pack_kernel, dim3(1), dim3(PACK_THREADS), 0, st, mask, blk0, rows, blk_meta, s.B, s.S, seg);
     } else {
         hipLaunchKernelGGL(fwd_plan_kernel, dim3(1), dim3(PLAN_THREADS), 0, st, len, blk0, s.B, seg);
         hipLaunchKernelGGL(fwd_rows_kernel, dim3(s.B), dim3(FWD_ROWS_THREADS), 0, st, len, pos, blk0, rows, blk_meta, s.S, seg);
@@ -502,7 +502,8 @@ int forward_impl(const lsr_head_desc* desc, const void* H, const void* W, const 
     if (ck.cut_possible) {
         if ((rc = launch_status()) != LSR_OK) return rc;
         prof.begin(2);
-        const dim3 grid((s.V + FWD_MERGE_THREADS - 1) / FWD_MERGE_THREADS, ck.n_chunks < FWD_MERGE_ROWS ? ck.n_chunks : FWD_MERGE_ROWS);
+        const int vgroups = (s.V + FWD_MERGE_THREADS - 1) / FWD_MERGE_THREADS;
+        const dim3 grid(vgroups, fwd_merge_rows(vgroups, ck.n_chunks));
         if (I) hipLaunchKernelGGL((fwd_merge_kernel<true>), grid, dim3(FWD_MERGE_THREADS), 0, st, blk0, blk_meta, part_m, part_s,
                                   bias, Y, I, s.B, s.V, ck.tpc, FWD_TM / seg);
         else   hipLaunchKernelGGL((fwd_merge_kernel<false>), grid, dim3(FWD_MERGE_THREADS), 0, st, blk0, blk_meta, part_m, part_s,

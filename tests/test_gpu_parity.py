@@ -834,3 +834,16 @@ def test_mfma_probe_reports_a_plausible_rate():
 def test_bucket_sort_pieces(B, S, D, V, dy_keep):
     """Sizes at which the pieces that the waves of the bucket sort take, and its prefix sums, end."""
     print(run_case(wl.make_custom(B, S, D, V, seed=B * 7 + S, len_lo=max(1, S // 2), dy_keep=dy_keep)))
+
+
+@pytest.mark.parametrize("B,S", [(64, 256), (1, 16384), (31, 513), (17, 512), (64, 2)])
+def test_packing_in_one_launch(B, S):
+    """The most sequences and mask entries that one workgroup packs, and lengths around its eight entries per lane;
+    a scattered mask with an empty first and last sequence."""
+    inp = wl.make_custom(B, S, 64, 300 if B * S > 128 else 33000, seed=B + S, backward=False)
+    mask = wl.scattered_mask(np.random.default_rng(S), B, S)
+    if B > 1:
+        mask[0, :] = 0
+        mask[B - 1, :] = 0
+    for m in (None, mask):
+        print(run_case(inp, mask=m, check_bwd=False))
