@@ -101,17 +101,16 @@ __global__ __launch_bounds__(FWD_ROWS_THREADS) void fwd_rows_kernel(const int* _
                            (k == 0 ? FWD_META_FIRST : 0);
 }
 
-// The three passes above in one launch of one workgroup, for batches of few sequences and tokens (the
-// host takes this path up to PACK_MAX_TOKENS mask entries and PACK_MAX_B sequences), where three
-// dependent launches cost more than the work in them (B=32 S=256: 15.6 -> 11.6 us, B=16 S=256: 13.5 ->
-// 9.8 us; with hundreds of sequences the waves' one-sequence-at-a-time loop loses: B=256 S=32 13.5 ->
-// 21.8 us, B=64 S=512 24 -> 37 us).  Wave w serves sequences w, w + 16, ...: it compacts the
+// The three passes above in one launch of one workgroup, for batches of few sequences and tokens, where three
+// dependent launches cost more than the work in them: up to PACK_MAX_TOKENS mask entries and 64 sequences, or
+// PACK_MAX_B of at most 64 tokens (packing as a profiled slot of its own, three launches -> one: B=100 S=40 13.8 -> 9.4 us,
+// B=128 S=64 11.2 -> 10.3, and the forward 28.9 -> 25.2 at |V|=1000; not B=256 S=32 11.2 -> 15.3).  Wave w serves sequences w, w + 16, ...: it compacts the
 // mask row (ballot + popcount) into LDS, and after the prefix sum of the block counts writes the
 // row table and block records of the same sequences.  What bounds it is latency, so PACK_U mask entries per lane are in
 // flight at a time, every wave forms the prefix sum for itself by shuffles (one barrier), and positions stay in LDS (against one
 // entry in flight, a prefix sum of 1024 partials and positions through memory: B=32 S=256 9.0 -> 4.9 us, B=8 S=512 7.4 -> 4.8).
 constexpr int PACK_THREADS = 1024;
-constexpr int PACK_MAX_B = 64;
+constexpr int PACK_MAX_B = 128;
 constexpr int PACK_MAX_TOKENS = 16384;
 constexpr int PACK_U = 8;
 
@@ -120,10 +119,30 @@ __global__ __launch_bounds__(PACK_THREADS) void fwd_pack_kernel(const uint8_t* _
                                                                  int B, int S, int seg) {
     __shared__ int s_len[PACK_MAX_B];
     __shared__ uint16_t s_pos[PACK_MAX_TOKENS];      // [B][S] valid positions, ascending
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int NW = PACK_THREADS / 64;
+    __shared__ int s_first[NW][PACK_MAX_B];          // first segment of each sequence, a copy per wave
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // 1. compaction
-    for (int b = wave; b < B; b += NW) {
+    if (S <= 64) {
+        // PACK_U sequences at a time
+        for (int b0 = wave; b0 < B; b0 += NW * PACK_U) {
+            uint8_t m[PACK_U];
+#pragma unroll
+            for (int u = 0; u < PACK_U; ++u) {
+                const int b = b0 + u * NW;
+                m[u] = b < B && lane < S ? mask[b * S + lane] : (uint8_t)0;
+            }
+#pragma unroll
+            for (int u = 0; u < PACK_U; ++u) {
+                const int b = b0 + u * NW;
+                const unsigned long long bal = __ballot(m[u] != 0);
+                if (m[u] != 0) s_pos[b * S + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)lane;
+                if (lane == 0 && b < B) s_len[b] = __popcll(bal);
+            }
+        }
+    }
+    // PACK_U entries per lane of a sequence at a time
+    for (int b = S <= 64 ? B : wave; b < B; b += NW) {
         const uint8_t* mrow = mask + (size_t)b * S;
         uint16_t* prow = s_pos + b * S;
         int base = 0;
@@ -144,24 +163,37 @@ __global__ __launch_bounds__(PACK_THREADS) void fwd_pack_kernel(const uint8_t* _
         if (lane == 0) s_len[b] = base;
     }
     __syncthreads();
-    // 2. exclusive prefix sum of the block counts: lane b holds sequence b
-    static_assert(PACK_MAX_B <= 64, "one wave holds all sequences");
-    const int mine = lane < B ? max(1, (s_len[lane] + seg - 1) / seg) : 0;
-    int incl = mine;
+    // 2. exclusive prefix sum of the block counts: lane l holds sequences 2 l and 2 l + 1
+    constexpr int PER = PACK_MAX_B / 64;
+    int nb[PER], sum = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int b = lane * PER + j;
+        nb[j] = b < B ? max(1, (s_len[b] + seg - 1) / seg) : 0;
+        sum += nb[j];
+    }
+    int incl = sum;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const int up = __shfl_up(incl, off);
         incl += lane >= off ? up : 0;
     }
-    if (wave == 0 && lane < B) {
-        blk0[lane] = incl - mine;
-        if (lane == B - 1) blk0[B] = incl;
+    int run = incl - sum;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int b = lane * PER + j;
+        // every wave writes the same values, and reads its own
+        if (b < B) s_first[wave][b] = run;
+        if (wave == 0 && b < B) blk0[b] = run;
+        run += nb[j];
+        if (wave == 0 && b == B - 1) blk0[B] = run;
     }
+    __builtin_amdgcn_wave_barrier();                 // LDS operations of one wave execute in program order
     // 3. row table and block records
     for (int b = wave; b < B; b += NW) {
         const int n = s_len[b];
-        const int g0 = __shfl(incl - mine, b);
-        const int nblk = __shfl(mine, b);
+        const int g0 = s_first[wave][b];
+        const int nblk = max(1, (n + seg - 1) / seg);
         const uint16_t* prow = s_pos + b * S;
         for (int k = lane; k < nblk * seg; k += 64) {
             const int s = n > 0 ? (int)prow[k < n ? k : n - 1] : 0;

@@ -400,6 +400,11 @@ struct Prof {
 
 inline int launch_status() { return hipGetLastError() == hipSuccess ? LSR_OK : LSR_ERR_LAUNCH; }
 
+// (see fwd_pack_kernel)
+bool pack_in_one_launch(const Shape& s) {
+    return (long)s.B * s.S <= PACK_MAX_TOKENS && s.B <= (s.S <= 64 ? PACK_MAX_B : 64);
+}
+
 template <typename T, bool DMA, int SEG, bool RES>
 void launch_fwd_cfg(FwdParams p, int V, bool arg, int n_cus, hipStream_t st) {
     constexpr int TN = fwd_tn(FWD_NWN);
@@ -470,7 +475,7 @@ int forward_impl(const lsr_head_desc* desc, const void* H, const void* W, const 
 
     prof.begin(0);
     // batches of few tokens are packed by one workgroup in one launch
-    const bool one_launch = s.B <= PACK_MAX_B && (long)s.B * s.S <= PACK_MAX_TOKENS;
+    const bool one_launch = pack_in_one_launch(s);
     if (!one_launch) hipLaunchKernelGGL(fwd_prep_kernel, dim3(s.B), dim3(PREP_THREADS), 0, st, mask, len, pos, s.S);
     char* base = static_cast<char*>(ws);
     int* blk0 = reinterpret_cast<int*>(base + w.blk0_off);

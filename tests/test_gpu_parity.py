@@ -836,7 +836,7 @@ def test_bucket_sort_pieces(B, S, D, V, dy_keep):
     print(run_case(wl.make_custom(B, S, D, V, seed=B * 7 + S, len_lo=max(1, S // 2), dy_keep=dy_keep)))
 
 
-@pytest.mark.parametrize("B,S", [(64, 256), (1, 16384), (31, 513), (17, 512), (64, 2)])
+@pytest.mark.parametrize("B,S", [(64, 256), (1, 16384), (31, 513), (17, 512), (64, 2), (128, 64), (65, 33), (129, 5)])
 def test_packing_in_one_launch(B, S):
     """The most sequences and mask entries that one workgroup packs, and lengths around its eight entries per lane;
     a scattered mask with an empty first and last sequence."""
