@@ -158,7 +158,8 @@ __global__ __launch_bounds__(SORT_MAX_THREADS) void bwd_count_kernel(const float
 // Per b: cnt[b][seg][s] becomes the number of earlier-segment entries of bucket s, and
 // bstart[b][0..S] the exclusive prefix of the bucket sizes (bstart[b][S] = non-zero pairs of row b).
 // A thread owns one bucket of every NT: its loads and stores are coalesced, and the prefix over the buckets goes
-// NT at a time (B=2 S=16 4.5 -> 2.5 us, B=64 S=512 with 64 segments 15 -> 10).
+// NT at a time (B=2 S=16 4.5 -> 2.5 us, B=64 S=512 with 64 segments 15 -> 10).  Beside a dW kernel that fills the chip the launch waits
+// for room whatever NT is (B=32 S=8192: steps of 1024 and of 256 threads both 1.03 times the serial prefix).
 template <int NT>
 __global__ __launch_bounds__(NT) void bwd_scan_kernel(int* __restrict__ cnt, int* __restrict__ bstart,
                                                       int S, int n_seg) {
