@@ -89,8 +89,8 @@ int lsr_gather_probe(const void* table, size_t window_bytes, int steps, int laun
  *   [15] float32: segments of the packed token list per window of a chunk (a chunk holds the sequences that begin in
  *        its window); 0 for bfloat16, whose chunks are [0] tiles long
  *   [16] 1 if dW and db run on the library's auxiliary stream beside dH where all three are requested
- *   [17] 1 if the forward is the one launch for calls of few tokens, which has no chunks ([0], [9], [10], [11] and [15] are then
- *        those of the kernel that it stands in for)
+ *   [17] 1 if the forward is the one launch for calls of few tokens, which needs neither packing nor chunks: [0], [9], [10],
+ *        [11] and [15] then describe the packed forward, which is not launched (the workspace is sized for it all the same)
  */
 #define LSR_PLAN_SLOTS 14
 int lsr_head_plan(const lsr_head_desc* desc, int32_t* plan);

@@ -175,6 +175,7 @@ LSR_PLAN_FIELDS = ("fwd_tiles_per_chunk", "sort_segments", "sort_segment_len", "
                    "dh_chunks", "dh_chunk_len", "dh_buckets_per_wave", "dw_tile_rows", "dw_sequences_per_launch",
                    "fwd_chunks", "fwd_segment_rows", "fwd_resident_workgroups", "dh_slices_owned_by_xcd",
                    "dw_lds_tile_passes", "dh_waves_per_bucket", "fwd_window_segments", "dw_beside_dh")
+LSR_PLAN_EX_FIELDS = LSR_PLAN_FIELDS + ("fwd_few_tokens",)
 
 
 def lsr_head_plan(B, S, D, V, hw_dtype):
@@ -183,6 +184,14 @@ def lsr_head_plan(B, S, D, V, hw_dtype):
     out = (ctypes.c_int32 * len(LSR_PLAN_FIELDS))()
     _check(load_library().lsr_head_plan_ex(ctypes.byref(d), out, len(LSR_PLAN_FIELDS)))
     return dict(zip(LSR_PLAN_FIELDS, (int(x) for x in out)))
+
+
+def lsr_head_plan_ex(B, S, D, V, hw_dtype):
+    """Every value of the launch plan, among them whether the forward is the one launch for calls of few tokens."""
+    d = _desc(B, S, D, V, hw_dtype)
+    out = (ctypes.c_int32 * len(LSR_PLAN_EX_FIELDS))()
+    _check(load_library().lsr_head_plan_ex(ctypes.byref(d), out, len(LSR_PLAN_EX_FIELDS)))
+    return dict(zip(LSR_PLAN_EX_FIELDS, (int(x) for x in out)))
 
 
 def lsr_mfma_peak_probe(iters, launches, sink, stream=None):

@@ -179,3 +179,33 @@ def test_bfloat16_gradients_are_staged_only_where_several_launches_add_up():
         if p["dw_tile_rows"] > 0 and p["dw_sequences_per_launch"] < B and p["dw_lds_tile_passes"] == 0:
             want += 4 * V * D
         assert want <= extra <= want + 2 * 256, (B, S, D, V)
+
+
+def test_every_value_of_the_plan_has_a_name():
+    import os
+    import re
+    header = open(os.path.join(os.path.dirname(os.path.abspath(__file__)), "..", "include", "lsr_head_measure.h")).read()
+    assert len(binding.LSR_PLAN_EX_FIELDS) == int(re.search(r"#define LSR_PLAN_EX_SLOTS (\d+)", header).group(1))
+    for shape in ((64, 512, 1024, 250002), (1, 32, 768, 30522)):
+        p = lsr.lsr_head_plan_ex(*shape, lsr.LSR_BF16)
+        assert list(p)[:-1] == list(binding.LSR_PLAN_FIELDS)
+        assert {k: p[k] for k in binding.LSR_PLAN_FIELDS} == lsr.lsr_head_plan(*shape, lsr.LSR_BF16)
+
+
+def test_which_forwards_are_calls_of_few_tokens():
+    """Both sides of each line: 64 tokens, the hidden states (in 32-row blocks) and logits in 156 KiB of LDS, 16 sequences
+    up to 32768 vocabulary entries; 8 sequences, bfloat16 and rows of 512 from 131072 entries on; nothing between."""
+    bf, f32 = lsr.LSR_BF16, lsr.LSR_F32
+    lines = [
+        ((1, 64, 768, 30522, bf), (1, 65, 768, 30522, bf)), ((8, 8, 64, 1000, f32), (5, 13, 64, 1000, f32)),
+        ((1, 32, 2176, 30522, bf), (1, 32, 2184, 30522, bf)), ((1, 64, 896, 30522, bf), (1, 64, 904, 30522, bf)),
+        ((1, 32, 2176, 30522, bf), (1, 33, 2176, 30522, bf)), ((1, 32, 1088, 300, f32), (1, 32, 1096, 300, f32)),
+        ((2, 32, 448, 128, f32), (2, 32, 456, 128, f32)), ((2, 16, 512, 128, f32), (2, 32, 512, 128, f32)),
+        ((16, 4, 768, 30522, bf), (17, 3, 768, 30522, bf)), ((16, 1, 8, 1, f32), (17, 1, 8, 1, f32)),
+        ((1, 32, 768, 32768, bf), (1, 32, 768, 32769, bf)), ((1, 32, 768, 32768, f32), (1, 32, 768, 32769, f32)),
+        ((1, 32, 768, 131072, bf), (1, 32, 768, 131071, bf)), ((1, 32, 512, 250002, bf), (1, 32, 504, 250002, bf)),
+        ((8, 8, 512, 131100, bf), (9, 7, 512, 131100, bf)), ((1, 16, 512, 250002, bf), (1, 16, 512, 250002, f32)),
+    ]
+    for yes, no in lines:
+        assert lsr.lsr_head_plan_ex(*yes)["fwd_few_tokens"] == 1, yes
+        assert lsr.lsr_head_plan_ex(*no)["fwd_few_tokens"] == 0, no
