@@ -197,7 +197,7 @@ __global__ __launch_bounds__(NT) void bwd_scan_kernel(int* __restrict__ cnt, int
 // Lanes holding the same position find each other by ballots (same_key_lanes), so every bucket ends up sorted by v
 // and the later sums have a fixed order.  What bounds it are the ballots and dependent LDS accesses of each step, so steps must not
 // wait for one another (waves that took turns behind a barrier per 64 pairs: with LDS staging B=2 S=16 |V|=1000 8.4 ->
-// 5.0 us, B=13 S=197 |V|=31091 11.4 -> 8.0, B=256 S=512 |V|=30522 82 -> 72, B=64 S=512 |V|=250002 157 -> 165;
+// 5.0 us, B=13 S=197 |V|=31091 11.8 -> 8.8, B=256 S=512 |V|=30522 66 -> 53, B=64 S=512 |V|=250002 145 -> 119;
 // without, from one wave per workgroup, B=32 S=8192 |V|=30522 230 -> 65).
 constexpr int PLACE_WAVES = 4;
 
@@ -286,12 +286,16 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_kernel(const float
 // first sorts its whole segment by bucket in LDS and then writes it out in sorted order:
 // the pairs a bucket receives from this segment (about a dozen at C5) leave as one contiguous run.
 //   1. every wave loads its piece of the segment, keeps (g, bucket) in registers and counts per bucket;
-//   2. exclusive prefix over buckets and waves = first local slot of each (bucket, wave); s_delta = first global
+//   2. exclusive prefix over buckets and waves = first local slot of each (bucket, wave); delta = first global
 //      slot of the bucket - its first local slot;
 //   3. steps of 64 pairs per wave: ballot ranking, staging;
 //   4. local slot k goes to global slot k + s_delta[bucket of k].
-// A staged pair is (v - vbeg) | bucket << 12 and g.   dynamic LDS: (PLACE_WAVES + 1) * S ints + seg_len pairs.
-// STEPS: steps of 64 per wave, at least seg_len / (64 * PLACE_WAVES).
+// A staged pair is (v - vbeg) | bucket << 12 and g.   dynamic LDS: PLACE_WAVES / 2 * S ints + seg_len pairs.
+// STEPS: steps of 64 per wave, at least seg_len / (64 * PLACE_WAVES); steps behind the end of a piece are left out.
+// Counts and slots of two waves share an int (a segment has at most 4096), and the deltas take their place once all is
+// staged, because the LDS decides how many workgroups a CU holds.  Against an int per wave, deltas of their own and every
+// step taken: B=64 S=512 |V|=250002 158 -> 119 us, B=256 S=1024 |V|=33700 98 -> 72 and, with one gradient in twenty, 86 -> 53
+// (nine steps of 16), B=64 S=128 |V|=135000 59 -> 49; 56 -> 43, B=2 S=16 |V|=1000 7.4 -> 7.5 for the barrier more.
 // ---------------------------------------------------------------------------------------------
 constexpr int PLACE_MAX_S = 1024;
 constexpr int PLACE_MAX_SEG = 4096;
@@ -307,12 +311,14 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_staged_kernel(cons
     constexpr int NT = 64 * PLACE_WAVES;
     extern __shared__ __attribute__((aligned(16))) int s_place[];
     uint2* s_stage = reinterpret_cast<uint2*>(s_place);             // [seg_len]
-    int* s_next = s_place + 2 * seg_len;    // [PLACE_WAVES][S] counts, then the next free local slot of each bucket
-    int* s_delta = s_next + PLACE_WAVES * S;                        // [S] global slot - local slot
+    unsigned* s_cnt = reinterpret_cast<unsigned*>(s_place + 2 * seg_len);      // [PLACE_WAVES / 2][S]: counts of waves 2 i and 2 i + 1
+    int* s_delta = s_place + 2 * seg_len;                           // [S] global slot - local slot, in the same place at the end
     __shared__ int s_wave[PLACE_WAVES];
     const int seg = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    int* const s_mine = s_next + wave * S;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = wave & 1;
+    unsigned* const s_count = s_cnt + (wave >> 1) * S;
+    uint16_t* const s_next = reinterpret_cast<uint16_t*>(s_count) + half;      // next free local slot of bucket s at [2 s]
     const int* c0 = cnt + ((size_t)b * n_seg + seg) * S;
     const int* b0 = bstart + (size_t)b * (S + 1);
 
@@ -332,11 +338,11 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_staged_kernel(cons
         key[i] = ok ? clamp_pos(I[row + v], S) : 0;
         g[i] = gate_grad(dy, y);                // 0 for lanes past the end (dy = 0, y = 0)
     }
-    for (int s = tid; s < PLACE_WAVES * S; s += NT) s_next[s] = 0;
+    for (int s = tid; s < PLACE_WAVES / 2 * S; s += NT) s_cnt[s] = 0;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < STEPS; ++i)
-        if (g[i] != 0.f) atomicAdd(&s_mine[key[i]], 1);
+        if (g[i] != 0.f) atomicAdd(&s_count[key[i]], 1u << (16 * half));
     __syncthreads();
 
     // 2. slots
@@ -345,16 +351,25 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_staged_kernel(cons
     int sum = 0;
     for (int s = lo; s < hi; ++s)
 #pragma unroll
-        for (int w = 0; w < PLACE_WAVES; ++w) sum += s_next[w * S + s];
+        for (int w = 0; w < PLACE_WAVES / 2; ++w) {
+            const unsigned c = s_cnt[w * S + s];
+            sum += (int)((c & 0xffffu) + (c >> 16));
+        }
     int total;
     int run = exclusive_scan<PLACE_WAVES>(sum, s_wave, &total);
-    for (int s = lo; s < hi; ++s) {
-        s_delta[s] = b0[s] + c0[s] - run;
+    int delta[PLACE_MAX_S / NT];
 #pragma unroll
-        for (int w = 0; w < PLACE_WAVES; ++w) {
-            const int c = s_next[w * S + s];
-            s_next[w * S + s] = run;
-            run += c;
+    for (int u = 0; u < PLACE_MAX_S / NT; ++u) {
+        const int s = lo + u;
+        if (s < hi) {
+            delta[u] = b0[s] + c0[s] - run;
+#pragma unroll
+            for (int w = 0; w < PLACE_WAVES / 2; ++w) {
+                const unsigned c = s_cnt[w * S + s];
+                const int next = run + (int)(c & 0xffffu);
+                s_cnt[w * S + s] = (unsigned)run | (unsigned)next << 16;
+                run = next + (int)(c >> 16);
+            }
         }
     }
     __syncthreads();
@@ -362,20 +377,25 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_staged_kernel(cons
     // 3. rank and stage
 #pragma unroll
     for (int i = 0; i < STEPS; ++i) {
+        if (vbeg + i * 64 >= vend) continue;     // the same for the whole wave
         const bool active = g[i] != 0.f;
         const LaneGroup lg = same_key_lanes(key[i], active, key_bits);
         int slot = 0;
         if (active) {
-            slot = s_mine[key[i]] + lg.rank;
+            slot = s_next[2 * key[i]] + lg.rank;
             s_stage[slot] = make_uint2((unsigned)(vbeg - vseg + i * 64 + lane) | ((unsigned)key[i] << 12), __float_as_uint(g[i]));
         }
         __builtin_amdgcn_wave_barrier();         // LDS operations of one wave execute in program order
-        if (active && lg.rank == lg.size - 1) s_mine[key[i]] = slot + 1;
+        if (active && lg.rank == lg.size - 1) s_next[2 * key[i]] = (uint16_t)(slot + 1);
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
 
     // 4. sorted write-out
+#pragma unroll
+    for (int u = 0; u < PLACE_MAX_S / NT; ++u)
+        if (lo + u < hi) s_delta[lo + u] = delta[u];
+    __syncthreads();
     for (int k = tid; k < total; k += NT) {
         const uint2 e = s_stage[k];
         perm[row + k + s_delta[e.x >> 12]] = make_uint2((unsigned)vseg + (e.x & 4095u), e.y);

@@ -824,7 +824,7 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
         prof.begin(2);
         const dim3 place_block(64 * PLACE_WAVES);
         if (L.staged_place) {
-            const size_t lds = sizeof(int) * (PLACE_WAVES + 1) * s.S + sizeof(uint2) * w.seg_len;
+            const size_t lds = sizeof(int) * (PLACE_WAVES / 2) * s.S + sizeof(uint2) * w.seg_len;
 #define LSR_PLACE(STEPS) hipLaunchKernelGGL(bwd_place_staged_kernel<STEPS>, seg_grid, place_block, lds, st, dY, Y, I, cnt, bstart, perm, s.S, \
                                             s.V, w.n_seg, w.seg_len, w.key_bits)
             if (w.seg_len <= 4 * 64 * PLACE_WAVES) LSR_PLACE(4);

@@ -830,6 +830,8 @@ def test_mfma_probe_reports_a_plausible_rate():
     (2, 1025, 64, 9001, None),     # the first that do not
     (1, 8192, 64, 25000, 0.9),     # the longest of all: four tables of 8192 buckets
     (2, 40, 64, 16384 + 1, None),  # a last segment of few entries
+    (1024, 8, 64, 4340, None),     # segments of 17 steps: pieces of five steps and one of two
+    (600, 24, 64, 12600, 0.3),     # segments of 33 steps: three pieces of nine, one of six; sparse
 ])
 def test_bucket_sort_pieces(B, S, D, V, dy_keep):
     """Sizes at which the pieces that the waves of the bucket sort take, and its prefix sums, end."""
