@@ -194,7 +194,9 @@ def test_every_value_of_the_plan_has_a_name():
 
 def test_which_forwards_are_calls_of_few_tokens():
     """Both sides of each line: 64 tokens, the hidden states (in 32-row blocks) and logits in 156 KiB of LDS, 16 sequences
-    up to 32768 vocabulary entries; 8 sequences, bfloat16 and rows of 512 from 131072 entries on; nothing between."""
+    up to 32768 vocabulary entries; bfloat16 and rows of 512 from 131072 entries on, nothing between.  There the sequences are
+    few enough to hide behind the loads: two, or one in 256 columns of D >= 1024 (not in rows of 4 KiB), three or four in an
+    odd number of rounds of 32768 entries, eight where the tile kernel could not load directly to LDS."""
     bf, f32 = lsr.LSR_BF16, lsr.LSR_F32
     lines = [
         ((1, 64, 768, 30522, bf), (1, 65, 768, 30522, bf)), ((8, 8, 64, 1000, f32), (5, 13, 64, 1000, f32)),
@@ -204,7 +206,11 @@ def test_which_forwards_are_calls_of_few_tokens():
         ((16, 4, 768, 30522, bf), (17, 3, 768, 30522, bf)), ((16, 1, 8, 1, f32), (17, 1, 8, 1, f32)),
         ((1, 32, 768, 32768, bf), (1, 32, 768, 32769, bf)), ((1, 32, 768, 32768, f32), (1, 32, 768, 32769, f32)),
         ((1, 32, 768, 131072, bf), (1, 32, 768, 131071, bf)), ((1, 32, 512, 250002, bf), (1, 32, 504, 250002, bf)),
-        ((8, 8, 512, 131100, bf), (9, 7, 512, 131100, bf)), ((1, 16, 512, 250002, bf), (1, 16, 512, 250002, f32)),
+        ((1, 16, 512, 250002, bf), (1, 16, 512, 250002, f32)), ((8, 8, 520, 131100, bf), (9, 7, 520, 131100, bf)),
+        ((2, 32, 512, 131072, bf), (3, 20, 512, 131072, bf)), ((3, 20, 512, 131100, bf), (4, 16, 512, 131100, bf)),
+        ((4, 16, 768, 163840, bf), (4, 16, 768, 163841, bf)), ((4, 8, 1024, 131072, bf), (5, 6, 1024, 131072, bf)),
+        ((8, 4, 2176, 131072, bf), (8, 4, 1984, 131072, bf)), ((2, 16, 2048, 131072, bf), (3, 10, 2048, 131072, bf)),
+        ((8, 8, 520, 131072, bf), (8, 8, 512, 131072, bf)), ((5, 6, 1280, 250002, bf), (6, 5, 1280, 250002, bf)),
     ]
     for yes, no in lines:
         assert lsr.lsr_head_plan_ex(*yes)["fwd_few_tokens"] == 1, yes
