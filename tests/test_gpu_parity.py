@@ -1,4 +1,6 @@
 """Parity of the HIP path against the fp64 oracle, element by element, through the C ABI."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 import torch
@@ -51,11 +53,13 @@ def test_c1_tiny_fp32_forward_backward():
     (5, 100, 192, 513, 3),      # up to four blocks per sequence
     (3, 300, 256, 1000, 200),   # sequences that straddle tiles
     (2, 129, 200, 260, 1),      # K tail (D not a multiple of 64): register-staged loader
-    (4, 1, 64, 257, 1),         # S = 1: a plain linear layer
+    (4, 1, 64, 257, 1),         # S = 1: a plain linear layer; few tokens, one launch
+    (70, 1, 64, 257, 1),        # S = 1 through the packed forward
     (9, 700, 64, 96, 1),        # long sequences, single narrow vocabulary tile, one K slab
     (300, 20, 64, 520, 1),      # more sequences than the planning pass scans at once; several row groups
     (40, 260, 128, 300, 100),   # several row groups of several tiles each
-    (1, 8, 8, 1, 1),            # smallest legal D, one vocabulary entry
+    (1, 8, 8, 1, 1),            # smallest legal D, one vocabulary entry; few tokens
+    (17, 4, 8, 1, 1),           # the same through the packed forward
     (2, 16, 128, 70000, 1),     # vocabulary wide enough that the dH gather runs in three vocabulary chunks
     (48, 200, 64, 70000, 1),    # enough workgroups per CU that the row-group cuts are nudged to whole tiles
     (2, 1024, 64, 300, 900),    # longest sequences whose bucket sort still places through LDS
@@ -86,7 +90,8 @@ def test_large_batches_whole_row_dw_beside_sliced_dh(B, S, D, V):
     print(run_case(inp))
 
 
-@pytest.mark.parametrize("B,S,D,V", [(3, 20, 72, 333), (2, 70, 96, 300), (2, 9, 256, 260)])
+# up to 64 tokens: the one launch for few tokens; beyond: the packed forward, with 32-row segments at S = 70 and 8-row segments
+@pytest.mark.parametrize("B,S,D,V", [(3, 20, 72, 333), (2, 70, 96, 300), (2, 9, 256, 260), (4, 20, 72, 333), (8, 9, 256, 260)])
 def test_fp32_logits_are_the_fma_chain_in_ascending_d(B, S, D, V):
     """Near-ties of float32 logits fall as they do for a scalar loop of FMAs: the arg-max is that loop's.  The chain is
     formed in float64 (the product is exact there) and rounded to float32 after every term; the sum is rounded twice,
@@ -188,8 +193,10 @@ def test_fp32_small_shapes():
 
 
 @pytest.mark.parametrize("B,S,D,V,len_lo", [
-    (1, 1, 8, 1, 1),           # smallest legal shape; register-staged loader, one short slab
-    (2, 16, 32, 257, 1),       # one slab of 32 through the direct loader
+    (1, 1, 8, 1, 1),           # smallest legal shape; few tokens, one launch
+    (2, 16, 32, 257, 1),       # few tokens, rows of 128 bytes
+    (17, 4, 8, 1, 1),          # register-staged loader, one short slab
+    (5, 16, 32, 257, 1),       # one slab of 32 through the direct loader
     (5, 64, 96, 300, 1),       # odd slab count, short segments
     (70, 33, 64, 600, 1),      # more than 64 sequences: the search for a chunk's first sequence takes two rounds
     (3, 300, 128, 700, 200),   # sequences longer than a tile
@@ -218,15 +225,21 @@ def test_fp32_matrix_core_forward(B, S, D, V, len_lo):
     (1, 64, 768, 32769, "bf16"),   # one entry more: the tile kernel
     (16, 4, 72, 129, "bf16"),      # odd number of 16-byte chunks; a ragged second workgroup; the most sequences
     (3, 11, 264, 640, "bf16"),     # 33 tokens: the second row block holds one; one k-step behind a batch of loads
-    (2, 32, 512, 128, "f32"),      # four batches of loads, one workgroup
+    (2, 32, 512, 128, "f32"),      # hidden states beyond the LDS: the tile kernel
+    (2, 16, 512, 128, "f32"),      # four batches of loads, one workgroup
+    (1, 32, 1088, 300, "f32"),     # the longest float32 rows: eight batches and a half
+    (1, 64, 448, 260, "f32"),      # two row blocks and three batches and a half
     (5, 7, 20 * 8, 200, "f32"),
-    (8, 8, 512, 131100, "bf16"),   # workgroups that walk several tiles of the vocabulary, the last one ragged
+    (8, 8, 512, 131100, "bf16"),   # wide vocabulary, too many sequences for rows of 512: the tile kernel
+    (8, 8, 520, 131100, "bf16"),   # workgroups that walk several tiles of the vocabulary, the last one ragged
     (1, 9, 1032, 131072, "bf16"),
 ])
 def test_calls_of_few_tokens(B, S, D, V, dtype):
     """The one-launch forward.  Products are exact in float32, so a logit is within D * 2^-24 of the sum of the
     magnitudes, and Y moves by no more than the logit does.  Scattered masks, an empty sequence, and the same result
     without the index."""
+    plan = lsr.lsr_head_plan_ex(B, S, D, V, lsr.LSR_F32 if dtype == "f32" else lsr.LSR_BF16)
+    assert plan["fwd_few_tokens"] == ((B, S, D, V) not in ((1, 64, 768, 32769), (2, 32, 512, 128), (8, 8, 512, 131100)))
     inp = wl.make_custom(B, S, D, V, dtype=dtype, seed=B * 100 + S, w_std=0.05, backward=False)
     rng = np.random.default_rng(D)
     m2 = wl.scattered_mask(rng, B, S)
@@ -248,8 +261,87 @@ def test_calls_of_few_tokens(B, S, D, V, dtype):
         assert np.abs(ys[0] - Y_ref).max() <= (D + 4) * 2.0 ** -24 * (size + np.abs(Y_ref).max())
 
 
+def forward_of(inp, mask, H):
+    head = DeviceHead(inp, mask=mask)
+    head.H.copy_(H)
+    head.poison_outputs()
+    head.forward()
+    return head.Y, head.I
+
+
+@pytest.mark.parametrize("B,S,D,V,dtype", [
+    (1, 1, 8, 1, "bf16"),
+    (1, 32, 768, 1000, "bf16"),
+    (1, 64, 896, 300, "bf16"),
+    (16, 4, 72, 129, "bf16"),      # odd number of 16-byte chunks
+    (3, 11, 264, 640, "bf16"),
+    (4, 16, 768, 131100, "bf16"),  # workgroups that walk the vocabulary
+    (8, 8, 520, 131100, "bf16"),   # ... with an odd number of chunks
+    (1, 8, 512, 131100, "bf16"),
+    (1, 1, 8, 1, "f32"),
+    (5, 7, 160, 333, "f32"),
+    (2, 16, 512, 300, "f32"),
+    (1, 64, 448, 260, "f32"),
+    (1, 32, 1088, 200, "f32"),
+])
+def test_calls_of_few_tokens_give_the_bits_of_the_packed_forward(B, S, D, V, dtype):
+    """The same tokens as they are, and behind them masked positions up to more than 64 tokens.  Masked positions hold NaN in
+    the first call and infinities in the second.  All tokens; scattered ones, with an empty sequence; tokens with
+    infinite and with NaN hidden states among them, or an infinite one alone (all logits -inf where its weight is
+    positive); none."""
+    dt, td = (lsr.LSR_F32, torch.float32) if dtype == "f32" else (lsr.LSR_BF16, torch.bfloat16)
+    S2 = 64 // B + 1
+    assert lsr.lsr_head_plan_ex(B, S, D, V, dt)["fwd_few_tokens"] == 1
+    assert lsr.lsr_head_plan_ex(B, S2, D, V, dt)["fwd_few_tokens"] == 0
+    inp = wl.make_custom(B, S, D, V, dtype=dtype, seed=D + S, w_std=0.05, backward=False)
+    wide = wl.make_custom(B, S2, D, 1, dtype=dtype, backward=False)      # only the shape counts
+    wide = replace(wide, workload=replace(wide.workload, V=V), W=inp.W, bias=inp.bias, W_bits=inp.W_bits)
+    rng = np.random.default_rng(V)
+    some = wl.scattered_mask(rng, B, S)
+    some[B - 1] = 0 if B > 1 else some[B - 1]
+    H0 = torch.from_numpy(inp.H).to(td).cuda()
+    H1 = H0.clone()
+    H1[:, 0, 3] = float("inf")
+    H1[:, S // 2, 5] = float("-inf")
+    H1[:, S - 1, 1] = float("nan")
+    full, none = np.ones((B, S), np.uint8), np.zeros((B, S), np.uint8)
+    alone = none.copy()
+    alone[:, S // 2] = 1
+    for mask, H in ((full, H0), (some, H0), (full, H1), (some, H1), (alone, H1), (none, H0)):
+        valid = torch.from_numpy(mask).bool().cuda()[:, :, None]
+        Y, I = forward_of(inp, mask, torch.where(valid, H, float("nan")))
+        mask2 = np.zeros((B, S2), np.uint8)
+        mask2[:, :S] = mask
+        Hw = torch.full((B, S2, D), float("inf"), device="cuda", dtype=td)
+        Hw[:, :S] = torch.where(valid, H, float("inf"))
+        Yw, Iw = forward_of(wide, mask2, Hw)
+        torch.cuda.synchronize()
+        assert torch.equal(Y, Yw) and torch.equal(I, Iw)
+        if not mask.any():
+            assert not bool(Y.any()) and not bool(I.any())
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("B,S,D,V", [(5, 24, 64, 300), (3, 100, 72, 300), (2, 300, 64, 520)])      # 8-row segments, 32-row segments, several tiles
+def test_exact_ties_in_calls_of_few_tokens(dtype):
+    """Each half of a sequence has lanes of its own: equal maxima across the halves and within either."""
+    inp = wl.make_custom(3, 20, 64, 500, dtype=dtype, seed=14, len_lo=20)
+    for arr in (inp.H,) if dtype == "f32" else (inp.H, inp.H_bits):
+        arr[0, 17] = arr[0, 12] = arr[0, 2]      # first half, second half
+        arr[1, 9] = arr[1, 0]                    # both in the first half
+        arr[2, 19] = arr[2, 11]                  # both in the second half
+    assert lsr.lsr_head_plan_ex(3, 20, 64, 500, lsr.LSR_F32 if dtype == "f32" else lsr.LSR_BF16)["fwd_few_tokens"] == 1
+    head = DeviceHead(inp)
+    head.forward()
+    torch.cuda.synchronize()
+    I = head.I.cpu().numpy()
+    assert np.any(I[0] == 2) and np.any(I[1] == 0) and np.any(I[2] == 11)
+    assert not np.any((I[0] == 17) | (I[0] == 12)) and not np.any(I[1] == 9) and not np.any(I[2] == 19)
+    parity.compare_forward(inp, head.Y.cpu().numpy(), I)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+# 8-row segments, 32-row segments, several tiles; few tokens, whose sequences have lanes for each half
+@pytest.mark.parametrize("B,S,D,V", [(5, 24, 64, 300), (3, 100, 72, 300), (2, 300, 64, 520), (4, 16, 64, 300), (1, 64, 72, 300)])
 def test_nan_tokens_are_never_selected(B, S, D, V, dtype):
     """A token whose hidden state holds a NaN has NaN logits; the maximum and its position are those of the other tokens.
     The patterns leave one half-wave of a segment (rows 0..3 of every eight, or 4..7), whole segments, whole tiles or
