@@ -158,8 +158,10 @@ __global__ __launch_bounds__(SORT_MAX_THREADS) void bwd_count_kernel(const float
 // Per b: cnt[b][seg][s] becomes the number of earlier-segment entries of bucket s, and
 // bstart[b][0..S] the exclusive prefix of the bucket sizes (bstart[b][S] = non-zero pairs of row b).
 // A thread owns one bucket of every NT: its loads and stores are coalesced, and the prefix over the buckets goes
-// NT at a time (B=2 S=16 4.5 -> 2.5 us, B=64 S=512 with 64 segments 15 -> 10).  Beside a dW kernel that fills the chip the launch waits
-// for room whatever NT is (B=32 S=8192: steps of 1024 and of 256 threads both 1.03 times the serial prefix).
+// NT at a time (B=2 S=16 4.5 -> 2.5 us, B=64 S=512 with 64 segments 15 -> 10; 1024 threads against 256: B=16 S=600 13.6 and 25, B=32
+// S=8192 14.8 and 29, B=256 S=512 7.2 and 8.4).  Beside a dW kernel that fills the chip the launch waits for room whatever NT is:
+// at B=32 S=8192 it takes 242 us there and ends when dW does, where the serial prefix took 122 behind a count that had waited 137
+// (count, scan and placement together 489 before, 316 now).
 template <int NT>
 __global__ __launch_bounds__(NT) void bwd_scan_kernel(int* __restrict__ cnt, int* __restrict__ bstart,
                                                       int S, int n_seg) {
@@ -198,7 +200,13 @@ __global__ __launch_bounds__(NT) void bwd_scan_kernel(int* __restrict__ cnt, int
 // and the later sums have a fixed order.  What bounds it are the ballots and dependent LDS accesses of each step, so steps must not
 // wait for one another (waves that took turns behind a barrier per 64 pairs: with LDS staging B=2 S=16 |V|=1000 8.4 ->
 // 5.0 us, B=13 S=197 |V|=31091 11.8 -> 8.8, B=256 S=512 |V|=30522 66 -> 53, B=64 S=512 |V|=250002 145 -> 119;
-// without, from one wave per workgroup, B=32 S=8192 |V|=30522 230 -> 65).
+// without, from one wave per workgroup, B=32 S=8192 |V|=30522 221 -> 62, B=64 S=8192 |V|=250002 598 -> 474, but with one gradient
+// in twenty 418 -> 437, B=64 S=4096 218 -> 241, where the count and the scan in front gain more).
+// Beside dW a shorter sort lets the two gathers run together for longer, and some shapes pay for that.  Whole backward, 196 shapes
+// of S > 1024: geometric mean 0.86, 13 above 1.02, the worst B=100 S=1025 D=128 |V|=26630 with one in twenty 105 -> 119 and B=200
+// S=3000 D=768 |V|=15000 612 -> 671; 193 shapes of 128 <= S <= 512: 0.99, 12 above 1.02, the worst B=200 S=128 D=768
+// |V|=26630 815 -> 875.  Fewer waves per segment leave that as it is (one 0.97, 21; two 0.89, 17), a dW that starts behind the scan or
+// behind the placement makes it worse (0.86, 38 and 0.90, 61; 128 <= S <= 512 1.05, 119 and 1.09, 134).
 constexpr int PLACE_WAVES = 4;
 
 // Long sequences: every pair is stored straight to its bucket.   dynamic LDS: PLACE_WAVES * S ints

@@ -16,7 +16,7 @@ namespace lsr {
 // The hidden states of the valid tokens (at most FEW_MAX_TOKENS) lie in LDS, compacted, in rows padded so that
 // fragment reads are free of bank conflicts; rows behind the last valid token are never filled and their products
 // never looked at.  Every logit is the same sequence of MFMAs as in the tile kernel, so the results are the same
-// bits.  The logits then go through an area of LDS that the wave has to itself to one pair of lanes per (sequence,
+// bits, which the tests hold it to.  The logits then go through an area of LDS that the wave has to itself to one pair of lanes per (sequence,
 // column), half a sequence each.  Workgroups stay and walk the vocabulary, FEW_COLS entries at a time, without a barrier.
 constexpr int FEW_THREADS = 256;
 constexpr int FEW_COLS = 32 * FEW_THREADS / 64;      // vocabulary entries per workgroup

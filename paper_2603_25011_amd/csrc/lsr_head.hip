@@ -77,7 +77,8 @@ bool fwd_direct(const Shape& s) {
 
 // Calls of few tokens go through one launch of their own (fwd_few_kernel), where the hidden states fit the LDS.  Forward, us,
 // packing and tile kernel -> one launch, all tokens valid (D=768 |V|=30522 bfloat16 where not said):
-//   one round of workgroups (|V| <= 32768 on 256 CUs), up to 16 sequences: B=1 S=32 22.1 -> 13.4, S=64 21.9 -> 17.3, D=2048 38.5 ->
+// The rule counts 256 CUs, as the others here do (a smaller partition of the device takes more rounds, with the same results).
+//   one round of workgroups (|V| <= 32768), up to 16 sequences: B=1 S=32 22.1 -> 13.4, S=64 21.9 -> 17.3, D=2048 38.5 ->
 //     28.1, B=8 S=8 24.6 -> 21.7, B=16 S=4 29.4 -> 25.3, B=1 S=16 D=384 14.1 -> 7.8, B=2 S=16 D=64 |V|=1000 11.3 -> 5.8; float32 B=1
 //     S=32 38.6 -> 30.6, B=8 S=8 D=384 |V|=20000 39.4 -> 30.2, B=2 S=16 D=64 |V|=1000 13.9 -> 6.9
 //   many rounds with long rows, which keep the loads of W going beside the sums: B=1 S=32 |V|=250002 97 -> 83, D=1024 115 -> 98,

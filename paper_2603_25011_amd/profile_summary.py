@@ -71,7 +71,7 @@ def mean(v):
 
 
 FWD_KERNELS = ("lsr::fwd_prep_kernel", "lsr::fwd_plan_kernel", "lsr::fwd_rows_kernel", "lsr::fwd_pack_kernel",
-               "lsr::fwd_mfma_kernel", "lsr::fwd_merge_kernel")
+               "lsr::fwd_few_kernel", "lsr::fwd_mfma_kernel", "lsr::fwd_merge_kernel")
 BWD_KERNELS = ("lsr::bwd_count_kernel", "lsr::bwd_scan_kernel", "lsr::bwd_place_staged_kernel", "lsr::bwd_place_kernel",
                "lsr::bwd_chunk_bounds_kernel", "lsr::bwd_dh_sliced_kernel", "lsr::bwd_dw_sliced_kernel",
                "lsr::bwd_dw_tile_kernel", "lsr::bwd_dh_kernel", "lsr::bwd_dw_kernel")
