@@ -82,13 +82,17 @@ bool fwd_direct(const Shape& s) {
 //     28.1, B=8 S=8 24.6 -> 21.7, B=16 S=4 29.4 -> 25.3, B=1 S=16 D=384 14.1 -> 7.8, B=2 S=16 D=64 |V|=1000 11.3 -> 5.8; float32 B=1
 //     S=32 38.6 -> 30.6, B=8 S=8 D=384 |V|=20000 39.4 -> 30.2, B=2 S=16 D=64 |V|=1000 13.9 -> 6.9
 //   many rounds with long rows, which keep the loads of W going beside the sums: B=1 S=32 |V|=250002 97 -> 83, D=1024 115 -> 98,
-//     |V|=160000 56 -> 44, B=1 S=16 D=512 |V|=250002 57.6 -> 47.4.  The sums grow with the sequences and the loads with the
-//     columns, so what hides behind the loads is two sequences (B=2 S=16 D=512 |V|=250002 59.5 -> 53.5) and, from D=1024 on, one
-//     in 256 columns (B=4 S=8 D=1024 |V|=250002 119 -> 112).  Not more (B=8 S=8 D=512 |V|=131072 40 -> 47, B=4 S=8 D=896 49 -> 53,
-//     B=8 S=4 D=1024 60 -> 63), but for three or four where the tile kernel's last round is at most half full (an odd number
-//     of rounds of 32768 entries: B=3 S=10 D=512 |V|=425000 118 -> 112, B=4 S=8 D=896 |V|=360000 163 -> 155).  Rows of 4 KiB, which
-//     share their memory channels, take two (B=3 S=10 D=2048 |V|=250002 203 -> 211, B=8 S=4 |V|=301233 264 -> 288).  Where the
-//     tile kernel loads through registers up to eight gain (B=8 S=8 D=568 |V|=702271 302 -> 263)
+//     |V|=160000 56 -> 44, B=1 S=16 D=512 |V|=250002 57.6 -> 47.4.  The sums grow with the sequences (and a little with the
+//     tokens) and the loads with the columns, so what hides behind the loads is a number of sequences.
+//     Odd numbers of rounds of 32768 entries, where the tile kernel's last round is at most half full: 4 (5 with up to 32 tokens),
+//     from D=768 on 6 (8), from D=1024 on 8: B=4 S=16 D=512 |V|=270000 80 -> 70, B=6 S=10 D=768 |V|=425000 179 -> 167, B=8 S=4
+//     D=1024 |V|=220000 126 -> 114; not B=8 S=8 D=512 |V|=147456 52 -> 56
+//     Even numbers: one more than a row has whole batches of FEW_U k-steps, two more with up to 32 tokens from D=768 on, 8 from
+//     D=1280 on: B=3 S=10 D=512 |V|=250002 62.7 -> 60.8, B=4 S=16 D=768 102 -> 92, B=5 S=6 D=1024 123 -> 115; not B=8 S=8 D=512
+//     |V|=131072 40 -> 47.  Rows that end in a part of a batch: 2, and 3, 6, 7, 8 from D=768, 1024, 1280, 1600 on: B=2 S=16 D=640
+//     |V|=250002 84 -> 77; not B=4 S=8 D=896 |V|=131072 49 -> 53.  Rows of 4 KiB, which share their memory channels: 2; not B=8 S=4
+//     D=2048 |V|=301233 264 -> 288
+//     Where the tile kernel loads through registers: 8 (B=8 S=8 D=568 |V|=702271 302 -> 263)
 //   not: two or three rounds (B=4 S=16 |V|=40000 24.6 -> 27.6, B=1 S=32 |V|=60000 25.1 -> 26.1, |V|=119547 40.2 -> 40.2), many rounds of
 //     short rows (B=1 S=64 D=384 |V|=119547 29.5 -> 33.5, B=8 S=8 D=128 |V|=250002 43 -> 58) or in float32 (B=1 S=16 D=512 |V|=250002
 //     121 -> 134), more sequences (the lanes of a column take them one after the other: B=64 S=1 45.6 -> 51.1)
@@ -98,9 +102,13 @@ bool fwd_few(const Shape& s) {
     constexpr int round = 256 * FEW_COLS;                // vocabulary entries that 256 CUs take at a time
     if (s.V <= round) return s.B <= 16;
     if (s.dtype != LSR_BF16 || s.V < 4 * round || s.D < 512 || s.B > 8) return false;
-    const bool odd_rounds = (s.V + round - 1) / round % 2 != 0;
-    const int hidden = odd_rounds ? (s.D >= 768 ? 4 : 3) : 2;
-    return !fwd_direct(s) || s.B <= hidden || (s.D >= 1024 && s.D % 2048 != 0 && 256 * s.B <= s.D);
+    if (!fwd_direct(s)) return true;
+    const bool small = tokens <= 32;
+    if ((s.V + round - 1) / round % 2 != 0) return s.B <= (s.D >= 1024 ? 8 : (s.D >= 768 ? (small ? 8 : 6) : (small ? 5 : 4)));
+    constexpr int batch = 16 * FEW_U;                    // columns of a batch of loads
+    if (s.D % 2048 == 0) return s.B <= 2;
+    if (s.D % batch == 0) return s.B <= (s.D >= 1280 ? 8 : s.D / batch + 1 + (small && s.D >= 768 ? 1 : 0));
+    return s.B <= (s.D >= 1600 ? 8 : s.D >= 1280 ? 7 : s.D >= 1024 ? 6 : s.D >= 768 ? 3 : 2);
 }
 
 // tpc: most tiles per chunk; window: float32 only, segments per window of a chunk (chunks are whole sequences, see

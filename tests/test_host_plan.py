@@ -195,8 +195,10 @@ def test_every_value_of_the_plan_has_a_name():
 def test_which_forwards_are_calls_of_few_tokens():
     """Both sides of each line: 64 tokens, the hidden states (in 32-row blocks) and logits in 156 KiB of LDS, 16 sequences
     up to 32768 vocabulary entries; bfloat16 and rows of 512 from 131072 entries on, nothing between.  There the sequences are
-    few enough to hide behind the loads: two, or one in 256 columns of D >= 1024 (not in rows of 4 KiB), three or four in an
-    odd number of rounds of 32768 entries, eight where the tile kernel could not load directly to LDS."""
+    few enough to hide behind the loads.  Odd numbers of rounds of 32768 entries: four (five with at most 32 tokens), from
+    D = 768 on six (eight), from D = 1024 on eight.  Even numbers: one more than the row has batches of 256 columns (from D = 768 on
+    two more with at most 32 tokens), eight from D = 1280 on; with a part of a batch two, and three, six, seven and eight from
+    D = 768, 1024, 1280 and 1600 on; two in rows of 4 KiB.  Eight where the tile kernel could not load directly to LDS."""
     bf, f32 = lsr.LSR_BF16, lsr.LSR_F32
     lines = [
         ((1, 64, 768, 30522, bf), (1, 65, 768, 30522, bf)), ((8, 8, 64, 1000, f32), (5, 13, 64, 1000, f32)),
@@ -207,10 +209,17 @@ def test_which_forwards_are_calls_of_few_tokens():
         ((1, 32, 768, 32768, bf), (1, 32, 768, 32769, bf)), ((1, 32, 768, 32768, f32), (1, 32, 768, 32769, f32)),
         ((1, 32, 768, 131072, bf), (1, 32, 768, 131071, bf)), ((1, 32, 512, 250002, bf), (1, 32, 504, 250002, bf)),
         ((1, 16, 512, 250002, bf), (1, 16, 512, 250002, f32)), ((8, 8, 520, 131100, bf), (9, 7, 520, 131100, bf)),
-        ((2, 32, 512, 131072, bf), (3, 20, 512, 131072, bf)), ((3, 20, 512, 131100, bf), (4, 16, 512, 131100, bf)),
-        ((4, 16, 768, 163840, bf), (4, 16, 768, 163841, bf)), ((4, 8, 1024, 131072, bf), (5, 6, 1024, 131072, bf)),
-        ((8, 4, 2176, 131072, bf), (8, 4, 1984, 131072, bf)), ((2, 16, 2048, 131072, bf), (3, 10, 2048, 131072, bf)),
-        ((8, 8, 520, 131072, bf), (8, 8, 512, 131072, bf)), ((5, 6, 1280, 250002, bf), (6, 5, 1280, 250002, bf)),
+        ((3, 20, 512, 131072, bf), (4, 16, 512, 131072, bf)), ((4, 16, 768, 131072, bf), (5, 12, 768, 131072, bf)),
+        ((6, 5, 1024, 250002, bf), (7, 4, 1024, 250002, bf)), ((2, 32, 640, 131072, bf), (3, 20, 640, 131072, bf)),
+        ((5, 6, 768, 131072, bf), (5, 7, 768, 131072, bf)), ((3, 10, 512, 131072, bf), (4, 8, 512, 131072, bf)),
+        ((8, 4, 1280, 131072, bf), (8, 4, 1344, 131072, bf)), ((8, 4, 1600, 131072, bf), (8, 4, 1472, 131072, bf)),
+        ((7, 4, 1344, 131072, bf), (7, 4, 1216, 131072, bf)), ((6, 5, 1088, 131072, bf), (6, 5, 960, 131072, bf)),
+        ((3, 20, 832, 131072, bf), (3, 20, 704, 131072, bf)),
+        ((2, 16, 2048, 131072, bf), (3, 10, 2048, 131072, bf)), ((4, 16, 640, 131100, bf), (5, 12, 640, 131100, bf)),
+        ((5, 6, 640, 131100, bf), (6, 5, 640, 131100, bf)), ((6, 10, 768, 163840, bf), (7, 9, 768, 163840, bf)),
+        ((8, 4, 768, 163840, bf), (8, 5, 768, 163840, bf)), ((8, 4, 1024, 131073, bf), (8, 4, 1024, 163841, bf)),
+        ((6, 10, 896, 131073, bf), (6, 10, 896, 131072, bf)),
+        ((8, 4, 2048, 131073, bf), (8, 4, 2048, 131072, bf)), ((8, 8, 520, 131072, bf), (8, 8, 512, 131072, bf)),
     ]
     for yes, no in lines:
         assert lsr.lsr_head_plan_ex(*yes)["fwd_few_tokens"] == 1, yes
