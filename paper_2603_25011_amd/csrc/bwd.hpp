@@ -74,6 +74,38 @@ template <> struct OutVec<uint16_t> {
                                                   f32_to_bf16_bits(x.z) | (f32_to_bf16_bits(x.w) << 16));
     }
 };
+// 1, 2, 4 or 8 consecutive elements
+template <int K> __device__ __forceinline__ void load_n(const float* p, float (&x)[K]) {
+    if constexpr (K == 1) x[0] = *p;
+    else if constexpr (K == 2) { const float2 t = *reinterpret_cast<const float2*>(p); x[0] = t.x; x[1] = t.y; }
+    else
+#pragma unroll
+        for (int i = 0; i < K; i += 4) { const float4 t = *reinterpret_cast<const float4*>(p + i); x[i] = t.x; x[i + 1] = t.y; x[i + 2] = t.z; x[i + 3] = t.w; }
+}
+template <int K> __device__ __forceinline__ void load_n(const uint16_t* p, float (&x)[K]) {
+    static_assert(K % 2 == 0, "pairs");
+    if constexpr (K == 2) {
+        const uint32_t t = *reinterpret_cast<const uint32_t*>(p);
+        x[0] = __uint_as_float(t << 16);
+        x[1] = __uint_as_float(t & 0xffff0000u);
+    } else
+#pragma unroll
+        for (int i = 0; i < K; i += 4) { const float4 t = OutVec<uint16_t>::load4(p + i); x[i] = t.x; x[i + 1] = t.y; x[i + 2] = t.z; x[i + 3] = t.w; }
+}
+template <int K, int M> __device__ __forceinline__ void store_n(float* p, const float (&x)[M]) {
+    if constexpr (K == 1) *p = x[0];
+    else if constexpr (K == 2) *reinterpret_cast<float2*>(p) = make_float2(x[0], x[1]);
+    else
+#pragma unroll
+        for (int i = 0; i < K; i += 4) OutVec<float>::store4(p + i, make_float4(x[i], x[i + 1], x[i + 2], x[i + 3]));
+}
+template <int K, int M> __device__ __forceinline__ void store_n(uint16_t* p, const float (&x)[M]) {
+    static_assert(K % 2 == 0, "pairs");
+    if constexpr (K == 2) *reinterpret_cast<uint32_t*>(p) = f32_to_bf16_bits(x[0]) | (f32_to_bf16_bits(x[1]) << 16);
+    else
+#pragma unroll
+        for (int i = 0; i < K; i += 4) OutVec<uint16_t>::store4(p + i, make_float4(x[i], x[i + 1], x[i + 2], x[i + 3]));
+}
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 
 // ---------------------------------------------------------------------------------------------
@@ -851,6 +883,21 @@ __global__ __launch_bounds__(256) void bwd_chunk_bounds_kernel(const int* __rest
     bounds[idx] = lo;
 }
 
+// x of the lane 8 places away in the row of 16, added to the lane's own (DPP: no LDS crossbar)
+__device__ __forceinline__ float add_half_row(float x) {
+    return x + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, true));      // row_ror:8
+}
+// Sums over two neighbouring rows of 16 lanes (two halves of the wave) of a and b: the even rows (lower half) keep a's, the
+// odd rows (upper half) b's.
+__device__ __forceinline__ float fold_rows(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float fold_halves(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 template <typename T, int BPW, int WPB, typename OT, bool OFF32>
 __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu(8, 8))) void bwd_dh_sliced_kernel(const T* __restrict__ W,
                                                             const int* __restrict__ bounds,
@@ -865,9 +912,11 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
     static_assert(EPG >= 1, "a bucket needs at least one row piece worth of lanes");
     constexpr int NLD = DH_NLD;                // gathers in flight per lane (8: more registers, fewer
                                                // waves; C5 2.83 -> 3.71 ms)
-    static_assert(2 * G <= PERM_SLACK, "entries read behind the end of a list stay inside the slack");
+    static_assert(G <= PERM_SLACK, "entries read behind the end of a list stay inside the slack");
     static_assert(WPB == 1 || BPW == 1, "either several buckets per wave or several waves per bucket");
     constexpr int BLK = G * WPB;               // entries between a wave's consecutive blocks
+    constexpr int E = WPB > 1 ? 1 : 4;         // blocks of entries requested at a time
+    constexpr int NV = N >> ((G >= 32) + (G >= 64));      // columns of a sum that a lane ends up with
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     int dc, g;
@@ -886,6 +935,19 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
     // some engines with twice the work of others.
     const int sg = xcd_own ? g / B : (int)blockIdx.y;
     const int b = xcd_own ? g - sg * B : (int)blockIdx.x;
+    const int col0 = dc * DWS_COLS + (lane % LPR) * N;
+    const bool col_ok = col0 < D;              // the last slice may be partly filled: the lanes behind D gather column 0
+    const int li = lane % G;                   // lane within its bucket
+    const int sub = li / LPR;
+    // the columns this lane writes (see the folds at the end): NV of its N
+    const int vcol = (G >= 32 && (lane & 16) ? N / 2 : 0) + (G >= 64 && (lane & 32) ? NV : 0);
+    const bool w_lane = col_ok && (LPR == 8 && G >= 16 ? (lane & 8) == 0 : true) && (WPB == 1 || wave == 0);
+    const char* const Wb = reinterpret_cast<const char*>(W);
+    const uint2* const pl = perm + (size_t)b * V;                   // b: the same for the whole workgroup
+    const uint32_t row_bytes = (uint32_t)D * (uint32_t)sizeof(T);
+    const uint32_t col_bytes = (uint32_t)(col_ok ? col0 : 0) * (uint32_t)sizeof(T);
+    const int src0 = (lane - li + sub) * 4;    // bpermute address of the lane holding entry `sub` of the block
+
     const int s = WPB > 1 ? sg : (sg * 4 + wave) * BPW + lane / G;
     const bool live = s < S;
     const int bq = live ? b * S + s : 0;
@@ -897,113 +959,128 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
     // waits at the barrier below (all waves of the workgroup see the same list).
     const bool alone = WPB > 1 && end - beg <= G;
     if (alone && wave > 0) return;
-    const int col0 = dc * DWS_COLS + (lane % LPR) * N;
-    const bool col_ok = col0 < D;              // the last slice may be partly filled: the lanes behind D gather column 0
-    const int sub = (lane % G) / LPR;
-    const bool writer = live && col_ok && sub == 0 && (write_all || beg < end) && (WPB == 1 || wave == 0);
-    const size_t o = (size_t)bq * D + col0;
+    const bool writer = w_lane && live && (write_all || beg < end);
+    const size_t o = (size_t)bq * D + col0 + vcol;
     float acc[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) acc[i] = 0.f;
-    float4 prev[N / 4];                        // the sum of the earlier chunks, requested early
+    float prev[NV];                            // the sum of the earlier chunks, requested early
 #pragma unroll
-    for (int i = 0; i < N / 4; ++i) prev[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = 0; i < NV; ++i) prev[i] = 0.f;
     if (writer) {
-        if (prev_sum) {
-#pragma unroll
-            for (int i = 0; i < N / 4; ++i) prev[i] = *reinterpret_cast<const float4*>(prev_sum + o + 4 * i);
-        }
+        if (prev_sum) load_n<NV>(prev_sum + o, prev);
         if (add_dst) {
+            float old[NV];
+            load_n<NV>(dH + o, old);
 #pragma unroll
-            for (int i = 0; i < N / 4; ++i) prev[i] = add4(prev[i], OutVec<OT>::load4(dH + o + 4 * i));
+            for (int i = 0; i < NV; ++i) prev[i] += old[i];
         }
     }
-    // What limits this loop is the number of vector-memory instructions a CU can issue (counters: one every
-    // 20 cycles per CU with an entry load per gather, each holding the address path for about 16), so the
-    // (v, g) entries are not fetched per gather slot.  The G lanes of a bucket load G consecutive entries with
-    // one coalesced instruction, a block that feeds RPB rounds of NLD gathers per lane; a lane takes the
-    // entry of its slot from the lane that loaded it (ds_bpermute, which goes through the LDS crossbar, not
-    // the memory path).  The next block is in flight while the current one is used.  Rows are addressed as
-    // wave-uniform base + 32-bit byte offset where W allows it.  A slot behind the end of its list
-    // contributes through a zero gradient and gathers the row of the block's first entry instead (a row
-    // the bucket uses anyway, so nothing that could be non-finite is multiplied by that zero); the entry
-    // it read belongs to a later bucket, to the next sequence, or to the PERM_SLACK entries the workspace
-    // keeps behind the last list, and is not looked at.
+    // What limits this loop is the number of vector-memory instructions a CU can issue and the time their data
+    // takes, so the (v, g) entries are not fetched per gather slot.  The G lanes of a bucket load G consecutive entries
+    // with one coalesced instruction, a block that feeds RPB rounds of NLD gathers per lane, and E blocks are
+    // requested at a time: loads return in order, so every gather behind an entry load waits until the entry has come from
+    // beyond L2 (a block at a time, requested a block ahead: C5 2348 -> 2228 us, B=256 S=512 |V|=30522 778 -> 733).  Waves that
+    // share a bucket take a block at a time, the next one in flight (four: B=32 S=128 D=1024 156 -> 159, B=2 S=16 D=64 |V|=1000
+    // forward and backward 27.5 -> 29.3).
+    // The lane that loads an entry settles what it stands for, once: the byte offset of its row (32 bits where W allows it)
+    // and its gradient, or, behind the end of the list, a zero gradient and the row of the block's first entry (a row
+    // the bucket uses anyway, so nothing that could be non-finite is multiplied by that zero; the entry
+    // read there belongs to a later bucket, to the next sequence, or to the PERM_SLACK entries the workspace
+    // keeps behind the last list, and is not looked at).  A lane takes the entry of its slot from the lane that loaded
+    // it (ds_bpermute, which goes through the LDS crossbar, not the memory path).  With that, and the folds below
+    // instead of bpermute butterflies, C5 2392 -> 2348, B=64 S=100 |V|=50000 with one gradient in twenty 93 -> 85.
     constexpr int RPB = G / (NLD * EPG);       // rounds per block of entries
     static_assert(RPB * NLD * EPG == G && RPB >= 1, "a block is a whole number of rounds");
-    const char* const Wb = reinterpret_cast<const char*>(W);
-    const uint2* const pl = perm + (size_t)b * V;                   // b: the same for the whole workgroup
-    const uint32_t row_bytes = (uint32_t)D * (uint32_t)sizeof(T);
-    const uint32_t col_bytes = (uint32_t)(col_ok ? col0 : 0) * (uint32_t)sizeof(T);
-    const int li = lane % G;                   // lane within its bucket
-    const int src0 = (lane - li + sub) * 4;    // bpermute address of the lane holding entry `sub` of the block
     int left = end - beg - (WPB > 1 ? wave * G : 0);                // entries from the block's start to the end of the list
     const uint2* pe = pl + beg + li + (WPB > 1 && left > 0 ? wave * G : 0);      // this lane's entry of the current block
-    uint2 cur = *pe;
-    for (; left > 0; left -= BLK) {
-        // with several waves per bucket only a block that exists is requested (BLK entries may be more than the slack)
-        pe += WPB == 1 || left > BLK ? BLK : 0;
-        const uint2 nxt = *pe;
-        __builtin_amdgcn_sched_barrier(0);                          // the next block is requested first
-        const int v_first = __builtin_amdgcn_ds_bpermute((lane - li) * 4, (int)cur.x);      // the block's first entry: inside the list
-        const int rem = left - sub;                                 // slot at block offset c + sub is inside when c < rem
+    uint2 ahead = make_uint2(0u, 0u);
+    if (WPB > 1) ahead = *pe;
+    for (; left > 0; left -= E * BLK) {
+        uint2 entries[E];
+        if constexpr (WPB > 1) {
+            entries[0] = ahead;
+            pe += left > BLK ? BLK : 0;        // only a block that exists is requested (BLK entries may be more than the slack)
+            ahead = *pe;
+        } else {
 #pragma unroll
-        for (int p = 0; p < RPB; ++p) {
-            if (p * NLD * EPG < left) {                             // the round has entries; the lanes of a bucket agree
-                // three phases, kept apart: the entries of all NLD slots, then all NLD gathers, then the FMAs
-                // (left to itself the compiler gathers two rows at a time)
-                uint32_t off[NLD];
-                float gq[NLD];
-                uint4 x[NLD];
+            for (int e = 0; e < E; ++e)
+                if (e == 0 || e * BLK < left) entries[e] = pe[e * BLK];
+            pe += E * BLK;
+        }
+        __builtin_amdgcn_sched_barrier(0);                          // all of them are requested first
 #pragma unroll
-                for (int u = 0; u < NLD; ++u) {
-                    const int c = p * NLD * EPG + u * EPG;          // block offset of the slot of sub-group 0
-                    const int from = src0 + c * 4;
-                    const int vx = __builtin_amdgcn_ds_bpermute(from, (int)cur.x);
-                    const int gy = __builtin_amdgcn_ds_bpermute(from, (int)cur.y);
-                    const bool inside = c < rem;
-                    const uint32_t v = (uint32_t)(inside ? vx : v_first);
-                    gq[u] = inside ? __int_as_float(gy) : 0.f;
-                    off[u] = OFF32 ? __umul24(v, row_bytes) + col_bytes : v;
+        for (int e = 0; e < E; ++e) {
+            const int rest = left - e * BLK;                        // entries from this block's start
+            if (e > 0 && rest <= 0) break;
+            const uint2 ent = entries[e];
+            const uint32_t v_first = G == 64 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)ent.x)      // the block's first entry: inside the list
+                                             : (uint32_t)__builtin_amdgcn_ds_bpermute((lane - li) * 4, (int)ent.x);
+            const bool inside = li < rest;
+            const uint32_t v = inside ? ent.x : v_first;
+            const int at = (int)(OFF32 ? __umul24(v, row_bytes) : v);
+            const int gv = inside ? (int)ent.y : 0;
+#pragma unroll
+            for (int p = 0; p < RPB; ++p) {
+                if (p * NLD * EPG < rest) {                         // the round has entries; the lanes of a bucket agree
+                    // three phases, kept apart: the entries of all NLD slots, then all NLD gathers, then the FMAs
+                    // (left to itself the compiler gathers two rows at a time)
+                    uint32_t off[NLD];
+                    float gq[NLD];
+                    uint4 x[NLD];
+#pragma unroll
+                    for (int u = 0; u < NLD; ++u) {
+                        const int from = src0 + (p * NLD * EPG + u * EPG) * 4;      // block offset of the slot of sub-group 0
+                        off[u] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, at);
+                        gq[u] = __int_as_float(__builtin_amdgcn_ds_bpermute(from, gv));
+                        if (OFF32) off[u] += col_bytes;
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int u = 0; u < NLD; ++u) {
+                        if constexpr (OFF32) x[u] = *reinterpret_cast<const uint4*>(Wb + off[u]);
+                        else x[u] = *reinterpret_cast<const uint4*>(Wb + ((size_t)off[u] * row_bytes + col_bytes));
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int u = 0; u < NLD; ++u) RowChunk<T>::fma(x[u], gq[u], acc);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int u = 0; u < NLD; ++u) {
-                    if constexpr (OFF32) x[u] = *reinterpret_cast<const uint4*>(Wb + off[u]);
-                    else x[u] = *reinterpret_cast<const uint4*>(Wb + ((size_t)off[u] * row_bytes + col_bytes));
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int u = 0; u < NLD; ++u) RowChunk<T>::fma(x[u], gq[u], acc);
             }
         }
-        cur = nxt;
     }
+    // The sub-groups' sums: every fold halves the columns a lane holds (NV are left), in a fixed order.
     if (__any(beg < end)) {
+        if (LPR == 8 && G >= 16) {
 #pragma unroll
-        for (int off = LPR; off < G; off <<= 1)
+            for (int i = 0; i < N; ++i) acc[i] = add_half_row(acc[i]);
+        }
+        if (G >= 32) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) acc[i] += __shfl_xor(acc[i], off);
+            for (int i = 0; i < N / 2; ++i) acc[i] = fold_rows(acc[i], acc[i + N / 2]);
+        }
+        if (G >= 64) {
+#pragma unroll
+            for (int i = 0; i < N / 4; ++i) acc[i] = fold_halves(acc[i], acc[i + N / 4]);
+        }
     }
     if (WPB > 1 && !alone) {
         // the waves' sums, added in wave order (the exits above leave all waves of a bucket or the first one)
         __shared__ __attribute__((aligned(16))) float s_sum[WPB][DWS_COLS];
-        if (sub == 0 && wave > 0) {
+        if ((LPR == 16 || (lane & 8) == 0) && wave > 0) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) s_sum[wave][(lane % LPR) * N + i] = acc[i];
+            for (int i = 0; i < NV; ++i) s_sum[wave][(lane % LPR) * N + vcol + i] = acc[i];
         }
         __syncthreads();
         if (!writer) return;
 #pragma unroll
         for (int w = 1; w < WPB; ++w)
 #pragma unroll
-            for (int i = 0; i < N; ++i) acc[i] += s_sum[w][(lane % LPR) * N + i];
+            for (int i = 0; i < NV; ++i) acc[i] += s_sum[w][(lane % LPR) * N + vcol + i];
     }
     if (writer) {
 #pragma unroll
-        for (int i = 0; i < N / 4; ++i)
-            OutVec<OT>::store4(dH + o + 4 * i, make_float4(prev[i].x + acc[4 * i], prev[i].y + acc[4 * i + 1],
-                                                           prev[i].z + acc[4 * i + 2], prev[i].w + acc[4 * i + 3]));
+        for (int i = 0; i < NV; ++i) acc[i] = prev[i] + acc[i];
+        store_n<NV>(dH + o, acc);
     }
 }
 
