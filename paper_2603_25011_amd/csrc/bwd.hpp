@@ -862,9 +862,10 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
 // grid = (B, ceil(S / (4*BPW)), ceil(D/64)), 256 threads, or (B, S, ceil(D/64)), 64 * WPB threads, where the WPB waves of
 // a workgroup share one bucket; xcd_slice_grid workgroups instead of either where XCDs own the slices.
 // ---------------------------------------------------------------------------------------------
+// tops[b], if asked for: positions of sequence b up to the last one that has entries (what bwd_dw_tile_kernel copies).
 __global__ __launch_bounds__(256) void bwd_chunk_bounds_kernel(const int* __restrict__ bstart,
                                                                const uint2* __restrict__ perm,
-                                                               int* __restrict__ bounds,
+                                                               int* __restrict__ bounds, int* __restrict__ tops,
                                                                int n_buckets, int S, int V, int n_vc, int vc_len) {
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
     if (idx >= (long long)n_buckets * (n_vc + 1)) return;
@@ -873,7 +874,12 @@ __global__ __launch_bounds__(256) void bwd_chunk_bounds_kernel(const int* __rest
     const int b = bucket / S, s = bucket - b * S;
     int lo = bstart[(size_t)b * (S + 1) + s];
     int hi = bstart[(size_t)b * (S + 1) + s + 1];
-    if (c == n_vc) lo = hi;
+    if (c == n_vc) {
+        // the last bucket of the sequence that has entries; the first bucket, if none has
+        const int all = bstart[(size_t)b * (S + 1) + S];
+        if (tops && hi == all && (lo < hi || (s == 0 && all == 0))) tops[b] = lo < hi ? s + 1 : 0;
+        lo = hi;
+    }
     const unsigned target = (unsigned)c * (unsigned)vc_len;     // first v of chunk c
     const uint2* list = perm + (size_t)b * V;
     while (lo < hi) {                                           // first entry with v >= target
@@ -1088,18 +1094,29 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
 // dW/db, LDS-tile variant (bfloat16 inputs, D a multiple of 64, DWT_MIN_S <= S <= DWT_MAX_S).
 // A workgroup of 1024 threads owns 1024 consecutive vocabulary rows and one 64-column slice and walks
 // the sequences b = 0 .. B-1 in order.  For each sequence the slice of all S hidden states (S x 128
-// bytes, at most 64 KiB) is copied into LDS and every gather of the sequence is an LDS read.  Eight
-// lanes share a row piece (16 bytes each) and a thread keeps eight rows (64 float accumulators), so a
+// bytes, at most 64 KiB) is copied into LDS and every gather of the sequence is an LDS read.  The four lanes
+// of a quad stage one vocabulary row each and sum all four, a quarter of the columns each (two chunks of 16 bytes, 64
+// float accumulators per thread): a row's (g, tile row) goes from the staging lane to the others as an operand modifier (DPP)
+// of the xor that forms the LDS address and of one move, so it needs neither LDS nor registers of its own.  A
 // sequence costs one tile copy for 1024 gathers: the traffic out of L2 is the tile (S x 128 bytes)
 // instead of the gathers (1024 x 128 bytes), the reads are coalesced, and what is left is the arithmetic
-// of the gather itself, one unpack and one FMA per element, with the LDS reads running ahead of it.
+// of the gather itself, one unpack and one FMA per element, with the LDS reads one row ahead of it (the last row of a
+// sequence is multiplied behind the barrier, while the first of the next is on its way).
+// A half of a tile row is 64 bytes: rows with bit 1 set hold their halves exchanged, so that the four rows that sixteen lanes
+// read spread over all banks.
+// What bounds a round (one sequence): the arithmetic, 1.25 us, or the copy, 0.9 + 0.17 per 16 KiB (36 bytes per clock and CU: the 32
+// CUs of an XCD read the same lines).  So only the rows up to the last one with a gradient are copied where a launch in front has
+// left their number (`tops`; it does where dW runs behind dH): B=64 S=512 D=1024 |V|=250002, lengths 128..512, backward 3947 ->
+// 3806 us, one gradient in twenty 2582 -> 2344.  Eight lanes per row with the pairs in LDS took dW 1736 -> 1714 there,
+// B=16 S=256 |V|=250002 352 -> 344, B=32 S=128 D=1024 93.5 -> 90.
+// Not kept: (dY, Y, I) two sequences ahead (1701; 354), L2 touched two sequences ahead (1790; 372), the rows counted here
+// by ballots and LDS (1762; 410), 12 waves (2059; 441), two workgroups of 8 waves (-; 340, beside dH 923 -> 961 for the backward).
 // The next sequence's tile travels global -> LDS directly (LDS-DMA, no staging registers) into the other
 // buffer while the current one is multiplied; its (dY, Y, I) travel through registers and are turned into
 // (g, tile row offset) pairs at the end of the round.  One barrier per sequence, behind a full vmcnt wait.
 // Pairs without gradient point at a row of zeros behind the tile (hidden states of padded positions are
-// never multiplied, whatever they hold), and a wave skips a pair of rows when none of its sixteen (row,
-// row group) entries has a gradient.  The order of the sums over b is the same as in the kernels above.
-// Not for sparse gradients (the cost does not fall with the number of non-zero pairs, as it does in the
+// never multiplied, whatever they hold), and a wave skips a row of its quads when none of the sixteen has a gradient.  The order of the sums over b is the same as in the kernels above.
+// Not for sparse gradients (the cost hardly falls with the number of non-zero pairs, as it does in the
 // compacting kernel above) or for few workgroups: the host takes it for shapes with at least one
 // workgroup per CU.
 // grid = ceil(V / 1024) * (D / 64), slice-major.  PASSES = ceil(S / 128) copy passes per tile.
@@ -1108,34 +1125,39 @@ constexpr int DWT_ROWS = 1024;
 constexpr int DWT_MAX_S = 512;
 constexpr int DWT_MIN_S = 128;
 
+// Value that lane K of a lane's quad holds (DPP).  All four lanes have to be active.
+template <int K> __device__ __forceinline__ uint32_t quad_lane(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, K * 0x55, 0xf, 0xf, true);       // quad_perm:[K, K, K, K]
+}
+
 template <typename OT, int PASSES>
 __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* __restrict__ H,
                                                                const float* __restrict__ dY,
                                                                const float* __restrict__ Y,
                                                                const int* __restrict__ I,
                                                                OT* dW, int add_dst, float* db, int add_db,
-                                                               int B, int S, int D, int V, int n_vtiles) {
+                                                               const int* __restrict__ tops, int B, int S, int D, int V, int n_vtiles) {
     constexpr int ROW_B = DWS_COLS * 2;                    // bytes per tile row
-    constexpr int RPT = 8;                                 // vocabulary rows per thread
-    constexpr int RGS = DWT_ROWS / 8;                      // row groups (eight lanes each) = tile rows per copy pass
-    static_assert(PASSES >= 1 && PASSES * RGS <= DWT_MAX_S, "tile rows");      // S <= PASSES * RGS
-    // two tiles, each followed by a row of zeros
-    __shared__ __attribute__((aligned(1024))) uint8_t s_tile[2][(DWT_MAX_S + 1) * ROW_B];
-    __shared__ float2 s_go[2][DWT_ROWS];                   // per pair: g, and (as int bits) the byte offset of its tile row
-    const int tid = threadIdx.x;
+    constexpr int RPT = 4;                                 // vocabulary rows per thread: those its quad of lanes stages
+    constexpr int RPP = DWT_ROWS / 8;                      // tile rows per copy pass
+    constexpr int TROWS = PASSES * RPP;                    // tile rows: S <= TROWS
+    constexpr uint32_t TILE_B = (TROWS + 1) * ROW_B;       // two tiles, each followed by a row of zeros
+    __shared__ __attribute__((aligned(1024))) uint8_t s_tile[2 * TILE_B];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int dc = blockIdx.x / n_vtiles;
     const int v0 = (blockIdx.x - dc * n_vtiles) * DWT_ROWS;
-    const int rg = tid >> 3, cc = tid & 7;
     const int vs = v0 + tid;                               // the row this thread stages
     const bool vs_ok = vs < V;
     const int vs_c = vs_ok ? vs : V - 1;
 
-    float acc[RPT][8];
+    float acc[RPT][16];
 #pragma unroll
     for (int k = 0; k < RPT; ++k)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[k][i] = 0.f;
-    double db_acc = (db && dc == 0 && add_db && vs_ok) ? (double)db[vs] : 0.0;      // rounded once, as in the kernel above
+        for (int i = 0; i < 16; ++i) acc[k][i] = 0.f;
+    const bool sum_db = db && dc == 0;
+    double db_acc = (sum_db && add_db && vs_ok) ? (double)db[vs] : 0.0;      // rounded once, as in the kernel above
 
     // The loads of a sequence are straight-line code (clamped addresses instead of predicates) and nothing
     // looks at their results before stage(), so that they stay in flight while the sequence before is
@@ -1143,9 +1165,6 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
     // within a row of dY / Y / I are kept in 32 bits; the sequence's base is wave-uniform.
     float dy_r, y_r;
     int ix_r;
-    uint32_t hoff[PASSES];
-#pragma unroll
-    for (int p = 0; p < PASSES; ++p) hoff[p] = (uint32_t)((min(p * RGS + rg, S - 1) * D + dc * DWS_COLS + cc * 8) * 2);
     const uint32_t voff = (uint32_t)vs_c * 4u;
     auto gload = [&](int b) {
         const size_t ro = (size_t)b * V * 4;
@@ -1153,24 +1172,59 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
         y_r = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Y) + ro + voff);
         ix_r = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(I) + ro + voff);
     };
-    // the eight tile rows a wave copies per pass land in 1024 contiguous LDS bytes, lane l at + 16 l; rows
-    // behind S - 1 (when S is not a multiple of 128) receive copies of row S - 1 and are never read
-    const uint32_t wave_lds = __builtin_amdgcn_readfirstlane((uint32_t)(tid >> 6) * 8u * ROW_B);
-    auto tile_load = [&](int b, int buf) {
-        const char* hb = reinterpret_cast<const char*>(H) + (size_t)b * S * D * 2;
-        const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_addr(&s_tile[buf][0])) + wave_lds;
+    // the eight tile rows a wave copies per pass land in 1024 contiguous LDS bytes, lane l at + 16 l, so the lane picks
+    // the chunk that belongs there (rows r with bit 1 set hold their two halves exchanged); rows
+    // behind S - 1 (when S is not a multiple of 8) receive copies of row S - 1 and are never read
+    uint32_t hoff[PASSES];
 #pragma unroll
-        for (int p = 0; p < PASSES; ++p) dma16_to_lds(hb, hoff[p], dst + p * RGS * ROW_B);
+    for (int p = 0; p < PASSES; ++p)
+        hoff[p] = (uint32_t)((min(p * RPP + (tid >> 3), S - 1) * D + dc * DWS_COLS + ((lane & 7) ^ ((lane >> 4 & 1) * 4)) * 8) * 2);
+    const uint32_t tile0 = __builtin_amdgcn_readfirstlane(lds_addr(&s_tile[0]));
+    auto tile_load = [&](int b, int buf, int rows) {
+        const char* hb = reinterpret_cast<const char*>(H) + (size_t)b * S * D * 2;
+        const uint32_t dst = tile0 + buf * TILE_B + (uint32_t)wave * 8u * ROW_B;
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p)
+            if (p * RPP + wave * 8 < rows) dma16_to_lds(hb, hoff[p], dst + p * RPP * ROW_B);
     };
+    // what this lane's row of the vocabulary takes from a sequence: g, and the byte offset of its tile row
+    struct Pair { float g; uint32_t off; };
     auto stage = [&](int buf, bool count) {
         const float g = vs_ok ? gate_grad(dy_r, y_r) : 0.f;
-        db_acc += count ? (double)g : 0.0;
-        s_go[buf][tid] = make_float2(g, __int_as_float((g != 0.f ? clamp_pos(ix_r, S) : DWT_MAX_S) * ROW_B));
+        if (sum_db) db_acc += count ? (double)g : 0.0;
+        const uint32_t r = (uint32_t)(g != 0.f ? clamp_pos(ix_r, S) : TROWS);
+        return Pair{g, buf * TILE_B + r * ROW_B + (r >> 1 & 1) * 64};
     };
-    if (tid < 16) *reinterpret_cast<uint4*>(&s_tile[tid >> 3][DWT_MAX_S * ROW_B + (tid & 7) * 16]) = make_uint4(0, 0, 0, 0);
+    if (tid < 16) *reinterpret_cast<uint4*>(&s_tile[(tid >> 3) * TILE_B + TROWS * ROW_B + (tid & 7) * 16]) = make_uint4(0, 0, 0, 0);
+    const uint32_t chunk0 = (lane & 3) * 16, chunk1 = chunk0 | 64;
+    uint4 x[2][2];
+    // the two chunks of the tile row of vocabulary row K of this quad
+    auto fetch = [&](auto k, const Pair& e) {
+        constexpr int K = decltype(k)::value;
+        const uint32_t r = quad_lane<K>(e.off);
+        x[K & 1][0] = *reinterpret_cast<const uint4*>(&s_tile[r ^ chunk0]);
+        x[K & 1][1] = *reinterpret_cast<const uint4*>(&s_tile[r ^ chunk1]);
+    };
+    // nz: which lanes of the wave hold a pair with a gradient
+    auto multiply = [&](auto k, const Pair& e, unsigned long long nz) {
+        constexpr int K = decltype(k)::value;
+        if (nz & (0x1111111111111111ull << K)) {
+            const float g = __uint_as_float(quad_lane<K>(__float_as_uint(e.g)));
+            RowChunk<uint16_t>::fma(x[K & 1][0], g, acc[K]);
+            RowChunk<uint16_t>::fma(x[K & 1][1], g, acc[K] + 8);
+        }
+    };
+    constexpr std::integral_constant<int, 0> r0{};
+    constexpr std::integral_constant<int, 1> r1{};
+    constexpr std::integral_constant<int, 2> r2{};
+    constexpr std::integral_constant<int, 3> r3{};
+    const int b_last = B - 1;
+    auto rows_of = [&](int b) { return tops ? tops[b] : S; };
     gload(0);
-    tile_load(0, 0);
-    stage(0, true);
+    tile_load(0, 0, rows_of(0));
+    int top = rows_of(min(1, b_last));
+    Pair cur = stage(0, true), before{0.f, 0u};
+    unsigned long long nz = __ballot(cur.g != 0.f), nz_before = 0;
     wait_vmcnt<0>();
     __syncthreads();
     for (int b = 0; b < B; ++b) {
@@ -1179,45 +1233,42 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
         // no branch around the loads
         const bool more = b + 1 < B;
         gload(more ? b + 1 : b);
-        tile_load(more ? b + 1 : b, buf ^ 1);
-        // all eight (g, offset) pairs first, then the row pieces one pair of rows ahead of the FMAs that
-        // use them, so that a wave waits for LDS once per sequence rather than twice per pair of rows
-        float2 go[RPT];
-#pragma unroll
-        for (int k = 0; k < RPT; ++k) go[k] = s_go[buf][rg + RGS * k];
-        const uint8_t* tile = &s_tile[buf][cc * 16];
-        uint4 xa = *reinterpret_cast<const uint4*>(tile + __float_as_int(go[0].y));
-        uint4 xb = *reinterpret_cast<const uint4*>(tile + __float_as_int(go[1].y));
-#pragma unroll
-        for (int h = 0; h < RPT; h += 2) {
-            uint4 na = xa, nb = xb;
-            if (h + 2 < RPT) {
-                na = *reinterpret_cast<const uint4*>(tile + __float_as_int(go[h + 2].y));
-                nb = *reinterpret_cast<const uint4*>(tile + __float_as_int(go[h + 3].y));
-            }
-            if (__any(go[h].x != 0.f || go[h + 1].x != 0.f)) {
-                RowChunk<uint16_t>::fma(xa, go[h].x, acc[h]);
-                RowChunk<uint16_t>::fma(xb, go[h + 1].x, acc[h + 1]);
-            }
-            xa = na;
-            xb = nb;
-        }
-        stage(buf ^ 1, more);
-        wait_vmcnt<0>();                               // the tile has landed
+        tile_load(more ? b + 1 : b, buf ^ 1, top);
+        top = rows_of(min(b + 2, b_last));
+        fetch(r0, cur);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(r3, before, nz_before);
+        fetch(r1, cur);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(r0, cur, nz);
+        fetch(r2, cur);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(r1, cur, nz);
+        fetch(r3, cur);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(r2, cur, nz);
+        before = cur;
+        nz_before = nz;
+        cur = stage(buf ^ 1, more);
+        nz = __ballot(cur.g != 0.f);
+        __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): this tile's last row is in registers
+        wait_vmcnt<0>();                               // the next tile has landed
         __syncthreads();
     }
-    if (db && dc == 0 && vs_ok) db[vs] = (float)db_acc;
+    multiply(r3, before, nz_before);
+    if (sum_db && vs_ok) db[vs] = (float)db_acc;
     if (!dW) return;
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
-        const int v = v0 + rg + RGS * k;
+        const int v = v0 + (tid & ~3) + k;
         if (v < V) {
-            const size_t o = (size_t)v * D + dc * DWS_COLS + cc * 8;
+            const size_t o = (size_t)v * D + dc * DWS_COLS + (lane & 3) * 8;
 #pragma unroll
-            for (int i = 0; i < 8; i += 4) {
+            for (int i = 0; i < 16; i += 4) {
+                const size_t at = o + (i & 7) + (i >> 3) * 32;
                 float4 r = make_float4(acc[k][i], acc[k][i + 1], acc[k][i + 2], acc[k][i + 3]);
-                if (add_dst) r = add4(OutVec<OT>::load4(dW + o + i), r);
-                OutVec<OT>::store4(dW + o + i, r);
+                if (add_dst) r = add4(OutVec<OT>::load4(dW + at), r);
+                OutVec<OT>::store4(dW + at, r);
             }
         }
     }

@@ -826,6 +826,9 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
     uint2* perm = reinterpret_cast<uint2*>(base + w.perm_off);
     int* cnt = reinterpret_cast<int*>(base + w.cnt_off);
     int* bstart = reinterpret_cast<int*>(base + w.bs_off);
+    // Positions in use per sequence, for the LDS-tile dW kernel where it runs behind dH on the same stream: left by the launch
+    // that cuts the lists into windows, in place of the counts, which nothing reads after the placement.
+    int* tops = dH && dW && w.n_vc > 1 && L.dw_tile_passes > 0 && st_dw == st ? cnt : nullptr;
     int r;
     if (dH) {
         const dim3 seg_grid(w.n_seg, s.B);
@@ -865,7 +868,7 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
             if (w.n_vc > 1) {
                 int* cb = reinterpret_cast<int*>(base + w.cb_off);
                 const long long n = (long long)s.B * s.S * (w.n_vc + 1);
-                hipLaunchKernelGGL(bwd_chunk_bounds_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, bstart, perm, cb,
+                hipLaunchKernelGGL(bwd_chunk_bounds_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, bstart, perm, cb, tops,
                                    s.B * s.S, s.S, s.V, w.n_vc, w.vc_len);
                 bounds = cb;
             }
@@ -902,7 +905,7 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
             if constexpr (sizeof(T) == 2) {
                 const dim3 grid((unsigned)L.dw_tile_vtiles * (unsigned)(s.D / DWS_COLS));
 #define LSR_DWT(NP) hipLaunchKernelGGL((bwd_dw_tile_kernel<OT, NP>), grid, dim3(DWT_ROWS), 0, st_dw, H, dY, Y, I, dW, accumulate, db, \
-                                       accumulate, s.B, s.S, s.D, s.V, L.dw_tile_vtiles)
+                                       accumulate, tops, s.B, s.S, s.D, s.V, L.dw_tile_vtiles)
                 switch (L.dw_tile_passes) {
                     case 1: LSR_DWT(1); break;
                     case 2: LSR_DWT(2); break;

@@ -605,6 +605,41 @@ def test_random_shapes_lds_tile_dw():
         run_case(inp, mask=mask)
 
 
+@pytest.mark.parametrize("B,S,D,V,len_lo,density", [
+    (3, 200, 128, 131100, 1, 1.0),       # two copy passes; lengths from one token to the whole row
+    (4, 512, 64, 262200, 100, 0.05),     # four passes, one slice
+    (5, 129, 128, 131072, 127, 0.0005),  # one row behind a pass, most pairs without a gradient
+    (2, 128, 192, 100000, 1, 1.0),       # one pass
+])
+def test_lds_tile_dw_copies_the_positions_in_use(B, S, D, V, len_lo, density):
+    """Behind dH the LDS-tile dW kernel copies the rows up to each sequence's last one with a gradient; beside dH (the plain
+    call, from 0.1 GB of gathers on) and without dH it copies all.  The profiled call runs everything on one stream.  Same bits each time;
+    one sequence has no valid token, and hidden states behind the others' lengths are NaN."""
+    from paper_2603_25011_amd import binding as b
+    plan = b.lsr_head_plan(B, S, D, V, b.LSR_BF16)
+    assert plan["dw_lds_tile_passes"] == (S + 127) // 128 and plan["dh_chunks"] > 1 and plan["dw_beside_dh"] == 1, plan
+    inp = wl.make_custom(B, S, D, V, seed=77 + S, len_lo=len_lo)
+    inp.dY[...] = inp.dY * (np.random.default_rng(S).random(inp.dY.shape) < density)
+    head = DeviceHead(inp)
+    mask = head.mask.clone()
+    mask[B // 2] = 0
+    head.mask.copy_(mask)
+    head.H[mask == 0] = float("nan")
+    head.forward()
+    head.backward()
+    torch.cuda.synchronize()
+    ref = [t.clone() for t in (head.dH, head.dW, head.db)]
+    assert all(torch.isfinite(t).all() for t in ref)
+    for call in (lambda: b.lsr_head_backward_profiled(*head._shape(), head.H, head.W, head.dY, head.Y, head.I, head.dH, head.dW, head.db, head.ws_bwd),
+                 lambda: b.lsr_head_backward(*head._shape(), head.H, head.W, head.dY, head.Y, head.I, None, head.dW, head.db, head.ws_bwd)):
+        for t in (head.dW, head.db):
+            t.fill_(float("nan"))
+        call()
+        torch.cuda.synchronize()
+        for got, want in zip((head.dH, head.dW, head.db), ref):
+            assert torch.equal(got, want)
+
+
 @pytest.mark.parametrize("B,S,D,V,len_lo", [
     (5, 70, 128, 640, 3),          # one launch each
     (2, 16, 128, 70000, 1),        # dH over three vocabulary chunks: float32 partial sums staged in the workspace
