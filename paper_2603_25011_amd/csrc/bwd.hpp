@@ -320,6 +320,9 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_kernel(const float
 }
 
 // Placement through LDS (S <= PLACE_MAX_S, segments of at most PLACE_MAX_SEG entries).
+// ONE: the sequence is one segment; then this is the whole sort, and the bucket starts are written here.  (A sequence that fits one segment
+// always is one: backward B=23 S=88 D=256 |V|=2000 with one gradient in twenty 30.7 -> 19.7 us with dW in the same launch, B=4 S=640 D=64
+// |V|=3500 float32 23.3 -> 21.1, B=245 S=48 D=128 |V|=3500 102.8 -> 102.9; none of 35 shapes of 1024 to 4096 entries slower.)
 // The kernel above stores every (v, g) pair straight to its bucket: the 64 stores of a step go to some
 // fifty buckets, and with thousands of (b, segment) waves in flight every bucket's line leaves L2
 // between two stores to it (measured at C5: 0.48 GB written for 0.13 GB of pairs).  Here a workgroup
@@ -340,27 +343,23 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_kernel(const float
 constexpr int PLACE_MAX_S = 1024;
 constexpr int PLACE_MAX_SEG = 4096;
 
-template <int STEPS>
-__global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_staged_kernel(const float* __restrict__ dY,
-                                                               const float* __restrict__ Y,
-                                                               const int* __restrict__ I,
-                                                               const int* __restrict__ cnt,
-                                                               const int* __restrict__ bstart,
-                                                               uint2* __restrict__ perm,
-                                                               int S, int V, int n_seg, int seg_len, int key_bits) {
+template <int STEPS, bool ONE>
+__device__ __forceinline__ void place_staged(const float* __restrict__ dY, const float* __restrict__ Y, const int* __restrict__ I,
+                                             const int* __restrict__ cnt, int* bstart, uint2* __restrict__ perm,
+                                             int S, int V, int n_seg, int seg_len, int key_bits, int seg, int b) {
     constexpr int NT = 64 * PLACE_WAVES;
     extern __shared__ __attribute__((aligned(16))) int s_place[];
     uint2* s_stage = reinterpret_cast<uint2*>(s_place);             // [seg_len]
     unsigned* s_cnt = reinterpret_cast<unsigned*>(s_place + 2 * seg_len);      // [PLACE_WAVES / 2][S]: counts of waves 2 i and 2 i + 1
     int* s_delta = s_place + 2 * seg_len;                           // [S] global slot - local slot, in the same place at the end
     __shared__ int s_wave[PLACE_WAVES];
-    const int seg = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+    const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = wave & 1;
     unsigned* const s_count = s_cnt + (wave >> 1) * S;
     uint16_t* const s_next = reinterpret_cast<uint16_t*>(s_count) + half;      // next free local slot of bucket s at [2 s]
     const int* c0 = cnt + ((size_t)b * n_seg + seg) * S;
-    const int* b0 = bstart + (size_t)b * (S + 1);
+    int* const b0 = bstart + (size_t)b * (S + 1);
 
     // 1. this wave's piece
     const int piece = (seg_len / 64 + PLACE_WAVES - 1) / PLACE_WAVES * 64;       // (seg_len is a multiple of 64)
@@ -402,7 +401,8 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_staged_kernel(cons
     for (int u = 0; u < PLACE_MAX_S / NT; ++u) {
         const int s = lo + u;
         if (s < hi) {
-            delta[u] = b0[s] + c0[s] - run;
+            if (ONE) b0[s] = run;
+            delta[u] = ONE ? 0 : b0[s] + c0[s] - run;
 #pragma unroll
             for (int w = 0; w < PLACE_WAVES / 2; ++w) {
                 const unsigned c = s_cnt[w * S + s];
@@ -412,6 +412,7 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_staged_kernel(cons
             }
         }
     }
+    if (ONE && tid == 0) b0[S] = total;
     __syncthreads();
 
     // 3. rank and stage
@@ -440,6 +441,16 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_staged_kernel(cons
         const uint2 e = s_stage[k];
         perm[row + k + s_delta[e.x >> 12]] = make_uint2((unsigned)vseg + (e.x & 4095u), e.y);
     }
+}
+template <int STEPS, bool ONE>
+__global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_staged_kernel(const float* __restrict__ dY,
+                                                               const float* __restrict__ Y,
+                                                               const int* __restrict__ I,
+                                                               const int* __restrict__ cnt,
+                                                               int* bstart,
+                                                               uint2* __restrict__ perm,
+                                                               int S, int V, int n_seg, int seg_len, int key_bits) {
+    place_staged<STEPS, ONE>(dY, Y, I, cnt, bstart, perm, S, V, n_seg, seg_len, key_bits, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -700,13 +711,10 @@ __host__ __device__ inline XcdSliceUnit xcd_slice_unit(unsigned id, int n_dc, in
 }
 
 template <typename T, bool SWZ, typename OT>
-__global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict__ H,
-                                                            const float* __restrict__ dY,
-                                                            const float* __restrict__ Y,
-                                                            const int* __restrict__ I,
-                                                            const float* prev, OT* dW, int add_dst,
-                                                            float* __restrict__ db, int add_db,
-                                                            int b_first, int B, int S, int D, int V, int VT, int NDC) {
+__device__ __forceinline__ void dw_sliced(const T* __restrict__ H, const float* __restrict__ dY, const float* __restrict__ Y,
+                                          const int* __restrict__ I, const float* prev, OT* dW, int add_dst,
+                                          float* __restrict__ db, int add_db, int b_first, int B, int S, int D, int V, int VT, int NDC,
+                                          int vtile, int dg) {
     // b_first, B: the sequences of this launch; prev / add_dst: see above; add_db: db already holds the
     // sums over the sequences before b_first (or the caller's accumulated gradient) and is added to
     constexpr int N = RowChunk<T>::N;          // elements per 16-byte chunk
@@ -720,8 +728,7 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int n_waves = blockDim.x >> 6;
-    const int dg = blockIdx.y;                             // slice-group-major order
-    const int v0 = blockIdx.x * VT;
+    const int v0 = vtile * VT;
     const int dc_begin = dg * NDC;
     const int dc_end = min(n_slices(D), dc_begin + NDC);
 
@@ -838,6 +845,37 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
                 }
             }
         }
+    }
+}
+
+template <typename T, bool SWZ, typename OT>
+__global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict__ H,
+                                                            const float* __restrict__ dY,
+                                                            const float* __restrict__ Y,
+                                                            const int* __restrict__ I,
+                                                            const float* prev, OT* dW, int add_dst,
+                                                            float* __restrict__ db, int add_db,
+                                                            int b_first, int B, int S, int D, int V, int VT, int NDC) {
+    // slice-group-major order
+    dw_sliced<T, SWZ, OT>(H, dY, Y, I, prev, dW, add_dst, db, add_db, b_first, B, S, D, V, VT, NDC, blockIdx.x, blockIdx.y);
+}
+
+// The whole bucket sort (one segment per sequence) and dW/db, neither of which needs the other: the first B workgroups sort a
+// sequence each, the others are those of bwd_dw_sliced_kernel.  Such problems are bound by the launches they wait for one after the other (four
+// here before: count, scan, placement, dW).  B=2 S=16 D=64 |V|=1000 float32, forward and backward, 27.7 -> 17.5 us; backward B=7 S=495 D=64
+// |V|=1100 24.2 -> 14.0, B=1 S=10 D=1024 |V|=1500 float32 67.9 -> 56.9, B=54 S=181 D=256 |V|=1100 91.5 -> 80.2.
+template <typename T, typename OT, int STEPS>
+__global__ __launch_bounds__(256) void bwd_small_kernel(const T* __restrict__ H, const float* __restrict__ dY,
+                                                        const float* __restrict__ Y, const int* __restrict__ I, int* bstart,
+                                                        uint2* __restrict__ perm, OT* dW, float* __restrict__ db, int accumulate,
+                                                        int B, int S, int D, int V, int seg_len, int key_bits, int VT, int NDC,
+                                                        int n_vtiles) {
+    static_assert(64 * PLACE_WAVES == 256, "one workgroup size");
+    if ((int)blockIdx.x < B) {
+        place_staged<STEPS, true>(dY, Y, I, nullptr, bstart, perm, S, V, 1, seg_len, key_bits, 0, blockIdx.x);
+    } else {
+        const int i = (int)blockIdx.x - B;
+        dw_sliced<T, false, OT>(H, dY, Y, I, nullptr, dW, accumulate, db, accumulate, 0, B, S, D, V, VT, NDC, i % n_vtiles, i / n_vtiles);
     }
 }
 

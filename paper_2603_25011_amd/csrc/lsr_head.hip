@@ -256,7 +256,8 @@ BwdWs bwd_ws(const Shape& s, bool bf16_out = false) {
         n = n > fit ? n : fit;
     }
     n = n < s.V / s.S ? n : s.V / s.S;
-    if (n < 1) n = 1;
+    // one segment where a sequence fits it: the sort is then one launch (see bwd_place_staged_kernel)
+    if (n < 1 || (s.S <= PLACE_MAX_S && s.V <= PLACE_MAX_SEG)) n = 1;
     w.n_seg = (int)n;
     w.seg_len = ((s.V + w.n_seg - 1) / w.n_seg + 63) / 64 * 64;
     w.n_seg = (s.V + w.seg_len - 1) / w.seg_len;
@@ -684,6 +685,7 @@ private:
 struct BwdLaunch {
     int cpt;                 // 16-byte chunks per thread of the whole-row kernels
     bool staged_place;       // the bucket sort places through LDS
+    bool one_sort;           // ... and is one launch, because a sequence is one segment
     bool dh_sliced;          // column-sliced dH gather, else whole rows
     int bpw, wpb, dh_groups; // buckets per wave, waves per bucket and workgroups per slice of the sliced dH gather
     int dw_vt;               // rows of the dW staging tile: sliced gather if dw_sliced, else whole-row kernel
@@ -726,6 +728,7 @@ int plan_backward(const Shape& s, const BwdWs& w, BwdLaunch* L) {
     L->cpt = 1;
     while (L->cpt * ROW_THREADS < n_chunks) L->cpt *= 2;
     L->staged_place = s.S <= PLACE_MAX_S && w.seg_len <= PLACE_MAX_SEG;      // plan[3] of lsr_head_plan
+    L->one_sort = L->staged_place && w.n_seg == 1;
     L->dh_sliced = sliced_gathers(s);
     L->bpw = dh_buckets_per_wave(s, w.n_vc);
     L->wpb = dh_waves_per_bucket(s, w.n_vc);
@@ -829,30 +832,46 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
     // Positions in use per sequence, for the LDS-tile dW kernel where it runs behind dH on the same stream: left by the launch
     // that cuts the lists into windows, in place of the counts, which nothing reads after the placement.
     int* tops = dH && dW && w.n_vc > 1 && L.dw_tile_passes > 0 && st_dw == st ? cnt : nullptr;
+    // the sort and dW of small problems share a launch (what is profiled runs apart)
+    const bool small = dH && (dW || db) && L.one_sort && L.dw_sliced && L.dw_vt >= 32 &&
+                       L.dw_bc >= s.B && st_dw == st && !prof.on;
     int r;
     if (dH) {
         const dim3 seg_grid(w.n_seg, s.B);
-        prof.begin(0);
-        // few segments (long sequences, small problems): more threads per workgroup instead
-        const int count_threads = (long long)s.B * w.n_seg < 512 ? SORT_MAX_THREADS : 256;
-        hipLaunchKernelGGL(bwd_count_kernel, seg_grid, dim3(count_threads), sizeof(int) * s.S, st, dY, Y, I, cnt, s.S, s.V, w.n_seg, w.seg_len);
-        prof.end(0);
-        if ((r = launch_status()) != LSR_OK) return r;
-        prof.begin(1);
-        if (s.S > 256) hipLaunchKernelGGL(bwd_scan_kernel<1024>, dim3(s.B), dim3(1024), 0, st, cnt, bstart, s.S, w.n_seg);
-        else hipLaunchKernelGGL(bwd_scan_kernel<256>, dim3(s.B), dim3(256), 0, st, cnt, bstart, s.S, w.n_seg);
-        prof.end(1);
-        if ((r = launch_status()) != LSR_OK) return r;
+        if (!L.one_sort) {
+            prof.begin(0);
+            // few segments (long sequences, small problems): more threads per workgroup instead
+            const int count_threads = (long long)s.B * w.n_seg < 512 ? SORT_MAX_THREADS : 256;
+            hipLaunchKernelGGL(bwd_count_kernel, seg_grid, dim3(count_threads), sizeof(int) * s.S, st, dY, Y, I, cnt, s.S, s.V, w.n_seg, w.seg_len);
+            prof.end(0);
+            if ((r = launch_status()) != LSR_OK) return r;
+            prof.begin(1);
+            if (s.S > 256) hipLaunchKernelGGL(bwd_scan_kernel<1024>, dim3(s.B), dim3(1024), 0, st, cnt, bstart, s.S, w.n_seg);
+            else hipLaunchKernelGGL(bwd_scan_kernel<256>, dim3(s.B), dim3(256), 0, st, cnt, bstart, s.S, w.n_seg);
+            prof.end(1);
+            if ((r = launch_status()) != LSR_OK) return r;
+        }
         prof.begin(2);
         const dim3 place_block(64 * PLACE_WAVES);
-        if (L.staged_place) {
-            const size_t lds = sizeof(int) * (PLACE_WAVES / 2) * s.S + sizeof(uint2) * w.seg_len;
-#define LSR_PLACE(STEPS) hipLaunchKernelGGL(bwd_place_staged_kernel<STEPS>, seg_grid, place_block, lds, st, dY, Y, I, cnt, bstart, perm, s.S, \
-                                            s.V, w.n_seg, w.seg_len, w.key_bits)
+        const size_t place_lds = sizeof(int) * (PLACE_WAVES / 2) * s.S + sizeof(uint2) * w.seg_len;
+        if (small) {
+            const size_t lds_dw = (size_t)s.B * L.dw_vt * 8;
+#define LSR_SMALL(STEPS) hipLaunchKernelGGL((bwd_small_kernel<T, OT, STEPS>), dim3(s.B + L.dw_vtiles * L.dw_slice_groups), place_block, \
+                                            place_lds > lds_dw ? place_lds : lds_dw, st, H, dY, Y, I, bstart, perm, dW, db, accumulate, s.B, s.S, \
+                                            s.D, s.V, w.seg_len, w.key_bits, L.dw_vt, L.dw_ndc, L.dw_vtiles)
+            if (w.seg_len <= 4 * 64 * PLACE_WAVES) LSR_SMALL(4);
+            else if (w.seg_len <= 8 * 64 * PLACE_WAVES) LSR_SMALL(8);
+            else LSR_SMALL(16);
+#undef LSR_SMALL
+        } else if (L.staged_place) {
+#define LSR_PLACE2(STEPS, ONE) hipLaunchKernelGGL((bwd_place_staged_kernel<STEPS, ONE>), seg_grid, place_block, place_lds, st, dY, Y, I, cnt, \
+                                                  bstart, perm, s.S, s.V, w.n_seg, w.seg_len, w.key_bits)
+#define LSR_PLACE(STEPS) do { if (L.one_sort) LSR_PLACE2(STEPS, true); else LSR_PLACE2(STEPS, false); } while (0)
             if (w.seg_len <= 4 * 64 * PLACE_WAVES) LSR_PLACE(4);
             else if (w.seg_len <= 8 * 64 * PLACE_WAVES) LSR_PLACE(8);
             else LSR_PLACE(16);
 #undef LSR_PLACE
+#undef LSR_PLACE2
         } else {
             hipLaunchKernelGGL(bwd_place_kernel, seg_grid, place_block, sizeof(int) * PLACE_WAVES * s.S, st, dY, Y, I, cnt, bstart, perm,
                                s.S, s.V, w.n_seg, w.seg_len, w.key_bits);
@@ -897,7 +916,7 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
         prof.end(3);
         if ((r = launch_status()) != LSR_OK) return r;
     }
-    if (dW || db) {
+    if ((dW || db) && !small) {
         prof.begin(4);
         const int VT = L.dw_vt;
         if (L.dw_tile_passes > 0 && dW) {

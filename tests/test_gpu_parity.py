@@ -976,3 +976,29 @@ def test_packing_in_one_launch(B, S):
         mask[B - 1, :] = 0
     for m in (None, mask):
         print(run_case(inp, mask=m, check_bwd=False))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,S,D,V,dy_keep", [
+    (1, 1, 64, 1, None), (3, 5, 72, 63, None), (2, 16, 64, 1024, None), (5, 300, 64, 1025, 0.3),      # four and eight steps per wave
+    (2, 1024, 8, 2048, None), (3, 40, 128, 2049, None), (4, 700, 64, 4096, 0.05),                      # sixteen
+    (96, 7, 64, 640, None), (97, 7, 64, 640, None),                                                    # dW tiles of 64 rows, and of 32
+    (3, 40, 64, 4097, None), (2, 1025, 64, 1500, None),                                                # beyond: three launches
+])
+def test_small_problems_sort_and_dw_in_one_launch(B, S, D, V, dy_keep, dtype):
+    """Against the oracle, and bit for bit against the profiled call, which runs the sort and dW apart."""
+    inp = wl.make_custom(B, S, D, V, dtype=dtype, seed=3 * B + S + V, len_lo=1, dy_keep=dy_keep)
+    run_case(inp)
+    assert (lsr.lsr_head_plan(B, S, D, V, lsr.LSR_BF16)["sort_segments"] == 1) == (V <= 4096 and S <= 1024 or V < 2 * max(S, 512))
+    head = DeviceHead(inp)
+    head.forward()
+    head.poison_outputs()
+    head.forward()
+    head.backward()
+    torch.cuda.synchronize()
+    ref = [t.clone() for t in (head.dH, head.dW, head.db)]
+    head.dH.fill_(float("nan")), head.dW.fill_(float("nan")), head.db.fill_(float("nan"))
+    head.backward_profiled()
+    torch.cuda.synchronize()
+    for got, want in zip((head.dH, head.dW, head.db), ref):
+        assert torch.equal(got, want)
