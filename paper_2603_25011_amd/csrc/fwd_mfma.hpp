@@ -15,7 +15,8 @@
 // Operand staging.  K (the hidden size D) is walked in slabs of BK elements through an NS-stage
 // ring of LDS tiles.  Two loaders:
 //   DMA = true  : global_load_lds (16 bytes per lane straight into LDS, no staging registers),
-//                 slabs issued NS-1 iterations ahead, one barrier per slab.  Needs D % BK == 0.
+//                 slabs issued NS-1 iterations ahead, one barrier per slab.  Where D % BK is not 0 the chunks
+//                 behind the end of a row are fetched from a piece of zeros.
 //   DMA = false : global -> registers -> LDS, one slab ahead (NS = 2).  Handles any D that
 //                 is a multiple of 8 (the last slab is zero-filled).
 // Rows are XOR-swizzled inside a slab so that the 16-byte fragment reads are bank-conflict free.
@@ -289,15 +290,21 @@ __device__ __forceinline__ void mma_dispatch(int na, const uint8_t* sa, int a_st
 //        B=2 S=16 D=64 |V|=1000 81 -> 11 us; the error against float64 logits is the same (3.2e-7 of the
 //        norm of Y).
 //   ARG  track the arg-max position (I requested)
-//   DMA  operands go global -> LDS directly (rows a multiple of 128 bytes, H and W below 4 GiB each); otherwise
+//   DMA  operands go global -> LDS directly (H and W below 4 GiB each); otherwise
 //        through registers, with 64-bit addresses and a zero-filled last slab
 //   SEG  rows per segment of the packed token list: 32 (FWD_BLK) or 8 (FWD_SEG_SHORT)
 //   RES  resident workgroups: a workgroup walks several units (see the schedule below); without it the
 //        grid has one workgroup per unit and the code that moves on to a next unit is not generated
 // (Built and measured slower, and not kept as parameters: two 4-wave workgroups per CU on 256 x 128
 //  tiles, which move 1.5x the bytes into LDS, -20 %; 32-deep slabs in four stages, -6 %.)
+//   TAIL the last slab of a row is not full (DMA only; the loads through registers always ask): its chunks behind the end of the
+//        row come from fwd_zeros, with 64-bit addresses in that slab alone.  Through registers, where the loads of a slab
+//        and their stores into LDS cannot overlap the MFMAs as freely, the same bits took (us -> direct): B=13 S=197 D=312
+//        |V|=31091 77 -> 59, B=44 S=452 D=888 |V|=28066 920 -> 648, B=130 S=39 D=1000 |V|=36147 392 -> 287, B=6 S=49 D=168 |V|=46465
+//        22.3 -> 22.2, float32 B=3 S=107 D=624 |V|=6965 104 -> 91; 39 shapes: 0.81 in the geometric mean, none slower.
 constexpr int FWD_NWN = 4;               // wave columns
-template <typename T, bool ARG, bool DMA, int SEG, bool RES>
+static __device__ const uint4 fwd_zeros = {0u, 0u, 0u, 0u};
+template <typename T, bool ARG, bool DMA, int SEG, bool RES, bool TAIL>
 __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_mfma_kernel(FwdParams p) {
     static_assert(SEG == 32 || SEG == 16 || SEG == 8, "a segment is a whole number of a lane's register quads");
     constexpr int SPB = FWD_BLK / SEG;       // segments per row block
@@ -528,8 +535,15 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_mfma_kernel(FwdPa
             // (lane l lands at +16 l); the wave-uniform base goes through M0.
             // load n (0 .. LPT-1) of a slab into ring stage ST: first the A rows, then the B rows; hb and wb
             // are the operand bases already advanced to the slab's K offset (wave-uniform, in SGPRs)
-            auto issue_one = [&](auto st, const char* hb, const char* wb, int n) {
+            const bool chunk_ok = !TAIL || gch < (D - (nk - 1) * BK) / EPC;      // this lane's chunk of the last slab
+            auto issue_one = [&](auto st, const char* hb, const char* wb, int n, bool last) {
                 const uint32_t dst = lds_addr(ring(st)) + wave_lds;
+                if (TAIL && last) {
+                    const char* src = n < IPA ? hb + hoff32[n] : wb + woff32[n - IPA];
+                    dma16_to_lds(chunk_ok ? src : reinterpret_cast<const char*>(&fwd_zeros),
+                                 n < IPA ? dst + n * JSTEP : dst + SLAB_A + (n - IPA) * JSTEP);
+                    return;
+                }
                 if (n < IPA) dma16_to_lds(hb, hoff32[n], dst + n * JSTEP);
                 else dma16_to_lds(wb, woff32[n - IPA], dst + SLAB_A + (n - IPA) * JSTEP);
             };
@@ -537,7 +551,7 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_mfma_kernel(FwdPa
                 const char* hb = Hb + (size_t)kt * RB;
                 const char* wb = Wb + (size_t)kt * RB;
 #pragma unroll
-                for (int n = 0; n < LPT; ++n) issue_one(st, hb, wb, n);
+                for (int n = 0; n < LPT; ++n) issue_one(st, hb, wb, n, kt == nk - 1);
             };
             // The whole slab loop is instantiated once per count NA of live row blocks and the choice is
             // made per tile, outside the loop, so that each instance is straight-line MFMA code.
@@ -563,8 +577,9 @@ __global__ __launch_bounds__(fwd_threads(FWD_NWN), 2) void fwd_mfma_kernel(FwdPa
                     const size_t kbytes = (size_t)(NEXT ? 0 : kt + 1) * RB;
                     const char* hb = Hb + kbytes;
                     const char* wb = Wb + kbytes;
+                    const bool last = TAIL && !NEXT && __builtin_amdgcn_readfirstlane(kt + 2 == nk ? 1 : 0) != 0;
                     auto dma = [&](int n) {
-                        if (more != 0) issue_one(std::integral_constant<int, (ST + 1) % NS>{}, hb, wb, n);
+                        if (more != 0) issue_one(std::integral_constant<int, (ST + 1) % NS>{}, hb, wb, n, last);
                     };
                     if constexpr (NA == 0) {        // no live row block in this wave: only its loads
 #pragma unroll

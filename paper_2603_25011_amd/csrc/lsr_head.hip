@@ -67,13 +67,14 @@ inline bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) &
 // (B=256, S=32, lengths 4..32: 8192 packed rows with 32-row segments, 5 400 with 8-row segments).
 int fwd_seg(const Shape& s) { return s.S <= FWD_SEG_SHORT_MAX_S ? FWD_SEG_SHORT : FWD_BLK; }
 
-// Kernel choice: the direct-to-LDS ring when a row is a whole number of 128-byte K slabs and H and W are
-// each below 4 GiB (32-bit byte offsets per lane), else the register-staged loader (64-bit addresses,
-// zero-fills the last slab).
+// Kernel choice: the direct-to-LDS ring when H and W are each below 4 GiB (32-bit byte offsets per lane), else the
+// register-staged loader (64-bit addresses).  Rows that are not a whole number of 128-byte K slabs take a variant of either
+// that zero-fills the last slab.
 bool fwd_direct(const Shape& s) {
     const size_t row = (size_t)s.D * (s.dtype == LSR_F32 ? 4 : 2);
-    return row % 128 == 0 && (size_t)s.B * s.S * row < ((size_t)1 << 32) && (size_t)s.V * row < ((size_t)1 << 32);
+    return (size_t)s.B * s.S * row < ((size_t)1 << 32) && (size_t)s.V * row < ((size_t)1 << 32);
 }
+bool fwd_whole_slabs(const Shape& s) { return (size_t)s.D * (s.dtype == LSR_F32 ? 4 : 2) % 128 == 0; }
 
 // Calls of few tokens go through one launch of their own (fwd_few_kernel), where the hidden states fit the LDS.  Forward, us,
 // packing and tile kernel -> one launch, all tokens valid (D=768 |V|=30522 bfloat16 where not said):
@@ -92,7 +93,7 @@ bool fwd_direct(const Shape& s) {
 //     |V|=131072 40 -> 47.  Rows that end in a part of a batch: 2, and 3, 6, 7, 8 from D=768, 1024, 1280, 1600 on: B=2 S=16 D=640
 //     |V|=250002 84 -> 77; not B=4 S=8 D=896 |V|=131072 49 -> 53.  Rows of 4 KiB, which share their memory channels: 2; not B=8 S=4
 //     D=2048 |V|=301233 264 -> 288
-//     Where the tile kernel loads through registers: 8 (B=8 S=8 D=568 |V|=702271 302 -> 263)
+//     Rows that are not whole slabs: 8 (B=8 S=8 D=568 |V|=702271 293 -> 263, B=2 S=16 D=712 |V|=250002 116 -> 88)
 //   not: two or three rounds (B=4 S=16 |V|=40000 24.6 -> 27.6, B=1 S=32 |V|=60000 25.1 -> 26.1, |V|=119547 40.2 -> 40.2), many rounds of
 //     short rows (B=1 S=64 D=384 |V|=119547 29.5 -> 33.5, B=8 S=8 D=128 |V|=250002 43 -> 58) or in float32 (B=1 S=16 D=512 |V|=250002
 //     121 -> 134), more sequences (the lanes of a column take them one after the other: B=64 S=1 45.6 -> 51.1)
@@ -102,7 +103,7 @@ bool fwd_few(const Shape& s) {
     constexpr int round = 256 * FEW_COLS;                // vocabulary entries that 256 CUs take at a time
     if (s.V <= round) return s.B <= 16;
     if (s.dtype != LSR_BF16 || s.V < 4 * round || s.D < 512 || s.B > 8) return false;
-    if (!fwd_direct(s)) return true;
+    if (!fwd_direct(s) || !fwd_whole_slabs(s)) return true;
     const bool small = tokens <= 32;
     if ((s.V + round - 1) / round % 2 != 0) return s.B <= (s.D >= 1024 ? 8 : (s.D >= 768 ? (small ? 8 : 6) : (small ? 5 : 4)));
     constexpr int batch = 16 * FEW_U;                    // columns of a batch of loads
@@ -114,7 +115,7 @@ bool fwd_few(const Shape& s) {
 // tpc: most tiles per chunk; window: float32 only, segments per window of a chunk (chunks are whole sequences, see
 // fwd_f32_window); n_chunks: chunks the grid provides for
 int fwd_f32_window(const Shape& s);
-struct FwdChunks { int tpc, window, n_chunks; bool cut_possible, direct, resident; };
+struct FwdChunks { int tpc, window, n_chunks; bool cut_possible, direct, tail, resident; };
 FwdChunks fwd_chunks(const Shape& s) {
     const int seg = fwd_seg(s);
     const long segs_max = (long)s.B * ((s.S + seg - 1) / seg);
@@ -133,9 +134,11 @@ FwdChunks fwd_chunks(const Shape& s) {
         const long longest = c.window - 1 + (s.S + seg - 1) / seg;        // segments of the sequences that begin in a window
         c.tpc = (int)(((longest < segs_max ? longest : segs_max) * seg + FWD_TM - 1) / FWD_TM);
     }
-    // the register-staged loader has no prefetch across units to gain from residency
+    // the register-staged loader has no prefetch across units to gain from residency, and rows with a partly filled last
+    // slab were not tried
     c.direct = fwd_direct(s);
-    c.resident = shallow && c.direct;
+    c.tail = !fwd_whole_slabs(s);
+    c.resident = shallow && c.direct && !c.tail;
     // a sequence of one segment can never lie across a chunk boundary: no pieces, no merge pass
     c.cut_possible = s.dtype == LSR_BF16 && s.S > seg && c.n_chunks > 1;
     return c;
@@ -425,7 +428,7 @@ bool pack_in_one_launch(const Shape& s) {
     return (long)s.B * s.S <= PACK_MAX_TOKENS && s.B <= (s.S <= 64 ? PACK_MAX_B : 64);
 }
 
-template <typename T, bool DMA, int SEG, bool RES>
+template <typename T, bool DMA, int SEG, bool RES, bool TAIL = false>
 void launch_fwd_cfg(FwdParams p, int V, bool arg, int n_cus, hipStream_t st) {
     constexpr int TN = fwd_tn(FWD_NWN);
     p.n_vtiles = (V + TN - 1) / TN;
@@ -436,15 +439,18 @@ void launch_fwd_cfg(FwdParams p, int V, bool arg, int n_cus, hipStream_t st) {
     const long long n_units = (long long)((p.n_vtiles + p.gv - 1) / p.gv) * p.gv * p.n_chunks;
     const int n_wg = RES ? (n_cus >= 8 ? n_cus / 8 * 8 : 8) : (int)((n_units + 7) / 8 * 8);
     const dim3 grid(n_wg), block(fwd_threads(FWD_NWN));
-    if (arg) hipLaunchKernelGGL((fwd_mfma_kernel<T, true, DMA, SEG, RES>), grid, block, 0, st, p);
-    else     hipLaunchKernelGGL((fwd_mfma_kernel<T, false, DMA, SEG, RES>), grid, block, 0, st, p);
+    if (arg) hipLaunchKernelGGL((fwd_mfma_kernel<T, true, DMA, SEG, RES, TAIL>), grid, block, 0, st, p);
+    else     hipLaunchKernelGGL((fwd_mfma_kernel<T, false, DMA, SEG, RES, TAIL>), grid, block, 0, st, p);
 }
 
 template <typename T>
-void launch_fwd(const FwdParams& p, int seg, bool direct, bool resident, bool arg, int n_cus, hipStream_t st) {
+void launch_fwd(const FwdParams& p, int seg, bool direct, bool tail, bool resident, bool arg, int n_cus, hipStream_t st) {
     if (!direct) {
         if (seg == FWD_BLK) launch_fwd_cfg<T, false, FWD_BLK, false>(p, p.V, arg, n_cus, st);
         else launch_fwd_cfg<T, false, FWD_SEG_SHORT, false>(p, p.V, arg, n_cus, st);
+    } else if (tail) {
+        if (seg == FWD_BLK) launch_fwd_cfg<T, true, FWD_BLK, false, true>(p, p.V, arg, n_cus, st);
+        else launch_fwd_cfg<T, true, FWD_SEG_SHORT, false, true>(p, p.V, arg, n_cus, st);
     } else if (seg == FWD_BLK) {
         if (resident) launch_fwd_cfg<T, true, FWD_BLK, true>(p, p.V, arg, n_cus, st);
         else launch_fwd_cfg<T, true, FWD_BLK, false>(p, p.V, arg, n_cus, st);
@@ -521,8 +527,8 @@ int forward_impl(const lsr_head_desc* desc, const void* H, const void* W, const 
     p.part_m = part_m; p.part_s = part_s;
     p.B = s.B; p.S = s.S; p.D = s.D; p.V = s.V;
     p.n_chunks = ck.n_chunks; p.tpc = s.dtype == LSR_F32 ? ck.window : ck.tpc;
-    if (s.dtype == LSR_F32) launch_fwd<float>(p, seg, ck.direct, ck.resident, I != nullptr, n_cus, st);
-    else launch_fwd<uint16_t>(p, seg, ck.direct, ck.resident, I != nullptr, n_cus, st);
+    if (s.dtype == LSR_F32) launch_fwd<float>(p, seg, ck.direct, ck.tail, ck.resident, I != nullptr, n_cus, st);
+    else launch_fwd<uint16_t>(p, seg, ck.direct, ck.tail, ck.resident, I != nullptr, n_cus, st);
     prof.end(1);
     if (ck.cut_possible) {
         if ((rc = launch_status()) != LSR_OK) return rc;

@@ -1002,3 +1002,27 @@ def test_small_problems_sort_and_dw_in_one_launch(B, S, D, V, dy_keep, dtype):
     torch.cuda.synchronize()
     for got, want in zip((head.dH, head.dW, head.db), ref):
         assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,S", [(5, 40), (2, 150)])         # 8-row and 32-row segments
+@pytest.mark.parametrize("D", [8, 24, 56, 72, 88, 120, 136, 200])
+def test_rows_that_end_inside_a_slab(B, S, D, dtype):
+    """A slab is 64 bfloat16 or 32 float32 columns; its chunks behind the end of a row are zeros, whatever follows the row in
+    memory: the hidden states behind each valid one are NaN (masked), and every second row of W is infinite."""
+    V = 300
+    inp = wl.make_custom(B, S, D, V, dtype=dtype, seed=D + S)
+    mask = np.zeros((B, S), dtype=np.uint8)
+    mask[:, ::2] = 1
+    run_case(inp, mask=mask, check_bwd=False)
+    head = DeviceHead(inp, mask=mask)
+    head.forward()
+    torch.cuda.synchronize()
+    ref = head.Y.clone(), head.I.clone()
+    head.H[head.mask == 0] = float("nan")
+    head.W[::2] = float("inf")
+    for index in (head.I, None):
+        head.Y.fill_(float("nan"))
+        lsr.lsr_head_forward(*head._shape(), head.H, head.W, head.bias, head.mask, head.Y, index, head.ws_fwd)
+        torch.cuda.synchronize()
+        assert torch.equal(head.Y[:, 1::2], ref[0][:, 1::2]) and torch.equal(head.I[:, 1::2], ref[1][:, 1::2])
