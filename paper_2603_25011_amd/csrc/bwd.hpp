@@ -860,21 +860,24 @@ __global__ __launch_bounds__(256) void bwd_dw_sliced_kernel(const T* __restrict_
     dw_sliced<T, SWZ, OT>(H, dY, Y, I, prev, dW, add_dst, db, add_db, b_first, B, S, D, V, VT, NDC, blockIdx.x, blockIdx.y);
 }
 
-// The whole bucket sort (one segment per sequence) and dW/db, neither of which needs the other: the first B workgroups sort a
-// sequence each, the others are those of bwd_dw_sliced_kernel.  Such problems are bound by the launches they wait for one after the other (four
-// here before: count, scan, placement, dW).  B=2 S=16 D=64 |V|=1000 float32, forward and backward, 27.7 -> 17.5 us; backward B=7 S=495 D=64
-// |V|=1100 24.2 -> 14.0, B=1 S=10 D=1024 |V|=1500 float32 67.9 -> 56.9, B=54 S=181 D=256 |V|=1100 91.5 -> 80.2.
-template <typename T, typename OT, int STEPS>
-__global__ __launch_bounds__(256) void bwd_small_kernel(const T* __restrict__ H, const float* __restrict__ dY,
-                                                        const float* __restrict__ Y, const int* __restrict__ I, int* bstart,
-                                                        uint2* __restrict__ perm, OT* dW, float* __restrict__ db, int accumulate,
-                                                        int B, int S, int D, int V, int seg_len, int key_bits, int VT, int NDC,
-                                                        int n_vtiles) {
+// The placement and dW/db in one launch, neither of which needs the other: the first B * n_seg workgroups place a segment each, the
+// others are those of bwd_dw_sliced_kernel.  Small problems are bound by the launches they wait for one after the other (count, scan, placement,
+// dW, dH; the first two go where a sequence is one segment).  B=2 S=16 D=64 |V|=1000 float32, forward and backward, 27.7 -> 17.5 us; backward
+// B=7 S=495 D=64 |V|=1100 24.2 -> 14.0, B=1 S=10 D=1024 |V|=1500 float32 67.9 -> 56.9, B=54 S=181 D=256 |V|=1100 91.5 -> 80.2.
+// When: see share_dw in lsr_head.hip.
+template <typename T, typename OT, int STEPS, bool ONE>
+__global__ __launch_bounds__(256) void bwd_place_dw_kernel(const T* __restrict__ H, const float* __restrict__ dY,
+                                                           const float* __restrict__ Y, const int* __restrict__ I,
+                                                           const int* __restrict__ cnt, int* bstart,
+                                                           uint2* __restrict__ perm, OT* dW, float* __restrict__ db, int accumulate,
+                                                           int B, int S, int D, int V, int n_seg, int seg_len, int key_bits, int VT, int NDC,
+                                                           int n_vtiles) {
     static_assert(64 * PLACE_WAVES == 256, "one workgroup size");
-    if ((int)blockIdx.x < B) {
-        place_staged<STEPS, true>(dY, Y, I, nullptr, bstart, perm, S, V, 1, seg_len, key_bits, 0, blockIdx.x);
+    const int i = (int)blockIdx.x - B * n_seg;
+    if (i < 0) {
+        const int b = (int)blockIdx.x / n_seg;
+        place_staged<STEPS, ONE>(dY, Y, I, cnt, bstart, perm, S, V, n_seg, seg_len, key_bits, (int)blockIdx.x - b * n_seg, b);
     } else {
-        const int i = (int)blockIdx.x - B;
         dw_sliced<T, false, OT>(H, dY, Y, I, nullptr, dW, accumulate, db, accumulate, 0, B, S, D, V, VT, NDC, i % n_vtiles, i / n_vtiles);
     }
 }
@@ -942,13 +945,11 @@ __device__ __forceinline__ float fold_halves(float a, float b) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// dc, sg, b: column slice, workgroup within the sequence (its bucket, if several waves share one) and sequence
 template <typename T, int BPW, int WPB, typename OT, bool OFF32>
-__global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu(8, 8))) void bwd_dh_sliced_kernel(const T* __restrict__ W,
-                                                            const int* __restrict__ bounds,
-                                                            const uint2* __restrict__ perm,
-                                                            const float* prev_sum, OT* dH, int add_dst, int write_all,
-                                                            int B, int S, int D, int V, int n_groups,
-                                                            int n_vc, int vc, int xcd_own) {
+__device__ __forceinline__ void dh_sliced(const T* __restrict__ W, const int* __restrict__ bounds, const uint2* __restrict__ perm,
+                                          const float* prev_sum, OT* dH, int add_dst, int write_all, int S, int D, int V,
+                                          int n_vc, int vc, int dc, int sg, int b) {
     constexpr int N = RowChunk<T>::N;
     constexpr int LPR = DWS_COLS / N;          // lanes per row piece
     constexpr int G = 64 / BPW;                // lanes per bucket
@@ -963,22 +964,6 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
     constexpr int NV = N >> ((G >= 32) + (G >= 64));      // columns of a sum that a lane ends up with
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    int dc, g;
-    if (xcd_own) {                                                 // slices owned by XCDs (see xcd_slice_unit)
-        const XcdSliceUnit u = xcd_slice_unit(blockIdx.x, n_slices(D), n_groups, 1);
-        if (!u.valid) return;
-        dc = u.dc_first;
-        g = u.item;
-    } else {
-        dc = blockIdx.z;                                           // slice-major order
-        g = 0;
-    }
-    // Within a slice, consecutive workgroups take the same positions of consecutive sequences
-    // (b fastest).  Workgroups are dealt to the chip's shader engines in a fixed rotation; with s
-    // fastest, the empty buckets behind the end of each sequence recur with a period that can leave
-    // some engines with twice the work of others.
-    const int sg = xcd_own ? g / B : (int)blockIdx.y;
-    const int b = xcd_own ? g - sg * B : (int)blockIdx.x;
     const int col0 = dc * DWS_COLS + (lane % LPR) * N;
     const bool col_ok = col0 < D;              // the last slice may be partly filled: the lanes behind D gather column 0
     const int li = lane % G;                   // lane within its bucket
@@ -1126,6 +1111,77 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
         for (int i = 0; i < NV; ++i) acc[i] = prev[i] + acc[i];
         store_n<NV>(dH + o, acc);
     }
+}
+
+template <typename T, int BPW, int WPB, typename OT, bool OFF32>
+__global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu(8, 8))) void bwd_dh_sliced_kernel(const T* __restrict__ W,
+                                                            const int* __restrict__ bounds,
+                                                            const uint2* __restrict__ perm,
+                                                            const float* prev_sum, OT* dH, int add_dst, int write_all,
+                                                            int B, int S, int D, int V, int n_groups,
+                                                            int n_vc, int vc, int xcd_own) {
+    // Within a slice, consecutive workgroups take the same positions of consecutive sequences
+    // (b fastest).  Workgroups are dealt to the chip's shader engines in a fixed rotation; with s
+    // fastest, the empty buckets behind the end of each sequence recur with a period that can leave
+    // some engines with twice the work of others.
+    int dc = blockIdx.z, sg = blockIdx.y, b = blockIdx.x;          // slice-major order
+    if (xcd_own) {                                                 // slices owned by XCDs (see xcd_slice_unit)
+        const XcdSliceUnit u = xcd_slice_unit(blockIdx.x, n_slices(D), n_groups, 1);
+        if (!u.valid) return;
+        dc = u.dc_first;
+        sg = u.item / B;
+        b = u.item - sg * B;
+    }
+    dh_sliced<T, BPW, WPB, OT, OFF32>(W, bounds, perm, prev_sum, dH, add_dst, write_all, S, D, V, n_vc, vc, dc, sg, b);
+}
+
+// dW/db and the (first) dH gather in one launch: the dW workgroups first, which run longer, and the dH gather fills the chip beside them.
+// The overlap is that of the auxiliary stream without its fork and join (32 us of the host's time, and waits on the GPU): whole
+// training step through autograd, bound by the host, B=14 S=38 D=512 |V|=29935 198 -> 138 us; backward B=5 S=34 D=384 |V|=22757 56 -> 34.
+// All workgroups of the launch carry the LDS of a dW tile, hence the limit on it.  When, and both sides: see share_dw in lsr_head.hip.
+struct DhDwArgs {
+    const void* H;
+    const void* W;
+    const float* dY;
+    const float* Y;
+    const int* I;
+    const int* bounds;
+    const uint2* perm;
+    void* dH;
+    void* dW;
+    float* db;
+    int accumulate;
+    int B, S, D, V;
+    int n_groups, n_vc, xcd_own;             // dH: as above
+    int VT, NDC, n_vtiles, n_dw, n_dw_pad;   // dW: as above; its workgroups, and the same as a multiple of 8
+};
+template <typename T, int BPW, int WPB, typename OT>
+__global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu(8, 8))) void bwd_dh_dw_kernel(DhDwArgs p) {
+    int id = blockIdx.x;
+    if (id < p.n_dw_pad) {
+        if (id >= p.n_dw) return;
+        const int dg = id / p.n_vtiles;
+        dw_sliced<T, false, OT>(static_cast<const T*>(p.H), p.dY, p.Y, p.I, nullptr, static_cast<OT*>(p.dW), p.accumulate, p.db, p.accumulate, 0, p.B,
+                                p.S, p.D, p.V, p.VT, p.NDC, id - dg * p.n_vtiles, dg);
+        return;
+    }
+    id -= p.n_dw_pad;
+    int dc, sg, b;
+    if (p.xcd_own) {
+        const XcdSliceUnit u = xcd_slice_unit(id, n_slices(p.D), p.n_groups, 1);
+        if (!u.valid) return;
+        dc = u.dc_first;
+        sg = u.item / p.B;
+        b = u.item - sg * p.B;
+    } else {
+        const int q = id / p.B, per = p.n_groups / p.B;
+        b = id - q * p.B;
+        dc = q / per;
+        sg = q - dc * per;
+    }
+    OT* const dH = static_cast<OT*>(p.dH);
+    dh_sliced<T, BPW, WPB, OT, true>(static_cast<const T*>(p.W), p.bounds, p.perm, nullptr, dH, p.accumulate, !p.accumulate, p.S, p.D, p.V, p.n_vc, 0, dc,
+                                     sg, b);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -568,12 +568,16 @@ void launch_dw(int cpt, dim3 grid, size_t lds, hipStream_t st, const T* H, const
     }
 }
 
+// 32-bit byte offsets into W (one multiplication of 24-bit factors per entry) where W allows them.
+bool off32_w(const Shape& s) {
+    const size_t row = (size_t)s.D * (s.dtype == LSR_F32 ? 4 : 2);
+    return (size_t)s.V * row <= 0xffffffffull && s.V <= (1 << 24) && row < (1u << 24);
+}
 // One launch of the sliced dH gather (vocabulary chunk vc) / of the sliced dW gather (sequences b0 .. b0+nb-1).
 template <typename T, typename OT>
 void launch_dh_sliced(int bpw, int wpb, dim3 grid, hipStream_t st, const T* W, const int* bounds, const uint2* perm, const float* prev,
                       OT* dst, int add_dst, int write_all, const Shape& s, int n_groups, int n_vc, int vc, bool xcd_own) {
-    // 32-bit byte offsets into W (one multiply-add of 24-bit factors per gather) where W allows them
-    const bool off32 = (size_t)s.V * s.D * sizeof(T) <= 0xffffffffull && s.V <= (1 << 24) && (size_t)s.D * sizeof(T) < (1u << 24);
+    const bool off32 = off32_w(s);
 #define LSR_DH2(BPW, WPB, O32) hipLaunchKernelGGL((bwd_dh_sliced_kernel<T, BPW, WPB, OT, O32>), grid, dim3(dh_threads(WPB)), 0, st, W, bounds, \
                                                   perm, prev, dst, add_dst, write_all, s.B, s.S, s.D, s.V, n_groups, n_vc, vc, xcd_own ? 1 : 0)
 #define LSR_DH(BPW, WPB) do { if (off32) LSR_DH2(BPW, WPB, true); else LSR_DH2(BPW, WPB, false); } while (0)
@@ -585,6 +589,17 @@ void launch_dh_sliced(int bpw, int wpb, dim3 grid, hipStream_t st, const T* W, c
     else if constexpr (sizeof(T) == 2) LSR_DH(8, 1);
 #undef LSR_DH
 #undef LSR_DH2
+}
+template <typename T, typename OT>
+void launch_dh_dw(int bpw, int wpb, unsigned grid, size_t lds, hipStream_t st, const DhDwArgs& a) {
+#define LSR_DH_DW(BPW, WPB) hipLaunchKernelGGL((bwd_dh_dw_kernel<T, BPW, WPB, OT>), dim3(grid), dim3(dh_threads(WPB)), lds, st, a)
+    if (wpb == 4) LSR_DH_DW(1, 4);
+    else if (wpb == 2) LSR_DH_DW(1, 2);
+    else if (bpw == 1) LSR_DH_DW(1, 1);
+    else if (bpw == 2) LSR_DH_DW(2, 1);
+    else if (bpw == 4 || sizeof(T) == 4) LSR_DH_DW(4, 1);
+    else if constexpr (sizeof(T) == 2) LSR_DH_DW(8, 1);
+#undef LSR_DH_DW
 }
 template <typename T, typename OT>
 void launch_dw_sliced(dim3 grid, dim3 block, size_t lds, hipStream_t st, const T* H, const float* dY, const float* Y,
@@ -603,9 +618,9 @@ void launch_dw_sliced(dim3 grid, dim3 block, size_t lds, hipStream_t st, const T
 // work, join before returning control of the caller's stream.  The fork and the join cost the host about 30 us
 // (two event records, two waits), and two gathers at a time help while they leave each other's windows in L2:
 //   - up to AUX_MIN_GATHER_BYTES of worst-case gather traffic (2 * B * |V| rows of D elements) the host's time is
-//     the longer one (forward and backward, us, without -> with: B=2 S=16 D=64 |V|=1000 float32 42.6 -> 52.1; B=10 S=60
-//     D=512 |V|=10000 float32, 0.41 GB, 177 -> 172; B=13 S=197 D=312 |V|=31091, 0.5 GB, 193 -> 182; backward alone B=4 S=64
-//     D=512 |V|=20000, 0.16 GB, 55 -> 59, B=8 S=32 |V|=8000, 0.2 GB, 70 -> 71, B=2 S=128 |V|=30522, 0.19 GB, 64 -> 68);
+//     the longer one (forward and backward, us, without -> with: B=2 S=16 D=64 |V|=1000 float32 42.6 -> 52.1; backward alone B=4 S=64
+//     D=512 |V|=20000, 0.16 GB, 55 -> 59, B=8 S=32 |V|=8000, 0.2 GB, 70 -> 71, B=2 S=128 |V|=30522, 0.19 GB, 64 -> 68), and up to 0.9 GB
+//     dW shares a launch of the chain where it can (share_dw);
 //   - up to AUX_MAX_GATHER_BYTES it pays nearly everywhere (backward, dense; one gradient in twenty: B=30 S=80 D=256 |V|=25000
 //     101 -> 87; 62 -> 61, B=64 S=100 D=768 |V|=50000 646 -> 579; 195 -> 176, B=24 S=400 |V|=100000 674 -> 626; 411 -> 363,
 //     B=16 S=256 |V|=250002 1026 -> 988; 581 -> 566; but B=256 S=512 D=384 |V|=30522 955 -> 985; 463 -> 371);
@@ -687,6 +702,7 @@ private:
     std::unique_lock<std::mutex> lock_;
 };
 
+enum class DwShare { none, placement, dh };
 // Everything the backward launches is decided here, from the shape alone, before anything is enqueued.
 struct BwdLaunch {
     int cpt;                 // 16-byte chunks per thread of the whole-row kernels
@@ -700,6 +716,7 @@ struct BwdLaunch {
     bool dh_xcd_own;         // sliced dH gather: column slices owned by XCDs
     int dw_tile_passes;      // LDS-tile dW kernel: copy passes per tile (ceil(S / 128)), or 0 when it does not apply
     int dw_tile_vtiles;
+    DwShare share;           // whose launch the sliced dW gather may share
 };
 // The sliced dH gather with its column slices owned by XCDs (xcd_slice_unit).  In the slice-major order every
 // XCD fetches the slice's window of W for itself and sees one eighth of its reuse, which is B / 8 gathers
@@ -720,15 +737,42 @@ int dw_tile_passes(const Shape& s) {
     if (units < 256 || units > 0x7fffffffll) return 0;
     return (s.S + 127) / 128;
 }
-// Whether dW/db run on the auxiliary stream beside dH (see AUX_MIN_GATHER_BYTES).
-bool dw_beside_dh(const Shape& s, int n_vc, bool want_dw) {
-    const double gather_bytes = 2.0 * s.B * s.V * s.D * (s.dtype == LSR_F32 ? 4 : 2);
+double worst_gather_bytes(const Shape& s) { return 2.0 * s.B * s.V * s.D * (s.dtype == LSR_F32 ? 4 : 2); }
+// Whose launch the sliced dW gather shares where all of dW/db is one launch, in tiles of 32 rows or more.
+//   The dH gather's (bwd_dh_dw_kernel) where that gathers slices with 32-bit offsets, all its workgroups find room for a dW tile in
+//   LDS, and bfloat16 gradients need no staging: up to 0.9 GB of worst-case gathers, 0.6 GB with several vocabulary windows (dW then overlaps the
+//   first window alone).  Backward; forward and backward; the same through autograd, us, auxiliary stream (below 0.1 GB: one after the other) -> here:
+//     0.02 GB  B=1 S=21 D=312 |V|=18974 37 -> 29; 45 -> 36; 136 -> 133          0.07  B=6 S=11 D=312 |V|=9013 37 -> 26; 57 -> 45; 138 -> 135
+//     0.15  B=7 S=52 D=312 |V|=17108 56 -> 35; 77 -> 59; 201 -> 148             0.43  B=25 S=63 D=512 |V|=8494 95 -> 85; 123 -> 113; 204 -> 140
+//     0.47  B=10 S=32 D=312 |V|=18822 float32 76 -> 80; 132 -> 137; 194 -> 143  0.50  B=16 S=78 D=600 |V|=13048, one in twenty, 57 -> 43; 94 -> 84; 192 -> 145
+//     0.71  B=10 S=21 D=256 |V|=34715 float32 103 -> 100; 166 -> 163; 203 -> 163  0.86  B=14 S=38 D=512 |V|=29935, one in twenty, 50 -> 43; 80 -> 73; 198 -> 138
+//     not  1.02  B=17 S=41 D=200 |V|=37401 float32 129 -> 137, 1.27  B=32 S=32 D=200 |V|=24838 float32 131 -> 157, and with windows
+//     0.64  B=2 S=15 D=512 |V|=77818 float32, one in twenty, 71 -> 84, 1.06  B=4 S=151 D=512 |V|=65002 float32, one in twenty, 73 -> 99
+//   Else the placement's (bwd_place_dw_kernel): below 0.1 GB, and there always where a sequence is one segment, because the sort then is that launch
+//   alone (placement against dH: B=5 S=163 D=64 |V|=1936 15 and 17, B=17 S=49 D=128 |V|=3023 float32 28 and 35); up to 0.3 GB otherwise
+//     0.25  B=3 S=870 D=200 |V|=105469 72 -> 69; 191 -> 187; 220 -> 187         0.30  B=3 S=11 D=512 |V|=49397, one in twenty, 66 -> 54; 78 -> 75; 192 -> 145
+//     not  0.62  B=91 S=155 D=128 |V|=13260 91 -> 115; 163 -> 184, 0.82  B=8 S=26 D=768 |V|=17108 float32 93 -> 108
+DwShare share_dw(const Shape& s, const BwdWs& w, bool bf16_out) {
+    const int vt = dw_stage_rows(s);
+    if (dw_tile_passes(s) > 0 || vt < 32 || dw_batch_chunk(s) < s.B) return DwShare::none;
+    const double bytes = worst_gather_bytes(s);
+    const bool staged_place = s.S <= PLACE_MAX_S && w.seg_len <= PLACE_MAX_SEG;
+    if (bytes < AUX_MIN_GATHER_BYTES && staged_place && w.n_seg == 1) return DwShare::placement;
+    const int wg_per_cu = dh_waves_per_bucket(s, w.n_vc) == 2 ? 16 : 8;      // at eight waves per SIMD
+    if (sliced_gathers(s) && off32_w(s) && (w.n_vc == 1 || !bf16_out) && (size_t)s.B * vt * 8 * wg_per_cu <= 160 * 1024 &&
+        bytes < (w.n_vc == 1 ? 0.9e9 : 0.6e9))
+        return DwShare::dh;
+    return staged_place && bytes < 0.3e9 ? DwShare::placement : DwShare::none;
+}
+// Whether dW/db run on the auxiliary stream beside dH (see AUX_MAX_GATHER_BYTES).
+bool dw_beside_dh(const Shape& s, const BwdWs& w, bool want_dw, bool bf16_out) {
+    const double gather_bytes = worst_gather_bytes(s);
     const size_t h_slice = (size_t)s.B * s.S * DWS_COLS * (s.dtype == LSR_F32 ? 4 : 2);
     const bool tile = dw_tile_passes(s) > 0 && want_dw;      // dW gathers from LDS
-    const bool apart = gather_bytes <= AUX_MAX_GATHER_BYTES || (tile ? n_vc == 1 : sliced_gathers(s) && h_slice <= AUX_SMALL_SLICE_BYTES);
-    return gather_bytes >= AUX_MIN_GATHER_BYTES && apart;
+    const bool apart = gather_bytes <= AUX_MAX_GATHER_BYTES || (tile ? w.n_vc == 1 : sliced_gathers(s) && h_slice <= AUX_SMALL_SLICE_BYTES);
+    return gather_bytes >= AUX_MIN_GATHER_BYTES && apart && share_dw(s, w, bf16_out) == DwShare::none;
 }
-int plan_backward(const Shape& s, const BwdWs& w, BwdLaunch* L) {
+int plan_backward(const Shape& s, const BwdWs& w, bool bf16_out, BwdLaunch* L) {
     const int chunk_elems = s.dtype == LSR_F32 ? 4 : 8;
     const int n_chunks = s.D / chunk_elems;
     L->cpt = 1;
@@ -770,6 +814,12 @@ int plan_backward(const Shape& s, const BwdWs& w, BwdLaunch* L) {
         L->dw_ndc = L->dw_slice_groups = 0;
         L->dw_vtiles = (s.V + VT - 1) / VT;
     }
+    L->share = share_dw(s, w, bf16_out);
+    if (L->share == DwShare::dh) {
+        // one grid dimension for all workgroups of 256 threads and fewer
+        const long long n_dh = L->dh_xcd_own ? xcd_slice_grid(n_slices(s.D), L->dh_groups, 1) : (long long)L->dh_groups * n_slices(s.D);
+        if (n_dh + (long long)L->dw_vtiles * L->dw_slice_groups + 8 > 0xffffffffll / 256) L->share = DwShare::none;
+    }
     return LSR_OK;
 }
 
@@ -798,7 +848,7 @@ int backward_impl(const lsr_head_desc* desc, const void* H, const void* W, const
     const BwdWs w = bwd_ws(s, bf16_out);
     if (!ws || ws_bytes < w.total) return LSR_ERR_WORKSPACE;
     BwdLaunch L;
-    if ((rc = plan_backward(s, w, &L)) != LSR_OK) return rc;
+    if ((rc = plan_backward(s, w, bf16_out, &L)) != LSR_OK) return rc;
     int n_cus = 0;
     rc = check_device(&n_cus);
     if (rc != LSR_OK) return rc;
@@ -808,7 +858,7 @@ int backward_impl(const lsr_head_desc* desc, const void* H, const void* W, const
     char* base = static_cast<char*>(ws);
 
     // fork: dW/db on the auxiliary stream, the dH chain on the caller's
-    const bool overlap = !prof.on && dH && (dW || db) && dw_beside_dh(s, w.n_vc, dW != nullptr);
+    const bool overlap = !prof.on && dH && (dW || db) && dw_beside_dh(s, w, dW != nullptr, bf16_out);
     AuxFork lane(overlap ? aux_lane_of_current_device() : nullptr, st);
     const hipStream_t st_dw = lane.side();
 
@@ -838,9 +888,9 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
     // Positions in use per sequence, for the LDS-tile dW kernel where it runs behind dH on the same stream: left by the launch
     // that cuts the lists into windows, in place of the counts, which nothing reads after the placement.
     int* tops = dH && dW && w.n_vc > 1 && L.dw_tile_passes > 0 && st_dw == st ? cnt : nullptr;
-    // the sort and dW of small problems share a launch (what is profiled runs apart)
-    const bool small = dH && (dW || db) && L.one_sort && L.dw_sliced && L.dw_vt >= 32 &&
-                       L.dw_bc >= s.B && st_dw == st && !prof.on;
+    // launches that dW shares (what is profiled runs apart)
+    const bool shared = dH && (dW || db) && !prof.on;
+    const bool place_dw = shared && L.share == DwShare::placement, dh_dw = shared && L.share == DwShare::dh;
     int r;
     if (dH) {
         const dim3 seg_grid(w.n_seg, s.B);
@@ -860,15 +910,17 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
         prof.begin(2);
         const dim3 place_block(64 * PLACE_WAVES);
         const size_t place_lds = sizeof(int) * (PLACE_WAVES / 2) * s.S + sizeof(uint2) * w.seg_len;
-        if (small) {
+        if (place_dw) {
             const size_t lds_dw = (size_t)s.B * L.dw_vt * 8;
-#define LSR_SMALL(STEPS) hipLaunchKernelGGL((bwd_small_kernel<T, OT, STEPS>), dim3(s.B + L.dw_vtiles * L.dw_slice_groups), place_block, \
-                                            place_lds > lds_dw ? place_lds : lds_dw, st, H, dY, Y, I, bstart, perm, dW, db, accumulate, s.B, s.S, \
-                                            s.D, s.V, w.seg_len, w.key_bits, L.dw_vt, L.dw_ndc, L.dw_vtiles)
-            if (w.seg_len <= 4 * 64 * PLACE_WAVES) LSR_SMALL(4);
-            else if (w.seg_len <= 8 * 64 * PLACE_WAVES) LSR_SMALL(8);
-            else LSR_SMALL(16);
-#undef LSR_SMALL
+#define LSR_PLACE_DW2(STEPS, ONE) hipLaunchKernelGGL((bwd_place_dw_kernel<T, OT, STEPS, ONE>), dim3(s.B * w.n_seg + L.dw_vtiles * L.dw_slice_groups), \
+                                                     place_block, place_lds > lds_dw ? place_lds : lds_dw, st, H, dY, Y, I, cnt, bstart, perm, dW, db, \
+                                                     accumulate, s.B, s.S, s.D, s.V, w.n_seg, w.seg_len, w.key_bits, L.dw_vt, L.dw_ndc, L.dw_vtiles)
+#define LSR_PLACE_DW(STEPS) do { if (L.one_sort) LSR_PLACE_DW2(STEPS, true); else LSR_PLACE_DW2(STEPS, false); } while (0)
+            if (w.seg_len <= 4 * 64 * PLACE_WAVES) LSR_PLACE_DW(4);
+            else if (w.seg_len <= 8 * 64 * PLACE_WAVES) LSR_PLACE_DW(8);
+            else LSR_PLACE_DW(16);
+#undef LSR_PLACE_DW
+#undef LSR_PLACE_DW2
         } else if (L.staged_place) {
 #define LSR_PLACE2(STEPS, ONE) hipLaunchKernelGGL((bwd_place_staged_kernel<STEPS, ONE>), seg_grid, place_block, place_lds, st, dY, Y, I, cnt, \
                                                   bstart, perm, s.S, s.V, w.n_seg, w.seg_len, w.key_bits)
@@ -901,6 +953,18 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
                                            : dim3((unsigned)s.B, (unsigned)(L.dh_groups / s.B), (unsigned)n_slices(s.D));
             float* stage = reinterpret_cast<float*>(base + w.dh_stage_off);
             for (int vc = 0; vc < w.n_vc; ++vc) {
+                if (vc == 0 && dh_dw) {
+                    DhDwArgs a;
+                    a.H = H; a.W = W; a.dY = dY; a.Y = Y; a.I = I; a.bounds = bounds; a.perm = perm; a.dH = dH; a.dW = dW; a.db = db;
+                    a.accumulate = accumulate;
+                    a.B = s.B; a.S = s.S; a.D = s.D; a.V = s.V;
+                    a.n_groups = L.dh_groups; a.n_vc = w.n_vc; a.xcd_own = L.dh_xcd_own ? 1 : 0;
+                    a.VT = L.dw_vt; a.NDC = L.dw_ndc; a.n_vtiles = L.dw_vtiles;
+                    a.n_dw = L.dw_vtiles * L.dw_slice_groups; a.n_dw_pad = (a.n_dw + 7) / 8 * 8;
+                    const long long n_dh = L.dh_xcd_own ? xcd_slice_grid(n_slices(s.D), L.dh_groups, 1) : (long long)L.dh_groups * n_slices(s.D);
+                    launch_dh_dw<T, OT>(L.bpw, L.wpb, (unsigned)(a.n_dw_pad + n_dh), (size_t)s.B * L.dw_vt * 8, st, a);
+                    continue;
+                }
                 const bool last = vc + 1 == w.n_vc;
                 if (OUT_F32) {
                     // partial sums live in dH itself; the first chunk of a fresh result writes every bucket
@@ -922,7 +986,7 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
         prof.end(3);
         if ((r = launch_status()) != LSR_OK) return r;
     }
-    if ((dW || db) && !small) {
+    if ((dW || db) && !place_dw && !dh_dw) {
         prof.begin(4);
         const int VT = L.dw_vt;
         if (L.dw_tile_passes > 0 && dW) {
@@ -1162,7 +1226,7 @@ int lsr_head_plan_ex(const lsr_head_desc* desc, int32_t* plan, int slots) {
         w.n_vc, w.vc_len, dh_buckets_per_wave(s, w.n_vc), dw_stage_rows(s),
         dw_batch_chunk(s), f.n_chunks, fwd_seg(s), f.resident ? 1 : 0,
         dh_slices_owned(s) ? 1 : 0, dw_tile_passes(s), dh_waves_per_bucket(s, w.n_vc), f.window,
-        dw_beside_dh(s, w.n_vc, true) ? 1 : 0, fwd_few(s) ? 1 : 0};
+        dw_beside_dh(s, w, true, false) ? 1 : 0, fwd_few(s) ? 1 : 0};
     for (int i = 0; i < slots && i < LSR_PLAN_EX_SLOTS; ++i) plan[i] = all[i];
     return LSR_OK;
 }

@@ -55,3 +55,8 @@ def test_forward_backward_replayed_from_a_graph(B, S, D, V):
 def test_forked_backward_replayed_from_a_graph():
     # 0.22 GB of worst-case gathers: the dW gather runs on the library's auxiliary stream beside dH
     test_forward_backward_replayed_from_a_graph(24, 64, 256, 9000)
+
+
+def test_forked_lds_tile_backward_replayed_from_a_graph():
+    # the LDS-tile dW kernel on the auxiliary stream beside dH, which takes several windows
+    test_forward_backward_replayed_from_a_graph(3, 128, 128, 131100)

@@ -1026,3 +1026,82 @@ def test_rows_that_end_inside_a_slab(B, S, D, dtype):
         lsr.lsr_head_forward(*head._shape(), head.H, head.W, head.bias, head.mask, head.Y, index, head.ws_fwd)
         torch.cuda.synchronize()
         assert torch.equal(head.Y[:, 1::2], ref[0][:, 1::2]) and torch.equal(head.I[:, 1::2], ref[1][:, 1::2])
+
+
+@pytest.mark.parametrize("B,S,D,V,dtype,dy_keep", [
+    (4, 30, 128, 60000, "bf16", None),       # slices owned by XCDs; several windows: float32 gradients
+    (13, 64, 312, 9000, "bf16", 0.05),       # partly filled last slice
+    (20, 40, 256, 6000, "bf16", None),       # slices in grid order
+    (40, 48, 512, 4500, "bf16", None),       # the most LDS per workgroup
+    (30, 100, 128, 9000, "f32", 0.3),
+    (2, 20, 1024, 20000, "f32", None),       # windows in float32
+    (12, 300, 64, 33000, "bf16", None),      # several buckets per wave
+    (3, 700, 72, 5000, "bf16", None),        # whole-row dH: the placement's launch
+    (70, 9, 64, 5000, "f32", 0.05),          # too much LDS for the dH gather's workgroups: the placement's launch
+])
+def test_dw_in_the_launch_of_dh_or_of_the_placement(B, S, D, V, dtype, dy_keep):
+    """Against the oracle, and bit for bit against the profiled call, which launches dW apart; overwriting and accumulating,
+    in float32 and, for bfloat16 parameters, in bfloat16."""
+    inp = wl.make_custom(B, S, D, V, dtype=dtype, seed=B + S + V, len_lo=1, dy_keep=dy_keep)
+    dt = lsr.LSR_BF16 if dtype == "bf16" else lsr.LSR_F32
+    assert lsr.lsr_head_plan(B, S, D, V, dt)["dw_beside_dh"] == 0
+    run_case(inp)
+    head = DeviceHead(inp)
+    head.forward()
+    for t in (head.dH, head.dW, head.db):
+        t.fill_(float("nan"))
+    head.backward_profiled()
+    torch.cuda.synchronize()
+    ref = [t.clone() for t in (head.dH, head.dW, head.db)]
+    head.backward()
+    torch.cuda.synchronize()
+    for got, want in zip((head.dH, head.dW, head.db), ref):
+        assert torch.equal(got, want)
+    for gt in ((lsr.LSR_F32, lsr.LSR_BF16) if dtype == "bf16" else (lsr.LSR_F32,)):
+        td = torch.bfloat16 if gt == lsr.LSR_BF16 else torch.float32
+        ws = torch.empty(lsr.lsr_head_backward_ex_workspace_bytes(B, S, D, V, dt, gt, True), dtype=torch.uint8, device="cuda")
+        for accumulate in (False, True):
+            dH, dW = (torch.ones_like(t, dtype=td) for t in (head.dH, head.dW))
+            db = torch.ones_like(head.db)
+            lsr.lsr_head_backward_ex(*head._shape(), head.H, head.W, head.dY, head.Y, head.I, dH, dW, db, gt, accumulate, ws)
+            torch.cuda.synchronize()
+            one = 1.0 if accumulate else 0.0
+            for got, want in ((dH, ref[0]), (dW, ref[1])):
+                # one rounding to the output type (a result that windows add up is rounded once per window in float32)
+                scale = (want.abs() + one).double()
+                tol = 2.0 ** -8 * scale if gt == lsr.LSR_BF16 else 2.0 ** -21 * scale
+                assert bool(((got.double() - (want.double() + one)).abs() <= tol + 1e-6).all())
+            assert torch.allclose(db, ref[2] + one, rtol=1e-6, atol=1e-6)
+
+
+def test_two_host_threads_share_the_auxiliary_stream():
+    """dW beside dH from LDS and from L2, in two threads on two streams: bit for bit what each call gives alone."""
+    import threading
+    heads = [DeviceHead(wl.make_custom(*shape, seed=113, len_lo=1)) for shape in ((3, 128, 128, 131100), (65, 40, 256, 14000))]
+    alone, errors = [], []
+    for h in heads:
+        assert lsr.lsr_head_plan(*h._shape())["dw_beside_dh"] == 1
+        h.forward()
+        h.backward()
+        torch.cuda.synchronize()
+        alone.append([t.clone() for t in (h.dH, h.dW, h.db)])
+
+    def worker(h, want):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                for _ in range(20):
+                    for t in (h.dH, h.dW, h.db):
+                        t.fill_(float("nan"))
+                    h.backward()
+                    stream.synchronize()
+                    assert all(torch.equal(a, b) for a, b in zip((h.dH, h.dW, h.db), want))
+        except BaseException as exc:      # surfaced in the main thread
+            errors.append(repr(exc))
+
+    threads = [threading.Thread(target=worker, args=a) for a in zip(heads, alone)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
