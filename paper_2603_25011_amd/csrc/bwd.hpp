@@ -1203,6 +1203,11 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
 // left their number (`tops`; it does where dW runs behind dH): B=64 S=512 D=1024 |V|=250002, lengths 128..512, backward 3947 ->
 // 3806 us, one gradient in twenty 2582 -> 2344.  Eight lanes per row with the pairs in LDS took dW 1736 -> 1714 there,
 // B=16 S=256 |V|=250002 352 -> 344, B=32 S=128 D=1024 93.5 -> 90.
+// The sixteen waves take four fifths of a CU's registers, so waves of dH or of the sort would find room beside them.  Where dH takes several
+// windows that helps (backward, against a kernel that takes all registers: B=64 S=128 D=512 |V|=60000 442 -> 407 us, one gradient in twenty 212 ->
+// 185, B=16 S=256 |V|=250002 940 -> 927).  Where it has one, which it gathers all at once, it depends on the layout in memory (B=200 S=128 |V|=26630 772 ->
+// 906, B=128 S=256 |V|=30522 619 -> 696, B=32 S=128 208 -> 226, but B=200 S=128 D=512 |V|=32000 625 -> 576, B=48 S=160 D=1024 336 -> 326; 792, 654, 206, 643 and 337
+// with the eight-lane kernel before), so there the workgroup keeps the CU to itself: ALONE.
 // Not kept: (dY, Y, I) two sequences ahead (1701; 354), L2 touched two sequences ahead (1790; 372), the rows counted here
 // by ballots and LDS (1762; 410), 12 waves (2059; 441), two workgroups of 8 waves (-; 340, beside dH 923 -> 961 for the backward).
 // The next sequence's tile travels global -> LDS directly (LDS-DMA, no staging registers) into the other
@@ -1224,7 +1229,7 @@ template <int K> __device__ __forceinline__ uint32_t quad_lane(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, K * 0x55, 0xf, 0xf, true);       // quad_perm:[K, K, K, K]
 }
 
-template <typename OT, int PASSES>
+template <typename OT, int PASSES, bool ALONE>
 __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* __restrict__ H,
                                                                const float* __restrict__ dY,
                                                                const float* __restrict__ Y,
@@ -1236,6 +1241,7 @@ __global__ __launch_bounds__(DWT_ROWS) void bwd_dw_tile_kernel(const uint16_t* _
     constexpr int RPP = DWT_ROWS / 8;                      // tile rows per copy pass
     constexpr int TROWS = PASSES * RPP;                    // tile rows: S <= TROWS
     constexpr uint32_t TILE_B = (TROWS + 1) * ROW_B;       // two tiles, each followed by a row of zeros
+    if (ALONE) asm volatile("" ::: "v127");                // 128 registers: sixteen waves take all of a CU's
     __shared__ __attribute__((aligned(1024))) uint8_t s_tile[2 * TILE_B];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -993,8 +993,9 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
             // one launch for all sequences; the sums start from zero, so bfloat16 results need no staging
             if constexpr (sizeof(T) == 2) {
                 const dim3 grid((unsigned)L.dw_tile_vtiles * (unsigned)(s.D / DWS_COLS));
-#define LSR_DWT(NP) hipLaunchKernelGGL((bwd_dw_tile_kernel<OT, NP>), grid, dim3(DWT_ROWS), 0, st_dw, H, dY, Y, I, dW, accumulate, db, \
+#define LSR_DWT2(NP, ALONE) hipLaunchKernelGGL((bwd_dw_tile_kernel<OT, NP, ALONE>), grid, dim3(DWT_ROWS), 0, st_dw, H, dY, Y, I, dW, accumulate, db, \
                                        accumulate, tops, s.B, s.S, s.D, s.V, L.dw_tile_vtiles)
+#define LSR_DWT(NP) do { if (w.n_vc == 1) LSR_DWT2(NP, true); else LSR_DWT2(NP, false); } while (0)
                 switch (L.dw_tile_passes) {
                     case 1: LSR_DWT(1); break;
                     case 2: LSR_DWT(2); break;
@@ -1002,6 +1003,7 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
                     default: LSR_DWT(4); break;
                 }
 #undef LSR_DWT
+#undef LSR_DWT2
             }
         } else if (L.dw_sliced) {
             // four waves also where the tile has fewer row groups than that (16 rows of bf16: two): the
