@@ -20,7 +20,8 @@
  *     and the call returns without synchronising.
  *   - State.  The library keeps no per-problem state.  Per device it keeps one auxiliary stream and
  *     two events, created by the first backward call that uses them and kept until the process ends:
- *     problems of a certain size (from 0.1 GB of gathers on; the rule stands in lsr_head.hip) run the dW/db
+ *     problems of a certain size (above small ones, whose dW/db gather shares a launch of the dH chain, and below the largest, where it
+ *     runs behind; the rule stands in lsr_head.hip) run the dW/db
  *     gather on that stream beside the dH chain, forked from and joined back into `stream`, so the caller sees ordinary stream order.  The fork..join enqueue is
  *     serialised per device by a mutex inside the library, so any number of host threads may call
  *     into the library concurrently, each on its own stream and buffers (their dW gathers then

@@ -88,7 +88,8 @@ int lsr_gather_probe(const void* table, size_t window_bytes, int steps, int laun
  *   [14] waves that share a bucket of the dH gather (1: none, see [6])
  *   [15] float32: segments of the packed token list per window of a chunk (a chunk holds the sequences that begin in
  *        its window); 0 for bfloat16, whose chunks are [0] tiles long
- *   [16] 1 if dW and db run on the library's auxiliary stream beside dH where all three are requested
+ *   [16] 1 if dW and db run on the library's auxiliary stream beside dH where all three are requested, in float32
+ *        (lsr_head_dw_route answers for either type of gradients)
  *   [17] 1 if the forward is the one launch for calls of few tokens, which needs neither packing nor chunks: [0], [9], [10],
  *        [11] and [15] then describe the packed forward, which is not launched (the workspace is sized for it all the same)
  */
@@ -96,6 +97,19 @@ int lsr_gather_probe(const void* table, size_t window_bytes, int steps, int laun
 int lsr_head_plan(const lsr_head_desc* desc, int32_t* plan);
 #define LSR_PLAN_EX_SLOTS 18
 int lsr_head_plan_ex(const lsr_head_desc* desc, int32_t* plan, int slots);
+
+/*
+ * Where a backward with these options (NULL: float32 gradients) runs dW and db when dH, dW and db are all requested, as one of the
+ * values below in the HOST int `route` (no device needed, nothing is launched).  The profiled backward runs everything apart, on
+ * one stream.
+ */
+enum {
+    LSR_DW_BEHIND_DH = 0,           /* in launches of its own behind the dH chain, on the caller's stream */
+    LSR_DW_ON_AUX_STREAM = 1,       /* on the auxiliary stream, beside the dH chain */
+    LSR_DW_IN_PLACEMENT_LAUNCH = 2, /* in the launch of the bucket sort's placement */
+    LSR_DW_IN_DH_LAUNCH = 3         /* in the (first) launch of the dH gather */
+};
+int lsr_head_dw_route(const lsr_head_desc* desc, const lsr_backward_opts* opts, int32_t* route);
 
 #ifdef __cplusplus
 }

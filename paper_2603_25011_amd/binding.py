@@ -15,6 +15,7 @@ LSR_F32 = 0
 LSR_BF16 = 1
 LSR_PROFILE_SLOTS = 8
 LSR_STATIC_SCRATCH_BYTES = 16 << 20
+LSR_DW_BEHIND_DH, LSR_DW_ON_AUX_STREAM, LSR_DW_IN_PLACEMENT_LAUNCH, LSR_DW_IN_DH_LAUNCH = range(4)
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "liblsr_head.so")
@@ -69,6 +70,8 @@ def load_library():
     lib.lsr_head_plan.argtypes = [dp, ctypes.POINTER(ctypes.c_int32)]
     lib.lsr_head_plan_ex.restype = ctypes.c_int
     lib.lsr_head_plan_ex.argtypes = [dp, ctypes.POINTER(ctypes.c_int32), ctypes.c_int]
+    lib.lsr_head_dw_route.restype = ctypes.c_int
+    lib.lsr_head_dw_route.argtypes = [dp, op, ctypes.POINTER(ctypes.c_int32)]
     lib.lsr_mfma_peak_probe.restype = ctypes.c_int
     lib.lsr_mfma_peak_probe.argtypes = [ctypes.c_int64, ctypes.c_int, vp, ctypes.POINTER(ctypes.c_double), vp]
     lib.lsr_copy_probe.restype = ctypes.c_int
@@ -192,6 +195,15 @@ def lsr_head_plan_ex(B, S, D, V, hw_dtype):
     out = (ctypes.c_int32 * len(LSR_PLAN_EX_FIELDS))()
     _check(load_library().lsr_head_plan_ex(ctypes.byref(d), out, len(LSR_PLAN_EX_FIELDS)))
     return dict(zip(LSR_PLAN_EX_FIELDS, (int(x) for x in out)))
+
+
+def lsr_head_dw_route(B, S, D, V, hw_dtype, grad_dtype=LSR_F32) -> int:
+    """Where the backward runs dW and db (one of the LSR_DW_* values; no device needed)."""
+    d = _desc(B, S, D, V, hw_dtype)
+    o = _BackwardOpts(int(grad_dtype), 0)
+    route = ctypes.c_int32(0)
+    _check(load_library().lsr_head_dw_route(ctypes.byref(d), ctypes.byref(o), ctypes.byref(route)))
+    return int(route.value)
 
 
 def lsr_mfma_peak_probe(iters, launches, sink, stream=None):

@@ -1233,6 +1233,24 @@ int lsr_head_plan_ex(const lsr_head_desc* desc, int32_t* plan, int slots) {
     return LSR_OK;
 }
 
+int lsr_head_dw_route(const lsr_head_desc* desc, const lsr_backward_opts* opts, int32_t* route) {
+    Shape s;
+    int rc = check_desc(desc, &s);
+    if (rc != LSR_OK) return rc;
+    const int grad_dtype = opts ? opts->grad_dtype : LSR_F32;
+    if (grad_dtype != LSR_F32 && (grad_dtype != LSR_BF16 || s.dtype != LSR_BF16)) return LSR_ERR_DTYPE;
+    if (!route) return LSR_ERR_NULL;
+    if (s.S > 8192 || s.B > 6144) return LSR_ERR_SHAPE;
+    const bool bf16_out = grad_dtype == LSR_BF16;
+    const BwdWs w = bwd_ws(s, bf16_out);
+    BwdLaunch L;
+    if ((rc = plan_backward(s, w, bf16_out, &L)) != LSR_OK) return rc;
+    *route = L.share == DwShare::dh ? LSR_DW_IN_DH_LAUNCH
+             : L.share == DwShare::placement ? LSR_DW_IN_PLACEMENT_LAUNCH
+             : dw_beside_dh(s, w, true, bf16_out) ? LSR_DW_ON_AUX_STREAM : LSR_DW_BEHIND_DH;
+    return LSR_OK;
+}
+
 int lsr_head_plan(const lsr_head_desc* desc, int32_t* plan) { return lsr_head_plan_ex(desc, plan, LSR_PLAN_SLOTS); }
 
 const char* lsr_status_string(int status) {

@@ -224,3 +224,29 @@ def test_which_forwards_are_calls_of_few_tokens():
     for yes, no in lines:
         assert lsr.lsr_head_plan_ex(*yes)["fwd_few_tokens"] == 1, yes
         assert lsr.lsr_head_plan_ex(*no)["fwd_few_tokens"] == 0, no
+
+
+def test_where_dw_runs():
+    """dW/db in a launch of the dH chain, on the auxiliary stream beside it or behind it.  With several vocabulary windows of dH
+    bfloat16 gradients are staged and keep a launch of their own; the plan's dw_beside_dh is the answer for float32 ones."""
+    bf, f32 = lsr.LSR_BF16, lsr.LSR_F32
+    behind, aux, placement, dh = lsr.LSR_DW_BEHIND_DH, lsr.LSR_DW_ON_AUX_STREAM, lsr.LSR_DW_IN_PLACEMENT_LAUNCH, lsr.LSR_DW_IN_DH_LAUNCH
+    for shape, dt, as_f32, as_bf16 in (
+            ((8, 30, 128, 100000), bf, dh, aux), ((12, 40, 64, 100000), bf, dh, aux), ((4, 30, 128, 100000), bf, dh, placement),
+            ((13, 64, 312, 9000), bf, dh, dh), ((65, 40, 256, 14000), bf, aux, aux), ((64, 512, 1024, 250002), bf, behind, behind),
+            ((3, 128, 128, 131100), bf, aux, aux), ((6, 70, 128, 900), bf, placement, placement),
+            ((8, 30, 128, 50000), f32, dh, None), ((2, 16, 64, 1000), f32, placement, None)):
+        assert lsr.lsr_head_dw_route(*shape, dt) == as_f32, (shape, dt)
+        assert lsr.lsr_head_plan(*shape, dt)["dw_beside_dh"] == (as_f32 == aux)
+        if as_bf16 is not None:
+            assert lsr.lsr_head_dw_route(*shape, dt, lsr.LSR_BF16) == as_bf16, shape
+    for bad, status in (((2, 16, 60, 1000, bf, f32), 2), ((2, 16, 64, 1000, f32, bf), 3), ((2, 16, 64, 1000, bf, 9), 3),
+                        ((2, 8193, 64, 1000, bf, f32), 2), ((6145, 2, 64, 1000, bf, f32), 2)):
+        with pytest.raises(lsr.LsrError) as e:
+            lsr.lsr_head_dw_route(*bad)
+        assert e.value.status == status, bad
+    route = ctypes.c_int32(-5)
+    d = binding._desc(2, 16, 64, 1000, bf)
+    assert binding.load_library().lsr_head_dw_route(ctypes.byref(d), None, None) == 1
+    assert binding.load_library().lsr_head_dw_route(None, None, ctypes.byref(route)) == 1 and route.value == -5
+    assert binding.load_library().lsr_head_dw_route(ctypes.byref(d), None, ctypes.byref(route)) == 0 and route.value == placement
