@@ -1155,8 +1155,10 @@ struct DhDwArgs {
     int n_groups, n_vc, xcd_own;             // dH: as above
     int VT, NDC, n_vtiles, n_dw, n_dw_pad;   // dW: as above; its workgroups, and the same as a multiple of 8
 };
+// (Workgroups of four waves only: dW wants four, and its db sums are the same as in a launch of its own.)
 template <typename T, int BPW, int WPB, typename OT>
 __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu(8, 8))) void bwd_dh_dw_kernel(DhDwArgs p) {
+    static_assert(dh_threads(WPB) == 256, "workgroups of four waves");
     int id = blockIdx.x;
     if (id < p.n_dw_pad) {
         if (id >= p.n_dw) return;

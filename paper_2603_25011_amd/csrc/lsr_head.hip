@@ -594,7 +594,6 @@ template <typename T, typename OT>
 void launch_dh_dw(int bpw, int wpb, unsigned grid, size_t lds, hipStream_t st, const DhDwArgs& a) {
 #define LSR_DH_DW(BPW, WPB) hipLaunchKernelGGL((bwd_dh_dw_kernel<T, BPW, WPB, OT>), dim3(grid), dim3(dh_threads(WPB)), lds, st, a)
     if (wpb == 4) LSR_DH_DW(1, 4);
-    else if (wpb == 2) LSR_DH_DW(1, 2);
     else if (bpw == 1) LSR_DH_DW(1, 1);
     else if (bpw == 2) LSR_DH_DW(2, 1);
     else if (bpw == 4 || sizeof(T) == 4) LSR_DH_DW(4, 1);
@@ -739,8 +738,8 @@ int dw_tile_passes(const Shape& s) {
 }
 double worst_gather_bytes(const Shape& s) { return 2.0 * s.B * s.V * s.D * (s.dtype == LSR_F32 ? 4 : 2); }
 // Whose launch the sliced dW gather shares where all of dW/db is one launch, in tiles of 32 rows or more.
-//   The dH gather's (bwd_dh_dw_kernel) where that gathers slices with 32-bit offsets, all its workgroups find room for a dW tile in
-//   LDS, and bfloat16 gradients need no staging: up to 0.9 GB of worst-case gathers, 0.6 GB with several vocabulary windows (dW then overlaps the
+//   The dH gather's (bwd_dh_dw_kernel) where that gathers slices with 32-bit offsets in workgroups of four waves, a dW tile is at most an eighth of
+//   a CU's LDS, and bfloat16 gradients need no staging: up to 0.9 GB of worst-case gathers, 0.6 GB with several vocabulary windows (dW then overlaps the
 //   first window alone).  Backward; forward and backward; the same through autograd, us, auxiliary stream (below 0.1 GB: one after the other) -> here:
 //     0.02 GB  B=1 S=21 D=312 |V|=18974 37 -> 29; 45 -> 36; 136 -> 133          0.07  B=6 S=11 D=312 |V|=9013 37 -> 26; 57 -> 45; 138 -> 135
 //     0.15  B=7 S=52 D=312 |V|=17108 56 -> 35; 77 -> 59; 201 -> 148             0.43  B=25 S=63 D=512 |V|=8494 95 -> 85; 123 -> 113; 204 -> 140
@@ -748,6 +747,13 @@ double worst_gather_bytes(const Shape& s) { return 2.0 * s.B * s.V * s.D * (s.dt
 //     0.71  B=10 S=21 D=256 |V|=34715 float32 103 -> 100; 166 -> 163; 203 -> 163  0.86  B=14 S=38 D=512 |V|=29935, one in twenty, 50 -> 43; 80 -> 73; 198 -> 138
 //     not  1.02  B=17 S=41 D=200 |V|=37401 float32 129 -> 137, 1.27  B=32 S=32 D=200 |V|=24838 float32 131 -> 157, and with windows
 //     0.64  B=2 S=15 D=512 |V|=77818 float32, one in twenty, 71 -> 84, 1.06  B=4 S=151 D=512 |V|=65002 float32, one in twenty, 73 -> 99
+//     not where two waves share a bucket: the dW workgroups of such a launch have two waves too, which walk their tile in twice the rounds
+//     (backward; forward and backward; autograd, us, auxiliary stream -> two-wave launch: 0.89  B=15 S=52 D=1536 |V|=4855 float32 221 -> 367; 466 -> 614; 466 -> 615,
+//     0.85  B=18 S=76 D=832 |V|=14269 117 -> 187; 172 -> 243; 202 -> 243, 0.86  B=13 S=109 D=768 |V|=21410 95 -> 129; 147 -> 183; 205 -> 189, 0.83  B=15
+//     S=150 D=512 |V|=26974, one in twenty, 57 -> 65; 106 -> 121; 195 -> 138), and sum db in another order than four
+//     (the tile is what is counted: four waves that share a bucket keep 1 KiB of their own beside it, so at 39 and 40 sequences seven of eight
+//     workgroups fit, which still is the better side of the auxiliary stream: 0.77  B=39 S=6 D=256 |V|=9611 float32 111 -> 98; 162 -> 148; 163 -> 148,
+//     0.62  B=40 S=86 D=128 |V|=30092 63 -> 60; 116 -> 113; 196 -> 136; 0.52  B=40 S=56 D=256 |V|=6376 float32, one in twenty, 53 -> 36; 136 -> 127)
 //   Else the placement's (bwd_place_dw_kernel): below 0.1 GB, and there always where a sequence is one segment, because the sort then is that launch
 //   alone (placement against dH: B=5 S=163 D=64 |V|=1936 15 and 17, B=17 S=49 D=128 |V|=3023 float32 28 and 35); up to 0.3 GB otherwise
 //     0.25  B=3 S=870 D=200 |V|=105469 72 -> 69; 191 -> 187; 220 -> 187         0.30  B=3 S=11 D=512 |V|=49397, one in twenty, 66 -> 54; 78 -> 75; 192 -> 145
@@ -758,8 +764,8 @@ DwShare share_dw(const Shape& s, const BwdWs& w, bool bf16_out) {
     const double bytes = worst_gather_bytes(s);
     const bool staged_place = s.S <= PLACE_MAX_S && w.seg_len <= PLACE_MAX_SEG;
     if (bytes < AUX_MIN_GATHER_BYTES && staged_place && w.n_seg == 1) return DwShare::placement;
-    const int wg_per_cu = dh_waves_per_bucket(s, w.n_vc) == 2 ? 16 : 8;      // at eight waves per SIMD
-    if (sliced_gathers(s) && off32_w(s) && (w.n_vc == 1 || !bf16_out) && (size_t)s.B * vt * 8 * wg_per_cu <= 160 * 1024 &&
+    // (a tile of 32 rows means sliced gathers.  Eight workgroups of four waves are the eight waves per SIMD of the dH gather.)
+    if (dh_waves_per_bucket(s, w.n_vc) != 2 && off32_w(s) && (w.n_vc == 1 || !bf16_out) && (size_t)s.B * vt * 8 * 8 <= 160 * 1024 &&
         bytes < (w.n_vc == 1 ? 0.9e9 : 0.6e9))
         return DwShare::dh;
     return staged_place && bytes < 0.3e9 ? DwShare::placement : DwShare::none;
@@ -816,7 +822,7 @@ int plan_backward(const Shape& s, const BwdWs& w, bool bf16_out, BwdLaunch* L) {
     }
     L->share = share_dw(s, w, bf16_out);
     if (L->share == DwShare::dh) {
-        // one grid dimension for all workgroups of 256 threads and fewer
+        // one grid dimension for all workgroups, of 256 threads each
         const long long n_dh = L->dh_xcd_own ? xcd_slice_grid(n_slices(s.D), L->dh_groups, 1) : (long long)L->dh_groups * n_slices(s.D);
         if (n_dh + (long long)L->dw_vtiles * L->dw_slice_groups + 8 > 0xffffffffll / 256) L->share = DwShare::none;
     }

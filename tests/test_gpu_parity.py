@@ -1105,3 +1105,26 @@ def test_two_host_threads_share_the_auxiliary_stream():
     for t in threads:
         t.join()
     assert not errors, errors
+
+
+@pytest.mark.parametrize("B,S,D,V,dtype", [(19, 64, 896, 11500, "bf16"), (19, 64, 896, 5801, "f32")])
+def test_buckets_of_two_waves_leave_dw_a_launch_of_its_own(B, S, D, V, dtype):
+    """dW in workgroups of two waves would take up to 1.7 times as long, and sum db in another order: against the profiled call, which runs dW apart, where
+    float64 terms of 2^60 cancel in one order of the sums and not in another."""
+    dt = lsr.LSR_BF16 if dtype == "bf16" else lsr.LSR_F32
+    assert lsr.lsr_head_plan(B, S, D, V, dt)["dh_waves_per_bucket"] == 2
+    assert lsr.lsr_head_dw_route(B, S, D, V, dt) == lsr.LSR_DW_ON_AUX_STREAM
+    head = DeviceHead(wl.make_custom(B, S, D, V, dtype=dtype, seed=5))
+    head.forward()
+    head.Y.fill_(1e-12)                     # exp(-Y) = 1
+    head.dY[0], head.dY[2] = 2.0 ** 60, -2.0 ** 60
+    head.dY[1].fill_(1.0)
+    head.backward_profiled()
+    torch.cuda.synchronize()
+    apart = [t.clone() for t in (head.dH, head.dW, head.db)]
+    for t in (head.dH, head.dW, head.db):
+        t.fill_(float("nan"))
+    head.backward()
+    torch.cuda.synchronize()
+    for got, want in zip((head.dH, head.dW, head.db), apart):
+        assert torch.equal(got, want)
