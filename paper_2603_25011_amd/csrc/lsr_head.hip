@@ -754,16 +754,24 @@ double worst_gather_bytes(const Shape& s) { return 2.0 * s.B * s.V * s.D * (s.dt
 //     (the tile is what is counted: four waves that share a bucket keep 1 KiB of their own beside it, so at 39 and 40 sequences seven of eight
 //     workgroups fit, which still is the better side of the auxiliary stream: 0.77  B=39 S=6 D=256 |V|=9611 float32 111 -> 98; 162 -> 148; 163 -> 148,
 //     0.62  B=40 S=86 D=128 |V|=30092 63 -> 60; 116 -> 113; 196 -> 136; 0.52  B=40 S=56 D=256 |V|=6376 float32, one in twenty, 53 -> 36; 136 -> 127)
+//   Neither, from 0.1 GB on, for up to three sequences with several windows and a dW of more than SHARE_MAX_DW elements: dW is then bound by its own output and outlasts
+//   the window (or the placement) that it overlaps, and the others follow it (backward; forward and backward, us, auxiliary stream -> the launch of
+//   dH: B=1 S=69 D=1024 |V|=46510 91 -> 107; 108 -> 99, B=1 S=130 D=768 |V|=86259 float32, one in twenty, 98 -> 117; 256 -> 274, B=1 S=71 D=1536 |V|=71646
+//   217 -> 231; 272 -> 307; into the placement's B=1 S=11 D=832 |V|=28884 float32 82 -> 99; 109 -> 126).  Of 210 shapes with several windows none with
+//   more sequences lost (0.55 to 0.97; 0.8 to 1.01), and with up to three 73 below the line 0.58 to 1.06; 0.79 to 1.02 and 98 above it
+//   0.83 to 1.19; 0.85 to 1.13.
 //   Else the placement's (bwd_place_dw_kernel): below 0.1 GB, and there always where a sequence is one segment, because the sort then is that launch
 //   alone (placement against dH: B=5 S=163 D=64 |V|=1936 15 and 17, B=17 S=49 D=128 |V|=3023 float32 28 and 35); up to 0.3 GB otherwise
 //     0.25  B=3 S=870 D=200 |V|=105469 72 -> 69; 191 -> 187; 220 -> 187         0.30  B=3 S=11 D=512 |V|=49397, one in twenty, 66 -> 54; 78 -> 75; 192 -> 145
 //     not  0.62  B=91 S=155 D=128 |V|=13260 91 -> 115; 163 -> 184, 0.82  B=8 S=26 D=768 |V|=17108 float32 93 -> 108
+constexpr double SHARE_MAX_DW = 17.5e6;      // 70 MB in float32
 DwShare share_dw(const Shape& s, const BwdWs& w, bool bf16_out) {
     const int vt = dw_stage_rows(s);
     if (dw_tile_passes(s) > 0 || vt < 32 || dw_batch_chunk(s) < s.B) return DwShare::none;
     const double bytes = worst_gather_bytes(s);
     const bool staged_place = s.S <= PLACE_MAX_S && w.seg_len <= PLACE_MAX_SEG;
     if (bytes < AUX_MIN_GATHER_BYTES && staged_place && w.n_seg == 1) return DwShare::placement;
+    if (bytes >= AUX_MIN_GATHER_BYTES && w.n_vc > 1 && s.B <= 3 && (double)s.V * s.D > SHARE_MAX_DW) return DwShare::none;
     // (a tile of 32 rows means sliced gathers.  Eight workgroups of four waves are the eight waves per SIMD of the dH gather.)
     if (dh_waves_per_bucket(s, w.n_vc) != 2 && off32_w(s) && (w.n_vc == 1 || !bf16_out) && (size_t)s.B * vt * 8 * 8 <= 160 * 1024 &&
         bytes < (w.n_vc == 1 ? 0.9e9 : 0.6e9))

@@ -235,6 +235,9 @@ def test_where_dw_runs():
             ((8, 30, 128, 100000), bf, dh, aux), ((12, 40, 64, 100000), bf, dh, aux), ((4, 30, 128, 100000), bf, dh, placement),
             ((13, 64, 312, 9000), bf, dh, dh), ((65, 40, 256, 14000), bf, aux, aux), ((64, 512, 1024, 250002), bf, behind, behind),
             ((3, 128, 128, 131100), bf, aux, aux), ((6, 70, 128, 900), bf, placement, placement),
+            # up to three sequences with several windows: by the size of dW
+            ((1, 69, 1024, 46510), bf, aux, aux), ((1, 14, 600, 90968), bf, aux, aux), ((3, 737, 1024, 17089), f32, dh, None), ((3, 737, 1024, 17090), f32, aux, None),
+            ((4, 15, 512, 55539), bf, dh, aux), ((2, 51, 600, 20036), f32, dh, None), ((1, 30, 600, 32769), bf, dh, placement),
             ((20, 64, 832, 12160), bf, aux, aux), ((5, 143, 1536, 14121), f32, aux, None), ((13, 109, 768, 21410), bf, aux, aux),      # two waves per bucket
             ((8, 30, 128, 50000), f32, dh, None), ((2, 16, 64, 1000), f32, placement, None)):
         assert lsr.lsr_head_dw_route(*shape, dt) == as_f32, (shape, dt)
