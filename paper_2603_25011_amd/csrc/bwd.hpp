@@ -333,8 +333,12 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_kernel(const float
 //      slot of the bucket - its first local slot;
 //   3. steps of 64 pairs per wave: ballot ranking, staging;
 //   4. local slot k goes to global slot k + s_delta[bucket of k].
-// A staged pair is (v - vbeg) | bucket << 12 and g.   dynamic LDS: PLACE_WAVES / 2 * S ints + seg_len pairs.
-// STEPS: steps of 64 per wave, at least seg_len / (64 * PLACE_WAVES); steps behind the end of a piece are left out.
+// A staged pair is (v - vbeg) | bucket << 12 and g.   dynamic LDS: NW / 2 * S ints + seg_len pairs.
+// NW: waves per segment.  PLACE_WAVES, and PLACE_ONE_WAVES where a sequence is one segment and the sort is this launch: a single workgroup has the whole
+// sequence then, whose steps follow one another (dH alone, us, segments of 512 entries in three launches -> one of four waves -> of eight: B=1 S=163 D=256
+// |V|=3856 20.1 -> 23.9 -> 17.9, one in twenty B=102 S=175 D=256 |V|=4016 20.0 -> 25.2 -> 18.6, B=62 S=4 D=1024 |V|=1032 19.3 -> 14.0 -> 13.4; 80 shapes of 1025
+// to 4096 entries 0.92 with four, the worst 1.26, 0.77 with eight, the worst 0.93).
+// STEPS: steps of 64 per wave, at least seg_len / (64 * NW); steps behind the end of a piece are left out.
 // Counts and slots of two waves share an int (a segment has at most 4096), and the deltas take their place once all is
 // staged, because the LDS decides how many workgroups a CU holds.  Against an int per wave, deltas of their own and every
 // step taken: B=64 S=512 |V|=250002 158 -> 119 us, B=256 S=1024 |V|=33700 98 -> 72 and, with one gradient in twenty, 86 -> 53
@@ -342,17 +346,18 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_kernel(const float
 // ---------------------------------------------------------------------------------------------
 constexpr int PLACE_MAX_S = 1024;
 constexpr int PLACE_MAX_SEG = 4096;
+constexpr int PLACE_ONE_WAVES = 8;
 
-template <int STEPS, bool ONE>
+template <int STEPS, int NW, bool ONE>
 __device__ __forceinline__ void place_staged(const float* __restrict__ dY, const float* __restrict__ Y, const int* __restrict__ I,
                                              const int* __restrict__ cnt, int* bstart, uint2* __restrict__ perm,
                                              int S, int V, int n_seg, int seg_len, int key_bits, int seg, int b) {
-    constexpr int NT = 64 * PLACE_WAVES;
+    constexpr int NT = 64 * NW;
     extern __shared__ __attribute__((aligned(16))) int s_place[];
     uint2* s_stage = reinterpret_cast<uint2*>(s_place);             // [seg_len]
-    unsigned* s_cnt = reinterpret_cast<unsigned*>(s_place + 2 * seg_len);      // [PLACE_WAVES / 2][S]: counts of waves 2 i and 2 i + 1
+    unsigned* s_cnt = reinterpret_cast<unsigned*>(s_place + 2 * seg_len);      // [NW / 2][S]: counts of waves 2 i and 2 i + 1
     int* s_delta = s_place + 2 * seg_len;                           // [S] global slot - local slot, in the same place at the end
-    __shared__ int s_wave[PLACE_WAVES];
+    __shared__ int s_wave[NW];
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = wave & 1;
@@ -362,7 +367,7 @@ __device__ __forceinline__ void place_staged(const float* __restrict__ dY, const
     int* const b0 = bstart + (size_t)b * (S + 1);
 
     // 1. this wave's piece
-    const int piece = (seg_len / 64 + PLACE_WAVES - 1) / PLACE_WAVES * 64;       // (seg_len is a multiple of 64)
+    const int piece = (seg_len / 64 + NW - 1) / NW * 64;       // (seg_len is a multiple of 64)
     const int vseg = seg * seg_len, n = min(V - vseg, seg_len);
     const int vbeg = vseg + min(n, wave * piece), vend = vseg + min(n, (wave + 1) * piece);
     const size_t row = (size_t)b * V;
@@ -377,7 +382,7 @@ __device__ __forceinline__ void place_staged(const float* __restrict__ dY, const
         key[i] = ok ? clamp_pos(I[row + v], S) : 0;
         g[i] = gate_grad(dy, y);                // 0 for lanes past the end (dy = 0, y = 0)
     }
-    for (int s = tid; s < PLACE_WAVES / 2 * S; s += NT) s_cnt[s] = 0;
+    for (int s = tid; s < NW / 2 * S; s += NT) s_cnt[s] = 0;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < STEPS; ++i)
@@ -390,12 +395,12 @@ __device__ __forceinline__ void place_staged(const float* __restrict__ dY, const
     int sum = 0;
     for (int s = lo; s < hi; ++s)
 #pragma unroll
-        for (int w = 0; w < PLACE_WAVES / 2; ++w) {
+        for (int w = 0; w < NW / 2; ++w) {
             const unsigned c = s_cnt[w * S + s];
             sum += (int)((c & 0xffffu) + (c >> 16));
         }
     int total;
-    int run = exclusive_scan<PLACE_WAVES>(sum, s_wave, &total);
+    int run = exclusive_scan<NW>(sum, s_wave, &total);
     int delta[PLACE_MAX_S / NT];
 #pragma unroll
     for (int u = 0; u < PLACE_MAX_S / NT; ++u) {
@@ -404,7 +409,7 @@ __device__ __forceinline__ void place_staged(const float* __restrict__ dY, const
             if (ONE) b0[s] = run;
             delta[u] = ONE ? 0 : b0[s] + c0[s] - run;
 #pragma unroll
-            for (int w = 0; w < PLACE_WAVES / 2; ++w) {
+            for (int w = 0; w < NW / 2; ++w) {
                 const unsigned c = s_cnt[w * S + s];
                 const int next = run + (int)(c & 0xffffu);
                 s_cnt[w * S + s] = (unsigned)run | (unsigned)next << 16;
@@ -442,15 +447,15 @@ __device__ __forceinline__ void place_staged(const float* __restrict__ dY, const
         perm[row + k + s_delta[e.x >> 12]] = make_uint2((unsigned)vseg + (e.x & 4095u), e.y);
     }
 }
-template <int STEPS, bool ONE>
-__global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_staged_kernel(const float* __restrict__ dY,
+template <int STEPS, int NW, bool ONE>
+__global__ __launch_bounds__(64 * NW) void bwd_place_staged_kernel(const float* __restrict__ dY,
                                                                const float* __restrict__ Y,
                                                                const int* __restrict__ I,
                                                                const int* __restrict__ cnt,
                                                                int* bstart,
                                                                uint2* __restrict__ perm,
                                                                int S, int V, int n_seg, int seg_len, int key_bits) {
-    place_staged<STEPS, ONE>(dY, Y, I, cnt, bstart, perm, S, V, n_seg, seg_len, key_bits, blockIdx.x, blockIdx.y);
+    place_staged<STEPS, NW, ONE>(dY, Y, I, cnt, bstart, perm, S, V, n_seg, seg_len, key_bits, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -876,7 +881,7 @@ __global__ __launch_bounds__(256) void bwd_place_dw_kernel(const T* __restrict__
     const int i = (int)blockIdx.x - B * n_seg;
     if (i < 0) {
         const int b = (int)blockIdx.x / n_seg;
-        place_staged<STEPS, ONE>(dY, Y, I, cnt, bstart, perm, S, V, n_seg, seg_len, key_bits, (int)blockIdx.x - b * n_seg, b);
+        place_staged<STEPS, PLACE_WAVES, ONE>(dY, Y, I, cnt, bstart, perm, S, V, n_seg, seg_len, key_bits, (int)blockIdx.x - b * n_seg, b);
     } else {
         dw_sliced<T, false, OT>(H, dY, Y, I, nullptr, dW, accumulate, db, accumulate, 0, B, S, D, V, VT, NDC, i % n_vtiles, i / n_vtiles);
     }

@@ -923,11 +923,11 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
         }
         prof.begin(2);
         const dim3 place_block(64 * PLACE_WAVES);
-        const size_t place_lds = sizeof(int) * (PLACE_WAVES / 2) * s.S + sizeof(uint2) * w.seg_len;
+        auto place_lds = [&](int waves) { return sizeof(int) * (waves / 2) * s.S + sizeof(uint2) * w.seg_len; };
         if (place_dw) {
-            const size_t lds_dw = (size_t)s.B * L.dw_vt * 8;
+            const size_t lds = place_lds(PLACE_WAVES), lds_dw = (size_t)s.B * L.dw_vt * 8;
 #define LSR_PLACE_DW2(STEPS, ONE) hipLaunchKernelGGL((bwd_place_dw_kernel<T, OT, STEPS, ONE>), dim3(s.B * w.n_seg + L.dw_vtiles * L.dw_slice_groups), \
-                                                     place_block, place_lds > lds_dw ? place_lds : lds_dw, st, H, dY, Y, I, cnt, bstart, perm, dW, db, \
+                                                     place_block, lds > lds_dw ? lds : lds_dw, st, H, dY, Y, I, cnt, bstart, perm, dW, db, \
                                                      accumulate, s.B, s.S, s.D, s.V, w.n_seg, w.seg_len, w.key_bits, L.dw_vt, L.dw_ndc, L.dw_vtiles)
 #define LSR_PLACE_DW(STEPS) do { if (L.one_sort) LSR_PLACE_DW2(STEPS, true); else LSR_PLACE_DW2(STEPS, false); } while (0)
             if (w.seg_len <= 4 * 64 * PLACE_WAVES) LSR_PLACE_DW(4);
@@ -936,9 +936,10 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
 #undef LSR_PLACE_DW
 #undef LSR_PLACE_DW2
         } else if (L.staged_place) {
-#define LSR_PLACE2(STEPS, ONE) hipLaunchKernelGGL((bwd_place_staged_kernel<STEPS, ONE>), seg_grid, place_block, place_lds, st, dY, Y, I, cnt, \
-                                                  bstart, perm, s.S, s.V, w.n_seg, w.seg_len, w.key_bits)
-#define LSR_PLACE(STEPS) do { if (L.one_sort) LSR_PLACE2(STEPS, true); else LSR_PLACE2(STEPS, false); } while (0)
+#define LSR_PLACE2(STEPS, NW, ONE) hipLaunchKernelGGL((bwd_place_staged_kernel<STEPS, NW, ONE>), seg_grid, dim3(64 * NW), place_lds(NW), st, dY, Y, I, cnt, \
+                                                      bstart, perm, s.S, s.V, w.n_seg, w.seg_len, w.key_bits)
+#define LSR_PLACE(STEPS) do { if (L.one_sort) LSR_PLACE2(STEPS / 2, PLACE_ONE_WAVES, true); else LSR_PLACE2(STEPS, PLACE_WAVES, false); } while (0)
+            static_assert(PLACE_ONE_WAVES == 2 * PLACE_WAVES, "half the steps");
             if (w.seg_len <= 4 * 64 * PLACE_WAVES) LSR_PLACE(4);
             else if (w.seg_len <= 8 * 64 * PLACE_WAVES) LSR_PLACE(8);
             else LSR_PLACE(16);
