@@ -334,7 +334,7 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_kernel(const float
 //   3. steps of 64 pairs per wave: ballot ranking, staging;
 //   4. local slot k goes to global slot k + s_delta[bucket of k].
 // A staged pair is (v - vbeg) | bucket << 12 and g.   dynamic LDS: NW / 2 * S ints + seg_len pairs.
-// NW: waves per segment.  PLACE_WAVES, and PLACE_ONE_WAVES where a sequence is one segment and the sort is this launch: a single workgroup has the whole
+// NW: waves per segment.  PLACE_WAVES, and PLACE_ONE_WAVES where a sequence is one segment and dW has launches of its own: a single workgroup has the whole
 // sequence then, whose steps follow one another (dH alone, us, segments of 512 entries in three launches -> one of four waves -> of eight: B=1 S=163 D=256
 // |V|=3856 20.1 -> 23.9 -> 17.9, one in twenty B=102 S=175 D=256 |V|=4016 20.0 -> 25.2 -> 18.6, B=62 S=4 D=1024 |V|=1032 19.3 -> 14.0 -> 13.4; 80 shapes of 1025
 // to 4096 entries 0.92 with four, the worst 1.26, 0.77 with eight, the worst 0.93).

@@ -706,7 +706,7 @@ enum class DwShare { none, placement, dh };
 struct BwdLaunch {
     int cpt;                 // 16-byte chunks per thread of the whole-row kernels
     bool staged_place;       // the bucket sort places through LDS
-    bool one_sort;           // ... and is one launch, because a sequence is one segment
+    bool one_sort;           // ... and is one launch, because a sequence is one segment (but see backward_impl)
     bool dh_sliced;          // column-sliced dH gather, else whole rows
     int bpw, wpb, dh_groups; // buckets per wave, waves per bucket and workgroups per slice of the sliced dH gather
     int dw_vt;               // rows of the dW staging tile: sliced gather if dw_sliced, else whole-row kernel
@@ -873,6 +873,12 @@ int backward_impl(const lsr_head_desc* desc, const void* H, const void* W, const
 
     // fork: dW/db on the auxiliary stream, the dH chain on the caller's
     const bool overlap = !prof.on && dH && (dW || db) && dw_beside_dh(s, w, dW != nullptr, bf16_out);
+    // A sort of one launch ends before a dW of more than 384 sequences (whole rows, or several launches) has begun, and the two then gather from
+    // the first workgroup on side by side; behind a count and a scan dH comes when dW has the chip.  Backward, us, one launch -> three (the same segments):
+    // B=2887 S=29 D=384 |V|=1430 2422 -> 1308, B=781 S=7 D=1024 |V|=3128 853 -> 660, B=2995 S=6 D=256 |V|=1324 float32, one in twenty, 250 -> 161; not
+    // B=2292 S=50 D=256 |V|=3692 2351 -> 2898, B=1782 S=38 D=768 |V|=740 828 -> 973; 70 shapes 0.97 in the mean, and with up to 384
+    // sequences 1.03 (one in twenty B=255 S=44 D=256 |V|=815 float32 44 -> 53).
+    if (overlap && s.B > 384) L.one_sort = false;
     AuxFork lane(overlap ? aux_lane_of_current_device() : nullptr, st);
     const hipStream_t st_dw = lane.side();
 
@@ -938,7 +944,9 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
         } else if (L.staged_place) {
 #define LSR_PLACE2(STEPS, NW, ONE) hipLaunchKernelGGL((bwd_place_staged_kernel<STEPS, NW, ONE>), seg_grid, dim3(64 * NW), place_lds(NW), st, dY, Y, I, cnt, \
                                                       bstart, perm, s.S, s.V, w.n_seg, w.seg_len, w.key_bits)
-#define LSR_PLACE(STEPS) do { if (L.one_sort) LSR_PLACE2(STEPS / 2, PLACE_ONE_WAVES, true); else LSR_PLACE2(STEPS, PLACE_WAVES, false); } while (0)
+#define LSR_PLACE(STEPS) do { if (L.one_sort) LSR_PLACE2(STEPS / 2, PLACE_ONE_WAVES, true); \
+                              else if (w.n_seg == 1) LSR_PLACE2(STEPS / 2, PLACE_ONE_WAVES, false); \
+                              else LSR_PLACE2(STEPS, PLACE_WAVES, false); } while (0)
             static_assert(PLACE_ONE_WAVES == 2 * PLACE_WAVES, "half the steps");
             if (w.seg_len <= 4 * 64 * PLACE_WAVES) LSR_PLACE(4);
             else if (w.seg_len <= 8 * 64 * PLACE_WAVES) LSR_PLACE(8);

@@ -1128,3 +1128,24 @@ def test_buckets_of_two_waves_leave_dw_a_launch_of_its_own(B, S, D, V, dtype):
     torch.cuda.synchronize()
     for got, want in zip((head.dH, head.dW, head.db), apart):
         assert torch.equal(got, want)
+
+
+def test_sort_of_one_segment_beside_a_dw_of_many_sequences():
+    """More than 384 sequences with dW on the auxiliary stream: one segment, counted, scanned and placed in three launches; the profiled
+    call sorts in one."""
+    B, S, D, V = 450, 12, 128, 700
+    assert lsr.lsr_head_dw_route(B, S, D, V, lsr.LSR_BF16) == lsr.LSR_DW_ON_AUX_STREAM
+    assert lsr.lsr_head_plan(B, S, D, V, lsr.LSR_BF16)["sort_segments"] == 1
+    inp = wl.make_custom(B, S, D, V, seed=9, len_lo=1)
+    run_case(inp)
+    head = DeviceHead(inp)
+    head.forward()
+    head.backward()
+    torch.cuda.synchronize()
+    ref = [t.clone() for t in (head.dH, head.dW, head.db)]
+    for t in (head.dH, head.dW, head.db):
+        t.fill_(float("nan"))
+    head.backward_profiled()
+    torch.cuda.synchronize()
+    for got, want in zip((head.dH, head.dW, head.db), ref):
+        assert torch.equal(got, want)
