@@ -1212,9 +1212,13 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
 // B=16 S=256 |V|=250002 352 -> 344, B=32 S=128 D=1024 93.5 -> 90.
 // The sixteen waves take four fifths of a CU's registers, so waves of dH or of the sort would find room beside them.  Where dH takes several
 // windows that helps (backward, against a kernel that takes all registers: B=64 S=128 D=512 |V|=60000 442 -> 407 us, one gradient in twenty 212 ->
-// 185, B=16 S=256 |V|=250002 940 -> 927).  Where it has one, which it gathers all at once, it depends on the layout in memory (B=200 S=128 |V|=26630 772 ->
-// 906, B=128 S=256 |V|=30522 619 -> 696, B=32 S=128 208 -> 226, but B=200 S=128 D=512 |V|=32000 625 -> 576, B=48 S=160 D=1024 336 -> 326; 792, 654, 206, 643 and 337
-// with the eight-lane kernel before), so there the workgroup keeps the CU to itself: ALONE.
+// 185, B=16 S=256 |V|=250002 940 -> 927).  Where it has one, which it gathers all at once, it slows the gather of dW's first rounds down, which is worth it
+// only if dH would otherwise have to wait for the end.  Workgroups that do not come out at full rounds of 256 CUs leave CUs to dH in the last one, so there the
+// workgroup keeps its CU to itself: ALONE (128 registers by name: sixteen waves of them are all a CU has).  Backward, us, beside -> ALONE: 1.27
+// rounds, B=200 S=128 |V|=26630, 910 -> 779, 1.41, B=128 S=256 |V|=30522, 728 -> 638, 1.06, B=171 S=151 D=1024 |V|=16875, 689 -> 548; 70 shapes
+// 0.96 in the mean, 11 above 1.03, the worst B=88 S=485 D=2048 |V|=24738 (3.1, one in twenty) 786 -> 856.  Full rounds: one, B=200 S=128 D=512
+// |V|=32000, 581 -> 627, one in twenty B=9 S=374 D=2048 |V|=7285 53 -> 59, two, B=4 S=438 D=1024 |V|=31989, 81 -> 90; 50
+// shapes of one round 1.04 in the mean, 45 of two and three 1.03.
 // Not kept: (dY, Y, I) two sequences ahead (1701; 354), L2 touched two sequences ahead (1790; 372), the rows counted here
 // by ballots and LDS (1762; 410), 12 waves (2059; 441), two workgroups of 8 waves (-; 340, beside dH 923 -> 961 for the backward).
 // The next sequence's tile travels global -> LDS directly (LDS-DMA, no staging registers) into the other

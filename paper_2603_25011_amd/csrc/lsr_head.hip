@@ -1018,7 +1018,8 @@ int backward_launches(const Shape& s, const BwdWs& w, const BwdLaunch& L, const 
                 const dim3 grid((unsigned)L.dw_tile_vtiles * (unsigned)(s.D / DWS_COLS));
 #define LSR_DWT2(NP, ALONE) hipLaunchKernelGGL((bwd_dw_tile_kernel<OT, NP, ALONE>), grid, dim3(DWT_ROWS), 0, st_dw, H, dY, Y, I, dW, accumulate, db, \
                                        accumulate, tops, s.B, s.S, s.D, s.V, L.dw_tile_vtiles)
-#define LSR_DWT(NP) do { if (w.n_vc == 1) LSR_DWT2(NP, true); else LSR_DWT2(NP, false); } while (0)
+                const bool alone = w.n_vc == 1 && grid.x % 256 != 0;
+#define LSR_DWT(NP) do { if (alone) LSR_DWT2(NP, true); else LSR_DWT2(NP, false); } while (0)
                 switch (L.dw_tile_passes) {
                     case 1: LSR_DWT(1); break;
                     case 2: LSR_DWT(2); break;
