@@ -5,6 +5,7 @@ result on the same inputs."""
 import pytest
 import torch
 
+from paper_2603_25011_amd import binding as lsr
 from paper_2603_25011_amd import inputs as wl
 from paper_2603_25011_amd.harness import DeviceHead
 
@@ -12,8 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("B,S,D,V", [
-    (6, 70, 128, 900),        # small: the dW gather runs on the library's auxiliary stream beside dH
-    (3, 40, 64, 70000),       # dH gathered in three vocabulary chunks (three launches in the graph)
+    (6, 70, 128, 900),        # small: the sort and dW in one launch
+    (3, 40, 64, 70000),       # dH gathered in three vocabulary chunks (three launches in the graph), dW in the first one's launch
 ])
 def test_forward_backward_replayed_from_a_graph(B, S, D, V):
     inp = wl.make_custom(B, S, D, V, seed=B * 100 + S, len_lo=3)
@@ -53,10 +54,15 @@ def test_forward_backward_replayed_from_a_graph(B, S, D, V):
 
 
 def test_forked_backward_replayed_from_a_graph():
-    # 0.22 GB of worst-case gathers: the dW gather runs on the library's auxiliary stream beside dH
-    test_forward_backward_replayed_from_a_graph(24, 64, 256, 9000)
+    # the sliced dW gather on the library's auxiliary stream beside dH
+    shape = (65, 40, 256, 5000)
+    assert lsr.lsr_head_dw_route(*shape, lsr.LSR_BF16) == lsr.LSR_DW_ON_AUX_STREAM and lsr.lsr_head_plan(*shape, lsr.LSR_BF16)["dw_lds_tile_passes"] == 0
+    test_forward_backward_replayed_from_a_graph(*shape)
 
 
 def test_forked_lds_tile_backward_replayed_from_a_graph():
     # the LDS-tile dW kernel on the auxiliary stream beside dH, which takes several windows
-    test_forward_backward_replayed_from_a_graph(3, 128, 128, 131100)
+    shape = (3, 128, 128, 131100)
+    plan = lsr.lsr_head_plan(*shape, lsr.LSR_BF16)
+    assert lsr.lsr_head_dw_route(*shape, lsr.LSR_BF16) == lsr.LSR_DW_ON_AUX_STREAM and plan["dw_lds_tile_passes"] == 1 and plan["dh_chunks"] > 1
+    test_forward_backward_replayed_from_a_graph(*shape)

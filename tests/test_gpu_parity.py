@@ -52,7 +52,7 @@ def test_c1_tiny_fp32_forward_backward():
     (7, 48, 64, 300, 5),        # one or two blocks per sequence
     (5, 100, 192, 513, 3),      # up to four blocks per sequence
     (3, 300, 256, 1000, 200),   # sequences that straddle tiles
-    (2, 129, 200, 260, 1),      # K tail (D not a multiple of 64): register-staged loader
+    (2, 129, 200, 260, 1),      # rows that end inside a slab (D not a multiple of 64)
     (4, 1, 64, 257, 1),         # S = 1: a plain linear layer; few tokens, one launch
     (70, 1, 64, 257, 1),        # S = 1 through the packed forward
     (9, 700, 64, 96, 1),        # long sequences, single narrow vocabulary tile, one K slab
@@ -195,7 +195,7 @@ def test_fp32_small_shapes():
 @pytest.mark.parametrize("B,S,D,V,len_lo", [
     (1, 1, 8, 1, 1),           # smallest legal shape; few tokens, one launch
     (2, 16, 32, 257, 1),       # few tokens, rows of 128 bytes
-    (17, 4, 8, 1, 1),          # register-staged loader, one short slab
+    (17, 4, 8, 1, 1),          # one short slab
     (5, 16, 32, 257, 1),       # one slab of 32 through the direct loader
     (5, 64, 96, 300, 1),       # odd slab count, short segments
     (70, 33, 64, 600, 1),      # more than 64 sequences: the search for a chunk's first sequence takes two rounds
@@ -551,7 +551,8 @@ def test_random_shapes_batched_long_and_wide():
 @pytest.mark.parametrize("B,S,D,V", [
     (5, 70, 128, 900),          # sliced gathers
     (3, 200, 128, 131100),      # LDS-tile dW kernel: the tile copy brings masked rows into LDS
-    (4, 50, 72, 300),           # whole-row kernels, register-staged forward loader
+    (4, 50, 728, 300),          # whole-row kernels; rows that end inside a slab
+    (4, 50, 72, 300),           # the same in slices, the last one partly filled
 ])
 def test_masked_positions_may_hold_anything(B, S, D, V):
     """Hidden states at masked positions are never multiplied, in the forward or in the backward: with
@@ -905,10 +906,12 @@ def test_two_host_threads_on_two_streams():
 
 
 def test_two_host_threads_whose_backwards_fork():
-    """Problems large enough that the dW gather goes to the library's shared auxiliary stream (0.12 GB and more of
-    worst-case gathers): calls of two threads on two streams give, bit for bit, what each gives alone."""
+    """Problems whose dW gather goes to the library's shared auxiliary stream: calls of two threads on two streams give, bit for
+    bit, what each gives alone."""
     import threading
-    inps = [wl.make_custom(20, 40, 256, 6000, seed=111, len_lo=3), wl.make_custom(17, 60, 320, 6100, seed=112, len_lo=1)]
+    shapes = ((65, 40, 256, 5000), (200, 20, 64, 2100))
+    assert all(lsr.lsr_head_dw_route(*s, lsr.LSR_BF16) == lsr.LSR_DW_ON_AUX_STREAM for s in shapes)
+    inps = [wl.make_custom(*s, seed=111 + k, len_lo=3 - 2 * k) for k, s in enumerate(shapes)]
     outs = lambda h: [t.clone() for t in (h.Y, h.I, h.dH, h.dW, h.db)]      # noqa: E731
     heads = [DeviceHead(i) for i in inps]
     alone = []
@@ -1028,23 +1031,34 @@ def test_rows_that_end_inside_a_slab(B, S, D, dtype):
         assert torch.equal(head.Y[:, 1::2], ref[0][:, 1::2]) and torch.equal(head.I[:, 1::2], ref[1][:, 1::2])
 
 
-@pytest.mark.parametrize("B,S,D,V,dtype,dy_keep", [
-    (4, 30, 128, 60000, "bf16", None),       # slices owned by XCDs; several windows: float32 gradients
-    (13, 64, 312, 9000, "bf16", 0.05),       # partly filled last slice
-    (20, 40, 256, 6000, "bf16", None),       # slices in grid order
-    (40, 48, 512, 4500, "bf16", None),       # the most LDS per workgroup
-    (30, 100, 128, 9000, "f32", 0.3),
-    (2, 20, 512, 34000, "f32", None),        # windows in float32
-    (12, 300, 64, 33000, "bf16", None),      # several buckets per wave
-    (3, 700, 72, 5000, "bf16", None),        # whole-row dH: the placement's launch
-    (70, 9, 64, 5000, "f32", 0.05),          # too much LDS for the dH gather's workgroups: the placement's launch
+PLACE, IN_DH = lsr.LSR_DW_IN_PLACEMENT_LAUNCH, lsr.LSR_DW_IN_DH_LAUNCH
+
+
+@pytest.mark.parametrize("B,S,D,V,dtype,dy_keep,routes,bpw,wpb", [
+    (4, 30, 128, 60000, "bf16", None, (IN_DH, PLACE), 1, 4),       # slices owned by XCDs; two windows: float32 gradients in the launch of dH
+    (13, 64, 312, 9000, "bf16", 0.05, (IN_DH, IN_DH), 1, 1),       # partly filled last slice
+    (20, 40, 256, 6000, "bf16", None, (IN_DH, IN_DH), 1, 4),       # slices in grid order, buckets shared by four waves
+    (40, 48, 512, 4500, "bf16", None, (IN_DH, IN_DH), 1, 1),       # the largest dW tile
+    (40, 8, 256, 10000, "bf16", 0.3, (IN_DH, IN_DH), 1, 4),        # the same beside the sums of four waves
+    (30, 100, 128, 9000, "f32", 0.3, (IN_DH,), 1, 4),
+    (2, 20, 512, 34000, "f32", None, (IN_DH,), 1, 4),              # windows in float32
+    (12, 300, 64, 33000, "bf16", None, (IN_DH, PLACE), 2, 4),      # two windows, four waves per bucket
+    (22, 230, 128, 12400, "bf16", 0.05, (IN_DH, IN_DH), 2, 1),     # two buckets per wave
+    (12, 120, 256, 9000, "f32", None, (IN_DH,), 2, 1),
+    (13, 300, 128, 5000, "bf16", None, (IN_DH, IN_DH), 4, 1),      # four
+    (13, 300, 128, 5000, "f32", 0.3, (IN_DH,), 4, 1),
+    (3, 700, 72, 5000, "bf16", None, (IN_DH, IN_DH), 8, 1),        # eight, and a partly filled last slice
+    (70, 9, 64, 5000, "f32", 0.05, (PLACE,), 1, 4),                # too large a dW tile for the launch of dH
 ])
-def test_dw_in_the_launch_of_dh_or_of_the_placement(B, S, D, V, dtype, dy_keep):
+def test_dw_in_the_launch_of_dh_or_of_the_placement(B, S, D, V, dtype, dy_keep, routes, bpw, wpb):
     """Against the oracle, and bit for bit against the profiled call, which launches dW apart; overwriting and accumulating,
-    in float32 and, for bfloat16 parameters, in bfloat16."""
+    in float32 and, for bfloat16 parameters, in bfloat16 (their routes, buckets per wave and waves per bucket are what the rows say)."""
     inp = wl.make_custom(B, S, D, V, dtype=dtype, seed=B + S + V, len_lo=1, dy_keep=dy_keep)
     dt = lsr.LSR_BF16 if dtype == "bf16" else lsr.LSR_F32
-    assert lsr.lsr_head_plan(B, S, D, V, dt)["dw_beside_dh"] == 0
+    plan = lsr.lsr_head_plan(B, S, D, V, dt)
+    assert (plan["dh_buckets_per_wave"], plan["dh_waves_per_bucket"]) == (bpw, wpb)
+    for grad_dtype, route in zip((lsr.LSR_F32, lsr.LSR_BF16), routes):
+        assert lsr.lsr_head_dw_route(B, S, D, V, dt, grad_dtype) == route
     run_case(inp)
     head = DeviceHead(inp)
     head.forward()
@@ -1149,3 +1163,46 @@ def test_sort_of_one_segment_beside_a_dw_of_many_sequences():
     torch.cuda.synchronize()
     for got, want in zip((head.dH, head.dW, head.db), ref):
         assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 72), ("f32", 32), ("f32", 40)])      # whole slabs, and a partly filled last one
+@pytest.mark.parametrize("B,S", [(5, 70), (12, 60)])                                            # 32-row and 8-row segments
+def test_forward_beyond_4_gib_of_w(B, S, dtype, D):
+    """W of 4 GiB goes through the register-staged loader with 64-bit addresses.  Its rows repeat those of a small W, whose result
+    (direct loads to LDS, held to the oracle) has to come back bit for bit in every period."""
+    P = 8209                                # not a multiple of a tile
+    inp = wl.make_custom(B, S, D, P, dtype=dtype, seed=D + S, len_lo=1)
+    run_case(inp, check_bwd=False)
+    head = DeviceHead(inp)
+    head.forward()
+    n = (1 << 32) // (P * D * head.W.element_size()) + 1
+    W, bias = head.W.repeat(n, 1), head.bias.repeat(n)
+    assert W.numel() * W.element_size() >= 1 << 32
+    ws = torch.empty(lsr.lsr_head_workspace_bytes(B, S, D, n * P, head.dt, False), dtype=torch.uint8, device="cuda")
+    Y = torch.full((B, n * P), float("nan"), device="cuda")
+    I = torch.full((B, n * P), -7, dtype=torch.int32, device="cuda")
+    for index in (I, None):
+        Y.fill_(float("nan"))
+        lsr.lsr_head_forward(B, S, D, n * P, head.dt, head.H, W, bias, head.mask, Y, index, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(Y.view(B, n, P), head.Y[:, None].expand(B, n, P))
+    assert torch.equal(I.view(B, n, P), head.I[:, None].expand(B, n, P))
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 72), ("f32", 40)])
+def test_forward_beyond_4_gib_of_hidden_states(dtype, D):
+    """The same for the hidden states: the sequences repeat those of a small batch."""
+    S, V, P = 8000, 300, 3
+    inp = wl.make_custom(P, S, D, V, dtype=dtype, seed=D, len_lo=S // 2)
+    run_case(inp, check_bwd=False)
+    head = DeviceHead(inp)
+    head.forward()
+    n = (1 << 32) // (head.H.numel() * head.H.element_size()) + 1
+    H, mask = head.H.repeat(n, 1, 1), head.mask.repeat(n, 1)
+    assert H.numel() * H.element_size() >= 1 << 32
+    ws = torch.empty(lsr.lsr_head_workspace_bytes(n * P, S, D, V, head.dt, False), dtype=torch.uint8, device="cuda")
+    Y = torch.full((n * P, V), float("nan"), device="cuda")
+    I = torch.full((n * P, V), -7, dtype=torch.int32, device="cuda")
+    lsr.lsr_head_forward(n * P, S, D, V, head.dt, H, head.W, head.bias, mask, Y, I, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(Y.view(n, P, V), head.Y.expand(n, P, V)) and torch.equal(I.view(n, P, V), head.I.expand(n, P, V))
