@@ -322,7 +322,7 @@ __global__ __launch_bounds__(64 * PLACE_WAVES) void bwd_place_kernel(const float
 // Placement through LDS (S <= PLACE_MAX_S, segments of at most PLACE_MAX_SEG entries).
 // ONE: the sequence is one segment; then this is the whole sort, and the bucket starts are written here.  (A sequence that fits one segment
 // always is one: backward B=23 S=88 D=256 |V|=2000 with one gradient in twenty 30.7 -> 19.7 us with dW in the same launch, B=4 S=640 D=64
-// |V|=3500 float32 23.3 -> 21.1, B=245 S=48 D=128 |V|=3500 102.8 -> 102.9; none of 35 shapes of 1024 to 4096 entries slower.)
+// |V|=3500 float32 23.3 -> 21.1, B=245 S=48 D=128 |V|=3500 102.8 -> 102.9; none of 35 backwards of 1024 to 4096 entries slower.  dH alone: see NW; many sequences beside dW: see backward_impl.)
 // The kernel above stores every (v, g) pair straight to its bucket: the 64 stores of a step go to some
 // fifty buckets, and with thousands of (b, segment) waves in flight every bucket's line leaves L2
 // between two stores to it (measured at C5: 0.48 GB written for 0.13 GB of pairs).  Here a workgroup
@@ -1194,8 +1194,8 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
 // ---------------------------------------------------------------------------------------------
 // dW/db, LDS-tile variant (bfloat16 inputs, D a multiple of 64, DWT_MIN_S <= S <= DWT_MAX_S).
 // A workgroup of 1024 threads owns 1024 consecutive vocabulary rows and one 64-column slice and walks
-// the sequences b = 0 .. B-1 in order.  For each sequence the slice of all S hidden states (S x 128
-// bytes, at most 64 KiB) is copied into LDS and every gather of the sequence is an LDS read.  The four lanes
+// the sequences b = 0 .. B-1 in order.  For each sequence the slice of its hidden states (up to S x 128
+// bytes, at most 64 KiB; see `tops` below) is copied into LDS and every gather of the sequence is an LDS read.  The four lanes
 // of a quad stage one vocabulary row each and sum all four, a quarter of the columns each (two chunks of 16 bytes, 64
 // float accumulators per thread): a row's (g, tile row) goes from the staging lane to the others as an operand modifier (DPP)
 // of the xor that forms the LDS address and of one move, so it needs neither LDS nor registers of its own.  A
@@ -1204,7 +1204,9 @@ __global__ __launch_bounds__(dh_threads(WPB)) __attribute__((amdgpu_waves_per_eu
 // of the gather itself, one unpack and one FMA per element, with the LDS reads one row ahead of it (the last row of a
 // sequence is multiplied behind the barrier, while the first of the next is on its way).
 // A half of a tile row is 64 bytes: rows with bit 1 set hold their halves exchanged, so that the four rows that sixteen lanes
-// read spread over all banks.
+// read spread over all banks where they differ modulo 4, which positions do in one case of eleven.  What is left of the conflicts costs little (dW, us,
+// positions as they come; made to differ; all equal modulo 4: B=64 S=512 D=1024 |V|=250002 1714; 1707; 1723, B=16 S=256 |V|=250002 350; 346; 358, B=32
+// S=128 D=1024 92.0; 91.6; 93.4, B=256 S=512 |V|=30522 894 each).
 // What bounds a round (one sequence): the arithmetic, 1.25 us, or the copy, 0.9 + 0.17 per 16 KiB (36 bytes per clock and CU: the 32
 // CUs of an XCD read the same lines).  So only the rows up to the last one with a gradient are copied where a launch in front has
 // left their number (`tops`; it does where dW runs behind dH): B=64 S=512 D=1024 |V|=250002, lengths 128..512, backward 3947 ->

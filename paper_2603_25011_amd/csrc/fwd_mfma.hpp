@@ -301,7 +301,9 @@ __device__ __forceinline__ void mma_dispatch(int na, const uint8_t* sa, int a_st
 //        row come from fwd_zeros, with 64-bit addresses in that slab alone.  Through registers, where the loads of a slab
 //        and their stores into LDS cannot overlap the MFMAs as freely, the same bits took (us -> direct): B=13 S=197 D=312
 //        |V|=31091 77 -> 59, B=44 S=452 D=888 |V|=28066 920 -> 648, B=130 S=39 D=1000 |V|=36147 392 -> 287, B=6 S=49 D=168 |V|=46465
-//        22.3 -> 22.2, float32 B=3 S=107 D=624 |V|=6965 104 -> 91; 39 shapes: 0.81 in the geometric mean, none slower.
+//        22.3 -> 22.2, float32 B=3 S=107 D=624 |V|=6965 104 -> 91; 110 shapes: 0.78 in the geometric mean, 1.02 at most.  The addresses of that
+//        slab take the bfloat16 kernels to all 256 registers, and the one with positions and 8-row segments spills ten of them (44 bytes of scratch
+//        per lane; through registers five).
 constexpr int FWD_NWN = 4;               // wave columns
 static __device__ const uint4 fwd_zeros = {0u, 0u, 0u, 0u};
 template <typename T, bool ARG, bool DMA, int SEG, bool RES, bool TAIL>

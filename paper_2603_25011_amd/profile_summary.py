@@ -14,7 +14,7 @@ Expected input: one directory with a sub-directory per profiler run (each run ma
 FETCH_SIZE / WRITE_SIZE readings are scaled by what the same counters read for the 1 GiB plain copies
 that `--calib-copy` appends (lsr::copy_probe_kernel: 1 048 576 KiB read and written per launch).
 
-    python -m paper_2603_25011_amd.profile_summary gpurun_out/prof c5_large_fwdbwd
+    python -m paper_2603_25011_amd.profile_summary prof c5_large_fwdbwd
 
 prints the summaries; with --write it stores them as profiles/<workload>_*.txt and updates
 profiles/traffic.json.
@@ -91,7 +91,7 @@ def main():
     if ks:
         lines = ["rocprofv3 --kernel-trace --stats, workload %s, MI355X, one GPU." % args.workload,
                  "Command (from the repository root):",
-                 "  rocprofv3 --kernel-trace --stats -d gpurun_out/prof/kt -o kt --output-format csv -- \\",
+                 "  rocprofv3 --kernel-trace --stats -d prof/kt -o kt --output-format csv -- \\",
                  "      python3 bench.py --no-cpu --no-extra --steps 20 --warmup 5", "",
                  "%-34s %6s %12s %12s %12s %7s" % ("kernel", "calls", "avg us", "min us", "max us", "% time")]
         for short, full, calls, avg, mn, mx, pct in sorted(ks, key=lambda r: -r[6]):
@@ -109,9 +109,9 @@ def main():
         sw = COPY_KIB / cw if cw else float("nan")
         lines = ["rocprofv3 memory-traffic counters, workload %s, MI355X, one GPU." % args.workload,
                  "Two runs (one counter each), from the repository root:",
-                 "  rocprofv3 --pmc FETCH_SIZE -d gpurun_out/prof/fetch -o fetch --output-format csv -- \\",
+                 "  rocprofv3 --pmc FETCH_SIZE -d prof/fetch -o fetch --output-format csv -- \\",
                  "      python3 bench.py --no-cpu --no-extra --steps 3 --warmup 1 --calib-copy",
-                 "  rocprofv3 --pmc WRITE_SIZE -d gpurun_out/prof/write -o write --output-format csv -- (same command)", "",
+                 "  rocprofv3 --pmc WRITE_SIZE -d prof/write -o write --output-format csv -- (same command)", "",
                  "Calibration: lsr::copy_probe_kernel copies 1 GiB (1 048 576 KiB read, 1 048 576 KiB written) per launch and reads",
                  "  FETCH_SIZE %.0f -> scale %.3f;  WRITE_SIZE %.0f -> scale %.3f." % (cf, sf, cw, sw), "",
                  "Mean per dispatch (counter units are KiB as printed), and GB per forward / backward call after scaling",
@@ -145,7 +145,7 @@ def main():
     l2 = counters(os.path.join(d, "l2"))
     if l2:
         lines = ["rocprofv3 L2 (TCC) counters of the backward gathers, workload %s, MI355X, one GPU." % args.workload,
-                 "  rocprofv3 --pmc TCC_HIT_sum TCC_MISS_sum TCC_REQ_sum -d gpurun_out/prof/l2 -o l2 --output-format csv -- \\",
+                 "  rocprofv3 --pmc TCC_HIT_sum TCC_MISS_sum TCC_REQ_sum -d prof/l2 -o l2 --output-format csv -- \\",
                  "      python3 bench.py --no-cpu --no-extra --steps 3 --warmup 1", "",
                  "%-32s %10s %16s %16s %16s %9s" % ("kernel", "dispatches", "TCC_REQ", "TCC_HIT", "TCC_MISS", "hit rate")]
         l2_json = {}
@@ -166,7 +166,7 @@ def main():
         c = {k: mean(v) for k, v in sq["lsr::fwd_mfma_kernel"].items()}
         lines = ["rocprofv3 SQ counters of lsr::fwd_mfma_kernel, workload %s, MI355X, one GPU (mean per dispatch)." % args.workload,
                  "  rocprofv3 --pmc SQ_INSTS_VALU_MFMA_MOPS_BF16 SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CYCLES SQ_WAVES SQ_LDS_BANK_CONFLICT \\",
-                 "      SQ_INSTS_LDS SQ_WAVE_CYCLES SQ_WAIT_INST_ANY GRBM_GUI_ACTIVE -d gpurun_out/prof/sq -o sq --output-format csv -- \\",
+                 "      SQ_INSTS_LDS SQ_WAVE_CYCLES SQ_WAIT_INST_ANY GRBM_GUI_ACTIVE -d prof/sq -o sq --output-format csv -- \\",
                  "      python3 bench.py --no-cpu --no-extra --steps 3 --warmup 1", ""]
         for k in sorted(c):
             lines.append("%-34s %18.4g" % (k, c[k]))
@@ -184,7 +184,7 @@ def main():
     if any(sqb.get(k) for k in GATHER_KERNELS):
         lines = ["rocprofv3 SQ counters of the backward's gather kernels, workload %s, MI355X, one GPU (mean per dispatch)." % args.workload,
                  "  rocprofv3 --pmc SQ_INSTS_VALU SQ_INSTS_LDS SQ_INSTS_VMEM_RD SQ_ACTIVE_INST_VALU SQ_WAVE_CYCLES SQ_BUSY_CYCLES \\",
-                 "      SQ_LDS_BANK_CONFLICT SQ_WAIT_INST_ANY GRBM_GUI_ACTIVE -d gpurun_out/prof/sqb -o sqb --output-format csv -- \\",
+                 "      SQ_LDS_BANK_CONFLICT SQ_WAIT_INST_ANY GRBM_GUI_ACTIVE -d prof/sqb -o sqb --output-format csv -- \\",
                  "      python3 bench.py --no-cpu --no-extra --steps 3 --warmup 1", "",
                  "VALU issue share = SQ_INSTS_VALU x 4 cycles / (4 SIMDs x 256 CUs x cycles): a wave-wide fp32 or integer",
                  "instruction occupies its SIMD's 16 lanes for 4 cycles (packed fp32 is not used)."]
